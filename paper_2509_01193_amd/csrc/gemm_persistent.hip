@@ -1,4 +1,4 @@
-// Persistent bf16 MFMA GEMM for gfx950 with the LoRA up projection fused into its epilogue (K a multiple of 64):
+// Persistent bf16 MFMA GEMM for gfx950 with the LoRA up projection fused into its epilogue:
 //     C[T, N] = Z[T, K] * op(W) + P[T, r] * M_t[r, N]
 // forward : Z = x,  op(W) = W   (W stored [K][N], N fastest),  P = s_t A_t x_i,  M = B  -> y
 // backward: Z = dy, op(W) = W^T (W stored [N][K], K fastest),  P = s_t B_t dy_i, M = A  -> dx
@@ -53,6 +53,15 @@
                              // accumulators; 0 / 2: timing variants (hardly any stores / plain stores)
 #endif
 
+// This file is compiled twice: as it is for K that is a multiple of 128, and by gemm_persistent_ktail.hip for any other K,
+// as kernels of another name (a flag of one template would do, but the two together cost the first one its last free
+// registers).
+#ifndef LOBRA_GP_KTAIL
+#define LOBRA_GP_KTAIL 0
+#define LOBRA_GP_KERNEL gemm_persistent_kernel
+#define LOBRA_GP_HOST gemm_persistent
+#endif
+
 namespace lobra {
 
 using namespace gemm;
@@ -95,13 +104,18 @@ constexpr int acc_reg(int mb, int nb) { return 4 * (NB * mb + nb); }   // first 
 
 template <bool W_KN>
 __global__ __launch_bounds__(64 * NW)
-void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
-                            const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
-                            uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                            int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t cpx,
-                            int32_t TPW, const int32_t* __restrict__ tile_tab, const int32_t* __restrict__ cseg_off,
-                            const int32_t* __restrict__ cseg_task, const int32_t* __restrict__ rank_off)
+void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
+                     const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
+                     uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                     int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t cpx,
+                     int32_t TPW, const int32_t* __restrict__ tile_tab, const int32_t* __restrict__ cseg_off,
+                     const int32_t* __restrict__ cseg_task, const int32_t* __restrict__ rank_off)
 {
+    constexpr bool KTAIL = LOBRA_GP_KTAIL;
+    // KTAIL: K is not a multiple of 128 (any multiple of 8 from kPersistentMinKTail on).  The last pair of K tiles is then partly,
+    // its second tile perhaps wholly, beyond K: their copies repeat the last valid chunk, and both operands' fragments
+    // are cleared in registers in front of the K steps that reach beyond K.  A kernel of its own, so that whole K tiles
+    // do not pay for it.
     // tile_tab, cseg_off, cseg_task, rank_off: pd's tables of those names once more, as arguments of their own that
     // promise not to alias anything the kernel writes: their entries are the same for every lane, and with the
     // promise the compiler fetches them with scalar loads, which no vector memory operation in flight - copies,
@@ -119,7 +133,8 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
     // (operands) or of 4 result rows of the "A" operand (columns of C)
     const int j = lane & 15, kg = lane >> 4;
     const int32_t T = pd.T;
-    const int32_t KT = K / BK;                       // the launcher guarantees K % (2 BK) == 0: an even number of K tiles
+    // an even number of K tiles (the launcher guarantees K % (2 BK) == 0 unless KTAIL)
+    const int32_t KT = KTAIL ? (K + 2 * BK - 1) / (2 * BK) * 2 : K / BK;
 
     // ---- this workgroup's output tiles.  Consecutive workgroup ids go to different XCDs (each with its own
     //      L2), so every XCD gets a contiguous range of the tile order; inside the order, GM tile-rows share one
@@ -222,14 +237,14 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
     // "A" operand of block nb out of a [k][256 n] tile at `base`: k rows krow0 + 8 kg + (j >> 2) + {0, 4}, the
     // 4-column group (j & 3) of the block - with block_col's dealing that is columns 32 (nb / 2) + 8 (j & 3)
     // + 4 ((nb + j) % 2) .. + 3 of the wave tile
-    auto read_kn = [&](const unsigned char* base, int krow0, int nb) __attribute__((always_inline)) {
+    auto read_kn = [&](const unsigned char* base, int krow0, int nb, int j, int kg) __attribute__((always_inline)) {
         const int krow = krow0 + 8 * kg + (j >> 2);
         const int n = wn * TN + 32 * (nb >> 1) + 8 * (j & 3) + 4 * ((nb ^ j) & 1);
         const int ch = (n >> 3) ^ kn_swz2(krow);
         return tr_pair(base + krow * 512 + ch * 16 + (n & 7) * 2, 512);
     };
     auto read_w = [&](const unsigned char* wa, int stage, int ks, int nb, bf16x8 (&wf)[NB]) __attribute__((always_inline)) {
-        if (W_KN) wf[nb] = read_kn(lds + stage * STAGE_BYTES + ZT_BYTES, 32 * ks, nb);
+        if (W_KN) wf[nb] = read_kn(lds + stage * STAGE_BYTES + ZT_BYTES, 32 * ks, nb, j, kg);
         else wf[nb] = *reinterpret_cast<const bf16x8*>(wa + nb * 16 * (BK * 2));
     };
     // One K step of 32: the MB NB = 64 MFMAs in NU = 16 sections of four.  A wave issues one instruction every
@@ -248,21 +263,49 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
     //       the 16 copies of the K tile at (zcur, wcur) into the stage at cst, which the barrier has freed
     //       (issued back to back the copies block their wave for as long as the texture unit takes to accept
     //       them): one read and one copy per section, two of each in sections 2 and 3.
-    enum { STEP_FIRST, STEP_PLAIN, STEP_COPY };
+    //   STEP_COPY_TAIL: the same with the copies of one of the two K tiles that may reach beyond K.  Their addresses are
+    //       taken from a base 128 k earlier, so that the offset of a chunk that is moved back stays positive.
+    enum { STEP_FIRST, STEP_PLAIN, STEP_COPY, STEP_COPY_TAIL };
     auto kstep = [&](auto mode_c, int rstage, int rks, bf16x8 (&zf)[MB], bf16x8 (&wc)[NB], bf16x8 (&wn_)[NB], uint32_t cst,
                      auto&& hook) __attribute__((always_inline)) {
         constexpr int mode = decltype(mode_c)::value;
+        constexpr bool copies = mode == STEP_COPY || mode == STEP_COPY_TAIL;
         // (opaque to the optimiser, so that the 16 landing addresses of a K tile are sums with a literal here
         //  instead of 16 loop-invariant registers that have to be spilled)
         asm volatile("" : "+s"(cst));
+        // (KTAIL: the loop's branches meet here, and where they do the compiler may have moved a fragment by a vector ALU
+        //  instruction: an MFMA statement must not read a register in the two wait states after such a write)
+        if constexpr (KTAIL) {
+            asm volatile("s_nop 1" : "+v"(zf[0]), "+v"(zf[1]), "+v"(zf[2]), "+v"(zf[3]), "+v"(zf[4]), "+v"(zf[5]), "+v"(zf[6]), "+v"(zf[7]),
+                                     "+v"(wc[0]), "+v"(wc[1]), "+v"(wc[2]), "+v"(wc[3]), "+v"(wc[4]), "+v"(wc[5]), "+v"(wc[6]), "+v"(wc[7]));
+        }
         agpr_fence();
         const unsigned char* za = zaddr(rstage, rks);
         const unsigned char* wa = waddr(rstage, rks);
-        auto copy_src = [&](int c) { return c < NBZ ? zcur : wcur; };
-        auto copy_off = [&](int c) { return c < NBZ ? zvo[c % NBZ] : wvo[c % NBZ]; };
+        // STEP_COPY_TAIL: k left in the K tile at the copy cursor (it may be negative), and how far back this lane's chunk
+        // of a [rows][64 k] tile moves (row and chunk of a lane are the same in all of its copies up to a multiple of 16)
+        // (lane opaque to the optimiser: worked out here, instead of in registers that live through the main loop)
+        int ln = lane;
+        if constexpr (mode == STEP_COPY_TAIL) asm volatile("" : "+v"(ln));
+        const int32_t left = K - c_kt * BK;
+        const uint32_t back = 2u * uint32_t(max(8 * ((ln % 8) ^ swz_row(8 * wave_u + ln / 8)) - (left - 8), 0));
+        auto copy_src = [&](int c) __attribute__((always_inline)) {
+            if constexpr (mode == STEP_COPY_TAIL) return c < NBZ ? zcur - 256 : wcur - (W_KN ? size_t(128) * ldw * 2 : size_t(256));
+            else return c < NBZ ? zcur : wcur;
+        };
+        auto copy_off = [&](int c) __attribute__((always_inline)) {
+            if constexpr (mode == STEP_COPY_TAIL) {
+                if (c < NBZ) return zvo[c % NBZ] + 256u - back;
+                if (!W_KN) return wvo[c % NBZ] + 256u - back;
+                const int krow = 2 * (wave_u + NW * (c % NBZ)) + (ln >> 5);
+                return wvo[c % NBZ] + uint32_t(128 - max(krow - (left - 1), 0)) * (uint32_t(ldw) * 2u);
+            } else {
+                return c < NBZ ? zvo[c % NBZ] : wvo[c % NBZ];
+            }
+        };
         static_for<0, NU>([&](auto u_c) {
             constexpr int u = decltype(u_c)::value, mb = u / 2, nb0 = (NB / 2) * (u % 2);
-            if constexpr (mode == STEP_COPY && u >= 2) {
+            if constexpr (copies && u >= 2) {
                 mfma2_dma16<acc_reg(mb, nb0), acc_reg(mb, nb0 + 1)>(wc[nb0], wc[nb0 + 1], zf[mb], copy_lds_addr(cst, u - 2),
                                                                    copy_src(u - 2), copy_off(u - 2));
                 __builtin_amdgcn_sched_barrier(0);
@@ -283,7 +326,7 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
                     if constexpr (q < 3) __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            if constexpr (mode != STEP_COPY) {
+            if constexpr (!copies) {
                 if constexpr (u % 2 == 0) read_w(wa, rstage, rks, u / 2, wn_);
                 else read_z(za, mb, zf);
             } else if constexpr (u == 2) {
@@ -302,6 +345,7 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
     using step_first = std::integral_constant<int, STEP_FIRST>;
     using step_plain = std::integral_constant<int, STEP_PLAIN>;
     using step_copy = std::integral_constant<int, STEP_COPY>;
+    using step_copy_tail = std::integral_constant<int, STEP_COPY_TAIL>;
 
     // ---- epilogue of the tile at (row0, col0): fused up projection, then fp32 -> bf16 and the stores.
     //      tab_*: the table entries of the first segment that crosses the tile, read when the tile's main loop
@@ -358,7 +402,17 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
                   (uint32_t(row) * uint32_t(pd.r_pad) + (8 * ch < r ? 8u * ch : 0u)) * 2u);
         }
     };
+    const int main_tid = tid, main_lane = lane, main_j = j, main_kg = kg;
     auto epilogue = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+        // (KTAIL: counted anew and opaque to the optimiser, so that the epilogue's addresses are worked out here, once per
+        //  output tile: kept through the main loop they would be spilled, and every reload waits for the copies in flight)
+        int lane = main_lane;
+        if constexpr (KTAIL) {
+            lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+            asm volatile("" : "+v"(lane));
+        }
+        const int tid = KTAIL ? wave_u * 64 + lane : main_tid;
+        const int j = KTAIL ? lane & 15 : main_j, kg = KTAIL ? lane >> 4 : main_kg;
         // the loop's MFMAs are asm statements, so the compiler does not know that the accumulators come out of
         // the matrix pipeline: keep the first read of them the documented number of wait states away
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
@@ -397,7 +451,7 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         union { bf16x8 b; u32x4 u; } cv;
-                        cv.b = read_kn(ml, 0, nb);
+                        cv.b = read_kn(ml, 0, nb, j, kg);
                         cv.u &= km;
                         mf[nb] = cv.b;
                     }
@@ -477,7 +531,7 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
                         if (kk > 0) load_p(k0 + kk);
                         bf16x8 mf[NB];
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, kk, nb);
+                        for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, kk, nb, j, kg);
                         static_for<0, MB>([&](auto mb_c) {
                             constexpr int mb = decltype(mb_c)::value;
                             const int32_t rb = wrow0 + mb * 16;
@@ -594,25 +648,49 @@ void gemm_persistent_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const ui
         wait_vmcnt<LOBRA_GP_STORES_IN_FLIGHT>();
         __builtin_amdgcn_s_barrier();
     };
+    // KTAIL: in front of K step q (0 .. 3) of a pair of K tiles, the fragments' lanes whose 8 k lie beyond K are
+    // cleared - in both operands, since what they hold instead is another k's value, perhaps no finite one.
+    auto clear_beyond = [&](int q, bf16x8 (&z)[MB], bf16x8 (&w)[NB]) __attribute__((always_inline)) {
+        const int32_t rem = K - t_kt * BK;           // 8 .. 120 in the last pair, more before
+        if (32 * q + 32 <= rem) return;              // uniform
+        const bool in = 32 * q + 8 * kg < rem;
+        const bf16x8 zero = as_bf16x8(zero4);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) z[i] = in ? z[i] : zero;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) w[i] = in ? w[i] : zero;
+    };
     // One K tile in stage STG: K step 0 (fragments in registers) reads the fragments of K step 1 and moves the
     // copy cursor on to the K tile after next; K step 1, once the barrier in its second section is passed,
     // reads the first fragments of the next K tile from the other stage and copies the K tile after next
     // into this one.
-    auto ktile = [&](auto stg_c, auto mode_c) __attribute__((always_inline)) {
+    // (copy_c: how the K tile after next is copied; MASK: this K tile may be one of the last pair, see clear_beyond)
+    auto ktile = [&](auto stg_c, auto mode_c, auto copy_c, auto mask_c) __attribute__((always_inline)) {
         constexpr int STG = decltype(stg_c)::value;
+        constexpr bool MASK = decltype(mask_c)::value;
+        if constexpr (MASK) clear_beyond(2 * STG, zf, wf[0]);
         kstep(mode_c, STG, 1, zf, wf[0], wf[1], 0, advance);
+        if constexpr (MASK) clear_beyond(2 * STG + 1, zf, wf[1]);
         if constexpr (decltype(mode_c)::value == STEP_FIRST)
-            kstep(step_copy{}, STG ^ 1, 0, zf, wf[1], wf[0], ldsw + uint32_t(STG) * STAGE_BYTES, tile_barrier_after_stores);
+            kstep(copy_c, STG ^ 1, 0, zf, wf[1], wf[0], ldsw + uint32_t(STG) * STAGE_BYTES, tile_barrier_after_stores);
         else
-            kstep(step_copy{}, STG ^ 1, 0, zf, wf[1], wf[0], ldsw + uint32_t(STG) * STAGE_BYTES, tile_barrier);
+            kstep(copy_c, STG ^ 1, 0, zf, wf[1], wf[0], ldsw + uint32_t(STG) * STAGE_BYTES, tile_barrier);
     };
+    using yes = std::true_type;
+    using no = std::false_type;
     using stage0 = std::integral_constant<int, 0>;
     using stage1 = std::integral_constant<int, 1>;
     for (;;) {
-        if (t_kt == 0) ktile(stage0{}, step_first{});
-        else ktile(stage0{}, step_plain{});
-        if (t_kt + 2 == KT) prefetch_adapter(t_row0, t_col0);   // waited for at the tile barrier that follows
-        ktile(stage1{}, step_plain{});
+        if (KTAIL && t_kt + 4 >= KT) {               // (uniform) the last pair of K tiles is copied, or multiplied, here
+            ktile(stage0{}, step_plain{}, step_copy_tail{}, yes{});
+            if (t_kt + 2 == KT) prefetch_adapter(t_row0, t_col0);
+            ktile(stage1{}, step_plain{}, step_copy_tail{}, yes{});
+        } else {
+            if (t_kt == 0) ktile(stage0{}, step_first{}, step_copy{}, no{});
+            else ktile(stage0{}, step_plain{}, step_copy{}, no{});
+            if (!KTAIL && t_kt + 2 == KT) prefetch_adapter(t_row0, t_col0);   // waited for at the tile barrier that follows
+            ktile(stage1{}, step_plain{}, step_copy{}, no{});
+        }
         t_kt += 2;
         if (t_kt == KT) {                            // uniform: an output tile is complete
             epilogue(t_row0, t_col0);
@@ -646,7 +724,7 @@ hipError_t launch_persistent(const PlanDev& pd, const void* Z, const void* W, co
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     int32_t ncu = cus[dev].load(std::memory_order_acquire);
     if (ncu == 0) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_persistent_kernel<W_KN>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&LOBRA_GP_KERNEL<W_KN>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         int n = 0;
@@ -661,17 +739,21 @@ hipError_t launch_persistent(const PlanDev& pd, const void* Z, const void* W, co
     const int64_t xmax = (ntiles + 7) / 8;                                    // tiles of the fullest XCD
     const int64_t rounds = (xmax + int64_t(cpx) * tpw - 1) / (int64_t(cpx) * tpw);
     const int64_t wgs = ntiles <= 8 * int64_t(cpx) ? ntiles : 8 * rounds * cpx;   // few tiles: one workgroup each
-    gemm_persistent_kernel<W_KN><<<dim3(uint32_t(wgs)), 64 * NW, LDS_BYTES, st>>>(
+    LOBRA_GP_KERNEL<W_KN><<<dim3(uint32_t(wgs)), 64 * NW, LDS_BYTES, st>>>(
         pd, (const uint16_t*)Z, (const uint16_t*)W, (const uint16_t*)P, (const uint16_t*)M, (uint16_t*)C,
         K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, cpx, tpw, pd.gemm_tile_tab, pd.cseg_off, pd.cseg_task, pd.rank_off);
     return hipGetLastError();
 }
 }  // namespace
 
-hipError_t gemm_persistent(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
+hipError_t LOBRA_GP_HOST(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                            const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj,
                            int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t gm, hipStream_t st)
 {
+#if !LOBRA_GP_KTAIL
+    if (K % (2 * BK) != 0)
+        return gemm_persistent_ktail(pd, transW, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, st);
+#endif
     if (transW) return launch_persistent<false>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, st);
     return launch_persistent<true>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, st);
 }

@@ -1,0 +1,508 @@
+// Tiled bf16 MFMA GEMM for gfx950 with the LoRA up projection fused into its epilogue, for the products that the
+// persistent kernel (gemm_persistent.hip) does not take: few output tiles, and K that is not a multiple of 128.
+//     C[T, N] = Z[T, K] * op(W) + P[T, r] * M_t[r, N]
+// forward : Z = x,  op(W) = W   (W stored [K][N], N fastest),  P = s_t A_t x_i,  M = B  -> y
+// backward: Z = dy, op(W) = W^T (W stored [N][K], K fastest),  P = s_t B_t dy_i, M = A  -> dx
+// (paper section 2.1: X W + X (down)(up); section 1: one shared base product for the fused batch,
+// a per-task adapter product on top of it).
+//
+// One workgroup per TM x TN output tile, WM x WN waves, K in steps of 64 through a ring of STAGES LDS slots that
+// direct global -> LDS copies fill (no registers, no ds_write).  Blocks of v_mfma_f32_16x16x32_bf16 with fp32
+// accumulators; the MFMA "A" operand is fed from W and the "B" operand from Z, so a lane ends up with four
+// consecutive output columns of one row.  Sums run over ascending k in steps of 32 like the persistent kernel's,
+// so both give the same bits.
+//
+// What bounds it: inside a compute unit, the copies (64 bytes a cycle) and the LDS reads of a 128 x 128 tile take as
+// long as its MFMAs (512 cycles per K tile each), so nothing may wait for anything else.  The order of a K step is
+// pinned (sched_barrier): every fragment read and every copy goes out behind an MFMA, a K tile's copies are dealt over
+// two K steps, and the only waits are one counted vmcnt and one barrier per K tile.  Left to the compiler, which put the
+// copies and the reads in front of the MFMAs, the same kernel took 61 instead of 39 us (x [1000, 4096] times W [4096, 4096],
+// 256 tiles of 128 x 128; without MFMAs 31 us, without fragment reads 34, without copies 36).
+//
+// K may be any multiple of 8 and T, N anything from 8 columns up: rows and columns beyond the edge repeat the last
+// valid one (what they produce is never stored), chunks beyond K repeat the last valid chunk and both operands'
+// fragments are cleared in registers, in the last K tile only.
+//
+// LDS layouts
+//   Z tile, and the W tile when K is fastest (backward): [rows][64 k], 128 bytes per row, 16-byte chunk c of a row
+//       stored at c ^ swz_row(row).
+//   W tile when N is fastest (forward), adapter slice: [k][TN n], chunk c of k-row k stored at c ^ swz_kn<TN>(k); the
+//       MFMA operand (8 consecutive k of one column) is gathered with two ds_read_b64_tr_b16.
+//   C staging in the epilogue: per wave [rows][cols + 8] bf16, written back with non-temporal stores.
+#include <atomic>
+
+#include "gemm_common.h"
+#include "kernels.h"
+
+namespace lobra {
+
+using namespace gemm;
+
+namespace {
+
+// Swizzle of a [k][TN n] tile.  A transpose read's two 16-lane groups of a pass touch 32 bytes in each of the k rows
+// k0 .. k0 + 3 and k0 + 8 .. k0 + 11: eight rows, whose pieces have to fall into the eight 32-byte parts of the 256
+// bytes that the banks span.  Rows of 256 bytes and more all start at bank 0, so three bits of k pick the part; rows
+// of 128 bytes start at bank 0 or 32 by their lowest bit, so two bits of k pick one of four.
+template <int TN> __device__ __forceinline__ int swz_kn(int k)
+{
+    if constexpr (TN >= 128) return kn_swz(k);
+    else return (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1);
+}
+
+template <int TM, int TN, int WN, int STAGES> constexpr int tile_lds_bytes()
+{
+    const int loop = STAGES * (TM + TN) * BK * 2;
+    const int cs = TM * (TN + 8 * WN) * 2;               // all waves' C staging
+    const int ms = LOBRA_MAX_RANK * TN * 2;              // adapter slice
+    return loop > cs ? (loop > ms ? loop : ms) : (cs > ms ? cs : ms);
+}
+
+}  // namespace
+
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4)
+void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
+                      const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
+                      uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM)
+{
+    // ldc: row pitch of C.  nproj > 1: this launch is projection `proj` of a fused shared-input
+    // call: of every task's rank rows (in M) and rank columns (in P) only the window
+    // [proj r, (proj + 1) r) takes part, r = the task's stacked rank / nproj.  proj < 0: the launch
+    // covers all projections (N = nproj * pd.dg, pd.dg a multiple of 256) and a tile takes
+    // the projection its columns lie in; M is then the compact [R_tot][pd.dg] array.
+    constexpr int NW = WM * WN, NT = 64 * NW;
+    constexpr int WTM = TM / WM, WTN = TN / WN;     // wave tile
+    constexpr int MB = WTM / 16, NB = WTN / 16;     // 16 x 16 blocks per wave
+    constexpr int ZT = TM * BK * 2, STAGE = (TM + TN) * BK * 2;
+    constexpr int ZC = TM / 8 / NW, WC = TN / 8 / NW, CPW = ZC + WC;   // 1 KiB copies per wave and K tile
+    constexpr int CR = TN / 8, RPC = 64 / CR;       // [k][n] tile: 16-byte chunks per k row, k rows per copy
+    constexpr int CS_PITCH = WTN + 8;
+    static_assert(ZC * 8 * NW == TM && WC * 8 * NW == TN && RPC * CR == 64, "whole copies");
+    static_assert(STAGES >= 2, "ring");
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    // MFMA 16x16x32 lanes: j = row of the "B" operand (a token) and of the result, kg = group of 8 k
+    // (operands) or of 4 result columns
+    const int j = lane & 15, kg = lane >> 4;
+    const int32_t T = pd.T;
+
+    // ---- workgroup -> tile: consecutive ids go to different XCDs, so give each XCD a contiguous
+    //      range of the tile order; inside it, GM tile-rows share one sweep over the tile-columns.
+    int32_t row0, col0;
+    {
+        const int32_t id = xcd_contiguous(blockIdx.x, tiles_m * tiles_n);
+        const int32_t group = id / (GM * tiles_n);
+        const int32_t first_m = group * GM;
+        const int32_t gsz = min(tiles_m - first_m, GM);
+        const int32_t in = id - group * GM * tiles_n;
+        row0 = (first_m + in % gsz) * TM;
+        col0 = in / gsz * TN;
+    }
+
+    // ---- copies.  Block b (1 KiB) of a [rows][64 k] tile holds rows 8 b .. 8 b + 7, of a [k][n] tile the k rows
+    //      RPC b ..; wave w moves blocks w, w + NW, ...; the swizzle is applied to the address a lane fetches from.
+    const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)lds));
+    const unsigned char* zbase = reinterpret_cast<const unsigned char*>(Z + size_t(row0) * K);
+    const unsigned char* wbase = reinterpret_cast<const unsigned char*>(W_KN ? W + col0 : W + size_t(col0) * ldw);
+    const size_t wstep = W_KN ? size_t(BK) * ldw * 2 : size_t(BK) * 2;
+    uint32_t zvo[ZC], wvo[WC];
+#pragma unroll
+    for (int c = 0; c < ZC; ++c) {
+        const int row = 8 * (wave + NW * c) + lane / 8;
+        zvo[c] = (uint32_t(min(row, T - 1 - row0)) * uint32_t(K) + 8u * ((lane % 8) ^ swz_row(row))) * 2u;
+    }
+#pragma unroll
+    for (int c = 0; c < WC; ++c) {
+        if (W_KN) {
+            const int krow = RPC * (wave + NW * c) + lane / CR;
+            wvo[c] = (uint32_t(krow) * uint32_t(ldw) + uint32_t(min(8 * ((lane % CR) ^ swz_kn<TN>(krow)), N - 8 - col0))) * 2u;
+        } else {
+            const int row = 8 * (wave + NW * c) + lane / 8;
+            wvo[c] = (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + 8u * ((lane % 8) ^ swz_row(row))) * 2u;
+        }
+    }
+    const int32_t KT = (K + BK - 1) / BK, ktail = K % BK;       // K tiles; k of a partial last one (0: none)
+    const unsigned char *zcur = zbase, *wcur = wbase;           // K tile the next copies fetch
+    auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {      // copy c of a whole K tile
+        constexpr int c = decltype(c_c)::value;
+        if constexpr (c < ZC) dma16(la + NW * c * 1024, zcur, zvo[c]);
+        else dma16(la + ZT + NW * (c - ZC) * 1024, wcur, wvo[c - ZC]);
+    };
+    auto next_copy_tile = [&]() __attribute__((always_inline)) {
+        zcur += BK * 2;
+        wcur += wstep;
+    };
+    auto copy_tail = [&](uint32_t la) {             // the partial last K tile: chunks beyond K repeat the last one
+#pragma unroll
+        for (int c = 0; c < ZC; ++c) {
+            const int ch = (lane % 8) ^ swz_row(8 * (wave + NW * c) + lane / 8);
+            dma16(la + NW * c * 1024, zcur, zvo[c] - 2u * uint32_t(max(8 * ch - (ktail - 8), 0)));
+        }
+#pragma unroll
+        for (int c = 0; c < WC; ++c) {
+            uint32_t vo;
+            if (W_KN) {
+                const int krow = RPC * (wave + NW * c) + lane / CR;
+                vo = wvo[c] - 2u * uint32_t(max(krow - (ktail - 1), 0)) * uint32_t(ldw);
+            } else {
+                const int ch = (lane % 8) ^ swz_row(8 * (wave + NW * c) + lane / 8);
+                vo = wvo[c] - 2u * uint32_t(max(8 * ch - (ktail - 8), 0));
+            }
+            dma16(la + ZT + NW * c * 1024, wcur, vo);
+        }
+    };
+
+    // ---- operand fragments of K step ks (32 k) of a slot
+    auto read_z = [&](const unsigned char* st, int ks, int mb) __attribute__((always_inline)) {
+        const int row = wm * WTM + mb * 16 + j;
+        return *reinterpret_cast<const bf16x8*>(st + row * (BK * 2) + (((4 * ks + kg) ^ swz_row(j)) << 4));
+    };
+    auto read_kn = [&](const unsigned char* base, int krow0, int nb) __attribute__((always_inline)) {
+        const int krow = krow0 + 8 * kg + (j >> 2);
+        const int n = wn * WTN + nb * 16 + 4 * (j & 3);
+        return tr_pair(base + krow * (TN * 2) + (((n >> 3) ^ swz_kn<TN>(krow)) << 4) + (n & 7) * 2, TN * 2);
+    };
+    auto read_w = [&](const unsigned char* st, int ks, int nb) __attribute__((always_inline)) {
+        if (W_KN) return read_kn(st + ZT, 32 * ks, nb);
+        const int row = wn * WTN + nb * 16 + j;
+        return *reinterpret_cast<const bf16x8*>(st + ZT + row * (BK * 2) + (((4 * ks + kg) ^ swz_row(j)) << 4));
+    };
+    const bf16x8 zero8 = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
+    // lane group kg holds k 32 ks + 8 kg .. + 7 of the tile in both operands
+    auto clear_tail = [&](int ks, bf16x8 (&zf)[MB], bf16x8 (&wf)[NB]) __attribute__((always_inline)) {
+        const bool in = 32 * ks + 8 * kg < ktail;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) zf[mb] = in ? zf[mb] : zero8;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) wf[nb] = in ? wf[nb] : zero8;
+    };
+
+    // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column nb 16 + 4 kg + v
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int jj = 0; jj < NB; ++jj) acc[i][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // One K step: MB NB MFMAs on (zf, wf) with the reads of the fragments (zn, wn_) of K step rks of the slot at rst
+    // and (COPY) the CPW copies of a K tile into the slot at la dealt evenly behind them, in this order.
+    auto kstep = [&](auto read_c, auto copy_c, const bf16x8 (&zf)[MB], const bf16x8 (&wf)[NB], const unsigned char* rst, int rks,
+                     bf16x8 (&zn)[MB], bf16x8 (&wn_)[NB], uint32_t la) __attribute__((always_inline)) {
+        constexpr bool READ = decltype(read_c)::value;
+        constexpr int C0 = decltype(copy_c)::value >> 8, NC = (decltype(copy_c)::value & 255) - C0;
+        constexpr int NM = MB * NB, NR = READ ? MB + NB : 0;
+        static_for<0, NM>([&](auto q_c) {
+            constexpr int q = decltype(q_c)::value, mb = q / NB, nb = q % NB;
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], zf[mb], acc[mb][nb], 0, 0, 0);
+            static_for<q * NR / NM, (q + 1) * NR / NM>([&](auto i_c) {
+                constexpr int i = decltype(i_c)::value;
+                if constexpr (i < NB) wn_[i] = read_w(rst, rks, i);
+                else zn[i - NB] = read_z(rst, rks, i - NB);
+            });
+            static_for<q * NC / NM, (q + 1) * NC / NM>([&](auto i_c) { copy(std::integral_constant<int, C0 + decltype(i_c)::value>{}, la); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    // copies [c0, c1) of a K tile, as kstep's argument
+    constexpr int CH = STAGES > 2 ? CPW / 2 : CPW;
+    using none = std::integral_constant<int, 0>;
+    using half0 = std::integral_constant<int, CH>;
+    using half1 = std::integral_constant<int, (CH << 8) | CPW>;
+
+    // The table entries of the first segment that crosses this tile (a chain of dependent loads) are read before the
+    // copies start: after them, the wait for a table entry would wait for the copies as well.
+    const int32_t sg_first = pd.rowblk_seg[row0 / kRowBlock];
+    const int32_t sf_lo = pd.cseg_off[sg_first], sf_hi = pd.cseg_off[sg_first + 1];
+    const int32_t sf_task = pd.cseg_task[sg_first];
+    const int32_t pj = proj >= 0 ? proj : col0 / pd.dg;          // this tile's projection
+    const int32_t mcol0 = proj >= 0 ? 0 : pj * pd.dg;            // first column of that projection
+    const int32_t mpitch = proj >= 0 ? N : pd.dg;                // row pitch of M
+    const int32_t sf_rw = sf_task >= 0 ? (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj : 0;
+    const int32_t sf_r0 = sf_task >= 0 ? pd.rank_off[sf_task] + pj * sf_rw : 0;
+
+    // ---- main loop.  A K tile's second K step is multiplied behind the barrier that hands its slot back: by then
+    //      its fragments are in registers, so the slot can be refilled and the next tile's first fragments are read
+    //      while the matrix cores work.
+    const uint32_t la0 = lds0 + wave * 1024;
+    const int32_t KF = K / BK;                       // whole K tiles
+    for (int s = 0; s < STAGES; ++s) {
+        if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * STAGE); });
+        else if (s < KT) copy_tail(la0 + s * STAGE);
+        next_copy_tile();
+    }
+    bf16x8 za[MB], wa[NB], zb[MB], wb[NB];
+    if (KT >= STAGES) wait_vmcnt<(STAGES - 1) * CPW>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) wa[nb] = read_w(lds, 0, nb);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) za[mb] = read_z(lds, 0, mb);
+    int32_t kt = 0, slot = 0;
+    const int32_t steady = KF - STAGES;              // K tiles behind which a whole K tile is still to be copied
+    uint32_t pla = 0;
+    auto body = [&](auto h_c) __attribute__((always_inline)) {
+        kstep(yes{}, h_c, za, wa, lds + slot * STAGE, 1, zb, wb, pla);
+        if constexpr (decltype(h_c)::value != 0) next_copy_tile();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_vmcnt<(STAGES - 2) * CPW>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int32_t ns = slot + 1 == STAGES ? 0 : slot + 1;
+        pla = la0 + slot * STAGE;
+        kstep(yes{}, half0{}, zb, wb, lds + ns * STAGE, 0, za, wa, pla);
+        if constexpr (CH == CPW) next_copy_tile();
+        slot = ns;
+    };
+    if (steady > 0) {
+        body(none{});
+        for (kt = 1; kt < steady; ++kt) body(std::conditional_t<CH == CPW, none, half1>{});
+    }
+    for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
+        const bool tail = ktail != 0 && kt + 1 == KT;           // uniform
+        if (tail) clear_tail(0, za, wa);
+        if (CH < CPW && steady > 0 && kt == steady) {
+            kstep(yes{}, half1{}, za, wa, lds + slot * STAGE, 1, zb, wb, pla);
+            next_copy_tile();
+        } else {
+            kstep(yes{}, none{}, za, wa, lds + slot * STAGE, 1, zb, wb, 0);
+        }
+        if (tail) clear_tail(1, zb, wb);
+        const int32_t ns = slot + 1 == STAGES ? 0 : slot + 1;
+        if (kt + 1 < KT) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (kt + STAGES < KT) copy_tail(la0 + slot * STAGE);
+            kstep(yes{}, none{}, zb, wb, lds + ns * STAGE, 0, za, wa, 0);
+        } else {
+            kstep(no{}, none{}, zb, wb, lds, 0, za, wa, 0);
+        }
+        slot = ns;
+    }
+
+    // ---- fused up projection: for every adapter segment that crosses this tile, ceil(r_t / 32) extra
+    //      K steps acc += M_t^T[:, cols] * P[rows, :]^T with the rows outside the segment masked to zero.
+    //      The M_t slice [r_t][TN cols] is staged in LDS (free now) in the [k][n] layout (rank rows up to the next
+    //      multiple of 32 zero) and gathered with the transpose read; P comes
+    //      straight from global memory, 16 bytes per lane.
+    //      The segment loop and its barriers are uniform over the workgroup.
+    if (P) {
+        const int32_t row_end = min(row0 + TM, T);
+        const int32_t wrow0 = row0 + wm * WTM;      // the wave's rows are wrow0 .. wrow0 + WTM - 1
+        for (int32_t sg = sg_first; sg < pd.nseg; ++sg) {
+            const bool cached = sg == sg_first;
+            const int32_t seg_lo = cached ? sf_lo : pd.cseg_off[sg];
+            if (seg_lo >= row_end) break;
+            const int32_t seg_hi = cached ? sf_hi : pd.cseg_off[sg + 1];
+            const int32_t t = cached ? sf_task : pd.cseg_task[sg];
+            if (t < 0 || seg_hi <= row0) continue;
+            const int32_t lo = max(seg_lo, row0), hi = min(seg_hi, row_end);
+            const int32_t r = cached ? sf_rw : (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj;
+            const int32_t r0 = cached ? sf_r0 : pd.rank_off[t] + pj * r;
+            const int32_t rp = (r + 31) & ~31;
+            const bool mine = hi > wrow0 && lo < wrow0 + WTM;  // wave-uniform: the segment crosses this wave's rows
+            // the P fragments of a rank step: lane (j, kg) holds the ranks kk + 8 kg .. + 7 of token row j of
+            // each 16-row block; groups that start beyond r_t hold padding, or another projection's ranks,
+            // and are not read.  The first step is fetched before the adapter slice is staged, so that its
+            // latency overlaps the staging and its barriers
+            u32x4 pv[MB];
+            const u32x4 zero4 = {0u, 0u, 0u, 0u};
+            auto load_p = [&](int32_t kk) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int32_t row = wrow0 + mb * 16 + j;
+                    pv[mb] = (mine && kk + 8 * kg < r && row >= lo && row < hi)
+                                 ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * r + kk + 8 * kg) : zero4;
+                }
+            };
+            load_p(0);
+            // the adapter slice is rp * CR chunks of 16 bytes; the first MCH * NT of them are fetched before
+            // the barrier that frees the LDS and written after it
+            constexpr int MCH = 2;
+            u32x4 mreg[MCH];
+            auto fetch_m = [&](int32_t base) {
+#pragma unroll
+                for (int q = 0; q < MCH; ++q) {
+                    const int32_t ch = base + tid + q * NT, kr = ch / CR, n = col0 + 8 * (ch % CR);
+                    mreg[q] = (kr < r && n < N)
+                                  ? *reinterpret_cast<const u32x4*>(M + size_t(r0 + kr) * mpitch + (n - mcol0)) : zero4;
+                }
+            };
+            auto store_m = [&](int32_t base) {
+#pragma unroll
+                for (int q = 0; q < MCH; ++q) {
+                    const int32_t ch = base + tid + q * NT, kr = ch / CR, c = ch % CR;
+                    if (kr < rp) *reinterpret_cast<u32x4*>(lds + kr * (TN * 2) + ((c ^ swz_kn<TN>(kr)) << 4)) = mreg[q];
+                }
+            };
+            fetch_m(0);
+            __syncthreads();                        // everybody is done with what the LDS held before
+            store_m(0);
+            for (int32_t base = MCH * NT; base < rp * CR; base += MCH * NT) {
+                fetch_m(base);
+                store_m(base);
+            }
+            __syncthreads();
+            if (!mine) continue;                    // wave-uniform; the barriers are above
+            for (int32_t kk = 0; kk < rp; kk += 32) {
+                if (kk > 0) load_p(kk);
+                bf16x8 wf[NB];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) wf[nb] = read_kn(lds, kk, nb);
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int32_t rb = wrow0 + mb * 16;
+                    if (hi <= rb || lo >= rb + 16) continue;        // wave-uniform
+                    const bf16x8 pf = as_bf16x8(pv[mb]);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf, acc[mb][nb], 0, 0, 0);
+                }
+            }
+        }
+    }
+    __syncthreads();                                // the C staging below reuses the same LDS
+
+    // ---- epilogue: fp32 -> bf16, stage the wave's block in LDS, store 16 bytes per lane
+    {
+        unsigned char* cs = lds + wave * (WTM * CS_PITCH * 2);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                bf16x4 o;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o[q] = (__bf16)acc[mb][nb][q];
+                const int m = mb * 16 + j, n = nb * 16 + 4 * kg;
+                *reinterpret_cast<bf16x4*>(cs + (m * CS_PITCH + n) * 2) = o;
+            }
+        // (the wave's own block: its LDS operations are carried out in order)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        constexpr int CPR = WTN / 8;                 // 16-byte chunks per row of the wave tile
+        constexpr int RPI = 64 / CPR;                // rows per store instruction
+        const int cchunk = lane % CPR, rsub = lane / CPR;
+        const int32_t col = col0 + wn * WTN + cchunk * 8;
+#pragma unroll 4
+        for (int i = 0; i < WTM / RPI; ++i) {
+            const int m = i * RPI + rsub;
+            const int32_t row = row0 + wm * WTM + m;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(cs + (m * CS_PITCH + cchunk * 8) * 2);
+            if (row < T && col < N) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(C + size_t(row) * ldc + col));
+        }
+    }
+}
+
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
+static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, const void* P,
+                              const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                              int32_t nproj, int32_t proj, hipStream_t st)
+{
+    constexpr int bytes = tile_lds_bytes<TM, TN, WN, STAGES>();
+    static_assert(bytes * OCC <= 160 * 1024, "LDS budget");
+    // the kernel needs more dynamic LDS than the default limit: raise it once per device
+    static std::atomic<uint64_t> raised{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = uint64_t(1) << (dev & 63);
+    if (!(raised.load(std::memory_order_acquire) & bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tile_kernel<W_KN, TM, TN, WM, WN, STAGES, OCC>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+        raised.fetch_or(bit, std::memory_order_release);
+    }
+    const int32_t tiles_m = (pd.T + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
+    gemm_tile_kernel<W_KN, TM, TN, WM, WN, STAGES, OCC><<<dim3(uint32_t(tiles_m) * uint32_t(tiles_n)), 64 * WM * WN, bytes, st>>>(
+        pd, (const uint16_t*)Z, (const uint16_t*)W, (const uint16_t*)P, (const uint16_t*)M, (uint16_t*)C,
+        K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, 1024 / TM);
+    return hipGetLastError();
+}
+
+namespace {
+
+// The kernels a product can run on and what a K tile of 64 costs there, measured (us, K = 4096; the tile kernels with
+// one workgroup per compute unit and, where two fit, with two; `fixed`: start, adapter term and stores of a tile):
+//     tile        persistent 256 x 256   128 x 256   128 x 128   128 x 64      64 x 64
+//     T = 40      112 us                 44          31          24            18
+//     T = 200     113                    46          33          25            21
+//     T = 500      80                    48          35          28 (256 wgs)  32 (512 wgs)
+//     T = 1000     81                    49          39 (256)    45 (512)      57
+//     T = 2000     84                    62 (256)    75          81            110
+//     T = 4096    102 (256)              122        156          193           261
+// (x [T, 4096] times W [4096, 4096]; the register-staged kernel that stood here before took 112 us below 256 tokens.)
+// A tile's bytes through the copy path and its LDS reads grow slower than its MFMAs, so the largest tile that still
+// gives every compute unit one is the best; what remains is the count of rounds, which this estimates.
+struct TileCost { int32_t tm, tn, per_cu; float k1, k2, fixed; };
+constexpr TileCost kTiles[] = {
+    {256, 256, 1, 1.35f, 0.f, 12.f},     // gemm_persistent_kernel
+    {128, 256, 1, 0.86f, 0.f, 6.f},
+    {128, 128, 1, 0.48f, 0.f, 6.f},
+    {128, 64, 2, 0.33f, 0.59f, 6.f},
+    {64, 64, 2, 0.23f, 0.39f, 6.f},
+};
+constexpr int32_t kCus = 256;            // fixed, so that the choice does not depend on the device
+
+float tile_cost(const TileCost& t, int64_t T, int32_t K, int32_t N)
+{
+    const int64_t n = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = int64_t(kCus) * t.per_cu;
+    const int64_t full = n / slots, rest = n % slots;
+    const float kt = float((K + BK - 1) / BK), most = t.per_cu == 2 ? t.k2 : t.k1;
+    return float(full) * (most * kt + t.fixed) + (rest ? (rest <= kCus ? t.k1 : most) * kt + t.fixed : 0.f);
+}
+
+}  // namespace
+
+bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw)
+{
+    if ((T + BM - 1) / BM * ((int64_t(N) + BN - 1) / BN) > 0x7fffffff) return false;
+    // 32-bit byte offsets inside a tile: 256 rows of K (or ldw) elements, 64 rows of ldw elements
+    if (int64_t(K) * 512 >= (int64_t(1) << 32) || int64_t(ldw) * 512 >= (int64_t(1) << 32)) return false;
+    return N >= 8 && K >= 8;
+}
+
+hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
+                     const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st,
+                     int32_t ldc, int32_t nproj, int32_t proj)
+{
+    if (pd.T == 0) return hipSuccess;
+    if (ldc == 0) ldc = N;
+    if (!gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;   // (plan creation has checked already)
+    int best = -1;
+    float least = 0.f;
+    for (int i = 0; i < int(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+        // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles
+        if (i == 0 && !((K % (2 * BK) == 0 || K >= kPersistentMinKTail) && pd.T >= BM && N >= BN)) continue;
+        const float c = tile_cost(kTiles[i], pd.T, K, N);
+        if (best < 0 || c < least) best = i, least = c;
+    }
+#define LOBRA_TILE(...)                                                                                          \
+    (transW ? launch_tile<false, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st)                 \
+            : launch_tile<true, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st))
+    switch (best) {
+    case 0: {
+        const int32_t tiles_m = (pd.T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+        // tile rows per sweep of the tile order: the workgroups that run on an XCD at one time share their
+        // Z and W panels through its L2 only while they walk K nearly in step, and the row bands that the 8
+        // XCDs sweep at one time (8 x rows x 256 x K x 2 bytes) should stay in the 256 MB infinity cache for
+        // their re-reads; measured on the five workloads, long K wants shorter sweeps (K = 8192 .. 28672:
+        // 4 rows up to 7 % faster than 8; K = 4096: 5 .. 8 alike)
+        return gemm_persistent(pd, transW, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, K > 4096 ? 4 : 6, st);
+    }
+    case 1: return LOBRA_TILE(128, 256, 2, 4, 3, 1);
+    case 2: return LOBRA_TILE(128, 128, 2, 2, 4, 1);
+    case 3: return LOBRA_TILE(128, 64, 2, 2, 3, 2);
+    default: return LOBRA_TILE(64, 64, 2, 2, 4, 2);
+    }
+#undef LOBRA_TILE
+}
+
+}  // namespace lobra

@@ -166,6 +166,70 @@ def test_persistent_gemm_tile_edges_and_round_remainders(T, d_in, d_out):
     check_problem(p, rows=rows, label="edges")
 
 
+@pytest.mark.parametrize("d_in,d_out", [
+    (72, 4104),       # a whole K tile and 8 of the next; backward: 65 K tiles, the last of 8, on two narrow column tiles
+    (8, 4000),        # K shorter than a K tile
+    (256, 4088),      # as many K tiles as the longest ring has slots; a partial last column tile
+    (328, 2056),      # one more than that, and a partial one
+    (4096, 264),      # backward wide: 16 column tiles of 256
+])
+def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
+    """The same first rows in batches of 40 to 2100 tokens: as the batch grows the product moves through tiles of
+    64 x 64, 128 x 64, 128 x 128 and 128 x 256 (which one is a matter of rows, columns and K).  The longest batch
+    against the oracle, the others bit for bit against it: every tile sums in the same order."""
+    import torch
+    lens, tasks = [], []
+    rng = np.random.default_rng(d_in + d_out)
+    for end in (40, 200, 500, 900, 2100):         # segments end where the shorter batches do
+        while sum(lens) < end:
+            lens.append(min(int(rng.choice([1, 31, 100, 257])), end - sum(lens)))
+            tasks.append((len(tasks) % 4) - 1)
+    off = np.concatenate([[0], np.cumsum(lens)])
+    p = wl.make_custom("tiles-%dx%d" % (d_in, d_out), "bf16", d_in, d_out, [16, 40, 8], off, tasks, 29, s=[2.0, -1.0, 0.5],
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, rows=sample_rows(p, 300), label="tiles")
+    for T in (1, 40, 200, 500, 900):
+        k = int(np.searchsorted(off, T))
+        q = wl.make_custom("tiles-%d" % T, "bf16", d_in, d_out, [16, 40, 8], np.minimum(off[:k + 1], T), tasks[:k], 29,
+                           s=[2.0, -1.0, 0.5], fill=False)
+        q.x, q.dy, q.W, q.A, q.B = p.x[:T], p.dy[:T], p.W, p.A, p.B
+        dq = bd.DeviceProblem(q)
+        dq.step()
+        torch.cuda.synchronize()
+        assert dq.guards_intact()
+        assert torch.equal(dq.y, dp.y[:T]) and torch.equal(dq.dx, dp.dx[:T]), T
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [
+    (4000, 520, 4040),     # forward: 8 k in the last pair of K tiles
+    (4100, 576, 4000),     # 64: its second tile lies wholly beyond K
+    (3900, 4040, 632),     # backward: 120
+    (4000, 4000, 712),     # backward: 72; forward on the tiled kernels
+    (300, 328, 136),       # tiled kernels in both directions
+])
+def test_gemm_k_beyond_the_last_whole_tile(T, d_in, d_out):
+    """K that is no multiple of a K tile, many output tiles (the persistent kernel's special last pairs) and few: against
+    the oracle, and with rows of infinities and NaNs, which must stay in their rows - what the copies put in place of
+    the k beyond K belongs to other k and must not be multiplied, not even by zero."""
+    import torch
+    lens = [1, 700, 33, 64, T - 798]
+    p = wl.make_custom("ktail-%dx%dx%d" % (T, d_in, d_out), "bf16", d_in, d_out, [16, 24], np.concatenate([[0], np.cumsum(lens)]),
+                       [0, 1, -1, 0, 1], 31, s=[2.0, -1.0], std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05) if T > 798 else \
+        wl.make_custom("ktail-%d" % T, "bf16", d_in, d_out, [16, 24], [0, 90, 200, T], [0, -1, 1], 31, s=[2.0, -1.0],
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, rows=sample_rows(p, 200), label="k tail")
+    want_y, want_dx = dp.y.clone(), dp.dx.clone()
+    bad = torch.tensor([5, T // 2, T - 1], device=dp.dev)
+    dp.x[bad] = float("inf")
+    dp.dy[bad] = float("nan")
+    dp.step()
+    torch.cuda.synchronize()
+    keep = torch.ones(T, dtype=torch.bool, device=dp.dev)
+    keep[bad] = False
+    assert torch.equal(dp.y[keep], want_y[keep]) and torch.equal(dp.dx[keep], want_dx[keep])
+    assert not bool(torch.isfinite(dp.y[bad].float()).any()) and bool(torch.isnan(dp.dx[bad].float()).all())
+
+
 @pytest.mark.parametrize("n_proj", [1, 2])
 def test_persistent_gemm_up_projection_at_every_kind_of_rank(n_proj):
     """The GEMM's fused up projection takes the operands of a tile's first segment from a copy made ahead of the

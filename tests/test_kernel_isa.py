@@ -117,6 +117,34 @@ def test_main_loop_has_no_instruction_clumps(kernels):
         assert best >= 128, (name, best)
 
 
+@pytest.fixture(scope="module")
+def ktail_kernels(tmp_path_factory):
+    """The same kernel for K that is no multiple of 128 (compiled from the same source as kernels of another name)."""
+    out = str(tmp_path_factory.mktemp("isa") / "gemm_persistent_ktail.s")
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "hip", "--cuda-device-only",
+           "-S", os.path.join(CSRC, "gemm_persistent_ktail.hip"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-3000:]
+    parts = re.split(r"^(_ZN5lobra28gemm_persistent_ktail_kernel\w+):", open(out).read(), flags=re.M)
+    ks = []
+    for i in range(1, len(parts), 2):
+        body = parts[i + 1]
+        end = body.index(".end_amdhsa_kernel")
+        code = [l.split(";")[0].strip() for l in body[:body.rindex("s_endpgm", 0, end) + 8].split("\n")]
+        ks.append((parts[i], [l for l in code if l and not l.startswith(".")], body[end:end + 3000]))
+    assert len(ks) == 2, [k[0] for k in ks]
+    return ks
+
+
+@pytest.mark.parametrize("check", [test_only_the_named_statements_touch_agprs, test_all_agprs_allocated_and_nothing_spilled,
+                                   test_m0_is_written_and_consumed_inside_one_statement,
+                                   test_no_mfma_reads_a_register_a_vector_alu_instruction_has_just_written,
+                                   test_main_loop_has_no_instruction_clumps], ids=lambda f: f.__name__)
+def test_ktail_kernels(ktail_kernels, check):
+    check(ktail_kernels)
+
+
 # ---------------------------------------------------------------------------------------------------------
 # The K-sliced rank-r kernel keeps several items' copies in flight and waits for them by count.  That only
 # works if the compiler adds no wait of its own that drains them: its tables must be read with scalar loads
