@@ -37,8 +37,8 @@
  * Two ways to call the layer:
  *   one-shot   lobra_mlora_workspace_bytes, lobra_mlora_fwd, lobra_mlora_bwd, lobra_token_task_map take the
  *              descriptor itself.  The library allocates no device memory and never synchronises: the
- *              tables derived from the descriptor are placed at the start of the caller's workspace by an
- *              asynchronous copy on the caller's stream.  Every call pays for building them on the host
+ *              tables derived from the descriptor are placed at the start of the caller's workspace, on the
+ *              caller's stream.  Every call pays for building them on the host
  *              (about 0.1 ms for 16384 tokens).
  *   with plan  a packed batch goes through every LoRA linear of every layer with the same segment table,
  *              so lobra_mlora_plan_init (device image in caller memory, asynchronous upload) or
@@ -251,10 +251,10 @@ LOBRA_API lobra_status lobra_mlora_plan_token_task_map(const lobra_mlora_plan *p
 
 /* ---- one-shot forms: the same operations on the descriptor itself (section 1 / Figure 1: the fused batch is
  * given as its task-tagged token runs; section 2.1: the layer).  Each call validates the descriptor, builds the
- * tables on the host, copies them asynchronously (on hip_stream) to the start of ws and runs the kernels behind
- * that copy.  No device memory is allocated or freed and nothing synchronises; the host image of the tables is
- * released by a host callback on the stream (which is why these forms cannot be captured in a HIP graph: use a
- * plan there).
+ * tables on the host, sends them (on hip_stream) to the start of ws - as kernel arguments, from 64 KiB on by an
+ * asynchronous copy whose source a host callback on the stream releases - and runs the kernels behind that.  No
+ * device memory is allocated or freed and nothing synchronises.  (Not for capture in a HIP graph: a replay would bring
+ * the same tables again; use a plan there.)
  *   lobra_mlora_workspace_bytes : bytes of ws that lobra_mlora_fwd (with h_save = NULL) and lobra_mlora_bwd
  *                                 need for this descriptor; host only, no HIP call; either out pointer may be NULL
  *   lobra_mlora_fwd / _bwd      : arguments as for the plan forms; ws (16-byte aligned, device) must hold

@@ -2,6 +2,7 @@
 // and the sequence of kernel launches of one forward / backward call.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -545,17 +546,36 @@ lobra_status lobra_mlora_plan_token_task_map(const lobra_mlora_plan* plan, int32
 }
 
 // ---- descriptor-taking one-shot forms: the plan of the call is built on the host, its device image is placed
-//      at the start of the caller's workspace by an asynchronous copy on the caller's stream, and the
-//      plan-taking entry point does the rest with what remains of the workspace.
+//      at the start of the caller's workspace on the caller's stream, and the plan-taking entry point
+//      does the rest with what remains of the workspace.
 namespace {
 
 inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+
+// A piece of a one-shot call's tables, on its way to the device as a kernel argument: the runtime has taken its copy
+// when the launch returns, so nothing of the host's has to outlive the call, and nothing waits.
+struct UploadPiece { int32_t v[1008]; };      // with the other arguments just below the 4 KiB of a launch
+// Up to this many bytes of tables go that way, in up to 17 launches of 2 us each; beyond it (some 70000 tokens) one copy
+// from pageable memory and a host callback that releases it are the cheaper way, or as cheap: at 2 KiB they cost 180 us of
+// stream time per call and a piece 3 us (padded chunks of 3072 tokens, four calls: 730 -> 173 us).
+constexpr size_t kUploadByArgument = 64 * 1024;
+
+__global__ __launch_bounds__(256) void upload_kernel(int32_t* __restrict__ dst, int32_t n, UploadPiece piece)
+{
+    const int32_t* src = piece.v;
+    for (int32_t i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
+}
+static_assert(sizeof(UploadPiece) + 16 <= 4096, "the arguments of a launch");
 
 // Frees a one-shot plan (and with it the host image its upload reads) once the stream has passed the upload.
 void free_oneshot_plan(void* p) { delete static_cast<lobra_mlora_plan*>(p); }
 
 lobra_status release_after(hipStream_t st, lobra_mlora_plan* p)
 {
+    if (p->blob_bytes <= kUploadByArgument) {       // nothing in flight reads it
+        delete p;
+        return LOBRA_OK;
+    }
     if (hipLaunchHostFunc(st, free_oneshot_plan, p) == hipSuccess) return LOBRA_OK;
     // no host callback on this stream: wait for the upload instead (slow path, never taken on a plain stream)
     const hipError_t e = hipStreamSynchronize(st);
@@ -567,8 +587,18 @@ lobra_status release_after(hipStream_t st, lobra_mlora_plan* p)
 lobra_status upload_oneshot(lobra_mlora_plan* p, void* dev, hipStream_t st)
 {
     if (hipGetDevice(&p->device) != hipSuccess) return LOBRA_ERR_HIP;
-    if (hipMemcpyAsync(dev, p->host_blob.data(), p->blob_bytes, hipMemcpyHostToDevice, st) != hipSuccess)
+    if (p->blob_bytes <= kUploadByArgument) {
+        constexpr size_t most = sizeof(UploadPiece::v) / sizeof(int32_t);
+        UploadPiece piece;
+        for (size_t at = 0; at < p->host_blob.size(); at += most) {
+            const size_t n = std::min(most, p->host_blob.size() - at);
+            std::memcpy(piece.v, p->host_blob.data() + at, n * sizeof(int32_t));
+            upload_kernel<<<1, 256, 0, st>>>(static_cast<int32_t*>(dev) + at, int32_t(n), piece);
+            if (hipGetLastError() != hipSuccess) return LOBRA_ERR_HIP;
+        }
+    } else if (hipMemcpyAsync(dev, p->host_blob.data(), p->blob_bytes, hipMemcpyHostToDevice, st) != hipSuccess) {
         return LOBRA_ERR_HIP;
+    }
     p->dev_blob = dev;
     p->owns_blob = false;
     return LOBRA_OK;

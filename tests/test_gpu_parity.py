@@ -568,6 +568,41 @@ def test_one_shot_descriptor_forms_against_the_oracle(which):
     assert np.array_equal(out_cnt.cpu().numpy(), np.bincount(ref[ref >= 0], minlength=p.n_tasks))
 
 
+@pytest.mark.parametrize("T", [31, 2016, 40000, 90000])
+def test_one_shot_tables_in_one_piece_in_several_and_by_copy(T):
+    """The one-shot calls' tables travel as kernel arguments (a launch per 4 KiB), large ones by a copy: several batches in
+    a row without a wait between them, whose descriptors are gone when the calls return, against the plan forms."""
+    import torch
+    rng = np.random.default_rng(T)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.choice([1, 30, 64, 500])), T - sum(lens)))
+    off = np.concatenate([[0], np.cumsum(lens)])
+    runs = []
+    for k in range(4):
+        p = wl.make_custom("tables-%d" % T, "bf16", 64, 72, [8, 16, 5], off, rng.integers(-1, 3, len(lens)), 77 + k)
+        dp = bd.DeviceProblem(p)
+        dp.step()
+        want = [t.clone() for t in (dp.y, dp.dx, dp.dA, dp.dB)]
+        for t in (dp.y, dp.dx, dp.dA, dp.dB):
+            t.fill_(7.0)
+        d, keep = bd.make_desc(p.dtype, p.T, p.d_in, p.d_out, p.rank_off, p.seg_off, p.seg_task)
+        runs.append((p, dp, want, torch.empty(max(bd.lobra_mlora_workspace_bytes(d)), dtype=torch.uint8, device="cuda")))
+    if T in (31, 90000):
+        assert (bd.plan_device_bytes(d) > 64 * 1024) == (T == 90000)
+    torch.cuda.synchronize()
+    for p, dp, _, ws in runs:
+        d, keep = bd.make_desc(p.dtype, p.T, p.d_in, p.d_out, p.rank_off, p.seg_off, p.seg_task)
+        bd.lobra_mlora_fwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, dp.h_save, ws)
+        bd.lobra_mlora_bwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, dp.h_save, dp.dx, dp.dA, dp.dB, 0, ws)
+        for a in keep:
+            a.fill(-1)
+    torch.cuda.synchronize()
+    for p, dp, want, _ in runs:
+        for a, b, name in zip(want, (dp.y, dp.dx, dp.dA, dp.dB), ("y", "dx", "dA", "dB")):
+            assert torch.equal(a, b), name
+
+
 def test_plan_in_caller_memory_and_under_graph_capture():
     """lobra_mlora_plan_init: the plan's device image lives in a buffer of the caller's (no hipMalloc, no blocking
     copy); its calls give the results of a lobra_mlora_plan_create plan bit for bit, also as replays of a HIP graph."""
