@@ -1,0 +1,406 @@
+// The fp32 path on the matrix cores (gfx950 v_mfma_f32_16x16x4_f32: fp32 operands, fp32 sums - twice the rate of the
+// vector ALUs, same precision):
+//   gemm        C = Z op(W) + P M_t        (y = x W + P B_t;  dx = dy W^T + P A_t)
+//   shrink      P = s_t Z M_t^T            (Z = x, M = A: s_t A_t x_i;  Z = dy, M = B: s_t B_t dy_i)
+//   gradreduce  dM_t = sum_i P_i^T Z_i     (dB_t from P = s h, Z = dy;  dA_t from P = s g, Z = x), stage 1
+// (paper section 2.1: X W + X (down)(up), applied per task to a fused batch, section 1, and its derivatives).
+//
+// Operands of the MFMA: lane (i, kg), i = lane % 16, kg = lane / 16, supplies element k = kg of row i of "A" and of
+// column i of "B"; a lane gets the results (4 kg .. 4 kg + 3, i).  A lane fetches four consecutive k of its row at a time
+// and uses them in four MFMAs, MFMA q taking the k {q, 4 + q, 8 + q, 12 + q} of a group of 16: any dealing of the k
+// will do as long as both operands follow it.
+//
+// VEC: rows start on 16-byte boundaries (widths that are multiples of 4), so four elements are one load.  Other
+// widths take the same kernels with four guarded loads.
+#include "kernels.h"
+
+namespace lobra {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// elements i .. i + 3 of the row at p; elements from n on read as 0
+template <bool VEC> __device__ __forceinline__ f32x4 load4(const float* __restrict__ p, int32_t i, int32_t n)
+{
+    if constexpr (VEC) {
+        return i < n ? *reinterpret_cast<const f32x4*>(p + i) : f32x4{0.f, 0.f, 0.f, 0.f};
+    } else {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = i + e < n ? p[i + e] : 0.f;
+        return v;
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+constexpr int FBK = 32;                  // K step of the GEMM: one 128-byte line per row
+constexpr int FPITCH = FBK + 4;          // [rows][k] tiles in LDS: 16 rows' 16-byte pieces fall into 16 bank groups
+
+}  // namespace
+
+// -------------------------------------------------------------------------------------------
+// gemm: TM x TN per workgroup of 2 x 2 waves, K step 32, global -> registers -> LDS one K step ahead.  Bound by the matrix
+// cores: a K step of a 64 x 64 tile is 1024 cycles of MFMAs and a quarter of that in LDS reads (8192 x 2048 x 2048: 120
+// TFLOP/s, without the global loads 127, of 157).  The adapter term is further K steps per segment, with the rows
+// outside the segment masked.
+// -------------------------------------------------------------------------------------------
+template <bool TRANSW, int TM, int TN, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
+                                                       const float* __restrict__ P, const float* __restrict__ M,
+                                                       float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                                                       int32_t nproj, int32_t proj, int32_t tiles_n)
+{
+    // ldc: row pitch of C.  nproj > 1: projection `proj` of a fused shared-input call - of every task's
+    // ranks only the window [proj r, (proj + 1) r) takes part (columns of P, rows of M; M pitch N)
+    constexpr int WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
+    constexpr int ZL = TM * (FBK / 4) / 256, WL = TN * (FBK / 4) / 256;     // 16-byte pieces per thread and K step
+    constexpr int NPITCH = TN + 4;       // [k][n] tile: k rows 4 apart start 16 banks apart
+    constexpr int ZS = TM * FPITCH, WS = TRANSW ? TN * FPITCH : FBK * NPITCH;
+    __shared__ __attribute__((aligned(16))) float lds[2][ZS + WS];
+    static_assert(16 * NPITCH <= WS, "the adapter's rank rows fit the W tile");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
+    const int32_t id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int32_t row0 = id / tiles_n * TM, col0 = id % tiles_n * TN;
+    const int32_t T = pd.T;
+
+    f32x4 acc[MB][NB];                   // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column nb 16 + 4 kg + v
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // rows beyond T and columns beyond N repeat the last one (what they produce is not stored); k beyond K reads as 0
+    f32x4 zr[ZL], wr[WL];
+    auto fetch = [&](int32_t k0) {
+#pragma unroll
+        for (int u = 0; u < ZL; ++u) {
+            const int c = tid + 256 * u, row = c / (FBK / 4), k = k0 + 4 * (c % (FBK / 4));
+            zr[u] = load4<VEC>(Z + size_t(min(row0 + row, T - 1)) * K, k, K);
+        }
+#pragma unroll
+        for (int u = 0; u < WL; ++u) {
+            const int c = tid + 256 * u;
+            if (TRANSW) {                // op(W)[k][n] = W[n*ldw + k]
+                const int row = c / (FBK / 4), k = k0 + 4 * (c % (FBK / 4));
+                wr[u] = load4<VEC>(W + size_t(min(col0 + row, N - 1)) * ldw, k, K);
+            } else {                     // op(W)[k][n] = W[k*ldw + n]
+                const int k = k0 + c / (TN / 4), n = col0 + 4 * (c % (TN / 4));
+                wr[u] = load4<VEC>(W + size_t(min(k, K - 1)) * ldw, k < K ? n : N, N);
+            }
+        }
+    };
+    auto stash = [&](float* zs) {
+#pragma unroll
+        for (int u = 0; u < ZL; ++u) {
+            const int c = tid + 256 * u;
+            *reinterpret_cast<f32x4*>(zs + c / (FBK / 4) * FPITCH + 4 * (c % (FBK / 4))) = zr[u];
+        }
+#pragma unroll
+        for (int u = 0; u < WL; ++u) {
+            const int c = tid + 256 * u;
+            if (TRANSW) *reinterpret_cast<f32x4*>(zs + ZS + c / (FBK / 4) * FPITCH + 4 * (c % (FBK / 4))) = wr[u];
+            else *reinterpret_cast<f32x4*>(zs + ZS + c / (TN / 4) * NPITCH + 4 * (c % (TN / 4))) = wr[u];
+        }
+    };
+    // 16 k from k0 on of the tiles at zs / ws
+    auto mac = [&](const float* zs, const float* ws, int k0, auto trans) {
+        f32x4 zf[MB], wf[NB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) zf[mb] = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + k0 + 4 * kg);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = wn * WTN + nb * 16 + j;
+            if constexpr (decltype(trans)::value) {
+                wf[nb] = *reinterpret_cast<const f32x4*>(ws + n * FPITCH + k0 + 4 * kg);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) wf[nb][q] = ws[(k0 + 4 * kg + q) * NPITCH + n];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(wf[nb][q], zf[mb][q], acc[mb][nb]);
+    };
+    using trans_c = std::integral_constant<bool, TRANSW>;
+
+    fetch(0);
+    stash(lds[0]);
+    __syncthreads();
+    int buf = 0;
+    for (int32_t k0 = 0; k0 < K; k0 += FBK) {
+        const bool more = k0 + FBK < K;
+        if (more) fetch(k0 + FBK);
+        mac(lds[buf], lds[buf] + ZS, 0, trans_c{});
+        mac(lds[buf], lds[buf] + ZS, 16, trans_c{});
+        if (more) stash(lds[buf ^ 1]);   // (its last readers are behind the previous barrier)
+        __syncthreads();
+        buf ^= 1;
+    }
+    // adapter term: for every adapter segment that crosses the tile, the task's ranks are further k of the same tile
+    // product, 16 at a time: acc += P[rows, ranks] M_t[ranks, cols], rows outside the segment and ranks beyond r_t zero
+    // (the loops are uniform over the workgroup)
+    if (P) {
+        const int32_t row_end = min(row0 + TM, T);
+        float *zs = lds[0], *ws = lds[0] + ZS;
+        for (int32_t sg = pd.rowblk_seg[row0 / kRowBlock]; sg < pd.nseg; ++sg) {
+            const int32_t seg_lo = pd.cseg_off[sg];
+            if (seg_lo >= row_end) break;
+            const int32_t t = pd.cseg_task[sg];
+            if (t < 0) continue;
+            const int32_t lo = max(seg_lo, row0), hi = min(pd.cseg_off[sg + 1], row_end);
+            const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
+            const int32_t r0 = pd.rank_off[t] + pofs;
+            for (int32_t c0 = 0; c0 < r; c0 += 16) {
+                for (int e = tid; e < TM * 16; e += 256) {
+                    const int kk = e & 15, row = row0 + (e >> 4);
+                    zs[(e >> 4) * FPITCH + kk] = (row >= lo && row < hi && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
+                }
+                for (int e = tid; e < TN * 16; e += 256) {
+                    const int n = col0 + e % TN, kk = e / TN;
+                    ws[kk * NPITCH + e % TN] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
+                }
+                __syncthreads();
+                mac(zs, ws, 0, std::false_type{});
+                __syncthreads();
+            }
+        }
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int32_t row = row0 + wm * WTM + mb * 16 + j;
+        if (row >= T) continue;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int32_t col = col0 + wn * WTN + nb * 16 + 4 * kg;
+            float* c = C + size_t(row) * ldc + col;
+            if (VEC && col < N) {
+                *reinterpret_cast<f32x4*>(c) = acc[mb][nb];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (col + v < N) c[v] = acc[mb][nb][v];
+            }
+        }
+    }
+}
+
+hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,
+                    int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st)
+{
+    const bool vec = ((K | N | ldw | ldc) & 3) == 0;
+    // The larger the tile the fewer loads and LDS writes per MFMA, as long as every compute unit has work (us per product;
+    // 8192 x 2048 x 2048: 775 with tiles of 32, 627 of 64, 571 of 128; 3000 x 1024 x 1024: 85, 75, 96; 2000 x 363 x 517: 29, 33, 54; the vector-ALU kernel that
+    // stood here before took 119 for the latter)
+    auto tiles = [&](int32_t t) { return int64_t((pd.T + t - 1) / t) * ((N + t - 1) / t); };
+    const int32_t tm = tiles(128) >= 384 ? 128 : (tiles(64) >= 512 ? 64 : 32), tiles_n = (N + tm - 1) / tm;
+    const dim3 grid(uint32_t((pd.T + tm - 1) / tm) * uint32_t(tiles_n));
+#define LOBRA_F32_GEMM(TR, TILE, VEC) \
+    gemm_f32_kernel<TR, TILE, TILE, VEC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
+#define LOBRA_F32_GEMM2(TR, TILE) do { if (vec) LOBRA_F32_GEMM(TR, TILE, true); else LOBRA_F32_GEMM(TR, TILE, false); } while (0)
+#define LOBRA_F32_GEMM3(TILE) do { if (transW) LOBRA_F32_GEMM2(true, TILE); else LOBRA_F32_GEMM2(false, TILE); } while (0)
+    if (tm == 128) LOBRA_F32_GEMM3(128);
+    else if (tm == 64) LOBRA_F32_GEMM3(64);
+    else LOBRA_F32_GEMM3(32);
+    return hipGetLastError();
+}
+
+// -------------------------------------------------------------------------------------------
+// shrink: one workgroup per half of a token block (16 tokens of one task), NW waves split K in groups of 16; both operands
+// go straight from global memory into registers, "A" = 16 rank rows, "B" = 16 token rows, four rank blocks at a time.
+// Latency and memory bound: a wave keeps the loads of two groups in flight.
+// -------------------------------------------------------------------------------------------
+template <int NRB, bool VEC>
+__global__ __launch_bounds__(512) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
+                                                         const float* __restrict__ s, float* __restrict__ P, int32_t D,
+                                                         int32_t ldz, int32_t nproj, int32_t proj)
+{
+    // nproj > 1 (fused shared-input projections): projection `proj` only - Z is its column block of
+    // dy (row pitch ldz), M its rows of the compact up factors, and of the task's ranks the window
+    // [proj r, (proj + 1) r) is read and written
+    constexpr int NW = 8;
+    __shared__ f32x4 red[NW][NRB][64];
+    const TokenBlock b = pd.tb[blockIdx.x >> 1];
+    const int half = blockIdx.x & 1;
+    if (16 * half >= b.nrows) return;
+    const int32_t r = (pd.rank_off[b.task + 1] - pd.rank_off[b.task]) / nproj;
+    const int32_t pofs = proj * r;
+    const int32_t plim = proj == nproj - 1 ? pd.r_max - pofs : r;   // ranks (and zero padding) stored here
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, kg = lane >> 4;
+    const int32_t tok = 16 * half + j;
+    const float* zrow = Z + size_t(b.row0 + min(tok, b.nrows - 1)) * ldz;    // rows beyond the block repeat its last one
+    const float st = s[b.task];
+    for (int32_t p0 = 0; p0 < plim; p0 += 16 * NRB) {
+        f32x4 acc[NRB];
+        const float* mrow[NRB];          // ranks beyond r_t repeat the last rank row; their sums are not stored
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            mrow[rb] = M + size_t(b.rank_row0 + pofs + min(p0 + 16 * rb + j, r - 1)) * D;
+        }
+        const int32_t nrb = min(NRB, (r - p0 + 15) >> 4);           // rank blocks with ranks of the task (uniform)
+        f32x4 z[2], m[2][NRB];
+        auto load = [&](int u, int32_t g) {
+            z[u] = load4<VEC>(zrow, 16 * g + 4 * kg, D);
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+                if (rb < nrb) m[u][rb] = load4<VEC>(mrow[rb], 16 * g + 4 * kg, D);
+        };
+        auto mac = [&](int u) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb)
+                    if (rb < nrb) acc[rb] = mfma4(m[u][rb][q], z[u][q], acc[rb]);
+        };
+        if (nrb > 0) {
+            const int32_t ng = (D + 15) >> 4;
+            load(0, wave);               // (groups beyond D read as zero)
+            for (int32_t g = wave; g < ng; g += 2 * NW) {
+                load(1, g + NW);
+                mac(0);
+                load(0, g + 2 * NW);
+                mac(1);
+            }
+        }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) red[wave][rb][lane] = acc[rb];
+        __syncthreads();
+        // rank block rb is summed by wave rb, in wave order: lane (j, kg) stores ranks 4 kg .. 4 kg + 3 of token j
+        if (wave < NRB) {
+            f32x4 sum = red[0][wave][lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) sum = sum + red[w][wave][lane];
+            if (tok < b.nrows)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int32_t p = p0 + 16 * wave + 4 * kg + v;
+                    if (p < plim) P[size_t(b.row0 + tok) * pd.r_max + pofs + p] = p < r ? st * sum[v] : 0.f;
+                }
+        }
+        __syncthreads();
+    }
+}
+
+hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
+                      int32_t nproj, int32_t proj, hipStream_t st)
+{
+    const bool vec = ((D | ldz) & 3) == 0;
+    const int nrb = (pd.r_max / nproj + 15) / 16;
+#define LOBRA_F32_SHRINK(NRB)                                                                                              \
+    do {                                                                                                                   \
+        if (vec) shrink_f32_kernel<NRB, true><<<2 * pd.ntb, 512, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);            \
+        else shrink_f32_kernel<NRB, false><<<2 * pd.ntb, 512, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);               \
+    } while (0)
+    if (nrb <= 1) LOBRA_F32_SHRINK(1);
+    else if (nrb <= 2) LOBRA_F32_SHRINK(2);
+    else LOBRA_F32_SHRINK(4);
+    return hipGetLastError();
+}
+
+// -------------------------------------------------------------------------------------------
+// gradreduce stage 1: one workgroup per (chunk, 256 columns), wave w owns 64 columns for all tokens of the chunk.  Lane (i, kg)
+// loads the four columns 4 i .. of token kg of a group of four tokens: element e feeds MFMA e, whose result columns are
+// {4 i + e}, so a lane ends up with four consecutive columns.  "A" = the projected activations, rank i of token kg.
+// -------------------------------------------------------------------------------------------
+template <int NRB, bool VEC>
+__global__ __launch_bounds__(256) void grad_f32_kernel(PlanDev pd, const float* __restrict__ P, const float* __restrict__ Z,
+                                                       float* __restrict__ part, int32_t D, int32_t ldz, int32_t nproj,
+                                                       int32_t proj, int32_t tiles_a, const float* __restrict__ P2,
+                                                       const float* __restrict__ Z2, float* __restrict__ part2, int32_t D2)
+{
+    // nproj > 1: projection `proj` of a fused call - Z is its column block (row pitch ldz), and of the
+    // task's ranks only the window [proj r, (proj + 1) r) is reduced (columns of P, rows of part).
+    // One launch can serve two gradients (nproj = 1): column tiles from tiles_a on belong to (P2, Z2, part2, D2).
+    int32_t coltile = blockIdx.y;
+    if (coltile >= tiles_a) {
+        coltile -= tiles_a;
+        P = P2;
+        Z = Z2;
+        part = part2;
+        D = ldz = D2;
+    }
+    const GradChunk c = pd.chunks[blockIdx.x];
+    const int32_t r = (pd.rank_off[c.task + 1] - pd.rank_off[c.task]) / nproj;
+    const int32_t pofs = proj * r;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, kg = lane >> 4;
+    const int32_t col = coltile * 256 + wave * 64 + 4 * i;
+    if (coltile * 256 + wave * 64 >= D) return;          // the wave has no column (it meets no barrier)
+    for (int32_t p0 = 0; p0 < r; p0 += 16 * NRB) {
+        f32x4 acc[NRB][4];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[rb][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int32_t nrb = min(NRB, (r - p0 + 15) >> 4);           // uniform
+        for (int32_t bi = c.tb_begin; bi < c.tb_end; ++bi) {
+            const TokenBlock b = pd.tb[bi];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (16 * h >= b.nrows) break;            // uniform
+                f32x4 z[4];
+                float p[NRB][4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {            // tokens beyond the block: zero in both operands
+                    const int32_t tok = 16 * h + 4 * q + kg;
+                    const size_t row = size_t(b.row0 + min(tok, b.nrows - 1));
+                    z[q] = load4<VEC>(Z + row * ldz, tok < b.nrows ? col : D, D);
+#pragma unroll
+                    for (int rb = 0; rb < NRB; ++rb) {
+                        const int32_t k = p0 + 16 * rb + i;
+                        p[rb][q] = (rb < nrb && tok < b.nrows && k < r) ? P[row * pd.r_max + pofs + k] : 0.f;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int rb = 0; rb < NRB; ++rb)
+                        if (rb < nrb)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[rb][e] = mfma4(p[rb][q], z[q][e], acc[rb][e]);
+            }
+        }
+        // acc[rb][e][v]: rank p0 + 16 rb + 4 kg + v, column col + e
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int32_t k = p0 + 16 * rb + 4 * kg + v;
+                if (k >= r || col >= D) continue;
+                float* dst = part + size_t(c.part_row0 + pofs + k) * D + col;
+                if constexpr (VEC) {
+                    *reinterpret_cast<f32x4*>(dst) = f32x4{acc[rb][0][v], acc[rb][1][v], acc[rb][2][v], acc[rb][3][v]};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < D) dst[e] = acc[rb][e][v];
+                }
+            }
+    }
+}
+
+hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, float* part, int32_t D, int32_t ldz, int32_t nproj,
+                           int32_t proj, const float* P2, const float* Z2, float* part2, int32_t D2, hipStream_t st)
+{
+    const int32_t tiles_a = (D + 255) / 256, tiles_b = P2 ? (D2 + 255) / 256 : 0;
+    const dim3 grid(pd.nchunks, tiles_a + tiles_b);
+    if (grid.y > 65535u) return hipErrorInvalidValue;
+    const bool vec = ((D | ldz | (P2 ? D2 : 0)) & 3) == 0;
+    const int nrb = (pd.r_max / nproj + 15) / 16;
+#define LOBRA_F32_GRAD(NRB)                                                                                                  \
+    do {                                                                                                                     \
+        if (vec) grad_f32_kernel<NRB, true><<<grid, 256, 0, st>>>(pd, P, Z, part, D, ldz, nproj, proj, tiles_a, P2, Z2, part2, D2); \
+        else grad_f32_kernel<NRB, false><<<grid, 256, 0, st>>>(pd, P, Z, part, D, ldz, nproj, proj, tiles_a, P2, Z2, part2, D2);    \
+    } while (0)
+    if (nrb <= 1) LOBRA_F32_GRAD(1);
+    else if (nrb <= 2) LOBRA_F32_GRAD(2);
+    else LOBRA_F32_GRAD(4);
+    return hipGetLastError();
+}
+
+}  // namespace lobra

@@ -49,6 +49,13 @@ hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const vo
 // One launch for up to two gradients (jb.out == nullptr: only ja).
 hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate,
                            hipStream_t st);
+// ---- fp32 storage on the matrix cores (fp32_mfma.hip), reached through the three above; arguments as there ------------
+hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
+                      int32_t nproj, int32_t proj, hipStream_t st);
+hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,
+                    int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st);
+hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, float* part, int32_t D, int32_t ldz, int32_t nproj,
+                           int32_t proj, const float* P2, const float* Z2, float* part2, int32_t D2, hipStream_t st);
 // ---- bf16 MFMA kernels ------------------------------------------------------------------------
 // C[T, N] = Z[T, K] * op(W) + P * M_t with P bf16 [T][r_pad] (already scaled by s_t, zero beyond r_t).
 // ldc: row pitch of C (0: N).  nproj > 1: projection `proj` of a fused shared-input call - of every

@@ -112,14 +112,11 @@ hipError_t plain_shrink(const PlanDev& pd, int dtype, const void* Z, const void*
 {
     if (pd.ntb == 0) return hipSuccess;
     if (ldz == 0) ldz = D;
-    const bool vec = (D & 3) == 0 && (ldz & 3) == 0;   // rows then start on 16-byte (fp32) or 8-byte (bf16) boundaries
+    if (dtype == LOBRA_F32) return shrink_f32(pd, (const float*)Z, (const float*)M, s, P, D, ldz, nproj, proj, st);
+    const bool vec = (D & 3) == 0 && (ldz & 3) == 0;   // rows then start on 8-byte boundaries
 #define LOBRA_PLAIN_SHRINK(E, VW) \
     plain_shrink_kernel<E, VW><<<pd.ntb, 256, 0, st>>>(pd, (const E*)Z, (const E*)M, s, P, D, ldz, nproj, proj)
-    if (dtype == LOBRA_F32) {
-        if (vec) LOBRA_PLAIN_SHRINK(float, 4); else LOBRA_PLAIN_SHRINK(float, 1);
-    } else {
-        if (vec) LOBRA_PLAIN_SHRINK(uint16_t, 4); else LOBRA_PLAIN_SHRINK(uint16_t, 1);
-    }
+    if (vec) LOBRA_PLAIN_SHRINK(uint16_t, 4); else LOBRA_PLAIN_SHRINK(uint16_t, 1);
 #undef LOBRA_PLAIN_SHRINK
     return hipGetLastError();
 }
@@ -256,15 +253,13 @@ hipError_t plain_gemm(const PlanDev& pd, int dtype, bool transW, const void* Z, 
 {
     if (pd.T == 0) return hipSuccess;
     if (ldc == 0) ldc = N;
+    if (dtype == LOBRA_F32)
+        return gemm_f32(pd, transW, (const float*)Z, (const float*)W, P, (const float*)M, (float*)C, K, N, ldw, ldc, nproj, proj, st);
     const dim3 grid((N + 63) / 64, (pd.T + 63) / 64);
     if (grid.y > 65535u) return hipErrorInvalidValue;
 #define LOBRA_LAUNCH(E, TR) \
     plain_gemm_kernel<E, TR><<<grid, 256, 0, st>>>(pd, (const E*)Z, (const E*)W, P, (const E*)M, (E*)C, K, N, ldw, ldc, nproj, proj)
-    if (dtype == LOBRA_F32) {
-        if (transW) LOBRA_LAUNCH(float, true); else LOBRA_LAUNCH(float, false);
-    } else {
-        if (transW) LOBRA_LAUNCH(uint16_t, true); else LOBRA_LAUNCH(uint16_t, false);
-    }
+    if (transW) LOBRA_LAUNCH(uint16_t, true); else LOBRA_LAUNCH(uint16_t, false);
 #undef LOBRA_LAUNCH
     return hipGetLastError();
 }
@@ -382,8 +377,18 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJo
         for (int q = 0; q < 4; ++q) res[q] = accumulate ? o[q] + acc[q] : acc[q];
         *reinterpret_cast<f4*>(o) = res;
     } else {
-        for (int32_t c = c0; c < c1; ++c)
-            for (int q = 0; q < nv; ++q) acc[q] += row_ptr(c)[q];
+        for (int32_t c = c0; c < c1; c += 8) {   // (the same for rows that do not start on 16-byte boundaries)
+            float v[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[u][q] = (c + u < c1 && q < nv) ? row_ptr(c + u)[q] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c + u < c1)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[q] += v[u][q];
+        }
         float* o = out + size_t(R) * D + col;
         for (int q = 0; q < nv; ++q) o[q] = accumulate ? o[q] + acc[q] : acc[q];
     }
@@ -408,13 +413,13 @@ hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const vo
     if (pd.nchunks == 0) return hipSuccess;
     if (ldz == 0) ldz = D;
     if (P2 && nproj != 1) return hipErrorInvalidValue;
+    if (dtype == LOBRA_F32)
+        return grad_f32_stage1(pd, (const float*)P, (const float*)Z, part, D, ldz, nproj, proj, (const float*)P2, (const float*)Z2,
+                               part2, D2, st);
     const int32_t tiles_a = (D + 255) / 256, tiles_b = P2 ? (D2 + 255) / 256 : 0;
     const dim3 grid(pd.nchunks, tiles_a + tiles_b);
     if (grid.y > 65535u) return hipErrorInvalidValue;
-    if (dtype == LOBRA_F32)
-        plain_gradreduce_kernel<float, float><<<grid, 256, 0, st>>>(pd, (const float*)P, pd.r_max, (const float*)Z, part, D, ldz, nproj, proj,
-                                                                     tiles_a, (const float*)P2, (const float*)Z2, part2, D2);
-    else if (!p_bf16)
+    if (!p_bf16)
         plain_gradreduce_kernel<uint16_t, float><<<grid, 256, 0, st>>>(pd, (const float*)P, pd.r_max, (const uint16_t*)Z, part, D, ldz, nproj, proj,
                                                                         tiles_a, (const float*)P2, (const uint16_t*)Z2, part2, D2);
     else

@@ -241,6 +241,10 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         //    [4, 64] token blocks ([1, 64] on the plain path); fewer, longer chunks mean less partial-sum traffic.
         const int64_t coltiles = (std::min(d->d_in, d->d_out) + 127) / 128;
         int64_t cb = (int64_t(T) * coltiles / 1024 + kTokenBlock - 1) / kTokenBlock;
+        // (fp32: some hundred workgroups of 256 columns, whose waves share no work; shorter chunks make more partial
+        //  sums than they are worth, longer ones a longer stage 1: chunks of 1 / 3 blocks at 3000 x 1024 x 1024 21 / 19 us for both
+        //  stages, of 4 / 16 blocks at 8192 x 2048 x 2048 33 / 48 us)
+        if (!p->mfma) cb = (int64_t(T) * coltiles / 512 + kTokenBlock - 1) / kTokenBlock;
         // Where dB rides with the projection of dy, stage 1 is one short launch for dA alone and what counts is
         // its balance: three workgroups per compute unit (at workload 2: 24 chunks of 21 or 22 blocks, 27.9 us,
         // against 36 of 16 or 3 blocks, 30.8 us; and a quarter fewer partial sums for stage 2)

@@ -250,6 +250,37 @@ def test_persistent_gemm_up_projection_at_every_kind_of_rank(n_proj):
     check_problem(p, label="up projection ranks %s x %d" % (ranks, n_proj))
 
 
+@pytest.mark.parametrize("T,d_in,d_out", [
+    (1, 1, 1), (33, 31, 5), (65, 16, 64), (300, 100, 36),     # tiles of 32, widths with and without 16-byte rows
+    (2100, 48, 1028), (2100, 1025, 130),                      # tiles of 64
+    (6200, 20, 1028), (6200, 1023, 1031),                     # tiles of 128
+])
+def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
+    """The fp32 path against the oracle at the edges of its tiles (32, 64, 128 by the number of tiles), K steps and 16-byte
+    rows, ranks below, at and above 16, 32 and 64; a row of infinities and one of NaNs stay in their rows."""
+    import torch
+    rng = np.random.default_rng(T + d_in)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.choice([1, 15, 16, 17, 31, 100, 300])), T - sum(lens)))
+    ranks = [1, 16, 17, 40, 128]
+    p = wl.make_custom("f32-%dx%dx%d" % (T, d_in, d_out), "f32", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]),
+                       rng.integers(-1, len(ranks), len(lens)), 41, s=[2.0, -1.0, 0.5, 1.0, 3.0], std_x=1.0, std_w=0.05,
+                       std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, rows=sample_rows(p, 300), label="f32 tiles")
+    if T < 33:
+        return
+    y, dx = dp.y.clone(), dp.dx.clone()
+    bad = torch.tensor([2, T - 1], device=dp.dev)
+    dp.x[bad], dp.dy[bad] = float("nan"), float("inf")
+    dp.step()
+    torch.cuda.synchronize()
+    keep = torch.ones(T, dtype=torch.bool, device=dp.dev)
+    keep[bad] = False
+    assert torch.equal(dp.y[keep], y[keep]) and torch.equal(dp.dx[keep], dx[keep])
+    assert bool(torch.isnan(dp.y[bad]).all()) and not bool(torch.isfinite(dp.dx[bad]).any())
+
+
 def test_config3_reversed_rank_pairing():
     p = wl.make_config(3, "shuffled", d_in=192, d_out=344, reverse_ranks=True)
     check_problem(p)
