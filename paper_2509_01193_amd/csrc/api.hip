@@ -374,7 +374,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     // fused shared-input projections: every column tile of y takes the rank window of H and the rows of
     // the compact B that belong to its projection - in one launch when no tile straddles two projections,
     // else in one launch per projection (its column block of W and y)
-    if (pd.dg % 256 == 0) {
+    if (pd.dg % 64 == 0) {
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, W, adapters ? hb + p.p_layout.p_tok : nullptr, B, y, pd.d_in,
                                pd.d_out, pd.d_out, st, pd.d_out, p.n_proj, -1));
@@ -483,13 +483,11 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
                                      p.sliced_in, spart));
             H = Hr;
         }
-        // G = s dy B^T; with fused projections one launch per projection: its column block of dy
-        // against its rows of the compact B, written into its rank window of G
-        for (int32_t j = 0; j < p.n_proj; ++j)
-            LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
-                         shrink_mfma(pd, static_cast<const char*>(dy) + size_t(j) * pd.dg * 2, B, s,
-                                     G + p.p_layout.p_tok, G + p.p_layout.p_blk, pd.dg, pd.d_out, p.n_proj, j, st,
-                                     p.sliced_out, spart, fused_db ? H + p.p_layout.p_blk : nullptr, part_b));
+        // G = s dy B^T; with fused projections every projection's column block of dy against its rows of the
+        // compact B, written into its rank window of G
+        LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
+                     shrink_mfma(pd, dy, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, pd.dg, pd.d_out, p.n_proj,
+                                 p.n_proj > 1 ? -1 : 0, st, p.sliced_out, spart, fused_db ? H + p.p_layout.p_blk : nullptr, part_b));
     }
     if (want_dx && p.desc.T > 0)
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,

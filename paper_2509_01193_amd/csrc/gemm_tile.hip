@@ -50,12 +50,47 @@ template <int TN> __device__ __forceinline__ int swz_kn(int k)
     else return (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1);
 }
 
-template <int TM, int TN, int WN, int STAGES> constexpr int tile_lds_bytes()
+// What a tile's rows belong to, in LDS behind the ring: the segments that cross the tile (at most one per row), each with
+// its first token, task, rank window and the first of them that has the same task; which of them are such firsts; and
+// per row the first segment of its task (-1: no adapter).
+template <int TM> struct TileTable {
+    int32_t lo[TM], task[TM], r0[TM], r[TM], first[TM], row[TM];
+    uint64_t firsts[(TM + 63) / 64];
+};
+
+// A set of segments of a tile, in scalar registers.
+template <int TM> struct TaskSet {
+    static_assert(TM <= 128, "two words");
+    uint64_t a, b;
+    static __device__ __forceinline__ uint64_t uniform(uint64_t v)
+    {
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v)), hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
+        return (uint64_t(hi) << 32) | lo;
+    }
+    __device__ __forceinline__ void load(const uint64_t* w)
+    {
+        a = uniform(w[0]);
+        b = TM > 64 ? uniform(w[TM > 64 ? 1 : 0]) : 0;
+    }
+    __device__ __forceinline__ bool empty() const { return (a | b) == 0; }
+    __device__ __forceinline__ int32_t lowest() const       // -1: empty
+    {
+        return a ? __builtin_ctzll(a) : (b ? 64 + __builtin_ctzll(b) : -1);
+    }
+    __device__ __forceinline__ void remove_lowest()
+    {
+        if (a) a &= a - 1;
+        else b &= b - 1;
+    }
+    __device__ __forceinline__ void remove(const TaskSet& o) { a &= ~o.a, b &= ~o.b; }
+};
+
+template <int TM, int TN, int WN, int STAGES> constexpr int ring_bytes()
 {
-    const int loop = STAGES * (TM + TN) * BK * 2;
-    const int cs = TM * (TN + 8 * WN) * 2;               // all waves' C staging
-    const int ms = LOBRA_MAX_RANK * TN * 2;              // adapter slice
-    return loop > cs ? (loop > ms ? loop : ms) : (cs > ms ? cs : ms);
+    constexpr int loop = STAGES * (TM + TN) * BK * 2;
+    static_assert(loop >= TM * (TN + 8 * WN) * 2, "all waves' C staging fits the ring");
+    static_assert(loop >= LOBRA_MAX_RANK * TN * 2, "an adapter slice of any rank fits the ring");
+    return loop;
 }
 
 }  // namespace
@@ -70,9 +105,9 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     // ldc: row pitch of C.  nproj > 1: this launch is projection `proj` of a fused shared-input
     // call: of every task's rank rows (in M) and rank columns (in P) only the window
     // [proj r, (proj + 1) r) takes part, r = the task's stacked rank / nproj.  proj < 0: the launch
-    // covers all projections (N = nproj * pd.dg, pd.dg a multiple of 256) and a tile takes
+    // covers all projections (N = nproj * pd.dg, pd.dg a multiple of the tile width) and a tile takes
     // the projection its columns lie in; M is then the compact [R_tot][pd.dg] array.
-    constexpr int NW = WM * WN, NT = 64 * NW;
+    constexpr int NW = WM * WN;
     constexpr int WTM = TM / WM, WTN = TN / WN;     // wave tile
     constexpr int MB = WTM / 16, NB = WTN / 16;     // 16 x 16 blocks per wave
     constexpr int ZT = TM * BK * 2, STAGE = (TM + TN) * BK * 2;
@@ -215,16 +250,15 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     using half0 = std::integral_constant<int, CH>;
     using half1 = std::integral_constant<int, (CH << 8) | CPW>;
 
-    // The table entries of the first segment that crosses this tile (a chain of dependent loads) are read before the
-    // copies start: after them, the wait for a table entry would wait for the copies as well.
-    const int32_t sg_first = pd.rowblk_seg[row0 / kRowBlock];
-    const int32_t sf_lo = pd.cseg_off[sg_first], sf_hi = pd.cseg_off[sg_first + 1];
-    const int32_t sf_task = pd.cseg_task[sg_first];
     const int32_t pj = proj >= 0 ? proj : col0 / pd.dg;          // this tile's projection
     const int32_t mcol0 = proj >= 0 ? 0 : pj * pd.dg;            // first column of that projection
     const int32_t mpitch = proj >= 0 ? N : pd.dg;                // row pitch of M
-    const int32_t sf_rw = sf_task >= 0 ? (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj : 0;
-    const int32_t sf_r0 = sf_task >= 0 ? pd.rank_off[sf_task] + pj * sf_rw : 0;
+    TileTable<TM>& tab = *reinterpret_cast<TileTable<TM>*>(lds + STAGES * STAGE);
+    auto lds_barrier = []() __attribute__((always_inline)) {     // (bare: a fence would wait for the copies in flight)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
 
     // ---- main loop.  A K tile's second K step is multiplied behind the barrier that hands its slot back: by then
     //      its fragments are in registers, so the slot can be refilled and the next tile's first fragments are read
@@ -235,6 +269,41 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * STAGE); });
         else if (s < KT) copy_tail(la0 + s * STAGE);
         next_copy_tile();
+    }
+    // What this tile's rows belong to, worked out while the first copies are on their way.  (A batch of decoding requests has
+    // a segment per token; one chain of table reads and one staging of adapter rows per segment, behind the main loop, took
+    // longer than the product: 39 us where this takes 24, 40 one-token segments of eight tasks, K = N = 4096.)
+    if (P) {
+        const int32_t sg = pd.rowblk_seg[row0 / kRowBlock] + tid;    // (the segment of the tile's first row, and those behind it)
+        const bool in = tid < TM && sg < pd.nseg && pd.cseg_off[min(sg, pd.nseg - 1)] < min(row0 + TM, T);
+        int32_t t = -1;
+        if (tid < TM) {
+            t = in ? pd.cseg_task[sg] : -1;
+            const int32_t r0 = t >= 0 ? pd.rank_off[t] : 0, r = t >= 0 ? (pd.rank_off[t + 1] - r0) / nproj : 0;
+            tab.lo[tid] = in ? pd.cseg_off[sg] : 0x7fffffff;
+            tab.task[tid] = t;
+            tab.r0[tid] = r0 + pj * r;
+            tab.r[tid] = r;
+        }
+        lds_barrier();
+        int32_t first = tid;
+        if (tid < TM) {
+            for (int32_t i = 0; i < TM && tab.lo[i] != 0x7fffffff; ++i)      // (uniform)
+                if (tab.task[i] == t) { first = min(first, i); break; }
+            tab.first[tid] = first;
+        }
+        const uint64_t firsts = __ballot(t >= 0 && first == tid);
+        if (wave < (TM + 63) / 64 && lane == 0) tab.firsts[wave] = firsts;
+        lds_barrier();
+        if (tid < TM) {
+            int32_t a = 0, b = TM;                   // the last segment that starts at or before the row
+            while (b - a > 1) {
+                const int32_t m = (a + b) >> 1;
+                if (tab.lo[m] <= row0 + tid) a = m;
+                else b = m;
+            }
+            tab.row[tid] = (row0 + tid < T && tab.task[a] >= 0) ? tab.first[a] : -1;
+        }
     }
     bf16x8 za[MB], wa[NB], zb[MB], wb[NB];
     if (KT >= STAGES) wait_vmcnt<(STAGES - 1) * CPW>();
@@ -289,83 +358,93 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
         slot = ns;
     }
 
-    // ---- fused up projection: for every adapter segment that crosses this tile, ceil(r_t / 32) extra
-    //      K steps acc += M_t^T[:, cols] * P[rows, :]^T with the rows outside the segment masked to zero.
-    //      The M_t slice [r_t][TN cols] is staged in LDS (free now) in the [k][n] layout (rank rows up to the next
-    //      multiple of 32 zero) and gathered with the transpose read; P comes
-    //      straight from global memory, 16 bytes per lane.
-    //      The segment loop and its barriers are uniform over the workgroup.
+    // ---- fused up projection: for every task with rows in this tile, ceil(r_t / 32) extra K steps
+    //      acc += M_t^T[:, cols] * P[rows, :]^T with the rows of other tasks masked to zero.  The M_t slices [r_t][TN cols] are
+    //      copied into the ring (free now) in the [k][n] layout, as many tasks at a time as fit, and gathered with the
+    //      transpose read; rows of a slice from r_t up to the next multiple of 32 repeat row r_t - 1 and are cleared in
+    //      registers.  P comes straight from global memory, 16 bytes per lane and rank step.
+    //      The loops over tasks and their barriers are uniform over the workgroup.
     if (P) {
-        const int32_t row_end = min(row0 + TM, T);
-        const int32_t wrow0 = row0 + wm * WTM;      // the wave's rows are wrow0 .. wrow0 + WTM - 1
-        for (int32_t sg = sg_first; sg < pd.nseg; ++sg) {
-            const bool cached = sg == sg_first;
-            const int32_t seg_lo = cached ? sf_lo : pd.cseg_off[sg];
-            if (seg_lo >= row_end) break;
-            const int32_t seg_hi = cached ? sf_hi : pd.cseg_off[sg + 1];
-            const int32_t t = cached ? sf_task : pd.cseg_task[sg];
-            if (t < 0 || seg_hi <= row0) continue;
-            const int32_t lo = max(seg_lo, row0), hi = min(seg_hi, row_end);
-            const int32_t r = cached ? sf_rw : (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj;
-            const int32_t r0 = cached ? sf_r0 : pd.rank_off[t] + pj * r;
-            const int32_t rp = (r + 31) & ~31;
-            const bool mine = hi > wrow0 && lo < wrow0 + WTM;  // wave-uniform: the segment crosses this wave's rows
-            // the P fragments of a rank step: lane (j, kg) holds the ranks kk + 8 kg .. + 7 of token row j of
-            // each 16-row block; groups that start beyond r_t hold padding, or another projection's ranks,
-            // and are not read.  The first step is fetched before the adapter slice is staged, so that its
-            // latency overlaps the staging and its barriers
-            u32x4 pv[MB];
-            const u32x4 zero4 = {0u, 0u, 0u, 0u};
-            auto load_p = [&](int32_t kk) {
+        constexpr int ROWS = STAGES * STAGE / (TN * 2);
+        const u32x4 zero4 = {0u, 0u, 0u, 0u};
+        auto rfl = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
+        // the P fragments of rank step s: lane (j, kg) holds the ranks 32 s + 8 kg .. + 7 of token row j of each 16-row
+        // block; groups that start beyond r_t hold padding, or another projection's ranks, and are not read
+        const int32_t nks = (pd.r_max / nproj + 31) >> 5;            // rank steps of the widest window (uniform)
+        int32_t of[MB], rw[MB];                      // first segment and rank of the row's task
+        u32x4 pv[MB], pn[MB];                        // this rank step's and the next one's
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const int32_t row = wrow0 + mb * 16 + j;
-                    pv[mb] = (mine && kk + 8 * kg < r && row >= lo && row < hi)
-                                 ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * r + kk + 8 * kg) : zero4;
-                }
-            };
-            load_p(0);
-            // the adapter slice is rp * CR chunks of 16 bytes; the first MCH * NT of them are fetched before
-            // the barrier that frees the LDS and written after it
-            constexpr int MCH = 2;
-            u32x4 mreg[MCH];
-            auto fetch_m = [&](int32_t base) {
+        for (int mb = 0; mb < MB; ++mb) {
+            of[mb] = tab.row[wm * WTM + mb * 16 + j];
+            rw[mb] = of[mb] >= 0 ? tab.r[of[mb]] : 0;
+        }
+        auto load_p = [&](int32_t s) {
 #pragma unroll
-                for (int q = 0; q < MCH; ++q) {
-                    const int32_t ch = base + tid + q * NT, kr = ch / CR, n = col0 + 8 * (ch % CR);
-                    mreg[q] = (kr < r && n < N)
-                                  ? *reinterpret_cast<const u32x4*>(M + size_t(r0 + kr) * mpitch + (n - mcol0)) : zero4;
-                }
-            };
-            auto store_m = [&](int32_t base) {
-#pragma unroll
-                for (int q = 0; q < MCH; ++q) {
-                    const int32_t ch = base + tid + q * NT, kr = ch / CR, c = ch % CR;
-                    if (kr < rp) *reinterpret_cast<u32x4*>(lds + kr * (TN * 2) + ((c ^ swz_kn<TN>(kr)) << 4)) = mreg[q];
-                }
-            };
-            fetch_m(0);
-            __syncthreads();                        // everybody is done with what the LDS held before
-            store_m(0);
-            for (int32_t base = MCH * NT; base < rp * CR; base += MCH * NT) {
-                fetch_m(base);
-                store_m(base);
+            for (int mb = 0; mb < MB; ++mb) {
+                const int32_t row = min(row0 + wm * WTM + mb * 16 + j, T - 1), k = 32 * s + 8 * kg;
+                pn[mb] = k < rw[mb] ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * rw[mb] + k) : zero4;
             }
-            __syncthreads();
-            if (!mine) continue;                    // wave-uniform; the barriers are above
-            for (int32_t kk = 0; kk < rp; kk += 32) {
-                if (kk > 0) load_p(kk);
-                bf16x8 wf[NB];
+        };
+        load_p(0);
+        TaskSet<TM> left;
+        left.load(tab.firsts);
+        while (!left.empty()) {
+            lds_barrier();                           // everybody is done with what the LDS held before
+            TaskSet<TM> batch = left;                // the tasks staged now: as many of those left as fit
+            int32_t rows = 0;
+            for (int32_t i = left.lowest(); i >= 0; i = left.lowest()) {
+                const int32_t r = rfl(tab.r[i]), rp = (r + 31) & ~31;
+                if (rows + rp > ROWS) break;
+                const unsigned char* mbase = reinterpret_cast<const unsigned char*>(M + size_t(rfl(tab.r0[i])) * mpitch + (col0 - mcol0));
+                for (int32_t c = wave; c < rp / RPC; c += NW) {
+                    const int krow = RPC * c + lane / CR;
+                    dma16(lds0 + rows * (TN * 2) + c * 1024, mbase,
+                          (uint32_t(min(krow, r - 1)) * uint32_t(mpitch) + uint32_t(min(8 * ((lane % CR) ^ swz_kn<TN>(krow)), N - 8 - col0))) * 2u);
+                }
+                rows += rp;
+                left.remove_lowest();
+            }
+            batch.remove(left);
+            wait_vmcnt<0>();
+            lds_barrier();
+            for (int32_t s = 0; s < nks; ++s) {
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) wf[nb] = read_kn(lds, kk, nb);
+                for (int mb = 0; mb < MB; ++mb) pv[mb] = pn[mb];
+                if (nks > 1) load_p(s + 1 < nks ? s + 1 : 0);
+                const unsigned char* slice = lds;
+                TaskSet<TM> todo = batch;
+                for (int32_t i = todo.lowest(); i >= 0; i = todo.lowest()) {
+                    todo.remove_lowest();
+                    const int32_t r = rfl(tab.r[i]);
+                    bool mine[MB], some = false;     // wave-uniform: a row of this block is the task's
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const int32_t rb = wrow0 + mb * 16;
-                    if (hi <= rb || lo >= rb + 16) continue;        // wave-uniform
-                    const bf16x8 pf = as_bf16x8(pv[mb]);
+                    for (int mb = 0; mb < MB; ++mb) {
+                        mine[mb] = __ballot(of[mb] == i) != 0;
+                        some |= mine[mb];
+                    }
+                    if (some && 32 * s < r) {
+                        const int nv = min(max(r - 32 * s - 8 * kg, 0), 8);
+                        u32x4 km;
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf, acc[mb][nb], 0, 0, 0);
+                        for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
+                        bf16x8 wf[NB];
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) {
+                            union { bf16x8 b; u32x4 u; } cv;
+                            cv.b = read_kn(slice, 32 * s, nb);
+                            cv.u &= km;
+                            wf[nb] = cv.b;
+                        }
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) {
+                            if (!mine[mb]) continue;
+                            const bf16x8 pf = as_bf16x8(of[mb] == i ? pv[mb] : zero4);
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb)
+                                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf, acc[mb][nb], 0, 0, 0);
+                        }
+                    }
+                    slice += ((r + 31) & ~31) * (TN * 2);
                 }
             }
         }
@@ -406,7 +485,7 @@ static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, c
                               const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
                               int32_t nproj, int32_t proj, hipStream_t st)
 {
-    constexpr int bytes = tile_lds_bytes<TM, TN, WN, STAGES>();
+    constexpr int bytes = ring_bytes<TM, TN, WN, STAGES>() + int(sizeof(TileTable<TM>));
     static_assert(bytes * OCC <= 160 * 1024, "LDS budget");
     // the kernel needs more dynamic LDS than the default limit: raise it once per device
     static std::atomic<uint64_t> raised{0};
@@ -481,6 +560,7 @@ hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* 
     for (int i = 0; i < int(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles
         if (i == 0 && !((K % (2 * BK) == 0 || K >= kPersistentMinKTail) && pd.T >= BM && N >= BN)) continue;
+        if (proj < 0 && pd.dg % kTiles[i].tn != 0) continue;         // no tile may straddle two projections
         const float c = tile_cost(kTiles[i], pd.T, K, N);
         if (best < 0 || c < least) best = i, least = c;
     }

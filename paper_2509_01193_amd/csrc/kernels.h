@@ -60,7 +60,7 @@ hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, fl
 // C[T, N] = Z[T, K] * op(W) + P * M_t with P bf16 [T][r_pad] (already scaled by s_t, zero beyond r_t).
 // ldc: row pitch of C (0: N).  nproj > 1: projection `proj` of a fused shared-input call - of every
 // task's ranks only the window [proj r, (proj+1) r) takes part (rows of M, columns of P); proj < 0: one
-// launch over all projections (N = nproj * pd.dg, pd.dg a multiple of 256), M compact [R_tot][pd.dg].
+// launch over all projections (N = nproj * pd.dg, pd.dg a multiple of 64), M compact [R_tot][pd.dg].
 hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                      const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st,
                      int32_t ldc = 0, int32_t nproj = 1, int32_t proj = 0);
@@ -77,7 +77,8 @@ hipError_t gemm_persistent_ktail(const PlanDev& pd, bool transW, const void* Z, 
                            int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t gm, hipStream_t st);
 bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw);
 // P = s_t Z M_t^T in bf16, written token-major [T][r_pad] and block-transposed [ntb][r_pad][32].
-// (ldz: row pitch of Z; nproj > 1: projection `proj` of a fused call - rank window, see the kernel)
+// (ldz: row pitch of Z; nproj > 1: projection `proj` of a fused call - rank window, see the kernel; proj < 0: all of
+//  them in one launch, Z with nproj * D columns)
 // sliced.nsl > 0 (chosen by the plan, see sliced_shrink_shape) and part != nullptr: the K-sliced kernel with its
 // fp32 partial projections in part [nsl][T][16], followed by the finish kernel.  Hblk, partb (and a plan with
 // fused_db): the same pass also accumulates sum_i Hblk_i^T Z_i (dB when Z = dy and Hblk = the block-transposed

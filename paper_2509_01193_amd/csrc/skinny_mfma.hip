@@ -62,9 +62,13 @@ __global__ __launch_bounds__(64 * NWV) void shrink_mfma_kernel(PlanDev pd, const
                                                           uint16_t* __restrict__ P_blk, int32_t D,
                                                           int32_t ldz, int32_t nproj, int32_t proj)
 {
-    // nproj > 1 (fused shared-input projections): this launch handles projection `proj` only - Z is
-    // that projection's column block of dy (row pitch ldz), M its rows of the compact up factors,
-    // and the task's rank rows it reads and writes are the window [proj r, (proj + 1) r).
+    // nproj > 1 (fused shared-input projections): a workgroup handles one projection only, `proj` or (proj < 0, Z is all of
+    // dy) the one in blockIdx.y - Z is that projection's column block of dy (row pitch ldz), M its rows of the compact
+    // up factors, and the task's rank rows it reads and writes are the window [proj r, (proj + 1) r).
+    if (proj < 0) {
+        proj = int32_t(blockIdx.y);
+        Z += size_t(proj) * D;
+    }
     __shared__ float red[NWV][2][NRB][64][4];   // [wave][token half][rank block][lane][4]
     // (a launch order by rank is dealt round-robin: contiguous ranges of it would give one XCD all the expensive blocks)
     const int32_t bi = pd.tb_order ? pd.tb_order[blockIdx.x]
@@ -188,6 +192,98 @@ __global__ __launch_bounds__(64 * NWV) void shrink_mfma_kernel(PlanDev pd, const
                     P_blk[(size_t(bi) * pd.r_pad + pofs + p0 + v) * kTokenBlock + tok] = c.u;
                 }
             }
+        }
+    }
+}
+
+// -------------------------------------------------------------------------------------------------
+// shrink for short batches (fewer token blocks than half the compute units): one workgroup per half of a token block
+// and 16 ranks, 16 waves split K.  What bounds such a launch is the time a workgroup takes, which is a chain of memory
+// round trips: the kernel above walks eight slabs of 128 per wave at K = 4096 and all rank blocks with them, and takes 12-14 us
+// at rank 16 and 22 us at rank 64 whether it has 1 or 256 blocks; here a wave walks two, both in flight at once (10 and
+// 9 us).  Operands and sums as above; a half without tokens only clears its part of P_blk.
+// -------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void shrink_short_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
+                                                           const uint16_t* __restrict__ M, const float* __restrict__ s,
+                                                           uint16_t* __restrict__ P_tok, uint16_t* __restrict__ P_blk,
+                                                           int32_t D, int32_t ldz, int32_t nproj, int32_t proj, int32_t nrb)
+{
+    // nproj, proj: as in shrink_mfma_kernel.  blockIdx.y = rank block (of nrb) + nrb * projection of the launch
+    constexpr int NWV = 16, DEPTH = 2;
+    __shared__ f32x4 red[NWV][64];
+    const int32_t bi = int32_t(blockIdx.x >> 1), half = int32_t(blockIdx.x & 1);
+    const int32_t rb = int32_t(blockIdx.y) % nrb;
+    if (proj < 0) {
+        proj = int32_t(blockIdx.y) / nrb;
+        Z += size_t(proj) * D;
+    }
+    const TokenBlock b = pd.tb[bi];
+    const int32_t r = (pd.rank_off[b.task + 1] - b.rank_row0) / nproj;
+    const int32_t pofs = proj * r;
+    const int32_t plim = proj == nproj - 1 ? pd.r_pad - pofs : r;    // ranks (and zero padding) stored for this projection
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane & 15, kg = lane >> 4;
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+    // (the last rank block also stores the padding beyond: with fused projections there can be more of it than 16)
+    const int32_t pbeg = 16 * rb, pend = rb == nrb - 1 ? plim : min(plim, pbeg + 16);
+    if (16 * half >= b.nrows) {
+        for (int32_t p = 2 * pbeg + int32_t(threadIdx.x); p < 2 * pend; p += 64 * NWV)
+            *reinterpret_cast<u32x4*>(P_blk + (size_t(bi) * pd.r_pad + pofs + (p >> 1)) * kTokenBlock + 16 + 8 * (p & 1)) = zero4;
+        return;
+    }
+    if (pbeg >= pend) return;
+    const int32_t tok = 16 * half + j;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (pbeg < r) {
+        const uint16_t* zrow = Z + size_t(b.row0 + min(tok, b.nrows - 1)) * ldz + 8 * kg;
+        const uint16_t* mrow = M + size_t(b.rank_row0 + pofs + min(pbeg + j, r - 1)) * D + 8 * kg;
+        struct Slab { u32x4 zv[4], mv[4]; };
+        auto load = [&](Slab& sl, int32_t k0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int32_t k = k0 + 32 * q;
+                const bool in = k + 8 * kg < D;      // columns beyond D read as 0
+                sl.zv[q] = in ? *reinterpret_cast<const u32x4*>(zrow + k) : zero4;
+                sl.mv[q] = in ? *reinterpret_cast<const u32x4*>(mrow + k) : zero4;
+            }
+        };
+        auto mac = [&](const Slab& sl) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(sl.mv[q]), as_bf16x8(sl.zv[q]), acc, 0, 0, 0);
+        };
+        const int32_t nsl = (D + 127) >> 7;
+        Slab buf[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (wave + NWV * d < nsl) load(buf[d], (wave + NWV * d) << 7);
+        for (int32_t i = wave; i < nsl; i += NWV * DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                const int32_t nx = i + NWV * (d + DEPTH - 1);
+                if (nx < nsl) load(buf[(d + DEPTH - 1) % DEPTH], nx << 7);
+                if (i + NWV * d < nsl) mac(buf[d]);
+            }
+        }
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    // wave 0 adds the sums in wave order and stores: lane (j, kg) ranks 4 kg .. 4 kg + 3 of the block, token j
+    if (wave > 0) return;
+    f32x4 sum = red[0][lane];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) sum = sum + red[w][lane];
+    const float st = s[b.task];
+    for (int32_t p0 = pbeg + 4 * kg; p0 < pend; p0 += 16) {          // (one turn, more only through padding)
+        bf16x4 o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = (__bf16)((p0 < pbeg + 16 && p0 + v < r && tok < b.nrows) ? st * sum[v] : 0.f);
+        if (tok < b.nrows) *reinterpret_cast<bf16x4*>(P_tok + size_t(b.row0 + tok) * pd.r_pad + pofs + p0) = o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            union { __bf16 b; uint16_t u; } c;
+            c.b = o[v];
+            P_blk[(size_t(bi) * pd.r_pad + pofs + p0 + v) * kTokenBlock + tok] = c.u;
         }
     }
 }
@@ -688,8 +784,13 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                                                             (uint16_t*)P_tok, (uint16_t*)P_blk, D);
         return hipGetLastError();
     }
+    if (pd.ntb <= 128) {
+        shrink_short_kernel<<<dim3(2 * pd.ntb, nrb * (proj < 0 ? nproj : 1)), 1024, 0, st>>>(
+            pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj, nrb);
+        return hipGetLastError();
+    }
 #define LOBRA_SHRINK(NRB, DEPTH)                                                                       \
-    shrink_mfma_kernel<NRB, 4, DEPTH><<<pd.ntb, 256, 0, st>>>(                                           \
+    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(pd.ntb, proj < 0 ? nproj : 1), 256, 0, st>>>(                                           \
         pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj)
     if (nrb <= 1) LOBRA_SHRINK(1, 3);
     else if (nrb <= 2) LOBRA_SHRINK(2, 2);

@@ -200,6 +200,26 @@ def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
         assert torch.equal(dq.y, dp.y[:T]) and torch.equal(dq.dx, dp.dx[:T]), T
 
 
+@pytest.mark.parametrize("T,d_in,d_out,n_proj", [
+    (64, 136, 200, 1), (130, 72, 4104, 1), (900, 72, 4000, 1), (300, 64, 128, 2), (128, 136, 72, 3),
+])
+def test_many_tasks_in_one_output_tile(T, d_in, d_out, n_proj):
+    """Segments of one to three tokens over 70 tasks of every rank: an output tile of the tiled GEMM then holds up to one
+    task per row, more adapter rows than its LDS takes at a time, tasks that come back after others, and rows without
+    adapter between them; the short-batch projection has blocks of one token."""
+    rng = np.random.default_rng(T + n_proj)
+    ranks = rng.choice([1, 5, 8, 16, 17, 33, 64, 128], 70) if n_proj == 1 else rng.choice([8, 16, 32, 40], 70)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.integers(1, 4)), T - sum(lens)))
+    tasks = rng.integers(-1, 70, len(lens))
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("many-tasks", "bf16", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]), tasks, 61,
+                       s=rng.uniform(-2, 2, 70).astype(np.float32), fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, label="many tasks")
+
+
 @pytest.mark.parametrize("T,d_in,d_out", [
     (4000, 520, 4040),     # forward: 8 k in the last pair of K tiles
     (4100, 576, 4000),     # 64: its second tile lies wholly beyond K
