@@ -204,9 +204,11 @@ LOBRA_API lobra_status lobra_mlora_plan_query(const lobra_mlora_plan *plan, int3
  *   h_save        : device, h_save_bytes, or NULL.  When given, bwd can reuse the
  *                   down-projected activations instead of recomputing them
  *   ws, ws_bytes  : device scratch of at least fwd_ws_bytes.  With h_save given only its first
- *                   fwd_ws_bytes - h_save_bytes bytes are used and checked: the partial sums of the
- *                   K-sliced down projection that long batches of ranks up to 16 take (0 bytes for all
- *                   other batches, for which ws may then be NULL)
+ *                   fwd_ws_bytes - h_save_bytes bytes are used: the partial sums of the K-sliced down
+ *                   projection that long batches of ranks up to 16 take, and those of a base product whose K is
+ *                   split (few tokens, long K; up to 12 MiB).  The former are needed and checked; without room for
+ *                   the latter the product is not split (slower, the same result up to the order of the sums), so
+ *                   that with h_save ws may be NULL for every batch that is not long
  *   hip_stream    : hipStream_t (NULL = default stream); work is enqueued, not awaited
  * x, W, A, B, s are read only; y and h_save are overwritten. */
 LOBRA_API lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan *plan, const void *x, const void *W,
@@ -219,8 +221,7 @@ LOBRA_API lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan *plan, const 
  * own device image instead of a caller buffer.  Arguments as for lobra_mlora_plan_fwd.  Makes no allocation
  * of any kind and does not synchronise.  LOBRA_ERR_WORKSPACE when the projected activations (h_save_bytes)
  * exceed LOBRA_STATIC_WS_BYTES (nothing is launched); a plan whose fwd_ws_bytes exceed the array only because of
- * the K-sliced projection's partial sums runs the one-block-per-workgroup projection here (same result up to the
- * order of the sums).  Each GPU has ONE such array, which keeps the last
+ * partial sums (K-sliced projection, split product) runs without them here (same result up to the order of the sums).  Each GPU has ONE such array, which keeps the last
  * call's contents: two calls of this function (or of lobra_token_task_map, which parks its tables there)
  * that overlap in time on the same GPU (different streams, or different threads) race on it and must be
  * ordered by the caller; the saved activations are not available to bwd (pass h_saved = NULL there). */

@@ -96,9 +96,9 @@ lobra_status fwd_check(const Plan& p, const void* x, const void* W, const void* 
     if (!aligned16(x) || !aligned16(W) || !aligned16(y) || !aligned16(A) || !aligned16(B) ||
         !aligned16(h_save) || !aligned16(ws))
         return LOBRA_ERR_ALIGN;
-    // the workspace holds the sliced projection's partial sums (if the plan uses it) and, without h_save, the
-    // projected activations behind them
-    const size_t need = (sliced ? p.fwd_off_p : 0) + (h_save ? 0 : p.p_layout.total);
+    // the workspace holds the sliced projection's partial sums (if the plan uses it), then those of a split base product
+    // in the same place, and, without h_save, the projected activations behind them
+    const size_t need = h_save ? (sliced ? p.fwd_spart : 0) : (sliced ? p.fwd_off_p : 0) + p.p_layout.total;
     if (adapters && need > 0 && (!ws || ws_bytes < need)) return LOBRA_ERR_WORKSPACE;
     return LOBRA_OK;
 }
@@ -328,8 +328,9 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
 }
 
 namespace {
-// The forward pass.  sliced = false: without the K-sliced projection even where the plan would take it (its
-// partial sums are most of the forward workspace): the projected activations then start at ws itself.
+// The forward pass.  sliced = false: without the K-sliced projection and without a split base product even where the
+// plan would take them (their partial sums are most of the forward workspace): the projected activations then start
+// at ws itself.
 lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W, const void* A, const void* B,
                       const float* s, void* y, void* h_save, void* ws, size_t ws_bytes, void* hip_stream, bool sliced)
 {
@@ -342,6 +343,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     const bool adapters = !p.tb.empty();
     void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (sliced ? p.fwd_off_p : 0);
     const SlicedShape sliced_in = sliced ? p.sliced_in : SlicedShape{};
+    float* const part = sliced && ws && ws_bytes >= p.fwd_part && p.fwd_part > 0 ? static_cast<float*>(ws) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const PlanDev pd = device_view(p);
     const int dt = p.desc.dtype;
@@ -368,7 +370,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     if (p.n_proj == 1) {
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, W, adapters ? hb + p.p_layout.p_tok : nullptr, B, y, pd.d_in,
-                               pd.d_out, pd.d_out, st));
+                               pd.d_out, pd.d_out, st, 0, 1, 0, part, p.fwd_part));
         return LOBRA_OK;
     }
     // fused shared-input projections: every column tile of y takes the rank window of H and the rows of
@@ -377,7 +379,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     if (pd.dg % 64 == 0) {
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, W, adapters ? hb + p.p_layout.p_tok : nullptr, B, y, pd.d_in,
-                               pd.d_out, pd.d_out, st, pd.d_out, p.n_proj, -1));
+                               pd.d_out, pd.d_out, st, pd.d_out, p.n_proj, -1, part, p.fwd_part));
         return LOBRA_OK;
     }
     for (int32_t j = 0; j < p.n_proj; ++j) {
@@ -385,7 +387,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, static_cast<const char*>(W) + col,
                                adapters ? hb + p.p_layout.p_tok : nullptr, B, static_cast<char*>(y) + col, pd.d_in,
-                               pd.dg, pd.d_out, st, pd.d_out, p.n_proj, j));
+                               pd.dg, pd.d_out, st, pd.d_out, p.n_proj, j, part, p.fwd_part));
     }
     return LOBRA_OK;
 }
@@ -492,7 +494,9 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
     if (want_dx && p.desc.T > 0)
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,
-                               pd.d_in, pd.d_out, st));
+                               pd.d_in, pd.d_out, st, 0, 1, 0,
+                               ws && ws_bytes >= p.bwd_ws_bytes && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr,
+                               p.bwd_part));
     if (p.R_tot > 0) {
         // dB (from s h and dy) and dA (from s g and x) share one launch per stage
         GradJob jb{adapters ? H + p.p_layout.p_blk : nullptr, dy, part_b, dB, pd.dg};
@@ -627,7 +631,7 @@ lobra_status lobra_mlora_fwd(const lobra_mlora_desc* desc, const void* x, const 
     const size_t img = align256(p->blob_bytes);
     char* rest = static_cast<char*>(ws) + img;
     if (p->desc.T == 0) st = LOBRA_OK;
-    else if (!ws || ws_bytes < img + p->fwd_off_p + (h_save ? 0 : p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
+    else if (!ws || ws_bytes < img + (h_save ? p->fwd_spart : p->fwd_off_p + p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
     else if (!aligned16(ws)) st = LOBRA_ERR_ALIGN;
     else if ((st = fwd_check(*p, x, W, A, B, s, y, h_save, rest, ws_bytes - img)) == LOBRA_OK &&
              (st = upload_oneshot(p, ws, stream)) == LOBRA_OK) {

@@ -29,6 +29,7 @@
 //   W tile when N is fastest (forward), adapter slice: [k][TN n], chunk c of k-row k stored at c ^ swz_kn<TN>(k); the
 //       MFMA operand (8 consecutive k of one column) is gathered with two ds_read_b64_tr_b16.
 //   C staging in the epilogue: per wave [rows][cols + 8] bf16, written back with non-temporal stores.
+#include <algorithm>
 #include <atomic>
 
 #include "gemm_common.h"
@@ -37,6 +38,8 @@
 namespace lobra {
 
 using namespace gemm;
+
+static_assert(kGemmKTile == BK && kGemmTiles[0].tm == BM && kGemmTiles[0].tn == BN, "the plan's choice is about these kernels");
 
 namespace {
 
@@ -53,7 +56,7 @@ template <int TN> __device__ __forceinline__ int swz_kn(int k)
 // What a tile's rows belong to, in LDS behind the ring: the segments that cross the tile (at most one per row), each with
 // its first token, task, rank window and the first of them that has the same task; which of them are such firsts; and
 // per row the first segment of its task (-1: no adapter).
-template <int TM> struct TileTable {
+template <int TM> struct alignas(16) TileTable {
     int32_t lo[TM], task[TM], r0[TM], r[TM], first[TM], row[TM];
     uint64_t firsts[(TM + 63) / 64];
 };
@@ -100,8 +103,12 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4)
 void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
                       const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
                       uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM)
+                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t splits,
+                      float* __restrict__ part)
 {
+    // splits > 1: that many workgroups per tile share the K tiles, and one more has the adapter term (if P): in the time
+    // that its chain of table reads, copies and products takes, the others are done with theirs.  Their fp32 sums go to
+    // part [splits (+ 1)][T][N]; gemm_add_kernel adds them and writes C.
     // ldc: row pitch of C.  nproj > 1: this launch is projection `proj` of a fused shared-input
     // call: of every task's rank rows (in M) and rank columns (in P) only the window
     // [proj r, (proj + 1) r) takes part, r = the task's stacked rank / nproj.  proj < 0: the launch
@@ -128,9 +135,12 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
 
     // ---- workgroup -> tile: consecutive ids go to different XCDs, so give each XCD a contiguous
     //      range of the tile order; inside it, GM tile-rows share one sweep over the tile-columns.
-    int32_t row0, col0;
+    int32_t row0, col0, split;
     {
-        const int32_t id = xcd_contiguous(blockIdx.x, tiles_m * tiles_n);
+        const int32_t per = splits + (splits > 1 && P ? 1 : 0);
+        const int32_t wid = xcd_contiguous(blockIdx.x, tiles_m * tiles_n * per);
+        const int32_t id = wid / per;
+        split = wid - id * per;
         const int32_t group = id / (GM * tiles_n);
         const int32_t first_m = group * GM;
         const int32_t gsz = min(tiles_m - first_m, GM);
@@ -161,8 +171,12 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
             wvo[c] = (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + 8u * ((lane % 8) ^ swz_row(row))) * 2u;
         }
     }
-    const int32_t KT = (K + BK - 1) / BK, ktail = K % BK;       // K tiles; k of a partial last one (0: none)
-    const unsigned char *zcur = zbase, *wcur = wbase;           // K tile the next copies fetch
+    // this workgroup's K tiles, and the k of a partial last one (0: none)
+    const int32_t KA = (K + BK - 1) / BK, kt0 = KA * split / splits;
+    const int32_t KT = split < splits ? KA * (split + 1) / splits - kt0 : 0;
+    const int32_t ktail = split + 1 == splits ? K % BK : 0;
+    const unsigned char *zcur = zbase + size_t(kt0) * (BK * 2), *wcur = wbase + size_t(kt0) * wstep;   // K tile the next copies fetch
+    if (splits > 1 && split < splits) P = nullptr;
     auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {      // copy c of a whole K tile
         constexpr int c = decltype(c_c)::value;
         if constexpr (c < ZC) dma16(la + NW * c * 1024, zcur, zvo[c]);
@@ -264,7 +278,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     //      its fragments are in registers, so the slot can be refilled and the next tile's first fragments are read
     //      while the matrix cores work.
     const uint32_t la0 = lds0 + wave * 1024;
-    const int32_t KF = K / BK;                       // whole K tiles
+    const int32_t KF = ktail ? KT - 1 : KT;          // whole K tiles
     for (int s = 0; s < STAGES; ++s) {
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * STAGE); });
         else if (s < KT) copy_tail(la0 + s * STAGE);
@@ -288,8 +302,14 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
         lds_barrier();
         int32_t first = tid;
         if (tid < TM) {
-            for (int32_t i = 0; i < TM && tab.lo[i] != 0x7fffffff; ++i)      // (uniform)
-                if (tab.task[i] == t) { first = min(first, i); break; }
+            // (eight at a time: one LDS latency per eight; what lies beyond the last segment has task -1)
+            for (int32_t i = 0; i < TM && tab.lo[i] != 0x7fffffff; i += 8) {         // (uniform)
+                const int4 a = *reinterpret_cast<const int4*>(&tab.task[i]), b = *reinterpret_cast<const int4*>(&tab.task[i + 4]);
+                const int32_t e[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+                for (int u = 7; u >= 0; --u)
+                    if (e[u] == t) first = min(first, i + u);
+            }
             tab.first[tid] = first;
         }
         const uint64_t firsts = __ballot(t >= 0 && first == tid);
@@ -449,6 +469,19 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
             }
         }
     }
+    if (splits > 1) {                               // the sums as they are, 16 bytes per lane
+        float* dst = part + size_t(split) * T * N;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int32_t row = row0 + wm * WTM + mb * 16 + j;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const int32_t col = col0 + wn * WTN + nb * 16 + 4 * kg;
+                if (row < T && col < N) *reinterpret_cast<f32x4*>(dst + size_t(row) * N + col) = acc[mb][nb];
+            }
+        }
+        return;
+    }
     __syncthreads();                                // the C staging below reuses the same LDS
 
     // ---- epilogue: fp32 -> bf16, stage the wave's block in LDS, store 16 bytes per lane
@@ -480,10 +513,33 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     }
 }
 
+// C = the sum of the splits' partial products, in split order, rounded once: 8 columns per thread.
+__global__ __launch_bounds__(256) void gemm_add_kernel(const float* __restrict__ part, uint16_t* __restrict__ C, int32_t splits,
+                                                       int64_t n, int32_t N, int32_t ldc)
+{
+    const int64_t i = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 8;
+    if (i >= n) return;
+    f32x4 v[kMaxSplits + 1][2];
+#pragma unroll
+    for (int s = 0; s <= kMaxSplits; ++s)
+        if (s < splits) {
+            v[s][0] = *reinterpret_cast<const f32x4*>(part + s * n + i);
+            v[s][1] = *reinterpret_cast<const f32x4*>(part + s * n + i + 4);
+        }
+    f32x4 a = v[0][0], b = v[0][1];
+#pragma unroll
+    for (int s = 1; s <= kMaxSplits; ++s)
+        if (s < splits) a = a + v[s][0], b = b + v[s][1];
+    bf16x8 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = (__bf16)a[q], o[4 + q] = (__bf16)b[q];
+    *reinterpret_cast<bf16x8*>(C + size_t(i / N) * ldc + size_t(i % N)) = o;
+}
+
 template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
 static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, const void* P,
                               const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                              int32_t nproj, int32_t proj, hipStream_t st)
+                              int32_t nproj, int32_t proj, hipStream_t st, int32_t splits, float* part)
 {
     constexpr int bytes = ring_bytes<TM, TN, WN, STAGES>() + int(sizeof(TileTable<TM>));
     static_assert(bytes * OCC <= 160 * 1024, "LDS budget");
@@ -500,45 +556,16 @@ static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, c
         raised.fetch_or(bit, std::memory_order_release);
     }
     const int32_t tiles_m = (pd.T + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
-    gemm_tile_kernel<W_KN, TM, TN, WM, WN, STAGES, OCC><<<dim3(uint32_t(tiles_m) * uint32_t(tiles_n)), 64 * WM * WN, bytes, st>>>(
+    const int32_t per = splits + (splits > 1 && P ? 1 : 0);          // workgroups per tile
+    gemm_tile_kernel<W_KN, TM, TN, WM, WN, STAGES, OCC><<<dim3(uint32_t(tiles_m) * uint32_t(tiles_n) * uint32_t(per)), 64 * WM * WN, bytes, st>>>(
         pd, (const uint16_t*)Z, (const uint16_t*)W, (const uint16_t*)P, (const uint16_t*)M, (uint16_t*)C,
-        K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, 1024 / TM);
+        K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, 1024 / TM, splits, part);
+    e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    const int64_t n = int64_t(pd.T) * N;             // (N is a multiple of 8)
+    gemm_add_kernel<<<dim3(uint32_t((n + 2047) / 2048)), 256, 0, st>>>(part, (uint16_t*)C, per, n, N, ldc);
     return hipGetLastError();
 }
-
-namespace {
-
-// The kernels a product can run on and what a K tile of 64 costs there, measured (us, K = 4096; the tile kernels with
-// one workgroup per compute unit and, where two fit, with two; `fixed`: start, adapter term and stores of a tile):
-//     tile        persistent 256 x 256   128 x 256   128 x 128   128 x 64      64 x 64
-//     T = 40      112 us                 44          31          24            18
-//     T = 200     113                    46          33          25            21
-//     T = 500      80                    48          35          28 (256 wgs)  32 (512 wgs)
-//     T = 1000     81                    49          39 (256)    45 (512)      57
-//     T = 2000     84                    62 (256)    75          81            110
-//     T = 4096    102 (256)              122        156          193           261
-// (x [T, 4096] times W [4096, 4096]; the register-staged kernel that stood here before took 112 us below 256 tokens.)
-// A tile's bytes through the copy path and its LDS reads grow slower than its MFMAs, so the largest tile that still
-// gives every compute unit one is the best; what remains is the count of rounds, which this estimates.
-struct TileCost { int32_t tm, tn, per_cu; float k1, k2, fixed; };
-constexpr TileCost kTiles[] = {
-    {256, 256, 1, 1.35f, 0.f, 12.f},     // gemm_persistent_kernel
-    {128, 256, 1, 0.86f, 0.f, 6.f},
-    {128, 128, 1, 0.48f, 0.f, 6.f},
-    {128, 64, 2, 0.33f, 0.59f, 6.f},
-    {64, 64, 2, 0.23f, 0.39f, 6.f},
-};
-constexpr int32_t kCus = 256;            // fixed, so that the choice does not depend on the device
-
-float tile_cost(const TileCost& t, int64_t T, int32_t K, int32_t N)
-{
-    const int64_t n = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = int64_t(kCus) * t.per_cu;
-    const int64_t full = n / slots, rest = n % slots;
-    const float kt = float((K + BK - 1) / BK), most = t.per_cu == 2 ? t.k2 : t.k1;
-    return float(full) * (most * kt + t.fixed) + (rest ? (rest <= kCus ? t.k1 : most) * kt + t.fixed : 0.f);
-}
-
-}  // namespace
 
 bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw)
 {
@@ -550,24 +577,16 @@ bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw)
 
 hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                      const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st,
-                     int32_t ldc, int32_t nproj, int32_t proj)
+                     int32_t ldc, int32_t nproj, int32_t proj, float* part, size_t part_bytes)
 {
     if (pd.T == 0) return hipSuccess;
     if (ldc == 0) ldc = N;
     if (!gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;   // (plan creation has checked already)
-    int best = -1;
-    float least = 0.f;
-    for (int i = 0; i < int(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
-        // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles
-        if (i == 0 && !((K % (2 * BK) == 0 || K >= kPersistentMinKTail) && pd.T >= BM && N >= BN)) continue;
-        if (proj < 0 && pd.dg % kTiles[i].tn != 0) continue;         // no tile may straddle two projections
-        const float c = tile_cost(kTiles[i], pd.T, K, N);
-        if (best < 0 || c < least) best = i, least = c;
-    }
+    const GemmChoice choice = choose_gemm(pd.T, K, N, proj < 0 ? pd.dg : 0, part ? std::min(part_bytes, kMaxPartBytes) : 0);
 #define LOBRA_TILE(...)                                                                                          \
-    (transW ? launch_tile<false, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st)                 \
-            : launch_tile<true, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st))
-    switch (best) {
+    (transW ? launch_tile<false, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part)                 \
+            : launch_tile<true, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part))
+    switch (choice.tile) {
     case 0: {
         const int32_t tiles_m = (pd.T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
         // tile rows per sweep of the tile order: the workgroups that run on an XCD at one time share their

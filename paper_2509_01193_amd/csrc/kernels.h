@@ -63,12 +63,12 @@ hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, fl
 // launch over all projections (N = nproj * pd.dg, pd.dg a multiple of 64), M compact [R_tot][pd.dg].
 hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                      const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st,
-                     int32_t ldc = 0, int32_t nproj = 1, int32_t proj = 0);
+                     int32_t ldc = 0, int32_t nproj = 1, int32_t proj = 0, float* part = nullptr, size_t part_bytes = 0);
+// part, part_bytes: scratch for the sums of a product whose K is split (choose_gemm; NULL, 0: it is not split).
 // The persistent direct-to-LDS kernel behind gemm_mfma for many output tiles (gemm_persistent.hip; T >= 256, N >= 256, K a
 // multiple of 128, or any multiple of 8 from kPersistentMinKTail on);
 // gm = tile rows per sweep of the tile order.  Everything else runs on the tiled kernels of gemm_tile.hip.
 // gemm_mfma_shape_ok: whether the kernels' 32-bit tile offsets can address the shape.
-constexpr int32_t kPersistentMinKTail = 520;   // an ordinary pair of K tiles, two pairs of the special kinds, and more
 hipError_t gemm_persistent(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                            const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj,
                            int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t gm, hipStream_t st);

@@ -292,8 +292,14 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         const size_t spart_in = align_up(size_t(p->sliced_in.nsl) * size_t(T) * 64, 256);
         const size_t spart_out = align_up(size_t(p->sliced_out.nsl) * size_t(T) * 64, 256);
         p->h_save_bytes = L.total;
-        p->fwd_off_p = spart_in;
-        p->fwd_ws_bytes = spart_in + L.total;
+        if (p->mfma && T > 0) {
+            const int32_t group = p->n_proj > 1 && p->dg % 64 == 0 ? p->dg : 0;      // (as the calls are launched)
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !group ? p->dg : d->d_out, group), 256);
+            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0), 256);
+        }
+        p->fwd_spart = spart_in;
+        p->fwd_off_p = std::max(spart_in, p->fwd_part);
+        p->fwd_ws_bytes = p->fwd_off_p + L.total;
         p->bwd_off_g = 0;
         p->bwd_off_h = L.total;
         p->bwd_off_part_b = 2 * L.total;
@@ -301,11 +307,42 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         p->bwd_off_part_a = p->bwd_off_part_b +
                             align_up(size_t(p->fused_db ? p->fb_rows : p->part_rows) * size_t(d->d_out) * 4, 256);
         p->bwd_off_spart = p->bwd_off_part_a + align_up(size_t(p->part_rows) * size_t(d->d_in) * 4, 256);
-        p->bwd_ws_bytes = p->bwd_off_spart + std::max(spart_in, spart_out);
+        p->bwd_ws_bytes = p->bwd_off_spart + std::max(p->bwd_part, std::max(spart_in, spart_out));
     } catch (const std::bad_alloc&) {
         return LOBRA_ERR_NOMEM;
     }
     return LOBRA_OK;
+}
+
+GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t part_bytes)
+{
+    constexpr int64_t cus = 256;             // fixed, so that the choice does not depend on the device
+    const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
+    GemmChoice best;
+    float least = -1.f;
+    for (int32_t i = 0; i < int32_t(sizeof(kGemmTiles) / sizeof(kGemmTiles[0])); ++i) {
+        const GemmTile& t = kGemmTiles[i];
+        // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles
+        if (i == 0 && !((K % (2 * kGemmKTile) == 0 || K >= kPersistentMinKTail) && T >= t.tm && N >= t.tn)) continue;
+        if (group > 0 && group % t.tn != 0) continue;
+        const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = cus * t.per_cu;
+        for (int32_t s = 1; s <= kMaxSplits; ++s) {
+            const int64_t bytes = int64_t(s + 1) * T * N * 4;      // (one more for the adapter term)
+            if (s > 1 && (i == 0 || K < kMinSplitK || kt < 4 * s || tiles * s > slots || uint64_t(bytes) > part_bytes)) break;
+            const int64_t full = tiles * s / slots, rest = tiles * s % slots;
+            const float per = float((kt + s - 1) / s), most = t.per_cu == 2 ? t.k2 : t.k1;
+            float cost = float(full) * (most * per + t.fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + t.fixed : 0.f);
+            if (s > 1) cost = 1.1f * (cost + 4.f + float(bytes) / 2e6f);     // (it has to be worth it)
+            if (least < 0.f || cost < least) best = GemmChoice{i, s}, least = cost;
+        }
+    }
+    return best;
+}
+
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group)
+{
+    const GemmChoice c = choose_gemm(T, K, N, group, kMaxPartBytes);
+    return c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0;
 }
 
 SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D)

@@ -28,6 +28,42 @@ constexpr int kSlicedGrid = 256;      // its workgroups: 8 XCDs x 32 compute uni
 // other ranks, too few items to keep every compute unit busy.
 SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 
+// The kernels a bf16 product can run on and what a K tile of 64 costs there, measured (us, K = 4096; the tiled kernels with
+// one workgroup per compute unit and, where two fit, with two; `fixed`: start, adapter term and stores of a tile):
+//     tile        persistent 256 x 256   128 x 256   128 x 128   128 x 64      64 x 64
+//     T = 40      112 us                 44          31          24            18
+//     T = 200     113                    46          33          25            21
+//     T = 500      80                    48          35          28 (256 wgs)  32 (512 wgs)
+//     T = 1000     81                    49          39 (256)    45 (512)      57
+//     T = 2000     84                    62 (256)    75          81            110
+//     T = 4096    102 (256)              122        156          193           261
+// (x [T, 4096] times W [4096, 4096]; a register-staged kernel took 112 us below 256 tokens.)
+// A tile's bytes through the copy path and its LDS reads grow slower than its MFMAs, so the largest tile that still
+// gives every compute unit one is the best; what remains is the count of rounds, which the choice estimates.
+struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed; };
+constexpr GemmTile kGemmTiles[] = {
+    {256, 256, 1, 1.35f, 0.f, 12.f},     // gemm_persistent_kernel
+    {128, 256, 1, 0.86f, 0.f, 6.f},
+    {128, 128, 1, 0.48f, 0.f, 6.f},
+    {128, 64, 2, 0.33f, 0.59f, 6.f},
+    {64, 64, 2, 0.23f, 0.39f, 6.f},
+};
+constexpr int32_t kGemmKTile = 64;
+constexpr int32_t kPersistentMinKTail = 520;   // an ordinary pair of K tiles, two pairs of the special kinds, and more
+// Where a product has fewer tiles than compute units and a long K (decoding, narrow shards), K is split among up to eight
+// workgroups per tile, each of which writes its fp32 sums to scratch; a small kernel adds them in order (4 us, and the
+// sums' way to memory and back at 4 TB/s): x [40, 4096] W [4096, 4096] with 8 adapters 24 -> 13.6 + 4.0 us, x [7, 5248]
+// W [5248, 1024] 22.8 -> 8.4 + 2.5 us.  At most kMaxPartBytes of them, so that they fit the library's static scratch
+// array next to the projected activations.
+constexpr int32_t kMaxSplits = 8, kMinSplitK = 1024;
+constexpr size_t kMaxPartBytes = size_t(12) << 20;
+struct GemmChoice { int32_t tile = 0, splits = 1; };
+// The choice for C [T, N] = Z [T, K] op(W) given part_bytes of scratch.  group > 0: no tile may straddle a multiple of
+// `group` columns (a multiple of 64).
+GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t part_bytes);
+// The scratch that choice would like to have (0: none).
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group);
+
 // Byte offsets of the sub-buffers inside h_save and the workspaces.
 struct BufferLayout {
     size_t p_tok = 0;     // token-major projected activations  [T][pstride]
@@ -71,7 +107,10 @@ struct Plan {
     // fp32 partial projections [nsl][T][16] go: at the start of the forward workspace (the projected
     // activations follow at fwd_off_p unless the caller gives h_save), at bwd_off_spart in the backward one
     SlicedShape sliced_in, sliced_out;
-    size_t fwd_off_p = 0, bwd_off_spart = 0;
+    // The same scratch then takes the split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm): the
+    // projection is done by that time.  They are welcome and not needed: a forward call with h_save and less workspace
+    // than fwd_part does without, it needs fwd_spart only.
+    size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0;
     // dB fused into the sliced projection of dy (one pass over dy for s_t B_t dy_i and for dB): a workgroup
     // keeps the dB sums of the (task, slice) it is working on and writes them out - 16 rank rows x 512
     // columns - whenever task or slice changes.  These tables say where: the runs of workgroup g are

@@ -175,8 +175,11 @@ def test_persistent_gemm_tile_edges_and_round_remainders(T, d_in, d_out):
 ])
 def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
     """The same first rows in batches of 40 to 2100 tokens: as the batch grows the product moves through tiles of
-    64 x 64, 128 x 64, 128 x 128 and 128 x 256 (which one is a matter of rows, columns and K).  The longest batch
-    against the oracle, the others bit for bit against it: every tile sums in the same order."""
+    64 x 64, 128 x 64, 128 x 128 and 128 x 256 (which one is a matter of rows, columns and K), and from K = 1024 on K is
+    split where tiles are few.  The longest batch against the oracle, the others against it: bit for bit below K = 1024,
+    where every tile sums in the same order; else two fp32 sums of the same products, each rounded to bf16 once, so that
+    they lie at most one bf16 step (2^-7 of the value at most) apart, plus the fp32 sums' own difference (1e-5 of the
+    largest value)."""
     import torch
     lens, tasks = [], []
     rng = np.random.default_rng(d_in + d_out)
@@ -197,7 +200,59 @@ def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
         dq.step()
         torch.cuda.synchronize()
         assert dq.guards_intact()
-        assert torch.equal(dq.y, dp.y[:T]) and torch.equal(dq.dx, dp.dx[:T]), T
+        for a, b, K in ((dq.y, dp.y[:T], d_in), (dq.dx, dp.dx[:T], d_out)):
+            if K < 1024:
+                assert torch.equal(a, b), T
+            else:
+                a, b = a.float(), b.float()
+                assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5 * b.abs().max()).all()), T
+
+
+@pytest.mark.parametrize("T,d_in,d_out,n_proj", [(1, 3072, 64, 1), (40, 4104, 136, 1), (70, 5128, 1032, 1), (33, 4096, 4096, 1),
+                                                 (64, 5000, 192, 2)])
+def test_split_k_product_in_every_entry_point(T, d_in, d_out, n_proj):
+    """Few tiles and a long K: the products' K is split and their sums pass through scratch.  Against the oracle through the
+    plan calls; the forward pass with h_save and no workspace goes without the split (as it must: it was accepted before
+    there was one), and the static array, the one-shot calls and graph replays give the split's bits."""
+    import torch
+    rng = np.random.default_rng(T)
+    ranks = [16, 40, 8] if n_proj == 1 else [16, 24, 8]
+    lens = [T // 3, T - T // 3] if T > 1 else [1]
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("split-%d" % T, "bf16", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]),
+                       rng.integers(0, 3, len(lens)), 71, s=[2.0, -1.0, 0.5], fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    dp, _ = check_problem(p, label="split K")
+    assert dp.plan.fwd_ws_bytes - dp.plan.h_save_bytes >= 2 * T * p.d_out * 4      # room for two partial products and more
+    want = [t.clone() for t in (dp.y, dp.dx, dp.dA, dp.dB)]
+    o = make_oracle(p)
+    dp.y.fill_(7.0)
+    bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, dp.h_save, None)
+    torch.cuda.synchronize()
+    assert relerr(dp.host(dp.y), o.y()) <= TOL["bf16"]
+    dp.y.fill_(7.0)
+    bd.lobra_mlora_fwd_static_ws(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y)
+    torch.cuda.synchronize()
+    assert torch.equal(dp.y, want[0])
+    d, keep = bd.make_desc(p.dtype, p.T, p.d_in, p.d_out, p.rank_off, p.seg_off, p.seg_task, n_proj)
+    ws = torch.empty(max(bd.lobra_mlora_workspace_bytes(d)), dtype=torch.uint8, device="cuda")
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            dp.step()
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for t in (dp.y, dp.dx, dp.dA, dp.dB):
+            t.fill_(7.0)
+        if rep < 2:
+            g.replay()
+        else:
+            bd.lobra_mlora_fwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, None, ws)
+            bd.lobra_mlora_bwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, None, dp.dx, dp.dA, dp.dB, 0, ws)
+        torch.cuda.synchronize()
+        for a, b, name in zip(want, (dp.y, dp.dx, dp.dA, dp.dB), ("y", "dx", "dA", "dB")):
+            assert torch.equal(a, b), (rep, name)
+    assert dp.guards_intact()
 
 
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [
