@@ -374,9 +374,9 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
         return LOBRA_OK;
     }
     // fused shared-input projections: every column tile of y takes the rank window of H and the rows of
-    // the compact B that belong to its projection - in one launch when no tile straddles two projections,
-    // else in one launch per projection (its column block of W and y)
-    if (pd.dg % 64 == 0) {
+    // the compact B that belong to its projection - in one launch when tiles that do not straddle two projections
+    // are no worse, else in one launch per projection (its column block of W and y)
+    if (p.fwd_group > 0) {
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, W, adapters ? hb + p.p_layout.p_tok : nullptr, B, y, pd.d_in,
                                pd.d_out, pd.d_out, st, pd.d_out, p.n_proj, -1, part, p.fwd_part));

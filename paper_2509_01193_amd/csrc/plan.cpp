@@ -293,8 +293,14 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         const size_t spart_out = align_up(size_t(p->sliced_out.nsl) * size_t(T) * 64, 256);
         p->h_save_bytes = L.total;
         if (p->mfma && T > 0) {
-            const int32_t group = p->n_proj > 1 && p->dg % 64 == 0 ? p->dg : 0;      // (as the calls are launched)
-            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !group ? p->dg : d->d_out, group), 256);
+            // fused projections: one launch over all of them if its tiles fit their widths - at a width like 53 x 64 only
+            // narrow tiles do, and a long batch is better off with a launch per projection (45861 x 904 x 2 x 3392: 1171
+            // against 732 us)
+            p->fwd_group = 0;
+            if (p->n_proj > 1 && p->dg % 64 == 0 &&
+                choose_gemm(T, d->d_in, d->d_out, p->dg, 0).cost <= float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, 0).cost + 3.f))
+                p->fwd_group = p->dg;
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group), 256);
             p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0), 256);
         }
         p->fwd_spart = spart_in;
@@ -333,7 +339,7 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t pa
             const float per = float((kt + s - 1) / s), most = t.per_cu == 2 ? t.k2 : t.k1;
             float cost = float(full) * (most * per + t.fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + t.fixed : 0.f);
             if (s > 1) cost = 1.1f * (cost + 4.f + float(bytes) / 2e6f);     // (it has to be worth it)
-            if (least < 0.f || cost < least) best = GemmChoice{i, s}, least = cost;
+            if (least < 0.f || cost < least) best = GemmChoice{i, s, cost}, least = cost;
         }
     }
     return best;

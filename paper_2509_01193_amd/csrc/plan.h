@@ -57,7 +57,7 @@ constexpr int32_t kPersistentMinKTail = 520;   // an ordinary pair of K tiles, t
 // array next to the projected activations.
 constexpr int32_t kMaxSplits = 8, kMinSplitK = 1024;
 constexpr size_t kMaxPartBytes = size_t(12) << 20;
-struct GemmChoice { int32_t tile = 0, splits = 1; };
+struct GemmChoice { int32_t tile = 0, splits = 1; float cost = -1.f; };    // cost: the estimate, us
 // The choice for C [T, N] = Z [T, K] op(W) given part_bytes of scratch.  group > 0: no tile may straddle a multiple of
 // `group` columns (a multiple of 64).
 GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t part_bytes);
@@ -110,6 +110,9 @@ struct Plan {
     // The same scratch then takes the split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm): the
     // projection is done by that time.  They are welcome and not needed: a forward call with h_save and less workspace
     // than fwd_part does without, it needs fwd_spart only.
+    // (fwd_group: fused projections' forward products run as one launch whose tiles do not straddle multiples of this
+    // many columns; 0: one launch per projection)
+    int32_t fwd_group = 0;
     size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0;
     // dB fused into the sliced projection of dy (one pass over dy for s_t B_t dy_i and for dB): a workgroup
     // keeps the dB sums of the (task, slice) it is working on and writes them out - 16 rank rows x 512
