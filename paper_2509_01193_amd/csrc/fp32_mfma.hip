@@ -10,8 +10,8 @@
 // and uses them in four MFMAs, MFMA q taking the k {q, 4 + q, 8 + q, 12 + q} of a group of 16: any dealing of the k
 // will do as long as both operands follow it.
 //
-// VEC: rows start on 16-byte boundaries (widths that are multiples of 4), so four elements are one load.  Other
-// widths take the same kernels with four guarded loads.
+// VEC: rows start on 16-byte boundaries and end on them (widths that are multiples of 4).  Other widths take the same
+// kernels with loads at any element and guards at the rows' ends.
 #include "kernels.h"
 
 namespace lobra {
@@ -19,6 +19,7 @@ namespace lobra {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // at any element
 
 // elements i .. i + 3 of the row at p; elements from n on read as 0
 template <bool VEC> __device__ __forceinline__ f32x4 load4(const float* __restrict__ p, int32_t i, int32_t n)
@@ -26,6 +27,9 @@ template <bool VEC> __device__ __forceinline__ f32x4 load4(const float* __restri
     if constexpr (VEC) {
         return i < n ? *reinterpret_cast<const f32x4*>(p + i) : f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
+        // (one load all the same - global memory takes 16 bytes at any address that is a multiple of 4 - except at the
+        //  row's end; four loads of 4 bytes, 16 bytes apart from lane to lane, cost the address unit four times as much)
+        if (i + 4 <= n) return *reinterpret_cast<const f32x4_any*>(p + i);
         f32x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = i + e < n ? p[i + e] : 0.f;
@@ -35,18 +39,15 @@ template <bool VEC> __device__ __forceinline__ f32x4 load4(const float* __restri
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-constexpr int FBK = 32;                  // K step of the GEMM: one 128-byte line per row
-constexpr int FPITCH = FBK + 4;          // [rows][k] tiles in LDS: 16 rows' 16-byte pieces fall into 16 bank groups
-
 }  // namespace
 
 // -------------------------------------------------------------------------------------------
-// gemm: TM x TN per workgroup of 2 x 2 waves, K step 32, global -> registers -> LDS one K step ahead.  Bound by the matrix
+// gemm: TM x TN per workgroup of 2 x 2 waves, K step FBK, global -> registers -> LDS one K step ahead.  Bound by the matrix
 // cores: a K step of a 64 x 64 tile is 1024 cycles of MFMAs and a quarter of that in LDS reads (8192 x 2048 x 2048: 120
 // TFLOP/s, without the global loads 127, of 157).  The adapter term is further K steps per segment, with the rows
 // outside the segment masked.
 // -------------------------------------------------------------------------------------------
-template <bool TRANSW, int TM, int TN, bool VEC>
+template <bool TRANSW, int TM, int TN, int FBK, int NBUF, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
                                                        const float* __restrict__ P, const float* __restrict__ M,
                                                        float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
@@ -56,9 +57,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     // ranks only the window [proj r, (proj + 1) r) takes part (columns of P, rows of M; M pitch N)
     constexpr int WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
     constexpr int ZL = TM * (FBK / 4) / 256, WL = TN * (FBK / 4) / 256;     // 16-byte pieces per thread and K step
+    constexpr int FPITCH = FBK + 4;      // [rows][k] tile: 16 rows' 16-byte pieces fall into 16 bank groups
     constexpr int NPITCH = TN + 4;       // [k][n] tile: k rows 4 apart start 16 banks apart
     constexpr int ZS = TM * FPITCH, WS = TRANSW ? TN * FPITCH : FBK * NPITCH;
-    __shared__ __attribute__((aligned(16))) float lds[2][ZS + WS];
+    __shared__ __attribute__((aligned(16))) float lds[NBUF][ZS + WS];
     static_assert(16 * NPITCH <= WS, "the adapter's rank rows fit the W tile");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
@@ -86,7 +88,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
             if (TRANSW) {                // op(W)[k][n] = W[n*ldw + k]
                 const int row = c / (FBK / 4), k = k0 + 4 * (c % (FBK / 4));
                 wr[u] = load4<VEC>(W + size_t(min(col0 + row, N - 1)) * ldw, k, K);
-            } else {                     // op(W)[k][n] = W[k*ldw + n]
+            } else if (!VEC) {           // op(W)[k][n] = W[k*ldw + n], an element per lane: whole lines of rows that start anywhere
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int ce = tid + 256 * (4 * u + e), k = k0 + ce / TN, n = col0 + ce % TN;
+                    wr[u][e] = k < K && n < N ? W[size_t(k) * ldw + n] : 0.f;
+                }
+            } else {
                 const int k = k0 + c / (TN / 4), n = col0 + 4 * (c % (TN / 4));
                 wr[u] = load4<VEC>(W + size_t(min(k, K - 1)) * ldw, k < K ? n : N, N);
             }
@@ -102,7 +110,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
         for (int u = 0; u < WL; ++u) {
             const int c = tid + 256 * u;
             if (TRANSW) *reinterpret_cast<f32x4*>(zs + ZS + c / (FBK / 4) * FPITCH + 4 * (c % (FBK / 4))) = wr[u];
-            else *reinterpret_cast<f32x4*>(zs + ZS + c / (TN / 4) * NPITCH + 4 * (c % (TN / 4))) = wr[u];
+            else if (VEC) *reinterpret_cast<f32x4*>(zs + ZS + c / (TN / 4) * NPITCH + 4 * (c % (TN / 4))) = wr[u];
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int ce = tid + 256 * (4 * u + e);
+                    zs[ZS + ce / TN * NPITCH + ce % TN] = wr[u][e];
+                }
         }
     };
     // 16 k from k0 on of the tiles at zs / ws
@@ -129,6 +143,32 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     };
     using trans_c = std::integral_constant<bool, TRANSW>;
 
+    // The adapter term's first step - the first segment's first 16 ranks - is fetched in front of the main loop: behind
+    // it, its chain of table reads and loads would stand alone (3 us of 8 at K = 256).
+    constexpr int ZA = TM * 16 / 256, WA = TN * 16 / 256;
+    float pa[ZA], ma[WA];
+    const int32_t row_end = min(row0 + TM, T);
+    int32_t sf = pd.rowblk_seg[row0 / kRowBlock];
+    if (P)
+        while (sf < pd.nseg && pd.cseg_task[sf] < 0 && pd.cseg_off[sf + 1] < row_end) ++sf;      // (uniform)
+    const int32_t sf_task = P && sf < pd.nseg ? pd.cseg_task[sf] : -1;
+    auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) {
+            const int e = tid + 256 * u, kk = e & 15, row = row0 + (e >> 4);
+            pa[u] = (row >= lo && row < hi && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < WA; ++u) {
+            const int e = tid + 256 * u, n = col0 + e % TN, kk = e / TN;
+            ma[u] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
+        }
+    };
+    if (sf_task >= 0) {
+        const int32_t r = (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj;
+        load_adapter(max(pd.cseg_off[sf], row0), min(pd.cseg_off[sf + 1], row_end), r, proj * r, pd.rank_off[sf_task] + proj * r, 0);
+    }
+
     fetch(0);
     stash(lds[0]);
     __syncthreads();
@@ -136,19 +176,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     for (int32_t k0 = 0; k0 < K; k0 += FBK) {
         const bool more = k0 + FBK < K;
         if (more) fetch(k0 + FBK);
-        mac(lds[buf], lds[buf] + ZS, 0, trans_c{});
-        mac(lds[buf], lds[buf] + ZS, 16, trans_c{});
-        if (more) stash(lds[buf ^ 1]);   // (its last readers are behind the previous barrier)
+#pragma unroll
+        for (int k = 0; k < FBK; k += 16)
+            if (k0 + k < K) mac(lds[buf], lds[buf] + ZS, k, trans_c{});         // (uniform)
+        if (NBUF == 1) __syncthreads();
+        else buf ^= 1;                   // (its last readers are behind the previous barrier)
+        if (more) stash(lds[buf]);
         __syncthreads();
-        buf ^= 1;
     }
     // adapter term: for every adapter segment that crosses the tile, the task's ranks are further k of the same tile
     // product, 16 at a time: acc += P[rows, ranks] M_t[ranks, cols], rows outside the segment and ranks beyond r_t zero
     // (the loops are uniform over the workgroup)
-    if (P) {
-        const int32_t row_end = min(row0 + TM, T);
-        float *zs = lds[0], *ws = lds[0] + ZS;
-        for (int32_t sg = pd.rowblk_seg[row0 / kRowBlock]; sg < pd.nseg; ++sg) {
+    if (sf_task >= 0) {
+        float *zs = lds[0], *ws = lds[0] + ZS;           // (everybody is done with the last K step)
+        for (int32_t sg = sf; sg < pd.nseg; ++sg) {
             const int32_t seg_lo = pd.cseg_off[sg];
             if (seg_lo >= row_end) break;
             const int32_t t = pd.cseg_task[sg];
@@ -157,14 +198,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
             const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
             const int32_t r0 = pd.rank_off[t] + pofs;
             for (int32_t c0 = 0; c0 < r; c0 += 16) {
-                for (int e = tid; e < TM * 16; e += 256) {
-                    const int kk = e & 15, row = row0 + (e >> 4);
-                    zs[(e >> 4) * FPITCH + kk] = (row >= lo && row < hi && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
-                }
-                for (int e = tid; e < TN * 16; e += 256) {
-                    const int n = col0 + e % TN, kk = e / TN;
-                    ws[kk * NPITCH + e % TN] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
-                }
+                if (sg != sf || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
+#pragma unroll
+                for (int u = 0; u < ZA; ++u) zs[((tid + 256 * u) >> 4) * FPITCH + (tid & 15)] = pa[u];
+#pragma unroll
+                for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
                 __syncthreads();
                 mac(zs, ws, 0, std::false_type{});
                 __syncthreads();
@@ -181,6 +219,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
             float* c = C + size_t(row) * ldc + col;
             if (VEC && col < N) {
                 *reinterpret_cast<f32x4*>(c) = acc[mb][nb];
+            } else if (!VEC && col + 4 <= N) {
+                *reinterpret_cast<f32x4_any*>(c) = acc[mb][nb];
             } else {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -196,12 +236,14 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
     const bool vec = ((K | N | ldw | ldc) & 3) == 0;
     // The larger the tile the fewer loads and LDS writes per MFMA, as long as every compute unit has work (us per product;
     // 8192 x 2048 x 2048: 775 with tiles of 32, 627 of 64, 571 of 128; 3000 x 1024 x 1024: 85, 75, 96; 2000 x 363 x 517: 29, 33, 54; the vector-ALU kernel that
-    // stood here before took 119 for the latter)
+    // stood here before took 119 for the latter).  Tiles of 32 run where there are few of them, so a workgroup has its compute
+    // unit almost to itself and what counts is the number of round trips to memory: K steps of 128 and loads
+    // that cover whole lines at odd widths, 43 -> 30 us at 148 x 1676 x 1357.
     auto tiles = [&](int32_t t) { return int64_t((pd.T + t - 1) / t) * ((N + t - 1) / t); };
     const int32_t tm = tiles(128) >= 384 ? 128 : (tiles(64) >= 512 ? 64 : 32), tiles_n = (N + tm - 1) / tm;
     const dim3 grid(uint32_t((pd.T + tm - 1) / tm) * uint32_t(tiles_n));
 #define LOBRA_F32_GEMM(TR, TILE, VEC) \
-    gemm_f32_kernel<TR, TILE, TILE, VEC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
+    gemm_f32_kernel<TR, TILE, TILE, (TILE == 32 ? 128 : 32), (TILE == 32 ? 1 : 2), VEC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
 #define LOBRA_F32_GEMM2(TR, TILE) do { if (vec) LOBRA_F32_GEMM(TR, TILE, true); else LOBRA_F32_GEMM(TR, TILE, false); } while (0)
 #define LOBRA_F32_GEMM3(TILE) do { if (transW) LOBRA_F32_GEMM2(true, TILE); else LOBRA_F32_GEMM2(false, TILE); } while (0)
     if (tm == 128) LOBRA_F32_GEMM3(128);
@@ -213,17 +255,17 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
 // -------------------------------------------------------------------------------------------
 // shrink: one workgroup per half of a token block (16 tokens of one task), NW waves split K in groups of 16; both operands
 // go straight from global memory into registers, "A" = 16 rank rows, "B" = 16 token rows, four rank blocks at a time.
-// Latency and memory bound: a wave keeps the loads of two groups in flight.
+// Latency and memory bound: a wave has the loads of four groups in flight (two at large ranks).
 // -------------------------------------------------------------------------------------------
 template <int NRB, bool VEC>
-__global__ __launch_bounds__(512) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
+__global__ __launch_bounds__(1024) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
                                                          const float* __restrict__ s, float* __restrict__ P, int32_t D,
                                                          int32_t ldz, int32_t nproj, int32_t proj)
 {
     // nproj > 1 (fused shared-input projections): projection `proj` only - Z is its column block of
     // dy (row pitch ldz), M its rows of the compact up factors, and of the task's ranks the window
     // [proj r, (proj + 1) r) is read and written
-    constexpr int NW = 8;
+    constexpr int NW = 16, DEPTH = NRB == 4 ? 2 : 4;      // (128 registers per wave)
     __shared__ f32x4 red[NW][NRB][64];
     const TokenBlock b = pd.tb[blockIdx.x >> 1];
     const int half = blockIdx.x & 1;
@@ -244,29 +286,24 @@ __global__ __launch_bounds__(512) void shrink_f32_kernel(PlanDev pd, const float
             mrow[rb] = M + size_t(b.rank_row0 + pofs + min(p0 + 16 * rb + j, r - 1)) * D;
         }
         const int32_t nrb = min(NRB, (r - p0 + 15) >> 4);           // rank blocks with ranks of the task (uniform)
-        f32x4 z[2], m[2][NRB];
-        auto load = [&](int u, int32_t g) {
-            z[u] = load4<VEC>(zrow, 16 * g + 4 * kg, D);
+        f32x4 z[DEPTH], m[DEPTH][NRB];
+        const int32_t ng = (D + 15) >> 4;
+        for (int32_t g = wave; nrb > 0 && g < ng; g += DEPTH * NW) {            // (groups beyond D read as zero)
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb)
-                if (rb < nrb) m[u][rb] = load4<VEC>(mrow[rb], 16 * g + 4 * kg, D);
-        };
-        auto mac = [&](int u) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int u = 0; u < DEPTH; ++u) {
+                const int32_t k = 16 * (g + u * NW) + 4 * kg;
+                z[u] = load4<VEC>(zrow, k, D);
 #pragma unroll
                 for (int rb = 0; rb < NRB; ++rb)
-                    if (rb < nrb) acc[rb] = mfma4(m[u][rb][q], z[u][q], acc[rb]);
-        };
-        if (nrb > 0) {
-            const int32_t ng = (D + 15) >> 4;
-            load(0, wave);               // (groups beyond D read as zero)
-            for (int32_t g = wave; g < ng; g += 2 * NW) {
-                load(1, g + NW);
-                mac(0);
-                load(0, g + 2 * NW);
-                mac(1);
+                    if (rb < nrb) m[u][rb] = load4<VEC>(mrow[rb], k, D);
             }
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int rb = 0; rb < NRB; ++rb)
+                        if (rb < nrb) acc[rb] = mfma4(m[u][rb][q], z[u][q], acc[rb]);
         }
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) red[wave][rb][lane] = acc[rb];
@@ -294,8 +331,8 @@ hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const f
     const int nrb = (pd.r_max / nproj + 15) / 16;
 #define LOBRA_F32_SHRINK(NRB)                                                                                              \
     do {                                                                                                                   \
-        if (vec) shrink_f32_kernel<NRB, true><<<2 * pd.ntb, 512, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);            \
-        else shrink_f32_kernel<NRB, false><<<2 * pd.ntb, 512, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);               \
+        if (vec) shrink_f32_kernel<NRB, true><<<2 * pd.ntb, 1024, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);            \
+        else shrink_f32_kernel<NRB, false><<<2 * pd.ntb, 1024, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);               \
     } while (0)
     if (nrb <= 1) LOBRA_F32_SHRINK(1);
     else if (nrb <= 2) LOBRA_F32_SHRINK(2);
