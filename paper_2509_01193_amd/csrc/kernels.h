@@ -6,7 +6,8 @@
 
 namespace lobra {
 
-// One gradient reduction dM = sum_i P_i^T Z_i: stage 1 writes `part`, stage 2 writes `out` [R_tot, D].
+// One gradient reduction dM = sum_i P_i^T Z_i: stage 1 writes `part`, stage 2 writes `out` [R_tot, D].  (grad_mfma writes the
+// rows of a task with a single reduction chunk to `out` itself, and reduce_partials is told to leave them alone.)
 struct GradJob {
     const void* P;   // projected activations (layout depends on the kernel family)
     const void* Z;   // [T, D]
@@ -47,7 +48,8 @@ hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const vo
 // Stage 2 (also used by the MFMA path): out[R, :] (+)= sum of the partial sums of task(R), in
 // chunk order, so that the result does not depend on scheduling.
 // One launch for up to two gradients (jb.out == nullptr: only ja).
-hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate,
+// skip_single: rows of tasks with exactly one reduction chunk are in place already (except a job with fcnt).
+hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, bool skip_single,
                            hipStream_t st);
 // ---- fp32 storage on the matrix cores (fp32_mfma.hip), reached through the three above; arguments as there ------------
 hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
@@ -91,7 +93,8 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
 
 // Stage 1 of dM_t = sum_i P_i^T Z_i from the block-transposed P; partial sums per reduction chunk.
 // (P = block-transposed bf16 copy; one launch for up to two gradients, jb.P == nullptr: only ja.)
-hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, hipStream_t st);
+// accumulate: what goes to `out` directly is added to it.
+hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st);
 
 // Fused Adam over the stacked adapters A [R_tot, d_in] and B [R_tot, d_out] (one launch).
 struct AdamTensor {

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const
 // stage 2: out[R, col] (+)= sum over the chunks of task(R), in chunk order.  One workgroup per
 // (rank row, 1024 columns), one float4 per thread, four chunk loads in flight.
 __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJob ja, GradJob jb,
-                                                              int32_t tiles_a, int accumulate)
+                                                              int32_t tiles_a, int accumulate, int skip_single)
 {
     const bool first = int32_t(blockIdx.y) < tiles_a;
     const float* __restrict__ part = first ? ja.part : jb.part;
@@ -340,6 +340,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJo
     const int32_t* fcnt = first ? ja.fcnt : jb.fcnt;
     const int32_t c0 = fcnt ? 0 : pd.task_chunk_off[t];
     const int32_t c1 = fcnt ? fcnt[t * (first ? ja.fnsl : jb.fnsl) + (col >> 9)] : pd.task_chunk_off[t + 1];
+    if (skip_single && !fcnt && c1 - c0 == 1) return;
     const int32_t frow = fcnt ? (first ? ja.frow0 : jb.frow0)[t] + p : 0;
     const int nv = min(4, D - col);                 // D need not be a multiple of 4 on the fp32 path
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -394,14 +395,14 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJo
     }
 }
 
-hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate,
+hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, bool skip_single,
                            hipStream_t st)
 {
     if (pd.R_tot == 0) return hipSuccess;
     const int32_t tiles_a = (ja.D + 1023) / 1024, tiles_b = jb.out ? (jb.D + 1023) / 1024 : 0;
     const dim3 grid(pd.R_tot, tiles_a + tiles_b);
     if (grid.y > 65535u) return hipErrorInvalidValue;
-    reduce_partials_kernel<<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, accumulate ? 1 : 0);
+    reduce_partials_kernel<<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, accumulate ? 1 : 0, skip_single ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -252,6 +252,19 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         // (the MFMA kernel gives each of its four waves a token block of the chunk at a time; the plain
         //  kernel walks a chunk's tokens one after the other, so small batches want short chunks there)
         cb = std::max<int64_t>(p->mfma ? 4 : 1, std::min<int64_t>(64, cb));
+        // Small batches: one chunk per task if that gives about every compute unit a workgroup of its own and no wave more
+        // than six blocks; the sums are then final and there is no second stage (1000 tokens, 4 tasks, 4096 x 4096:
+        // stage 1 6.6 -> 7.5 us, stage 2 4.2 us gone)
+        if (p->mfma && !p->fused_db) {
+            int64_t most = 0, active = 0;
+            for (int32_t t = 0; t < n; ++t) {
+                const int64_t nb = p->task_tb_off[t + 1] - p->task_tb_off[t];
+                most = std::max(most, nb);
+                active += nb > 0;
+            }
+            const int64_t tiles = (d->d_in + 127) / 128 + (d->d_out + 127) / 128;
+            if (most <= 24 && active * tiles >= 192) cb = std::max(cb, most);
+        }
         p->chunk_blocks = int32_t(cb);
         p->chunks.clear();
         p->task_chunk_off.assign(size_t(n) + 1, 0);
@@ -270,6 +283,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             }
             p->task_chunk_off[t + 1] = int32_t(p->chunks.size());
         }
+
+        p->single_chunks = n > 0;
+        for (int32_t t = 0; t < n; ++t) p->single_chunks &= p->task_chunk_off[t + 1] - p->task_chunk_off[t] == 1;
 
         // (the reduction kernels put chunks x column tiles of at least 64 columns on grid.x)
         if (int64_t(p->chunks.size()) * ((int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64) > 0x7fffffff)

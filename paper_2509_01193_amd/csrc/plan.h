@@ -97,6 +97,7 @@ struct Plan {
     std::vector<int32_t> tb_order, sb_order;
     std::vector<GradChunk> chunks;      // grouped by task
     std::vector<int32_t> task_chunk_off;// [n_tasks+1]
+    bool single_chunks = false;         // every task has exactly one chunk: no partial sums to add
     int32_t part_rows = 0;              // rows of the partial-sum buffer = sum over chunks of r_t
     int32_t chunk_blocks = 0;           // token blocks per reduction chunk
 

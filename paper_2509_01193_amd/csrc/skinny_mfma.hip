@@ -800,6 +800,17 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
     return hipGetLastError();
 }
 
+// Where a chunk's sums go: to its rows of the partial sums, which stage 2 adds up, or, if it is its task's only chunk, to the
+// gradient itself (added to what is there with accumulate).
+struct GradRows { float* base; bool add; };
+__device__ __forceinline__ GradRows grad_rows(const PlanDev& pd, const GradChunk& ch, const GradJob& job, int32_t accumulate)
+{
+    const int32_t ldp = job.ldp ? job.ldp : job.D;
+    if (pd.task_chunk_off[ch.task + 1] - pd.task_chunk_off[ch.task] == 1)
+        return {job.out + size_t(pd.rank_off[ch.task]) * ldp, accumulate != 0};
+    return {job.part + size_t(ch.part_row0) * ldp, false};
+}
+
 // -------------------------------------------------------------------------------------------------
 // grad stage 1: partial dM over one reduction chunk and 16 CW columns per workgroup of 4 waves
 // (CW = 8: 128 columns; CW = 4: 64 columns, for large ranks, where the accumulators of a
@@ -813,7 +824,7 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
 // The four waves' sums are combined through LDS in two steps (fixed order: ((w0+w2)+(w1+w3))).
 // -------------------------------------------------------------------------------------------------
 template <int NRB, int CW, bool STREAM>
-__global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all)
+__global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all, int32_t accumulate)
 {
     typedef uint32_t zvec __attribute__((ext_vector_type(CW / 2)));
     typedef float ovec __attribute__((ext_vector_type(4)));
@@ -833,7 +844,6 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
     const bool first = tile_y < tiles_a;
     const uint16_t* __restrict__ P_blk = static_cast<const uint16_t*>(first ? ja.P : jb.P);
     const uint16_t* __restrict__ Z = static_cast<const uint16_t*>(first ? ja.Z : jb.Z);
-    float* __restrict__ part = first ? ja.part : jb.part;
     const int32_t D = first ? ja.D : jb.D;
     const int32_t ldz = (first ? ja.ldz : jb.ldz) ? (first ? ja.ldz : jb.ldz) : D;   // row pitch of Z (elements)
     const int32_t nproj = first ? ja.nproj : jb.nproj;    // > 1: only the rank window of one projection
@@ -925,18 +935,20 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
                     for (int v = 0; v < 4; ++v) red[0][rb][jj][lane][v] = acc[rb][jj][v];
     __syncthreads();
     if (wave == 0 && col_in) {
+        const GradRows gr = grad_rows(pd, ch, first ? ja : jb, accumulate);
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int32_t p = 16 * (rb0 + rb) + 4 * g + v;
                 if (p >= r) continue;
-                float* dst = part + size_t(ch.part_row0 + pofs + p) * ldp + (col - pcol0);
+                float* dst = gr.base + size_t(pofs + p) * ldp + (col - pcol0);
 #pragma unroll
                 for (int j4 = 0; j4 < CW; j4 += 4) {
                     ovec o;
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) o[jj] = acc[rb][j4 + jj][v] + red[0][rb][j4 + jj][lane][v];
+                    if (gr.add) o = *reinterpret_cast<const ovec*>(dst + j4) + o;
                     *reinterpret_cast<ovec*>(dst + j4) = o;
                 }
             }
@@ -954,7 +966,7 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
 // Operand layouts as in grad_mfma_kernel with CW = 4.
 // -------------------------------------------------------------------------------------------------
 template <int NRB>
-__global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all)
+__global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all, int32_t accumulate)
 {
     constexpr int CW = 4, TW = 4 * 16 * CW;     // rank blocks per pass, columns per lane, tile width
     typedef uint32_t zvec __attribute__((ext_vector_type(CW / 2)));
@@ -971,7 +983,6 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
     const bool first = tile_y < tiles_a;
     const uint16_t* __restrict__ P_blk = static_cast<const uint16_t*>(first ? ja.P : jb.P);
     const uint16_t* __restrict__ Z = static_cast<const uint16_t*>(first ? ja.Z : jb.Z);
-    float* __restrict__ part = first ? ja.part : jb.part;
     const int32_t D = first ? ja.D : jb.D;
     const int32_t ldz = (first ? ja.ldz : jb.ldz) ? (first ? ja.ldz : jb.ldz) : D;
     const int32_t nproj = first ? ja.nproj : jb.nproj;
@@ -1052,6 +1063,7 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
         mac(zb, 1);
     }
     if (!col_in) return;
+    const GradRows gr = grad_rows(pd, ch, first ? ja : jb, accumulate);
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
@@ -1061,11 +1073,13 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
             ovec o;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) o[jj] = acc[rb][jj][v];
-            *reinterpret_cast<ovec*>(part + size_t(ch.part_row0 + pofs + p) * ldp + (col - pcol0)) = o;
+            float* dst = gr.base + size_t(pofs + p) * ldp + (col - pcol0);
+            if (gr.add) o = *reinterpret_cast<const ovec*>(dst) + o;
+            *reinterpret_cast<ovec*>(dst) = o;
         }
 }
 
-hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, hipStream_t st)
+hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st)
 {
     if (pd.nchunks == 0) return hipSuccess;
     // rank blocks of the widest window (both jobs of a launch have the same nproj)
@@ -1076,8 +1090,8 @@ hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, hi
         (ja.proj >= 0 || pd.dg % 256 == 0) && (!jb.P || jb.proj >= 0 || pd.dg % 256 == 0)) {
         const int32_t ta = (ja.D + 255) / 256, tb = jb.P ? (jb.D + 255) / 256 : 0;
         const dim3 grid(uint32_t(pd.nchunks) * uint32_t(ta + tb), (nrb + 3) / 4);     // (plan creation bounds the product)
-        if (NRB == 2) grad_lds_kernel<2><<<dim3(grid.x, 1), 256, 0, st>>>(pd, ja, jb, ta, ta + tb);
-        else grad_lds_kernel<4><<<grid, 256, 0, st>>>(pd, ja, jb, ta, ta + tb);
+        if (NRB == 2) grad_lds_kernel<2><<<dim3(grid.x, 1), 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);
+        else grad_lds_kernel<4><<<grid, 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);
         return hipGetLastError();
     }
     const int cw = NRB == 4 ? 4 : 8;
@@ -1088,8 +1102,8 @@ hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, hi
     const bool stream = int64_t(pd.T) * (int64_t(ja.D) + (jb.P ? jb.D : 0)) * 2 > (int64_t(512) << 20);
 #define LOBRA_GRAD(NRB_, CW_)                                                                  \
     do {                                                                                       \
-        if (stream) grad_mfma_kernel<NRB_, CW_, true><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b);  \
-        else grad_mfma_kernel<NRB_, CW_, false><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b);        \
+        if (stream) grad_mfma_kernel<NRB_, CW_, true><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);  \
+        else grad_mfma_kernel<NRB_, CW_, false><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);        \
     } while (0)
     if (NRB == 1) LOBRA_GRAD(1, 8);
     else if (NRB == 2) LOBRA_GRAD(2, 8);

@@ -449,6 +449,35 @@ def test_flags_saved_h_determinism_and_canaries(dtype):
     assert (dp.dx == 3.0).all().item()
 
 
+@pytest.mark.parametrize("ranks,n_proj,empty_task", [([8, 16, 4], 1, False), ([8, 40, 100], 1, True), ([16, 24, 8], 2, False),
+                                                     ([8, 16, 40], 2, True)])
+def test_gradients_of_tasks_with_a_single_chunk(ranks, n_proj, empty_task):
+    """Tasks of at most four token blocks have one reduction chunk, whose sums go straight to dA and dB (next to tasks with
+    several chunks, and a task without tokens, whose rows stage 2 clears): overwritten, accumulated, and without stage 2."""
+    import torch
+    lens = [60, 128, 33, 1] + ([400] if empty_task else [])
+    tasks = [0, 1, 2, 0] + ([1] if empty_task else [])
+    ranks = ranks + ([16] if empty_task else [])
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("single-chunk", "bf16", 136, 264, ranks, np.concatenate([[0], np.cumsum(lens)]), tasks, 83,
+                       s=np.linspace(-1, 2, len(ranks)).astype(np.float32), fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
+    chunks = np.diff(plan.query(bd.Q_TASK_CHUNKS)).tolist()
+    plan.close()
+    assert chunks[0] == 1 and chunks[2] == 1 and (chunks[1] > 1 and chunks[3] == 0 if empty_task else chunks[1] == 1), chunks
+    dp, _ = check_problem(p, label="single chunks")
+    first = [dp.dA.clone(), dp.dB.clone()]
+    dp.dA.fill_(1.0)
+    dp.dB.fill_(-2.0)
+    dp.bwd(flags=bd.FLAG_ACCUMULATE_GRADS)
+    torch.cuda.synchronize()
+    assert torch.equal(dp.dA, first[0] + 1.0) and torch.equal(dp.dB, first[1] - 2.0)       # one fp32 addition each
+    dp.bwd()
+    torch.cuda.synchronize()
+    assert torch.equal(dp.dA, first[0]) and torch.equal(dp.dB, first[1]) and dp.guards_intact()
+
+
 def test_empty_batch_and_argument_errors():
     import torch
     p = wl.make_custom("empty", "bf16", 64, 64, [8], [0], [], 5)
