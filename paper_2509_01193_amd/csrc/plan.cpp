@@ -353,8 +353,8 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t pa
             if (s > 1 && (i == 0 || K < kMinSplitK || kt < 4 * s || tiles * s > slots || uint64_t(bytes) > part_bytes)) break;
             const int64_t full = tiles * s / slots, rest = tiles * s % slots;
             const float per = float((kt + s - 1) / s), most = t.per_cu == 2 ? t.k2 : t.k1;
-            float cost = float(full) * (most * per + t.fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + t.fixed : 0.f);
-            if (s > 1) cost = 1.1f * (cost + 4.f + float(bytes) / 2e6f);     // (it has to be worth it)
+            float cost = float(full) * (most * per + t.fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + t.fixed : 0.f) + t.once;
+            if (s > 1) cost += 3.f + float(bytes) / 3e6f;
             if (least < 0.f || cost < least) best = GemmChoice{i, s, cost}, least = cost;
         }
     }

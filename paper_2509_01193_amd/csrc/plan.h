@@ -29,7 +29,8 @@ constexpr int kSlicedGrid = 256;      // its workgroups: 8 XCDs x 32 compute uni
 SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 
 // The kernels a bf16 product can run on and what a K tile of 64 costs there, measured (us, K = 4096; the tiled kernels with
-// one workgroup per compute unit and, where two fit, with two; `fixed`: start, adapter term and stores of a tile):
+// one workgroup per compute unit and, where two fit, with two; `fixed`: start, adapter term and stores of a tile; `once`: what
+// the persistent kernel, whose tiles follow each other in one stream, pays only at the start):
 //     tile        persistent 256 x 256   128 x 256   128 x 128   128 x 64      64 x 64
 //     T = 40      112 us                 44          31          24            18
 //     T = 200     113                    46          33          25            21
@@ -40,19 +41,21 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 // (x [T, 4096] times W [4096, 4096]; a register-staged kernel took 112 us below 256 tokens.)
 // A tile's bytes through the copy path and its LDS reads grow slower than its MFMAs, so the largest tile that still
 // gives every compute unit one is the best; what remains is the count of rounds, which the choice estimates.
-struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed; };
+struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed, once; };
 constexpr GemmTile kGemmTiles[] = {
-    {256, 256, 1, 1.35f, 0.f, 12.f},     // gemm_persistent_kernel
-    {128, 256, 1, 0.86f, 0.f, 6.f},
-    {128, 128, 1, 0.48f, 0.f, 6.f},
-    {128, 64, 2, 0.33f, 0.59f, 6.f},
-    {64, 64, 2, 0.23f, 0.39f, 6.f},
+    {256, 256, 1, 1.35f, 0.f, 5.f, 7.f},     // gemm_persistent_kernel
+    {128, 256, 1, 0.86f, 0.f, 6.f, 0.f},
+    {128, 128, 1, 0.48f, 0.f, 6.f, 0.f},
+    {128, 64, 2, 0.36f, 0.59f, 6.f, 0.f},
+    {64, 64, 2, 0.23f, 0.39f, 6.f, 0.f},
 };
 constexpr int32_t kGemmKTile = 64;
 constexpr int32_t kPersistentMinKTail = 520;   // an ordinary pair of K tiles, two pairs of the special kinds, and more
 // Where a product has fewer tiles than compute units and a long K (decoding, narrow shards), K is split among up to eight
-// workgroups per tile, each of which writes its fp32 sums to scratch; a small kernel adds them in order (4 us, and the
-// sums' way to memory and back at 4 TB/s): x [40, 4096] W [4096, 4096] with 8 adapters 24 -> 13.6 + 4.0 us, x [7, 5248]
+// workgroups per tile, each of which writes its fp32 sums to scratch; a small kernel adds them in order (3 us, and the
+// sums' way to memory and back, mostly through the caches, at 6 TB/s: with a tile's time as above that puts 519 x 5504 x 1928
+// on two splits of 128 x 128, 29 us instead of 36, 1720 x 8192 x 768 likewise, 39 instead of 46, and leaves 200 x 4096 x 4096
+// unsplit, 21 instead of 24): x [40, 4096] W [4096, 4096] with 8 adapters 24 -> 13.6 + 4.0 us, x [7, 5248]
 // W [5248, 1024] 22.8 -> 8.4 + 2.5 us.  At most kMaxPartBytes of them, so that they fit the library's static scratch
 // array next to the projected activations.
 constexpr int32_t kMaxSplits = 8, kMinSplitK = 1024;
