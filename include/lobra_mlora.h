@@ -90,8 +90,8 @@ enum {
 enum {
     LOBRA_PLAN_HOST_ONLY = 1, /* build and keep the plan on the host only: no HIP call is made,
                                  the plan can be inspected with lobra_mlora_plan_query but not run */
-    LOBRA_PLAN_PLAIN_KERNELS = 2 /* bf16 only: run the plain fp32-FMA kernels of the fp32 path on
-                                    bf16 storage instead of the MFMA kernels (slow; a cross-check) */
+    LOBRA_PLAN_PLAIN_KERNELS = 2 /* bf16 only: run plain fp32-FMA kernels on the bf16 storage
+                                    instead of the MFMA kernels (slow; a cross-check) */
 };
 
 /* Problem descriptor.  Plain data; the three tables are HOST pointers that are read

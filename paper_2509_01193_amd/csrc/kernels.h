@@ -26,7 +26,7 @@ struct GradJob {
     int32_t fnsl = 0;
 };
 
-// ---- plain fp32-FMA kernels (fp32 path; bf16 storage as a cross-check) ---------------------
+// ---- fp32 storage: fp32 matrix-core kernels; bf16 storage: plain fp32-FMA kernels, a cross-check --
 // P[row, :r_t] = s_t * Z[row, :] M_t^T for every token of an adapter segment (fp32, stride r_max).
 // (ldz: row pitch of Z, 0 = D.  nproj > 1: projection `proj` of a fused shared-input call - only the
 //  rank window [proj r, (proj+1) r) of every task; the same three arguments below mean the same.)
@@ -40,8 +40,8 @@ hipError_t plain_gemm(const PlanDev& pd, int dtype, bool transW, const void* Z, 
                       hipStream_t st, int32_t ldc = 0, int32_t nproj = 1, int32_t proj = 0);
 // Stage 1 of dM_t = sum over the tokens of task t of P[i, :]^T Z[i, :]: one partial sum per
 // reduction chunk, written to part[chunk.part_row0 + rho, :].
-// P is fp32 [T][r_max], or (p_bf16) bf16 [T][r_pad].
-hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const void* P, const void* Z,
+// P is fp32 [T][r_max].
+hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, const void* P, const void* Z,
                              float* part, int32_t D, hipStream_t st, int32_t ldz = 0, int32_t nproj = 1,
                              int32_t proj = 0, const void* P2 = nullptr, const void* Z2 = nullptr,
                              float* part2 = nullptr, int32_t D2 = 0);

@@ -1,5 +1,6 @@
-// Plain fp32-FMA kernels: the fp32 path of the library, and (on bf16 storage) a slow
-// cross-check of the MFMA kernels.  Straightforward tiling, no matrix cores.
+// Plain fp32-FMA kernels on bf16 storage: a slow cross-check of the MFMA kernels (straightforward
+// tiling, no matrix cores); and the second stage of the gradients and the optimizer step, which
+// every path uses.  The launchers send fp32 storage to the fp32 matrix-core kernels.
 //
 // They implement the four products of the LoRA layer (paper section 2.1: X W + X (down)(up),
 // applied per task to a fused batch, section 1) and their derivatives:
@@ -18,29 +19,19 @@ namespace lobra {
 // same loop one element at a time.
 // -------------------------------------------------------------------------------------------
 namespace {
-template <typename E> struct Vec4;
-template <> struct Vec4<float> {
-    static __device__ __forceinline__ void load(const float* p, size_t i, float (&v)[4])
-    {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 t = *reinterpret_cast<const f4*>(p + i);
-        v[0] = t[0], v[1] = t[1], v[2] = t[2], v[3] = t[3];
-    }
-};
-template <> struct Vec4<uint16_t> {
-    static __device__ __forceinline__ void load(const uint16_t* p, size_t i, float (&v)[4])
-    {
-        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        const u2 t = *reinterpret_cast<const u2*>(p + i);
-        v[0] = __uint_as_float(t[0] << 16), v[1] = __uint_as_float(t[0] & 0xffff0000u);
-        v[2] = __uint_as_float(t[1] << 16), v[3] = __uint_as_float(t[1] & 0xffff0000u);
-    }
-};
+// four bf16 elements as fp32 (8-byte aligned)
+__device__ __forceinline__ void load4(const uint16_t* p, size_t i, float (&v)[4])
+{
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    const u2 t = *reinterpret_cast<const u2*>(p + i);
+    v[0] = __uint_as_float(t[0] << 16), v[1] = __uint_as_float(t[0] & 0xffff0000u);
+    v[2] = __uint_as_float(t[1] << 16), v[3] = __uint_as_float(t[1] & 0xffff0000u);
+}
 }  // namespace
 
-template <typename E, int VW>   // VW: elements per lane and step (4, or 1 for odd widths)
-__global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const E* __restrict__ Z,
-                                                           const E* __restrict__ M,
+template <int VW>   // VW: elements per lane and step (4, or 1 for odd widths)
+__global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
+                                                           const uint16_t* __restrict__ M,
                                                            const float* __restrict__ s,
                                                            float* __restrict__ P, int32_t D, int32_t ldz,
                                                            int32_t nproj, int32_t proj)
@@ -73,13 +64,13 @@ __global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const E* 
                 float z[8][VW], m[8][VW];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    if constexpr (VW == 4) Vec4<E>::load(Z, zoff[i] + k, z[i]);
-                    else z[i][0] = Elem<E>::load(Z, zoff[i] + k);
+                    if constexpr (VW == 4) load4(Z, zoff[i] + k, z[i]);
+                    else z[i][0] = Elem<uint16_t>::load(Z, zoff[i] + k);
                 }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
-                    if constexpr (VW == 4) Vec4<E>::load(M, moff[q] + k, m[q]);
-                    else m[q][0] = Elem<E>::load(M, moff[q] + k);
+                    if constexpr (VW == 4) load4(M, moff[q] + k, m[q]);
+                    else m[q][0] = Elem<uint16_t>::load(M, moff[q] + k);
                 }
 #pragma unroll
                 for (int e = 0; e < VW; ++e)
@@ -114,9 +105,9 @@ hipError_t plain_shrink(const PlanDev& pd, int dtype, const void* Z, const void*
     if (ldz == 0) ldz = D;
     if (dtype == LOBRA_F32) return shrink_f32(pd, (const float*)Z, (const float*)M, s, P, D, ldz, nproj, proj, st);
     const bool vec = (D & 3) == 0 && (ldz & 3) == 0;   // rows then start on 8-byte boundaries
-#define LOBRA_PLAIN_SHRINK(E, VW) \
-    plain_shrink_kernel<E, VW><<<pd.ntb, 256, 0, st>>>(pd, (const E*)Z, (const E*)M, s, P, D, ldz, nproj, proj)
-    if (vec) LOBRA_PLAIN_SHRINK(uint16_t, 4); else LOBRA_PLAIN_SHRINK(uint16_t, 1);
+#define LOBRA_PLAIN_SHRINK(VW) \
+    plain_shrink_kernel<VW><<<pd.ntb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s, P, D, ldz, nproj, proj)
+    if (vec) LOBRA_PLAIN_SHRINK(4); else LOBRA_PLAIN_SHRINK(1);
 #undef LOBRA_PLAIN_SHRINK
     return hipGetLastError();
 }
@@ -124,11 +115,11 @@ hipError_t plain_shrink(const PlanDev& pd, int dtype, const void* Z, const void*
 // -------------------------------------------------------------------------------------------
 // gemm: 64 x 64 tile, K step 16, 4 x 4 outputs per thread, the adapter term as further K steps per segment
 // -------------------------------------------------------------------------------------------
-template <typename E, bool TRANSW>
-__global__ __launch_bounds__(256) void plain_gemm_kernel(PlanDev pd, const E* __restrict__ Z,
-                                                         const E* __restrict__ W,
+template <bool TRANSW>
+__global__ __launch_bounds__(256) void plain_gemm_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
+                                                         const uint16_t* __restrict__ W,
                                                          const float* __restrict__ P,
-                                                         const E* __restrict__ M, E* __restrict__ C,
+                                                         const uint16_t* __restrict__ M, uint16_t* __restrict__ C,
                                                          int32_t K, int32_t N, int32_t ldw, int32_t ldc,
                                                          int32_t nproj, int32_t proj)
 {
@@ -150,16 +141,16 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlanDev pd, const E* __
             {   // Z tile: 64 rows x 16 k, k fastest in memory
                 const int kk = e & 15, m = e >> 4;
                 const int32_t row = row0 + m, k = k0 + kk;
-                zr[u] = (row < T && k < K) ? Elem<E>::load(Z, size_t(row) * K + k) : 0.f;
+                zr[u] = (row < T && k < K) ? Elem<uint16_t>::load(Z, size_t(row) * K + k) : 0.f;
             }
             if (TRANSW) {   // op(W)[k][n] = W[n*ldw + k]: k fastest
                 const int kk = e & 15, nn = e >> 4;
                 const int32_t n = col0 + nn, k = k0 + kk;
-                wr[u] = (n < N && k < K) ? Elem<E>::load(W, size_t(n) * ldw + k) : 0.f;
+                wr[u] = (n < N && k < K) ? Elem<uint16_t>::load(W, size_t(n) * ldw + k) : 0.f;
             } else {        // op(W)[k][n] = W[k*ldw + n]: n fastest
                 const int nn = e & 63, kk = e >> 6;
                 const int32_t n = col0 + nn, k = k0 + kk;
-                wr[u] = (n < N && k < K) ? Elem<E>::load(W, size_t(k) * ldw + n) : 0.f;
+                wr[u] = (n < N && k < K) ? Elem<uint16_t>::load(W, size_t(k) * ldw + n) : 0.f;
             }
         }
     };
@@ -216,7 +207,7 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlanDev pd, const E* __
                     {
                         const int nn = e & 63, kk = e >> 6;
                         const int32_t n = col0 + nn;
-                        Ws[kk][nn] = (c0 + kk < r && n < N) ? Elem<E>::load(M, size_t(r0 + c0 + kk) * N + n) : 0.f;
+                        Ws[kk][nn] = (c0 + kk < r && n < N) ? Elem<uint16_t>::load(M, size_t(r0 + c0 + kk) * N + n) : 0.f;
                     }
                 }
                 __syncthreads();
@@ -242,7 +233,7 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlanDev pd, const E* __
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int32_t col = col0 + tx * 4 + j;
-            if (col < N) Elem<E>::store(C, size_t(row) * ldc + col, acc[i][j]);
+            if (col < N) Elem<uint16_t>::store(C, size_t(row) * ldc + col, acc[i][j]);
         }
     }
 }
@@ -257,9 +248,10 @@ hipError_t plain_gemm(const PlanDev& pd, int dtype, bool transW, const void* Z, 
         return gemm_f32(pd, transW, (const float*)Z, (const float*)W, P, (const float*)M, (float*)C, K, N, ldw, ldc, nproj, proj, st);
     const dim3 grid((N + 63) / 64, (pd.T + 63) / 64);
     if (grid.y > 65535u) return hipErrorInvalidValue;
-#define LOBRA_LAUNCH(E, TR) \
-    plain_gemm_kernel<E, TR><<<grid, 256, 0, st>>>(pd, (const E*)Z, (const E*)W, P, (const E*)M, (E*)C, K, N, ldw, ldc, nproj, proj)
-    if (transW) LOBRA_LAUNCH(uint16_t, true); else LOBRA_LAUNCH(uint16_t, false);
+#define LOBRA_LAUNCH(TR)                                                                                      \
+    plain_gemm_kernel<TR><<<grid, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)W, P, (const uint16_t*)M, \
+                                                (uint16_t*)C, K, N, ldw, ldc, nproj, proj)
+    if (transW) LOBRA_LAUNCH(true); else LOBRA_LAUNCH(false);
 #undef LOBRA_LAUNCH
     return hipGetLastError();
 }
@@ -267,12 +259,11 @@ hipError_t plain_gemm(const PlanDev& pd, int dtype, bool transW, const void* Z, 
 // -------------------------------------------------------------------------------------------
 // gradreduce stage 1: one workgroup per (chunk, 256 columns), one thread per column
 // -------------------------------------------------------------------------------------------
-template <typename E, typename PE>
-__global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const PE* __restrict__ P,
-                                                               int32_t pstride, const E* __restrict__ Z,
+__global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const float* __restrict__ P,
+                                                               const uint16_t* __restrict__ Z,
                                                                float* __restrict__ part, int32_t D, int32_t ldz,
                                                                int32_t nproj, int32_t proj, int32_t tiles_a,
-                                                               const PE* __restrict__ P2, const E* __restrict__ Z2,
+                                                               const float* __restrict__ P2, const uint16_t* __restrict__ Z2,
                                                                float* __restrict__ part2, int32_t D2)
 {
     // nproj > 1: projection `proj` of a fused call - Z is its column block (row pitch ldz), and of the
@@ -301,14 +292,14 @@ __global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const
                 float z[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    z[u] = (live && rr + u < b.nrows) ? Elem<E>::load(Z, size_t(b.row0 + rr + u) * ldz + col) : 0.f;
+                    z[u] = (live && rr + u < b.nrows) ? Elem<uint16_t>::load(Z, size_t(b.row0 + rr + u) * ldz + col) : 0.f;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (rr + u >= b.nrows) break;
                     const size_t row = size_t(b.row0 + rr + u);
 #pragma unroll
                     for (int q = 0; q < 16; ++q)
-                        if (p0 + q < r) acc[q] = fmaf(Elem<PE>::load(P, row * pstride + pofs + p0 + q), z[u], acc[q]);
+                        if (p0 + q < r) acc[q] = fmaf(P[row * pd.r_max + pofs + p0 + q], z[u], acc[q]);
                 }
             }
         }
@@ -342,7 +333,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJo
     const int32_t c1 = fcnt ? fcnt[t * (first ? ja.fnsl : jb.fnsl) + (col >> 9)] : pd.task_chunk_off[t + 1];
     if (skip_single && !fcnt && c1 - c0 == 1) return;
     const int32_t frow = fcnt ? (first ? ja.frow0 : jb.frow0)[t] + p : 0;
-    const int nv = min(4, D - col);                 // D need not be a multiple of 4 on the fp32 path
+    const int nv = min(4, D - col);                 // D need not be a multiple of 4 outside the bf16 MFMA path
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     auto row_ptr = [&](int32_t c) {
         return part + size_t(fcnt ? frow + 16 * c : pd.chunks[c].part_row0 + p) * D + col;
@@ -406,7 +397,7 @@ hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& 
     return hipGetLastError();
 }
 
-hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const void* P, const void* Z,
+hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, const void* P, const void* Z,
                              float* part, int32_t D, hipStream_t st, int32_t ldz, int32_t nproj, int32_t proj,
                              const void* P2, const void* Z2, float* part2, int32_t D2)
 {
@@ -420,12 +411,8 @@ hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, bool p_bf16, const vo
     const int32_t tiles_a = (D + 255) / 256, tiles_b = P2 ? (D2 + 255) / 256 : 0;
     const dim3 grid(pd.nchunks, tiles_a + tiles_b);
     if (grid.y > 65535u) return hipErrorInvalidValue;
-    if (!p_bf16)
-        plain_gradreduce_kernel<uint16_t, float><<<grid, 256, 0, st>>>(pd, (const float*)P, pd.r_max, (const uint16_t*)Z, part, D, ldz, nproj, proj,
-                                                                        tiles_a, (const float*)P2, (const uint16_t*)Z2, part2, D2);
-    else
-        plain_gradreduce_kernel<uint16_t, uint16_t><<<grid, 256, 0, st>>>(pd, (const uint16_t*)P, pd.r_pad, (const uint16_t*)Z, part, D, ldz, nproj, proj,
-                                                                           tiles_a, (const uint16_t*)P2, (const uint16_t*)Z2, part2, D2);
+    plain_gradreduce_kernel<<<grid, 256, 0, st>>>(pd, (const float*)P, (const uint16_t*)Z, part, D, ldz, nproj, proj, tiles_a,
+                                                  (const float*)P2, (const uint16_t*)Z2, part2, D2);
     return hipGetLastError();
 }
 
