@@ -328,8 +328,9 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     bf16x8 za[MB], wa[NB], zb[MB], wb[NB];
     if (KT >= STAGES) wait_vmcnt<(STAGES - 1) * CPW>();
     else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    // (the barrier does not wait for LDS, and with a single K tile, or none - the adapter term's workgroup of a split
+    //  product -, it is the last one in front of the epilogue's reads of tab.row)
+    lds_barrier();
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) wa[nb] = read_w(lds, 0, nb);
 #pragma unroll

@@ -194,3 +194,75 @@ def test_sliced_kernel_waits_for_its_copies_by_count(sliced_kernels):
         for i, l in enumerate(code):
             if l == "s_barrier":
                 assert not any(re.match(r"s_waitcnt.*vmcnt\(0\)", code[k]) for k in range(max(0, i - 3), i)), (name, code[i - 4:i + 1])
+
+
+# ---------------------------------------------------------------------------------------------------------
+# The kernels with hand-placed barriers: the barrier instruction does not wait for LDS, so whatever a wave has written there
+# for others must be waited for in front of it, on every path.
+# ---------------------------------------------------------------------------------------------------------
+def _lds_writes_pending_at_a_barrier(lines):
+    """Follows every path through a kernel's assembly; returns the barriers (as the lines in front of them) at which a wave
+    may arrive with an LDS write of its own in flight.  LDS operations of a wave end in order, so `lgkmcnt(n)` covers a write
+    behind which n or more have been issued; the youngest write is the one to follow, and of two paths that meet, the one with fewer
+    operations behind it."""
+    labels = {l[:-1]: i for i, l in enumerate(lines) if l.endswith(":")}
+    none = 1 << 30                                   # no write in flight
+    best, todo, bad = {}, [(0, none)], set()
+    while todo:
+        i, behind = todo.pop()
+        while i < len(lines) and behind < best.get(i, none + 1):
+            best[i] = behind
+            l = lines[i]
+            if l.startswith("ds_write"):
+                behind = 0
+            elif l.startswith("ds_") and behind < none:
+                behind += 1
+            m = re.match(r"s_waitcnt\b.*lgkmcnt\((\d+)\)", l)
+            if m and behind >= int(m.group(1)):
+                behind = none
+            if l.startswith("s_barrier") and behind < none:
+                bad.add(i)
+            if l.startswith("s_endpgm"):
+                break
+            m = re.match(r"s_c?branch\w*\s+(\S+)$", l)
+            if m:
+                todo.append((labels[m.group(1)], behind))
+                if l.startswith("s_branch"):
+                    break
+            i += 1
+    return [lines[max(0, i - 6):i + 1] for i in sorted(bad)]
+
+
+def test_the_barrier_check_itself():
+    wait, nowait = "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_waitcnt vmcnt(0)"
+    assert not _lds_writes_pending_at_a_barrier(["ds_write_b32 v0, v1", wait, "s_barrier", "s_endpgm"])
+    assert _lds_writes_pending_at_a_barrier(["ds_write_b32 v0, v1", nowait, "s_barrier", "s_endpgm"])
+    # covered by count only if that many operations lie behind the write
+    assert not _lds_writes_pending_at_a_barrier(["ds_write_b32 v0, v1", "ds_read_b32 v2, v3", "s_waitcnt lgkmcnt(1)", "s_barrier", "s_endpgm"])
+    assert _lds_writes_pending_at_a_barrier(["ds_write_b32 v0, v1", "s_waitcnt lgkmcnt(1)", "s_barrier", "s_endpgm"])
+    # one of two paths waits
+    assert _lds_writes_pending_at_a_barrier(["ds_write_b32 v0, v1", "s_cbranch_scc0 .L", wait, ".L:", "s_barrier", "s_endpgm"])
+    # a write at a loop's end, a barrier at its head
+    assert _lds_writes_pending_at_a_barrier([".L:", "s_barrier", "ds_write_b32 v0, v1", "s_cbranch_scc0 .L", "s_endpgm"])
+
+
+@pytest.mark.parametrize("source,least", [("gemm_tile.hip", 8), ("gemm_persistent.hip", 2), ("gemm_persistent_ktail.hip", 2),
+                                          ("skinny_mfma.hip", 10), ("fp32_mfma.hip", 12)])
+def test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, source, least):
+    out = str(tmp_path / "k.s")
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "hip", "--cuda-device-only",
+           "-S", os.path.join(CSRC, source), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-3000:]
+    parts = re.split(r"^(_ZN5lobra\w+):", open(out).read(), flags=re.M)
+    kernels = barriers = 0
+    for name, body in zip(parts[1::2], parts[2::2]):
+        if ".end_amdhsa_kernel" not in body:
+            continue
+        lines = [l.split(";")[0].strip() for l in body[:body.index(".end_amdhsa_kernel")].split("\n")]
+        lines = [l for l in lines if l and (not l.startswith(".") or l.endswith(":"))]
+        kernels += 1
+        barriers += sum(l.startswith("s_barrier") for l in lines)
+        assert not _lds_writes_pending_at_a_barrier(lines), (name, _lds_writes_pending_at_a_barrier(lines)[0])
+    assert kernels >= least and barriers >= kernels, (kernels, barriers)
