@@ -67,7 +67,7 @@ typedef enum {
     LOBRA_ERR_SEGMENTS = -4,  /* seg_off[0] != 0, decreasing, or seg_off[S] != T */
     LOBRA_ERR_TASK_ID = -5,   /* a seg_task outside [-1, n_tasks) */
     LOBRA_ERR_RANK = -6,      /* rank_off[0] != 0 or a rank outside [1, LOBRA_MAX_RANK] */
-    LOBRA_ERR_WORKSPACE = -7, /* workspace NULL or smaller than lobra_mlora_workspace_bytes / _plan_sizes say */
+    LOBRA_ERR_WORKSPACE = -7, /* workspace NULL or too small: lobra_mlora_workspace_bytes / _plan_sizes say what is enough */
     LOBRA_ERR_ALIGN = -8,     /* a pointer not 16-byte aligned, or bf16 d_in/d_out not a multiple of 8 */
     LOBRA_ERR_HIP = -9,       /* a HIP runtime call failed (no device, launch error, ...) */
     LOBRA_ERR_PLAN = -10,     /* plan is NULL, host-only, or was built for another device */
@@ -157,7 +157,9 @@ LOBRA_API lobra_status lobra_mlora_plan_init(const lobra_mlora_desc *desc, uint3
 LOBRA_API lobra_status lobra_mlora_plan_destroy(lobra_mlora_plan *plan);
 
 /* Buffer sizes in bytes (each may be 0): h_save = the saved down-projected activations that
- * fwd can hand to bwd; fwd_ws / bwd_ws = scratch for one call.  Any out pointer may be NULL. */
+ * fwd can hand to bwd; fwd_ws / bwd_ws = scratch for one call.  Any out pointer may be NULL.
+ * (fwd_ws and bwd_ws include up to 12 MiB for the sums of a base product whose K is split: few tokens, long K.  A call with
+ * less workspace than that, down to what it needs without, runs the product unsplit: slower, the same result up to the order of the sums.) */
 LOBRA_API lobra_status lobra_mlora_plan_sizes(const lobra_mlora_plan *plan, size_t *h_save_bytes,
                                     size_t *fwd_ws_bytes, size_t *bwd_ws_bytes);
 
@@ -206,9 +208,8 @@ LOBRA_API lobra_status lobra_mlora_plan_query(const lobra_mlora_plan *plan, int3
  *   ws, ws_bytes  : device scratch of at least fwd_ws_bytes.  With h_save given only its first
  *                   fwd_ws_bytes - h_save_bytes bytes are used: the partial sums of the K-sliced down
  *                   projection that long batches of ranks up to 16 take, and those of a base product whose K is
- *                   split (few tokens, long K; up to 12 MiB).  The former are needed and checked; without room for
- *                   the latter the product is not split (slower, the same result up to the order of the sums), so
- *                   that with h_save ws may be NULL for every batch that is not long
+ *                   split.  Only the former are needed and checked (see lobra_mlora_plan_sizes), so that with h_save ws
+ *                   may be NULL for every batch that is not long
  *   hip_stream    : hipStream_t (NULL = default stream); work is enqueued, not awaited
  * x, W, A, B, s are read only; y and h_save are overwritten. */
 LOBRA_API lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan *plan, const void *x, const void *W,
@@ -258,8 +259,9 @@ LOBRA_API lobra_status lobra_mlora_plan_token_task_map(const lobra_mlora_plan *p
  * the same tables again; use a plan there.)
  *   lobra_mlora_workspace_bytes : bytes of ws that lobra_mlora_fwd (with h_save = NULL) and lobra_mlora_bwd
  *                                 need for this descriptor; host only, no HIP call; either out pointer may be NULL
- *   lobra_mlora_fwd / _bwd      : arguments as for the plan forms; ws (16-byte aligned, device) must hold
- *                                 *fwd_bytes / *bwd_bytes (LOBRA_ERR_WORKSPACE otherwise, before any launch)
+ *   lobra_mlora_fwd / _bwd      : arguments as for the plan forms; ws (16-byte aligned, device) should hold
+ *                                 *fwd_bytes / *bwd_bytes (LOBRA_ERR_WORKSPACE, before any launch, when it is too small; a
+ *                                 split product's sums are optional as in the plan forms)
  *   lobra_token_task_map        : has no workspace argument: its tables go into the library's static device
  *                                 array (see lobra_mlora_fwd_static_ws for the sharing rule; LOBRA_ERR_WORKSPACE
  *                                 beyond LOBRA_STATIC_WS_BYTES, about 30 million tokens) */

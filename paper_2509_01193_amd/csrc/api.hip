@@ -96,9 +96,9 @@ lobra_status fwd_check(const Plan& p, const void* x, const void* W, const void* 
     if (!aligned16(x) || !aligned16(W) || !aligned16(y) || !aligned16(A) || !aligned16(B) ||
         !aligned16(h_save) || !aligned16(ws))
         return LOBRA_ERR_ALIGN;
-    // the workspace holds the sliced projection's partial sums (if the plan uses it), then those of a split base product
-    // in the same place, and, without h_save, the projected activations behind them
-    const size_t need = h_save ? (sliced ? p.fwd_spart : 0) : (sliced ? p.fwd_off_p : 0) + p.p_layout.total;
+    // the workspace holds the sliced projection's partial sums (if the plan uses it), then, if there is room, those of a
+    // split base product in the same place, and, without h_save, the projected activations behind them
+    const size_t need = (sliced ? p.fwd_spart : 0) + (h_save ? 0 : p.p_layout.total);
     if (adapters && need > 0 && (!ws || ws_bytes < need)) return LOBRA_ERR_WORKSPACE;
     return LOBRA_OK;
 }
@@ -119,7 +119,7 @@ lobra_status bwd_check(const Plan& p, const void* x, const void* W, const void* 
     if (!aligned16(x) || !aligned16(W) || !aligned16(A) || !aligned16(B) || !aligned16(dy) ||
         !aligned16(h_saved) || !aligned16(dx) || !aligned16(dA) || !aligned16(dB) || !aligned16(ws))
         return LOBRA_ERR_ALIGN;
-    if (p.bwd_ws_bytes > 0 && adapters && (!ws || ws_bytes < p.bwd_ws_bytes)) return LOBRA_ERR_WORKSPACE;
+    if (p.bwd_need > 0 && adapters && (!ws || ws_bytes < p.bwd_need)) return LOBRA_ERR_WORKSPACE;
     return LOBRA_OK;
 }
 
@@ -328,9 +328,9 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
 }
 
 namespace {
-// The forward pass.  sliced = false: without the K-sliced projection and without a split base product even where the
-// plan would take them (their partial sums are most of the forward workspace): the projected activations then start
-// at ws itself.
+// The forward pass.  A workspace without room for the partial sums of a split base product goes without the split; sliced =
+// false: without the K-sliced projection either, even where the plan would take it (its partial sums are most of what the
+// workspace must hold then): the projected activations then start at ws itself.
 lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W, const void* A, const void* B,
                       const float* s, void* y, void* h_save, void* ws, size_t ws_bytes, void* hip_stream, bool sliced)
 {
@@ -341,9 +341,10 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     rs = fwd_check(p, x, W, A, B, s, y, h_save, ws, ws_bytes, sliced);
     if (rs != LOBRA_OK) return rs;
     const bool adapters = !p.tb.empty();
-    void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (sliced ? p.fwd_off_p : 0);
+    const bool room = sliced && ws && ws_bytes >= (h_save ? p.fwd_part : p.fwd_ws_bytes);       // for a split product's sums
+    void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (room ? p.fwd_off_p : (sliced ? p.fwd_spart : 0));
     const SlicedShape sliced_in = sliced ? p.sliced_in : SlicedShape{};
-    float* const part = sliced && ws && ws_bytes >= p.fwd_part && p.fwd_part > 0 ? static_cast<float*>(ws) : nullptr;
+    float* const part = room && p.fwd_part > 0 ? static_cast<float*>(ws) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const PlanDev pd = device_view(p);
     const int dt = p.desc.dtype;
@@ -408,7 +409,7 @@ lobra_status lobra_mlora_fwd_static_ws(const lobra_mlora_plan* plan, const void*
     if (rs != LOBRA_OK) return rs;
     // a batch whose K-sliced projection needs more than the array for its partial sums goes without it: the
     // one-block-per-workgroup projection needs the projected activations only
-    const bool sliced = plan->fwd_ws_bytes <= size_t(LOBRA_STATIC_WS_BYTES);
+    const bool sliced = plan->fwd_spart + plan->p_layout.total <= size_t(LOBRA_STATIC_WS_BYTES);
     if (!sliced && plan->p_layout.total > size_t(LOBRA_STATIC_WS_BYTES)) return LOBRA_ERR_WORKSPACE;
     // the kernels get the array's device address, looked up when the plan was created on this device
     return plan_fwd(plan, x, W, A, B, s, y, nullptr, plan->static_ws, size_t(LOBRA_STATIC_WS_BYTES), hip_stream, sliced);
@@ -495,7 +496,7 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,
                                pd.d_in, pd.d_out, st, 0, 1, 0,
-                               ws && ws_bytes >= p.bwd_ws_bytes && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr,
+                               ws && ws_bytes >= p.bwd_off_spart + p.bwd_part && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr,
                                p.bwd_part));
     if (p.R_tot > 0) {
         // dB (from s h and dy) and dA (from s g and x) share one launch per stage
@@ -632,7 +633,7 @@ lobra_status lobra_mlora_fwd(const lobra_mlora_desc* desc, const void* x, const 
     const size_t img = align256(p->blob_bytes);
     char* rest = static_cast<char*>(ws) + img;
     if (p->desc.T == 0) st = LOBRA_OK;
-    else if (!ws || ws_bytes < img + (h_save ? p->fwd_spart : p->fwd_off_p + p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
+    else if (!ws || ws_bytes < img + p->fwd_spart + (h_save ? 0 : p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
     else if (!aligned16(ws)) st = LOBRA_ERR_ALIGN;
     else if ((st = fwd_check(*p, x, W, A, B, s, y, h_save, rest, ws_bytes - img)) == LOBRA_OK &&
              (st = upload_oneshot(p, ws, stream)) == LOBRA_OK) {
@@ -654,7 +655,7 @@ lobra_status lobra_mlora_bwd(const lobra_mlora_desc* desc, const void* x, const 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const size_t img = align256(p->blob_bytes);
     char* rest = static_cast<char*>(ws) + img;
-    if (!ws || ws_bytes < img + p->bwd_ws_bytes) st = LOBRA_ERR_WORKSPACE;
+    if (!ws || ws_bytes < img + p->bwd_need) st = LOBRA_ERR_WORKSPACE;
     else if (!aligned16(ws)) st = LOBRA_ERR_ALIGN;
     else if ((st = bwd_check(*p, x, W, A, B, s, dy, h_saved, dx, dA, dB, flags, rest, ws_bytes - img)) == LOBRA_OK &&
              (st = upload_oneshot(p, ws, stream)) == LOBRA_OK) {

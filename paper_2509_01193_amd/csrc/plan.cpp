@@ -329,7 +329,8 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         p->bwd_off_part_a = p->bwd_off_part_b +
                             align_up(size_t(p->fused_db ? p->fb_rows : p->part_rows) * size_t(d->d_out) * 4, 256);
         p->bwd_off_spart = p->bwd_off_part_a + align_up(size_t(p->part_rows) * size_t(d->d_in) * 4, 256);
-        p->bwd_ws_bytes = p->bwd_off_spart + std::max(p->bwd_part, std::max(spart_in, spart_out));
+        p->bwd_need = p->bwd_off_spart + std::max(spart_in, spart_out);
+        p->bwd_ws_bytes = std::max(p->bwd_need, p->bwd_off_spart + p->bwd_part);
     } catch (const std::bad_alloc&) {
         return LOBRA_ERR_NOMEM;
     }

@@ -112,12 +112,13 @@ struct Plan {
     // activations follow at fwd_off_p unless the caller gives h_save), at bwd_off_spart in the backward one
     SlicedShape sliced_in, sliced_out;
     // The same scratch then takes the split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm): the
-    // projection is done by that time.  They are welcome and not needed: a forward call with h_save and less workspace
-    // than fwd_part does without, it needs fwd_spart only.
+    // projection is done by that time.  They are welcome and not needed: fwd_ws_bytes and bwd_ws_bytes have room for them, but
+    // a call is refused only below what it cannot do without - fwd_spart, and without h_save the projected activations
+    // (then at fwd_spart), in a forward call, bwd_need in a backward one.
     // (fwd_group: fused projections' forward products run as one launch whose tiles do not straddle multiples of this
     // many columns; 0: one launch per projection)
     int32_t fwd_group = 0;
-    size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0;
+    size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0, bwd_need = 0;
     // dB fused into the sliced projection of dy (one pass over dy for s_t B_t dy_i and for dB): a workgroup
     // keeps the dB sums of the (task, slice) it is working on and writes them out - 16 rank rows x 512
     // columns - whenever task or slice changes.  These tables say where: the runs of workgroup g are

@@ -255,6 +255,57 @@ def test_split_k_product_in_every_entry_point(T, d_in, d_out, n_proj):
     assert dp.guards_intact()
 
 
+@pytest.mark.parametrize("T,d_in,d_out,n_proj", [(40, 4104, 136, 1), (33, 4096, 4096, 1), (64, 5000, 192, 2)])
+def test_split_k_product_in_a_workspace_without_room_for_its_sums(T, d_in, d_out, n_proj):
+    """Workspaces of exactly what a call needs without the split, and of one alignment unit below what it takes: the products
+    run unsplit, the same bits in both and in the one-shot form, inside the workspace; below the least, an error and no launch."""
+    import torch
+    rng = np.random.default_rng(T)
+    ranks = [16, 40, 8] if n_proj == 1 else [16, 24, 8]
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("unsplit-%d" % T, "bf16", d_in, d_out, ranks, [0, T // 3, T], rng.integers(0, 3, 2), 73, s=[2.0, -1.0, 0.5],
+                       fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    dp = bd.DeviceProblem(p)
+    up = lambda v: (v + 255) // 256 * 256
+    tasks = dp.plan.query(bd.Q_GRAD_CHUNKS).reshape(-1, 4)[:, 2]
+    rows = int(np.diff(np.asarray(p.rank_off))[tasks].sum())
+    need_f = dp.plan.h_save_bytes
+    need_b = 2 * dp.plan.h_save_bytes + up(rows * p.d_out * 4) + up(rows * p.d_in * 4)
+    assert dp.plan.fwd_ws_bytes > need_f and dp.plan.bwd_ws_bytes >= need_b
+    d, keep = bd.make_desc(p.dtype, p.T, p.d_in, p.d_out, p.rank_off, p.seg_off, p.seg_task, n_proj)
+    img = up(bd.plan_device_bytes(d))
+    o = make_oracle(p)
+    dA, dB = o.grads()
+    ref = dict(y=o.y(), dx=o.dx(), dA=dA, dB=dB)
+    first = None
+    # (the last workspaces are one alignment unit short of the sizes reported; an unsplit backward product reports what it needs)
+    for nf, nb, oneshot in ((need_f, need_b, False), (need_f, need_b, True),
+                            (dp.plan.fwd_ws_bytes - 16, max(dp.plan.bwd_ws_bytes - 16, need_b), False)):
+        wf, wb = dp._guarded((nf + (img if oneshot else 0),), torch.uint8), dp._guarded((nb + (img if oneshot else 0),), torch.uint8)
+        for t in (dp.y, dp.dx, dp.dA, dp.dB):
+            t.fill_(7.0)
+        if oneshot:
+            bd.lobra_mlora_fwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, None, wf)
+            bd.lobra_mlora_bwd(d, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, None, dp.dx, dp.dA, dp.dB, 0, wb)
+        else:
+            bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, None, wf)
+            bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, None, dp.dx, dp.dA, dp.dB, 0, wb)
+        torch.cuda.synchronize()
+        got = dict(y=dp.y, dx=dp.dx, dA=dp.dA, dB=dp.dB)
+        assert dp.guards_intact(), (nf, nb)
+        for k in got:
+            assert relerr(dp.host(got[k]), ref[k]) <= TOL["bf16"], (k, nf, nb)
+        first = first or {k: v.clone() for k, v in got.items()}
+        assert all(torch.equal(got[k], first[k]) for k in got), (nf, nb)
+    short = torch.empty(need_f - 1, dtype=torch.uint8, device=dp.dev)
+    assert bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, None, short, check=False) == -7
+    short = torch.empty(need_b - 1, dtype=torch.uint8, device=dp.dev)
+    assert bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, None, dp.dx, dp.dA, dp.dB, 0, short, check=False) == -7
+    torch.cuda.synchronize()
+    assert torch.equal(dp.y, first["y"]) and torch.equal(dp.dx, first["dx"])
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [
     (64, 136, 200, 1), (130, 72, 4104, 1), (900, 72, 4000, 1), (300, 64, 128, 2), (128, 136, 72, 3),
 ])

@@ -140,6 +140,33 @@ def test_workspace_bytes_and_one_shot_argument_errors():
     assert L.lobra_mlora_fwd(ctypes.byref(e), None, None, None, None, None, None, None, None, 0, None) == 0
 
 
+def split_k_floor(plan, rank_off):
+    """Least (forward without h_save, backward) workspace of a short MFMA batch: the projected activations, once and twice,
+    and the reduction's partial sums (a split product's sums are not needed)."""
+    up = lambda v: (v + 255) // 256 * 256
+    tasks = plan.query(bd.Q_GRAD_CHUNKS).reshape(-1, 4)[:, 2]
+    rows = int(np.diff(np.asarray(rank_off))[tasks].sum()) if len(tasks) else 0
+    return plan.h_save_bytes, 2 * plan.h_save_bytes + up(rows * plan.d_out * 4) + up(rows * plan.d_in * 4)
+
+
+@pytest.mark.parametrize("tasks", [[0, 1, -1], [-1, -1, -1]])
+def test_one_shot_workspace_without_room_for_a_split_products_sums(tasks):
+    """Both products of this batch split K, and the sizes reported have room for their sums; a workspace without it is
+    accepted all the same (a misaligned one is refused as such), one byte less is too small."""
+    rank_off = [0, 16, 24]
+    d, keep = bd.make_desc("bf16", 40, 4096, 4096, rank_off, [0, 10, 30, 40], tasks)
+    plan = bd.Plan("bf16", 40, 4096, 4096, rank_off, [0, 10, 30, 40], tasks, bd.PLAN_HOST_ONLY)
+    fwd, bwd = split_k_floor(plan, rank_off)
+    assert plan.fwd_ws_bytes >= fwd + 2 * 40 * 4096 * 4 and plan.bwd_ws_bytes >= bwd + 2 * 40 * 4096 * 4
+    img = (bd.plan_device_bytes(d) + 255) // 256 * 256
+    L, one, odd = bd.lib(), ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004)       # never dereferenced
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, None, odd, img + fwd, None) == -8
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, None, odd, img + fwd - 1, None) == -7
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, one, odd, img, None) == -8
+    assert L.lobra_mlora_bwd(ctypes.byref(d), one, one, one, one, one, one, None, one, one, one, 0, odd, img + bwd, None) == -8
+    assert L.lobra_mlora_bwd(ctypes.byref(d), one, one, one, one, one, one, None, one, one, one, 0, odd, img + bwd - 1, None) == -7
+
+
 def test_plan_init_argument_errors():
     """The errors of lobra_mlora_plan_init that precede its first HIP call."""
     p = wl.make_config(1, fill=False)
