@@ -252,18 +252,33 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         // (the MFMA kernel gives each of its four waves a token block of the chunk at a time; the plain
         //  kernel walks a chunk's tokens one after the other, so small batches want short chunks there)
         cb = std::max<int64_t>(p->mfma ? 4 : 1, std::min<int64_t>(64, cb));
-        // Small batches: one chunk per task if that gives about every compute unit a workgroup of its own and no wave more
-        // than six blocks; the sums are then final and there is no second stage (1000 tokens, 4 tasks, 4096 x 4096:
-        // stage 1 6.6 -> 7.5 us, stage 2 4.2 us gone)
+        // Small batches: one chunk per task where that is the faster way to the gradients: the sums are then final and there
+        // is no second stage (6 us and the partial sums' way to memory and back), but a launch lasts as long as its longest chain
+        // of blocks.  Both stages, several chunks per task against one, with n blocks in the largest task (us):
+        //   ranks up to 16 (the kernel's four waves take blocks in turn, 128 columns a workgroup): one is better at every measured
+        //     point, n = 5 .. 24, 1 .. 16 tasks: 4 tasks, 4096 x 4096, n = 24: 21.9 / 13.5
+        //   ranks above 16 (every wave walks all blocks, 256 columns a workgroup: about 1 us a block): up to n = 12 one is better
+        //     (4 tasks of rank 24, 4096 x 4096: 19.2 / 16.5; n = 16: 19.2 / 20.1, n = 24: 25.1 / 27.8), and beyond where there are so
+        //     many partial sums that writing and adding them costs more: rank rows x column tiles of 10240 (3 tasks of rank 48, 9216:
+        //     n = 24 26.5 / 27.5; 3 of 64, 12288: 29.1 / 27.9; 16 of 64: 74.9 / 41.6)
+        //   fused projections (dA and dB in launches of their own, each with fewer workgroups): up to n = 10, or from 40960 on
+        //     (P = 2, 4096 x 8192, 4 tasks of stacked rank 64: n = 10 30.9 / 30.2, n = 12 31.4 / 33.6; 24576 against 49152, n = 24: 42.4 /
+        //     49.5 and 61.5 / 53.1); where dB takes a launch per projection, up to n = 6 (P = 3, 2048 x 3192, 8 tasks of stacked rank
+        //     24 and 96: n = 6 35.0 / 33.2 and 48.4 / 46.4, n = 8 37.2 / 36.4 and 51.6 / 53.0)
+        // In every case only with a workgroup for most compute units.
         if (p->mfma && !p->fused_db) {
-            int64_t most = 0, active = 0;
+            int64_t most = 0, active = 0, rows = 0;
             for (int32_t t = 0; t < n; ++t) {
                 const int64_t nb = p->task_tb_off[t + 1] - p->task_tb_off[t];
                 most = std::max(most, nb);
                 active += nb > 0;
+                if (nb > 0) rows += (p->rank_off[t + 1] - p->rank_off[t] + 15) / 16 * 16;
             }
             const int64_t tiles = (d->d_in + 127) / 128 + (d->d_out + 127) / 128;
-            if (most <= 24 && active * tiles >= 192) cb = std::max(cb, most);
+            int64_t limit = 24;
+            if (p->n_proj > 1 && p->dg % 128 != 0) limit = 6;
+            else if (p->r_pad > 16 && rows * tiles < (p->n_proj > 1 ? 40960 : 10240)) limit = p->n_proj > 1 ? 10 : 12;
+            if (most <= limit && active * tiles >= 192) cb = std::max(cb, most);
         }
         p->chunk_blocks = int32_t(cb);
         p->chunks.clear();

@@ -140,6 +140,27 @@ def test_workspace_bytes_and_one_shot_argument_errors():
     assert L.lobra_mlora_fwd(ctypes.byref(e), None, None, None, None, None, None, None, None, 0, None) == 0
 
 
+@pytest.mark.parametrize("d_in,d_out,n_proj,rank,tasks,one,several", [
+    (4096, 4096, 1, 16, 4, 24, 25),        # ranks up to 16: up to 24 blocks
+    (4096, 4096, 1, 24, 4, 12, 13),        # above: up to 12,
+    (4096, 4096, 1, 64, 4, 24, 25),        #   or where there are many partial sums
+    (4096, 4096, 1, 24, 8, 24, 25),
+    (4096, 12288, 3, 48, 4, 10, 11),       # fused projections
+    (4096, 12288, 3, 96, 8, 24, 25),
+    (2048, 3192, 3, 24, 8, 6, 7),          #   whose dB takes a launch per projection
+    (4096, 12288, 2, 16, 4, 24, 25),
+])
+def test_one_reduction_chunk_per_task_only_where_it_is_faster(d_in, d_out, n_proj, rank, tasks, one, several):
+    """A task's gradient sums take one chunk up to `one` token blocks and several from `several` on."""
+    for blocks, chunks in ((one, 1), (several, 2)):
+        T = 32 * blocks * tasks
+        plan = bd.Plan("bf16", T, d_in, d_out, np.arange(tasks + 1) * rank, np.arange(tasks + 1) * (T // tasks), np.arange(tasks),
+                       bd.PLAN_HOST_ONLY, n_proj)
+        per_task = np.diff(plan.query(bd.Q_TASK_CHUNKS))
+        assert plan.query(bd.Q_SLICED)[2] == 0
+        assert (per_task == 1).all() if chunks == 1 else (per_task > 1).all(), (blocks, per_task)
+
+
 def split_k_floor(plan, rank_off):
     """Least (forward without h_save, backward) workspace of a short MFMA batch: the projected activations, once and twice,
     and the reduction's partial sums (a split product's sums are not needed)."""
