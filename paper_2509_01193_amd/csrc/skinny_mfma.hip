@@ -197,7 +197,7 @@ __global__ __launch_bounds__(64 * NWV) void shrink_mfma_kernel(PlanDev pd, const
 }
 
 // -------------------------------------------------------------------------------------------------
-// shrink for short batches (fewer token blocks than half the compute units): one workgroup per half of a token block
+// shrink for short batches (where: see the launcher below): one workgroup per half of a token block
 // and 16 ranks, 16 waves split K.  What bounds such a launch is the time a workgroup takes, which is a chain of memory
 // round trips: the kernel above walks eight slabs of 128 per wave at K = 4096 and all rank blocks with them, and takes 12-14 us
 // at rank 16 and 22 us at rank 64 whether it has 1 or 256 blocks; here a wave walks two, both in flight at once (10 and
@@ -784,13 +784,27 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                                                             (uint16_t*)P_tok, (uint16_t*)P_blk, D);
         return hipGetLastError();
     }
-    if (pd.ntb <= 128) {
-        shrink_short_kernel<<<dim3(2 * pd.ntb, nrb * (proj < 0 ? nproj : 1)), 1024, 0, st>>>(
+    // Short batches: the kernel that splits K over 16 waves, rank blocks and token halves over workgroups, two of which fit a
+    // compute unit - faster as long as there are few of them, then slower than the kernel that keeps a token block's ranks
+    // together (us, that one / the short one):
+    //     ntb        D 256, rank 16   1024, 24     4096, 16      4096, 64      8192, 64      4096, 128
+    //     32          6.2 / 6.2       8.8 / 6.8    15.4 / 12.2   27.9 / 12.7   49.3 / 20.2   43.3 / 20.9
+    //     64          6.2 / 6.2       8.9 / 6.9    15.6 / 12.6   28.8 / 21.2   49.5 / 35.0   44.6 / 37.2
+    //     80          6.1 / 6.2       8.9 / 8.8    15.9 / 12.8   28.9 / 28.9   49.4 / 50.2   44.6 / 45.4
+    //     96          6.2 / 6.2       8.9 / 9.1    16.3 / 12.8   29.3 / 29.0   49.5 / 51.3   44.6 / 53.2
+    //     128         6.2 / 6.3       9.0 / 9.3    16.6 / 13.2   29.4 / 37.6   50.1 / 67.8   44.4 / 69.1
+    // With fused projections the other kernel has a workgroup per block and projection as well, and the line lies where the
+    // short one's are one per compute unit (dg 4096, rank 16 each: 2 projections, 64 / 80 blocks 16.4 / 13.7 and 16.5 / 21.4; 4
+    // projections, 32 / 48 blocks 16.3 / 13.4 and 16.8 / 20.8; rank 32 each, 2 projections, 32 / 48 blocks 23.1 / 13.1 and, at dg
+    // 512, 7.5 / 7.9).
+    const int32_t np = proj < 0 ? nproj : 1;
+    if (np > 1 ? 2 * int64_t(pd.ntb) * nrb * np <= 256 : pd.ntb <= (nrb <= 1 ? 128 : (nrb <= 2 ? 96 : 72))) {
+        shrink_short_kernel<<<dim3(2 * pd.ntb, nrb * np), 1024, 0, st>>>(
             pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj, nrb);
         return hipGetLastError();
     }
 #define LOBRA_SHRINK(NRB, DEPTH)                                                                       \
-    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(pd.ntb, proj < 0 ? nproj : 1), 256, 0, st>>>(                                           \
+    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(pd.ntb, np), 256, 0, st>>>(                                           \
         pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj)
     if (nrb <= 1) LOBRA_SHRINK(1, 3);
     else if (nrb <= 2) LOBRA_SHRINK(2, 2);

@@ -356,6 +356,23 @@ def test_gemm_k_beyond_the_last_whole_tile(T, d_in, d_out):
     assert not bool(torch.isfinite(dp.y[bad].float()).any()) and bool(torch.isnan(dp.dx[bad].float()).all())
 
 
+@pytest.mark.parametrize("blocks,ranks,n_proj", [
+    (128, [16, 8], 1), (129, [16, 8], 1), (96, [32, 17], 1), (97, [32, 17], 1), (72, [40, 128], 1), (73, [40, 128], 1),
+    (64, [8, 16], 2), (65, [8, 16], 2), (21, [8, 32], 3), (22, [8, 32], 3),
+])
+def test_projection_on_both_sides_of_the_short_batch_rule(blocks, ranks, n_proj):
+    """The last batch (in token blocks) that the kernel for short batches takes and the first that it leaves to the other (ranks per
+    projection), in
+    both directions, at one, two and more rank blocks and with fused projections."""
+    T = 32 * blocks - 5
+    cut = 32 * (blocks // 3)
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("short-rule-%d" % blocks, "bf16", 136, 72, ranks, [0, cut, 2 * cut, T], [0, 1, 0], 91, s=[2.0, -1.0],
+                       fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, label="%d blocks" % blocks)
+
+
 @pytest.mark.parametrize("n_proj", [1, 2])
 def test_persistent_gemm_up_projection_at_every_kind_of_rank(n_proj):
     """The GEMM's fused up projection takes the operands of a tile's first segment from a copy made ahead of the
