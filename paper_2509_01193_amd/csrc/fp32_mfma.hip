@@ -253,19 +253,21 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
 }
 
 // -------------------------------------------------------------------------------------------
-// shrink: one workgroup per half of a token block (16 tokens of one task), NW waves split K in groups of 16; both operands
-// go straight from global memory into registers, "A" = 16 rank rows, "B" = 16 token rows, four rank blocks at a time.
+// shrink: one workgroup per half of a token block (16 tokens of one task), NW waves (16, or 4 for longer batches) split K in
+// groups of 16; both operands go straight from global memory into registers, "A" = 16 rank rows, "B" = 16 token rows, four
+// rank blocks at a time.
 // Latency and memory bound: a wave has the loads of four groups in flight (two at large ranks).
 // -------------------------------------------------------------------------------------------
-template <int NRB, bool VEC>
-__global__ __launch_bounds__(1024) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
+template <int NRB, int NW, bool VEC>
+__global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
                                                          const float* __restrict__ s, float* __restrict__ P, int32_t D,
                                                          int32_t ldz, int32_t nproj, int32_t proj)
 {
     // nproj > 1 (fused shared-input projections): projection `proj` only - Z is its column block of
     // dy (row pitch ldz), M its rows of the compact up factors, and of the task's ranks the window
     // [proj r, (proj + 1) r) is read and written
-    constexpr int NW = 16, DEPTH = NRB == 4 ? 2 : 4;      // (128 registers per wave)
+    constexpr int DEPTH = NRB == 4 ? 2 : 4;          // (128 registers per wave)
+    static_assert(NW >= NRB, "a wave per rank block adds the sums");
     __shared__ f32x4 red[NW][NRB][64];
     const TokenBlock b = pd.tb[blockIdx.x >> 1];
     const int half = blockIdx.x & 1;
@@ -329,11 +331,19 @@ hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const f
 {
     const bool vec = ((D | ldz) & 3) == 0;
     const int nrb = (pd.r_max / nproj + 15) / 16;
-#define LOBRA_F32_SHRINK(NRB)                                                                                              \
+    // 16 waves where every compute unit has at most one workgroup, so that what counts is how long one takes; else 4: a
+    // workgroup's waves are then as many fewer to start (us, 4 / 16 waves, blocks of 32 tokens: 128 blocks x 1024, rank 64 23.6 /
+    // 16.7, 192 27.9 / 27.4, 4096 340 / 379; 128 x 256, rank 16 6.1 / 6.4, 4096 36 / 62; blocks of one token, 4096 x 256, rank 16:
+    // 26 / 59).  It also keeps the launch below 2^32 threads, beyond which the grid wraps silently, at any number of
+    // blocks: 512 threads each, and no more blocks than tokens (kPlainMaxTokens).
+    static_assert(kPlainMaxTokens * 2 * 256 < (int64_t(1) << 32), "the grid of four waves per half block");
+    const bool few = pd.ntb <= 128;
+#define LOBRA_F32_SHRINK2(NRB, NW)                                                                                         \
     do {                                                                                                                   \
-        if (vec) shrink_f32_kernel<NRB, true><<<2 * pd.ntb, 1024, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);            \
-        else shrink_f32_kernel<NRB, false><<<2 * pd.ntb, 1024, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);               \
+        if (vec) shrink_f32_kernel<NRB, NW, true><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);     \
+        else shrink_f32_kernel<NRB, NW, false><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);        \
     } while (0)
+#define LOBRA_F32_SHRINK(NRB) do { if (few) LOBRA_F32_SHRINK2(NRB, 16); else LOBRA_F32_SHRINK2(NRB, 4); } while (0)
     if (nrb <= 1) LOBRA_F32_SHRINK(1);
     else if (nrb <= 2) LOBRA_F32_SHRINK(2);
     else LOBRA_F32_SHRINK(4);

@@ -1,6 +1,7 @@
 // Plain fp32-FMA kernels on bf16 storage: a slow cross-check of the MFMA kernels (straightforward
 // tiling, no matrix cores); and the second stage of the gradients and the optimizer step, which
-// every path uses.  The launchers send fp32 storage to the fp32 matrix-core kernels.
+// every path uses.  The launchers send fp32 storage to the fp32 matrix-core kernels, except for projections of
+// very short token blocks (see plain_shrink).
 //
 // They implement the four products of the LoRA layer (paper section 2.1: X W + X (down)(up),
 // applied per task to a fused batch, section 1) and their derivatives:
@@ -15,11 +16,17 @@ namespace lobra {
 // shrink: one workgroup per token block; wave w takes the rows 8w .. 8w+7 and, eight ranks at a
 // time, keeps an 8 x 8 block of sums in registers while its lanes stride over D four elements at
 // a time (so a rank row fetched from the cache serves eight token rows); the 64 lanes' partial
-// sums are combined with shuffles at the end.  Widths that are not a multiple of 4 take the
-// same loop one element at a time.
+// sums are combined with shuffles at the end.  fp32 widths that are not a multiple of 4 take the
+// same loop one element at a time (bf16 widths are multiples of 8).
 // -------------------------------------------------------------------------------------------
 namespace {
-// four bf16 elements as fp32 (8-byte aligned)
+// four elements as fp32 (aligned to their size together)
+__device__ __forceinline__ void load4(const float* p, size_t i, float (&v)[4])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 t = *reinterpret_cast<const f4*>(p + i);
+    v[0] = t[0], v[1] = t[1], v[2] = t[2], v[3] = t[3];
+}
 __device__ __forceinline__ void load4(const uint16_t* p, size_t i, float (&v)[4])
 {
     typedef uint32_t u2 __attribute__((ext_vector_type(2)));
@@ -29,9 +36,9 @@ __device__ __forceinline__ void load4(const uint16_t* p, size_t i, float (&v)[4]
 }
 }  // namespace
 
-template <int VW>   // VW: elements per lane and step (4, or 1 for odd widths)
-__global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
-                                                           const uint16_t* __restrict__ M,
+template <typename E, int VW>   // VW: elements per lane and step (4, or 1 for odd widths)
+__global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const E* __restrict__ Z,
+                                                           const E* __restrict__ M,
                                                            const float* __restrict__ s,
                                                            float* __restrict__ P, int32_t D, int32_t ldz,
                                                            int32_t nproj, int32_t proj)
@@ -65,12 +72,12 @@ __global__ __launch_bounds__(256) void plain_shrink_kernel(PlanDev pd, const uin
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     if constexpr (VW == 4) load4(Z, zoff[i] + k, z[i]);
-                    else z[i][0] = Elem<uint16_t>::load(Z, zoff[i] + k);
+                    else z[i][0] = Elem<E>::load(Z, zoff[i] + k);
                 }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     if constexpr (VW == 4) load4(M, moff[q] + k, m[q]);
-                    else m[q][0] = Elem<uint16_t>::load(M, moff[q] + k);
+                    else m[q][0] = Elem<E>::load(M, moff[q] + k);
                 }
 #pragma unroll
                 for (int e = 0; e < VW; ++e)
@@ -103,13 +110,30 @@ hipError_t plain_shrink(const PlanDev& pd, int dtype, const void* Z, const void*
 {
     if (pd.ntb == 0) return hipSuccess;
     if (ldz == 0) ldz = D;
-    if (dtype == LOBRA_F32) return shrink_f32(pd, (const float*)Z, (const float*)M, s, P, D, ldz, nproj, proj, st);
-    const bool vec = (D & 3) == 0 && (ldz & 3) == 0;   // rows then start on 8-byte boundaries
-#define LOBRA_PLAIN_SHRINK(VW) \
-    plain_shrink_kernel<VW><<<pd.ntb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s, P, D, ldz, nproj, proj)
-    if (vec) LOBRA_PLAIN_SHRINK(4); else LOBRA_PLAIN_SHRINK(1);
+#define LOBRA_PLAIN_SHRINK(E, VW) \
+    plain_shrink_kernel<E, VW><<<pd.ntb, 256, 0, st>>>(pd, (const E*)Z, (const E*)M, s, P, D, ldz, nproj, proj)
+    if (dtype != LOBRA_F32) {
+        LOBRA_PLAIN_SHRINK(uint16_t, 4);
+        return hipGetLastError();
+    }
+    // fp32: the matrix-core kernel, except for many blocks of a few tokens (a batch of requests, each of another task than its
+    // neighbours).  Those are bound by the rank rows that every block reads again, which this kernel fetches a kilobyte
+    // of a row at a time and the matrix core's operands 64 bytes of 16 rows (us, this kernel / the other):
+    //     blocks x width           1024 x 1024  4096 x 1021   1024 x 4096   4096 x 4096
+    //     rank 8, 1 / 8 tokens     18/23, 24/27  40/84, 44/93  39/77, 54/84  107/287, 234/332
+    //     rank 16, 1 / 4 / 8       29/26, 37/29  69/92, 70/96  72/87, 93/94  192/319, 263/343, 400/410
+    //     rank 32, 1 / 2 / 4       50/41         123/129       133/144, 151/145, 180/153   361/521
+    //     rank 128, 1 / 2          176/143       460/477       504/529, 583/530            1412/1980
+    // (256 blocks: the other, at any width and rank)
+    const int32_t r_win = pd.r_max / nproj;
+    const int64_t most = r_win <= 8 ? 8 : (r_win <= 16 ? 4 : 2), least = r_win <= 8 ? 1000000 : 4000000;
+    if (pd.ntb >= 512 && pd.T <= most * pd.ntb && int64_t(pd.ntb) * D >= least) {
+        if (((D | ldz) & 3) == 0) LOBRA_PLAIN_SHRINK(float, 4);      // rows start on 16-byte boundaries
+        else LOBRA_PLAIN_SHRINK(float, 1);
+        return hipGetLastError();
+    }
 #undef LOBRA_PLAIN_SHRINK
-    return hipGetLastError();
+    return shrink_f32(pd, (const float*)Z, (const float*)M, s, P, D, ldz, nproj, proj, st);
 }
 
 // -------------------------------------------------------------------------------------------

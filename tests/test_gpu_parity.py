@@ -424,6 +424,34 @@ def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
     assert bool(torch.isnan(dp.y[bad]).all()) and not bool(torch.isfinite(dp.dx[bad]).any())
 
 
+@pytest.mark.parametrize("blocks,tokens,d_in,d_out,ranks,n_proj", [
+    (128, 30, 68, 40, [8, 40], 1), (129, 30, 68, 40, [8, 40], 1),        # 16 waves a workgroup, then 4
+    (1030, 1, 4100, 24, [16, 8], 1), (1030, 2, 4097, 5, [16, 3], 1),     # blocks so short that the vector kernel takes them,
+    (1030, 4, 4100, 24, [16, 8], 1), (1030, 5, 4100, 24, [16, 8], 1),    #   and just no longer,
+    (1030, 2, 24, 4100, [20, 40], 1), (1030, 3, 24, 4100, [20, 40], 1),  #   at higher ranks
+    (1030, 8, 1000, 24, [8, 3], 1), (1030, 9, 1000, 24, [8, 3], 1),      #   at lower ones
+    (1030, 1, 40, 4104, [8, 16], 2),
+])
+def test_fp32_projection_on_both_sides_of_its_rules(blocks, tokens, d_in, d_out, ranks, n_proj):
+    T = blocks * tokens
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("f32-projection-%d" % T, "f32", d_in, d_out, ranks, np.arange(blocks + 1) * tokens, np.arange(blocks) % 2, 43,
+                       s=[2.0, -1.0], fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, rows=np.arange(0, T, max(1, T // 400)), label="f32 projection")
+
+
+def test_fp32_batch_of_two_million_token_blocks():
+    """2.2 million segments of one token: more token blocks than a launch with a workgroup of 1024 threads per half block can
+    have (2^32 threads, beyond which the grid wraps and most blocks are never projected).  Width 1 takes the matrix-core projection, width 2 the vector one.  (The gradients add some 17200
+    partial sums one after the other: up to that many roundings of 2^-24 each.)"""
+    T = 2200000
+    p = wl.make_custom("f32-2M-blocks", "f32", 1, 2, [2, 3], np.arange(T + 1), np.arange(T) % 2, 47, s=[2.0, -1.0], std_x=1.0, std_w=0.5,
+                       std_a=0.5, std_b=0.5)
+    rows = np.concatenate([[0, 1, T // 2, T - 2, T - 1], np.random.default_rng(0).integers(0, T, 2000)])
+    check_problem(p, rows=np.unique(rows), tol=17200 * 2.0 ** -24, label="2M blocks")
+
+
 def test_config3_reversed_rank_pairing():
     p = wl.make_config(3, "shuffled", d_in=192, d_out=344, reverse_ranks=True)
     check_problem(p)
