@@ -45,8 +45,11 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __bui
 // gemm: TM x TN per workgroup of 2 x 2 waves, K step FBK, global -> registers -> LDS one K step ahead.  Bound by the matrix
 // cores: a K step of a 64 x 64 tile is 1024 cycles of MFMAs and a quarter of that in LDS reads (8192 x 2048 x 2048: 120
 // TFLOP/s, without the global loads 127, of 157).  The adapter term is further K steps per segment, with the rows
-// outside the segment masked.
+// outside the segment masked; where more than kFewSegments segments cross the tile, per task that has rows in it (8000
+// one-token segments of 8 tasks of rank 128, 10 x 1373: 4820 -> 290 us; 10119 tokens in segments of 3, rank 8, 64 x 1920: 390 -> 112).
 // -------------------------------------------------------------------------------------------
+constexpr int kFewSegments = 4;
+
 template <bool TRANSW, int TM, int TN, int FBK, int NBUF, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
                                                        const float* __restrict__ P, const float* __restrict__ M,
@@ -62,6 +65,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     constexpr int ZS = TM * FPITCH, WS = TRANSW ? TN * FPITCH : FBK * NPITCH;
     __shared__ __attribute__((aligned(16))) float lds[NBUF][ZS + WS];
     static_assert(16 * NPITCH <= WS, "the adapter's rank rows fit the W tile");
+    static_assert(TM <= 128, "two words of firsts");
+    __shared__ __attribute__((aligned(16))) int32_t row_task[TM];    // (see the adapter term of many segments)
+    __shared__ uint64_t firsts[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
     const int32_t id = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -149,20 +155,32 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     float pa[ZA], ma[WA];
     const int32_t row_end = min(row0 + TM, T);
     int32_t sf = pd.rowblk_seg[row0 / kRowBlock];
-    if (P)
+    const int32_t s0 = sf;                               // the segment of the tile's first row
+    const bool many = P && s0 + kFewSegments < pd.nseg && pd.cseg_off[s0 + kFewSegments] < row_end;    // (uniform)
+    if (P && !many)
         while (sf < pd.nseg && pd.cseg_task[sf] < 0 && pd.cseg_off[sf + 1] < row_end) ++sf;      // (uniform)
-    const int32_t sf_task = P && sf < pd.nseg ? pd.cseg_task[sf] : -1;
-    auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
+    const int32_t sf_task = P && !many && sf < pd.nseg ? pd.cseg_task[sf] : -1;
+    // (mine(u, row): whether the row of piece u is the segment's, or the task's)
+    auto load_adapter_of = [&](auto mine, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
 #pragma unroll
         for (int u = 0; u < ZA; ++u) {
             const int e = tid + 256 * u, kk = e & 15, row = row0 + (e >> 4);
-            pa[u] = (row >= lo && row < hi && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
+            pa[u] = (mine(u, row) && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < WA; ++u) {
             const int e = tid + 256 * u, n = col0 + e % TN, kk = e / TN;
             ma[u] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
         }
+    };
+    auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
+        load_adapter_of([&](int, int32_t row) { return row >= lo && row < hi; }, r, pofs, r0, c0);
+    };
+    auto stash_adapter = [&](float* zs, float* ws) {
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) zs[((tid + 256 * u) >> 4) * FPITCH + (tid & 15)] = pa[u];
+#pragma unroll
+        for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
     };
     if (sf_task >= 0) {
         const int32_t r = (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj;
@@ -199,14 +217,64 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
             const int32_t r0 = pd.rank_off[t] + pofs;
             for (int32_t c0 = 0; c0 < r; c0 += 16) {
                 if (sg != sf || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
-#pragma unroll
-                for (int u = 0; u < ZA; ++u) zs[((tid + 256 * u) >> 4) * FPITCH + (tid & 15)] = pa[u];
-#pragma unroll
-                for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
+                stash_adapter(zs, ws);
                 __syncthreads();
                 mac(zs, ws, 0, std::false_type{});
                 __syncthreads();
             }
+        }
+    }
+    // many segments: the same steps, once per task with rows in the tile (in the order of their first rows), each with all of the
+    // task's rows; the next step's pieces are fetched while one is multiplied
+    if (many) {
+        if (tid < TM) {
+            const int32_t sg = s0 + tid;                 // (at most one segment per row)
+            if (sg < pd.nseg && pd.cseg_off[sg] < row_end) {
+                const int32_t t = pd.cseg_task[sg], hi = min(pd.cseg_off[sg + 1], row_end) - row0;
+                for (int32_t i = max(pd.cseg_off[sg], row0) - row0; i < hi; ++i) row_task[i] = t;
+            }
+            if (row0 + tid >= row_end) row_task[tid] = -1;
+        }
+        __syncthreads();
+        const int32_t own = tid < TM ? row_task[tid] : -1;
+        bool first = own >= 0;
+        for (int i = 0; i < TM; i += 4) {
+            const int4 a = *reinterpret_cast<const int4*>(&row_task[i]);
+            first &= !((a.x == own && i < tid) || (a.y == own && i + 1 < tid) || (a.z == own && i + 2 < tid) || (a.w == own && i + 3 < tid));
+        }
+        const uint64_t word = __ballot(first);
+        if (wave < 2 && lane == 0) firsts[wave] = word;
+        int32_t rt[ZA];                                  // tasks of this thread's rows
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) rt[u] = row_task[(tid + 256 * u) >> 4];
+        __syncthreads();
+        auto uniform = [](uint64_t v) {
+            return (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32)))) << 32) |
+                   uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v)));
+        };
+        uint64_t left[2] = {uniform(firsts[0]), uniform(firsts[1])};
+        int32_t t = -1, r = 0, c0 = 0;
+        auto next = [&]() {                              // moves to the next 16 ranks, of the next task at a task's end
+            c0 += 16;
+            if (c0 < r) return true;
+            const int w = left[0] ? 0 : 1;
+            if (!left[w]) return false;
+            t = __builtin_amdgcn_readfirstlane(row_task[64 * w + __builtin_ctzll(left[w])]);
+            left[w] &= left[w] - 1;
+            r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj;
+            c0 = 0;
+            return true;
+        };
+        auto load = [&]() { load_adapter_of([&](int u, int32_t) { return rt[u] == t; }, r, proj * r, pd.rank_off[t] + proj * r, c0); };
+        bool more = next();
+        if (more) load();
+        while (more) {
+            stash_adapter(lds[0], lds[0] + ZS);
+            __syncthreads();
+            more = next();
+            if (more) load();
+            mac(lds[0], lds[0] + ZS, 0, std::false_type{});
+            __syncthreads();
         }
     }
 #pragma unroll

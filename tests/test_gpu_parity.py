@@ -424,6 +424,25 @@ def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
     assert bool(torch.isnan(dp.y[bad]).all()) and not bool(torch.isfinite(dp.dx[bad]).any())
 
 
+@pytest.mark.parametrize("T,d_in,d_out,n_proj", [
+    (33, 40, 64, 1), (300, 100, 36, 1), (2100, 48, 1028, 1), (2100, 31, 1025, 1), (6200, 20, 1028, 1), (6200, 23, 1031, 1), (6200, 16, 1032, 2),
+])
+@pytest.mark.parametrize("lens", [(1, 2, 3), (1, 9, 33, 64), (32, 1)])
+def test_fp32_many_segments_in_one_output_tile(T, d_in, d_out, n_proj, lens):
+    """Segments of a few tokens over 70 tasks of every rank, in tiles of 32, 64 and 128: the adapter term then goes by task (more
+    than four segments in a tile) or by segment, with tasks that come back after others and rows without adapter between them."""
+    rng = np.random.default_rng(T + n_proj)
+    ranks = rng.choice([1, 5, 8, 16, 17, 33, 64, 128], 70) if n_proj == 1 else rng.choice([8, 16, 32, 40], 70)
+    cut = []
+    while sum(cut) < T:
+        cut.append(min(int(lens[len(cut) % 2] if len(lens) == 2 else rng.choice(lens)), T - sum(cut)))
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("f32-many", "f32", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(cut)]), rng.integers(-1, 70, len(cut)), 61,
+                       s=rng.uniform(-2, 2, 70).astype(np.float32), fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, rows=np.arange(0, T, max(1, T // 700)), label="f32 many segments")
+
+
 @pytest.mark.parametrize("blocks,tokens,d_in,d_out,ranks,n_proj", [
     (128, 30, 68, 40, [8, 40], 1), (129, 30, 68, 40, [8, 40], 1),        # 16 waves a workgroup, then 4
     (1030, 1, 4100, 24, [16, 8], 1), (1030, 2, 4097, 5, [16, 3], 1),     # blocks so short that the vector kernel takes them,
