@@ -1,5 +1,5 @@
-// Pieces shared by the bf16 MFMA kernels (the persistent GEMM, the tiled GEMM and the K-sliced rank-r kernel): vector types, the LDS swizzles, the
-// direct global -> LDS copy and the in-place MFMA on AGPR accumulators.
+// Pieces shared by the bf16 MFMA kernels (the persistent, tiled and register-staged GEMMs and the K-sliced rank-r kernel):
+// vector types, the LDS swizzles, the direct global -> LDS copy and the in-place MFMA on AGPR accumulators.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>

@@ -1,5 +1,6 @@
-// Tiled bf16 MFMA GEMM for gfx950 with the LoRA up projection fused into its epilogue, for the products that the
-// persistent kernel (gemm_persistent.hip) does not take: few output tiles, and K that is not a multiple of 128.
+// Tiled bf16 MFMA GEMM for gfx950 with the LoRA up projection fused into its epilogue, for products of few output tiles and,
+// where K is no multiple of 128, batches of short segments; the others run on the persistent kernel (gemm_persistent.hip) and
+// the register-staged one (gemm_staged.hip), see choose_gemm.
 //     C[T, N] = Z[T, K] * op(W) + P[T, r] * M_t[r, N]
 // forward : Z = x,  op(W) = W   (W stored [K][N], N fastest),  P = s_t A_t x_i,  M = B  -> y
 // backward: Z = dy, op(W) = W^T (W stored [N][K], K fastest),  P = s_t B_t dy_i, M = A  -> dx
@@ -9,8 +10,8 @@
 // One workgroup per TM x TN output tile, WM x WN waves, K in steps of 64 through a ring of STAGES LDS slots that
 // direct global -> LDS copies fill (no registers, no ds_write).  Blocks of v_mfma_f32_16x16x32_bf16 with fp32
 // accumulators; the MFMA "A" operand is fed from W and the "B" operand from Z, so a lane ends up with four
-// consecutive output columns of one row.  Sums run over ascending k in steps of 32 like the persistent kernel's,
-// so both give the same bits.
+// consecutive output columns of one row.  Sums run over ascending k in steps of 32 like the other kernels',
+// so all give the same bits.
 //
 // What bounds it: inside a compute unit, the copies (64 bytes a cycle) and the LDS reads of a 128 x 128 tile take as
 // long as its MFMAs (512 cycles per K tile each), so nothing may wait for anything else.  The order of a K step is
@@ -583,24 +584,27 @@ hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* 
     if (pd.T == 0) return hipSuccess;
     if (ldc == 0) ldc = N;
     if (!gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;   // (plan creation has checked already)
-    const GemmChoice choice = choose_gemm(pd.T, K, N, proj < 0 ? pd.dg : 0, part ? std::min(part_bytes, kMaxPartBytes) : 0);
+    const GemmChoice choice = choose_gemm(pd.T, K, N, proj < 0 ? pd.dg : 0, P ? pd.nseg : 0, part ? std::min(part_bytes, kMaxPartBytes) : 0);
 #define LOBRA_TILE(...)                                                                                          \
     (transW ? launch_tile<false, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part)                 \
             : launch_tile<true, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part))
     switch (choice.tile) {
-    case 0: {
+    case kPersistentTile:
+    case kStagedTile: {
         const int32_t tiles_m = (pd.T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
         // tile rows per sweep of the tile order: the workgroups that run on an XCD at one time share their
         // Z and W panels through its L2 only while they walk K nearly in step, and the row bands that the 8
         // XCDs sweep at one time (8 x rows x 256 x K x 2 bytes) should stay in the 256 MB infinity cache for
         // their re-reads; measured on the five workloads, long K wants shorter sweeps (K = 8192 .. 28672:
         // 4 rows up to 7 % faster than 8; K = 4096: 5 .. 8 alike)
-        return gemm_persistent(pd, transW, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, K > 4096 ? 4 : 6, st);
+        return (choice.tile == kStagedTile ? gemm_staged : gemm_persistent)(pd, transW, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m,
+                                                                           tiles_n, K > 4096 ? 4 : 6, st);
     }
     case 1: return LOBRA_TILE(128, 256, 2, 4, 3, 1);
     case 2: return LOBRA_TILE(128, 128, 2, 2, 4, 1);
     case 3: return LOBRA_TILE(128, 64, 2, 2, 3, 2);
-    default: return LOBRA_TILE(64, 64, 2, 2, 4, 2);
+    case 4: return LOBRA_TILE(64, 64, 2, 2, 4, 2);
+    default: return hipErrorInvalidValue;
     }
 #undef LOBRA_TILE
 }

@@ -69,7 +69,8 @@ hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* 
 // part, part_bytes: scratch for the sums of a product whose K is split (choose_gemm; NULL, 0: it is not split).
 // The persistent direct-to-LDS kernel behind gemm_mfma for many output tiles (gemm_persistent.hip; T >= 256, N >= 256, K a
 // multiple of 128, or any multiple of 8 from kPersistentMinKTail on);
-// gm = tile rows per sweep of the tile order.  Everything else runs on the tiled kernels of gemm_tile.hip.
+// gm = tile rows per sweep of the tile order.  Everything else runs on the tiled kernels of gemm_tile.hip and the
+// register-staged one of gemm_staged.hip (choose_gemm).
 // gemm_mfma_shape_ok: whether the kernels' 32-bit tile offsets can address the shape.
 hipError_t gemm_persistent(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                            const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj,
@@ -77,6 +78,9 @@ hipError_t gemm_persistent(const PlanDev& pd, bool transW, const void* Z, const 
 hipError_t gemm_persistent_ktail(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                            const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj,
                            int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t gm, hipStream_t st);
+hipError_t gemm_staged(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
+                       const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj,
+                       int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t gm, hipStream_t st);
 bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw);
 // P = s_t Z M_t^T in bf16, written token-major [T][r_pad] and block-transposed [ntb][r_pad][32].
 // (ldz: row pitch of Z; nproj > 1: projection `proj` of a fused call - rank window, see the kernel; proj < 0: all of

@@ -328,11 +328,12 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             // narrow tiles do, and a long batch is better off with a launch per projection (45861 x 904 x 2 x 3392: 1171
             // against 732 us)
             p->fwd_group = 0;
+            const int32_t ns = ntb > 0 ? nseg : 0;
             if (p->n_proj > 1 && p->dg % 64 == 0 &&
-                choose_gemm(T, d->d_in, d->d_out, p->dg, 0).cost <= float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, 0).cost + 3.f))
+                choose_gemm(T, d->d_in, d->d_out, p->dg, ns, 0).cost <= float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, ns, 0).cost + 3.f))
                 p->fwd_group = p->dg;
-            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group), 256);
-            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0), 256);
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns), 256);
+            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns), 256);
         }
         p->fwd_spart = spart_in;
         p->fwd_off_p = std::max(spart_in, p->fwd_part);
@@ -352,24 +353,37 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
     return LOBRA_OK;
 }
 
-GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t part_bytes)
+GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, size_t part_bytes)
 {
     constexpr int64_t cus = 256;             // fixed, so that the choice does not depend on the device
     const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
+    const bool ktail = K % (2 * kGemmKTile) != 0;
+    const float segments = std::max(0.f, float(nseg) * kGemmTileRows / float(T) - 1.f);      // per tile row, beyond the first
     GemmChoice best;
     float least = -1.f;
     for (int32_t i = 0; i < int32_t(sizeof(kGemmTiles) / sizeof(kGemmTiles[0])); ++i) {
         const GemmTile& t = kGemmTiles[i];
-        // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles
-        if (i == 0 && !((K % (2 * kGemmKTile) == 0 || K >= kPersistentMinKTail) && T >= t.tm && N >= t.tn)) continue;
+        // the persistent kernel: at least one whole output tile, and enough K for its special last pairs of K tiles; where
+        // it runs without those the staged kernel is never better
+        const bool whole = T >= t.tm && N >= t.tn;
+        if (i == kPersistentTile && !(whole && (!ktail || K >= kPersistentMinKTail))) continue;
+        if (i == kStagedTile && whole && !ktail) continue;
         if (group > 0 && group % t.tn != 0) continue;
+        // a Z beyond the 256 MB infinity cache is read once where one column tile takes all of N (47000 x 3200 x 248: 128 x 256
+        // 99 us, 128 x 128 118, 128 x 64 145)
+        if (group == 0 && N <= 256 && t.tn < N && int64_t(T) * K * 2 > (int64_t(256) << 20)) continue;
+        float fixed = t.fixed;
+        if (i == kPersistentTile && ktail) fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kSegmentCost.ktail * segments;
+        if (i == kStagedTile) fixed += kSegmentCost.staged * segments;
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = cus * t.per_cu;
         for (int32_t s = 1; s <= kMaxSplits; ++s) {
             const int64_t bytes = int64_t(s + 1) * T * N * 4;      // (one more for the adapter term)
-            if (s > 1 && (i == 0 || K < kMinSplitK || kt < 4 * s || tiles * s > slots || uint64_t(bytes) > part_bytes)) break;
+            if (s > 1 && (i == kPersistentTile || i == kStagedTile || K < kMinSplitK || kt < 4 * s || tiles * s > slots ||
+                          uint64_t(bytes) > part_bytes))
+                break;
             const int64_t full = tiles * s / slots, rest = tiles * s % slots;
             const float per = float((kt + s - 1) / s), most = t.per_cu == 2 ? t.k2 : t.k1;
-            float cost = float(full) * (most * per + t.fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + t.fixed : 0.f) + t.once;
+            float cost = float(full) * (most * per + fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + fixed : 0.f) + t.once;
             if (s > 1) cost += 3.f + float(bytes) / 3e6f;
             if (least < 0.f || cost < least) best = GemmChoice{i, s, cost}, least = cost;
         }
@@ -377,9 +391,9 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, size_t pa
     return best;
 }
 
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group)
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg)
 {
-    const GemmChoice c = choose_gemm(T, K, N, group, kMaxPartBytes);
+    const GemmChoice c = choose_gemm(T, K, N, group, nseg, kMaxPartBytes);
     return c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0;
 }
 

@@ -247,7 +247,7 @@ def test_the_barrier_check_itself():
 
 
 @pytest.mark.parametrize("source,least", [("gemm_tile.hip", 8), ("gemm_persistent.hip", 2), ("gemm_persistent_ktail.hip", 2),
-                                          ("skinny_mfma.hip", 10), ("fp32_mfma.hip", 12)])
+                                          ("skinny_mfma.hip", 10), ("fp32_mfma.hip", 12), ("gemm_staged.hip", 2)])
 def test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, source, least):
     out = str(tmp_path / "k.s")
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
