@@ -7,7 +7,7 @@
 //
 // For many output tiles of a short K that the persistent kernel does not take, or pays too much for (K below some 1000 that
 // is no multiple of 128, or fewer than 256 columns; choose_gemm).  Such a product is bound by the stores and by the fixed part of a
-// tile - tables, adapter rows, staging -, which the largest tile has least of: 8 us per round of 256 tiles at K = 64, where the
+// tile - tables, adapter rows, staging -, which the largest tile has least of: 9.3 us per round of 256 tiles at K = 64, where the
 // tiled kernel's 128 x 256, half as large, take 7 (30000 x 64 x 7552: 125 against 194 us; 55000 x 328 x 7552: 446 against 641).
 // From a longer K on the copies through registers cost more than that: 10 % over the persistent kernel's at K = 712, 15 %
 // at 1376.  One workgroup per 256 x 256 tile, eight waves of 64 x 128, global -> VGPR -> LDS with a zero-filled K tail, two LDS

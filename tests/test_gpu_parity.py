@@ -326,6 +326,44 @@ def test_many_tasks_in_one_output_tile(T, d_in, d_out, n_proj):
     check_problem(p, label="many tasks")
 
 
+@pytest.mark.parametrize("T,d_in,d_out,n_proj", [
+    (20000, 72, 2056, 1), (20000, 456, 1000, 1),      # forward; a K tile and 8, seven and 8, a ragged last column tile
+    (9000, 648, 5240, 1),                             # where the persistent kernel would do
+    (50000, 128, 248, 1), (50000, 248, 128, 1),       # whole K tiles, one column tile; backward
+    (20000, 72, 1024, 2),                             # fused projections in one launch
+])
+def test_register_staged_gemm(T, d_in, d_out, n_proj):
+    """Many output tiles and a short K run on the register-staged kernel, a few rows of the same batch on the tiled ones: against
+    the oracle, and, in the rows without adapter, against each other bit for bit (both sum in ascending steps of 32 k; with an
+    adapter the two batches' projections, summed in different orders, differ by roundings); rows of infinities stay in their rows."""
+    import torch
+    lens = [1, 200, 33, 700, 64]
+    lens.append(T - sum(lens))
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("staged-%dx%d" % (d_in, d_out), "bf16", d_in, d_out, [16, 40, 128] if n_proj == 1 else [16, 8, 64],
+                       np.concatenate([[0], np.cumsum(lens)]), [0, 1, -1, 2, 0, 1], 33, s=[2.0, -1.0, 0.5], fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    dp, _ = check_problem(p, rows=sample_rows(p, 200), label="staged")
+    y, dx = dp.y.clone(), dp.dx.clone()
+    n = 234                                           # the first three segments
+    q = wl.make_custom("staged-few", "bf16", p.d_in, p.d_out, p.ranks, [0, 1, 201, n], [0, 1, -1], 33, s=[2.0, -1.0, 0.5], fill=False)
+    q.n_proj, q.x, q.dy, q.W, q.A, q.B = n_proj, p.x[:n], p.dy[:n], p.W, p.A, p.B
+    dq = bd.DeviceProblem(q)
+    dq.step()
+    torch.cuda.synchronize()
+    if p.d_in < 1024:
+        assert torch.equal(dq.y[201:], y[201:n])
+    if p.d_out < 1024:
+        assert torch.equal(dq.dx[201:], dx[201:n])
+    bad = torch.tensor([5, T // 2, T - 1], device=dp.dev)
+    dp.x[bad], dp.dy[bad] = float("inf"), float("inf")
+    dp.step()
+    torch.cuda.synchronize()
+    keep = torch.ones(T, dtype=torch.bool, device=dp.dev)
+    keep[bad] = False
+    assert torch.equal(dp.y[keep], y[keep]) and torch.equal(dp.dx[keep], dx[keep]) and dp.guards_intact()
+
+
 @pytest.mark.parametrize("T,d_in,d_out", [
     (4000, 520, 4040),     # forward: 8 k in the last pair of K tiles
     (4100, 576, 4000),     # 64: its second tile lies wholly beyond K
