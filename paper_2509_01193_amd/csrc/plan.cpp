@@ -259,8 +259,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         //     point, n = 5 .. 24, 1 .. 16 tasks: 4 tasks, 4096 x 4096, n = 24: 21.9 / 13.5
         //   ranks above 16 (every wave walks all blocks, 256 columns a workgroup: about 1 us a block): up to n = 12 one is better
         //     (4 tasks of rank 24, 4096 x 4096: 19.2 / 16.5; n = 16: 19.2 / 20.1, n = 24: 25.1 / 27.8), and beyond where there are so
-        //     many partial sums that writing and adding them costs more: rank rows x column tiles of 10240 (3 tasks of rank 48, 9216:
-        //     n = 24 26.5 / 27.5; 3 of 64, 12288: 29.1 / 27.9; 16 of 64: 74.9 / 41.6)
+        //     many partial sums that writing and adding them costs more: from 12800 rank rows x column tiles on, a task's rows
+        //     counted by its share of the largest task's blocks (3 tasks of rank 48, 9216: n = 24 26.5 / 27.5; 4 of 64, 16384: 34.2 / 28.6;
+        //     16 of 64: 74.9 / 41.6; one task of 24 blocks and 7 of 4, rank 64, 8832: 23.1 / 29.7; rank 128, 17728: 36.1 / 34.2)
         //   fused projections (dA and dB in launches of their own, each with fewer workgroups): up to n = 10, or from 40960 on
         //     (P = 2, 4096 x 8192, 4 tasks of stacked rank 64: n = 10 30.9 / 30.2, n = 12 31.4 / 33.6; 24576 against 49152, n = 24: 42.4 /
         //     49.5 and 61.5 / 53.1); where dB takes a launch per projection, up to n = 6 (P = 3, 2048 x 3192, 8 tasks of stacked rank
@@ -272,12 +273,13 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 const int64_t nb = p->task_tb_off[t + 1] - p->task_tb_off[t];
                 most = std::max(most, nb);
                 active += nb > 0;
-                if (nb > 0) rows += (p->rank_off[t + 1] - p->rank_off[t] + 15) / 16 * 16;
+                rows += nb * ((p->rank_off[t + 1] - p->rank_off[t] + 15) / 16 * 16);
             }
+            if (most > 0) rows /= most;          // (a task with fewer blocks has fewer partial sums)
             const int64_t tiles = (d->d_in + 127) / 128 + (d->d_out + 127) / 128;
             int64_t limit = 24;
             if (p->n_proj > 1 && p->dg % 128 != 0) limit = 6;
-            else if (p->r_pad > 16 && rows * tiles < (p->n_proj > 1 ? 40960 : 10240)) limit = p->n_proj > 1 ? 10 : 12;
+            else if (p->r_pad > 16 && rows * tiles < (p->n_proj > 1 ? 40960 : 12800)) limit = p->n_proj > 1 ? 10 : 12;
             if (most <= limit && active * tiles >= 192) cb = std::max(cb, most);
         }
         p->chunk_blocks = int32_t(cb);

@@ -161,6 +161,15 @@ def test_one_reduction_chunk_per_task_only_where_it_is_faster(d_in, d_out, n_pro
         assert (per_task == 1).all() if chunks == 1 else (per_task > 1).all(), (blocks, per_task)
 
 
+def test_one_reduction_chunk_per_task_with_one_large_task():
+    """Seven tasks of 4 blocks beside one of 24: several chunks at rank 64 (few partial sums), one at rank 128."""
+    off = np.concatenate([[0], np.cumsum([32 * 24] + [32 * 4] * 7)])
+    for rank, chunks in ((64, 3), (128, 1)):
+        plan = bd.Plan("bf16", off[-1], 4096, 4096, np.arange(9) * rank, off, np.arange(8), bd.PLAN_HOST_ONLY)
+        per_task = np.diff(plan.query(bd.Q_TASK_CHUNKS))
+        assert (per_task[0] == 1) == (chunks == 1) and (per_task[1:] == 1).all(), (rank, per_task)
+
+
 def split_k_floor(plan, rank_off):
     """Least (forward without h_save, backward) workspace of a short MFMA batch: the projected activations, once and twice,
     and the reduction's partial sums (a split product's sums are not needed)."""
