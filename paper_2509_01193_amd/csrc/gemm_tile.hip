@@ -123,7 +123,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     constexpr int CR = TN / 8, RPC = 64 / CR;       // [k][n] tile: 16-byte chunks per k row, k rows per copy
     constexpr int CS_PITCH = WTN + 8;
     static_assert(ZC * 8 * NW == TM && WC * 8 * NW == TN && RPC * CR == 64, "whole copies");
-    static_assert(STAGES >= 2, "ring");
+    static_assert(STAGES > 2, "a K tile's copies are dealt over two K steps");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -260,7 +260,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     using yes = std::true_type;
     using no = std::false_type;
     // copies [c0, c1) of a K tile, as kstep's argument
-    constexpr int CH = STAGES > 2 ? CPW / 2 : CPW;
+    constexpr int CH = CPW / 2;
     using none = std::integral_constant<int, 0>;
     using half0 = std::integral_constant<int, CH>;
     using half1 = std::integral_constant<int, (CH << 8) | CPW>;
@@ -349,17 +349,16 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
         const int32_t ns = slot + 1 == STAGES ? 0 : slot + 1;
         pla = la0 + slot * STAGE;
         kstep(yes{}, half0{}, zb, wb, lds + ns * STAGE, 0, za, wa, pla);
-        if constexpr (CH == CPW) next_copy_tile();
         slot = ns;
     };
     if (steady > 0) {
         body(none{});
-        for (kt = 1; kt < steady; ++kt) body(std::conditional_t<CH == CPW, none, half1>{});
+        for (kt = 1; kt < steady; ++kt) body(half1{});
     }
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;           // uniform
         if (tail) clear_tail(0, za, wa);
-        if (CH < CPW && steady > 0 && kt == steady) {
+        if (steady > 0 && kt == steady) {
             kstep(yes{}, half1{}, za, wa, lds + slot * STAGE, 1, zb, wb, pla);
             next_copy_tile();
         } else {

@@ -14,7 +14,9 @@ constexpr int kRowBlock = 32;     // granularity of the row -> segment lookup ta
 constexpr int kGemmTileRows = 256;    // token rows of a base-GEMM output tile
 constexpr int kGemmTileRec = 8;       // ints per record of Plan::gemm_tile_tab
 constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
-constexpr int64_t kPlainMaxTokens = 65535 * 64;   // the plain kernels put 64-token tiles on grid.y
+// Most tokens of an fp32 batch and of LOBRA_PLAN_PLAIN_KERNELS: the plain kernels put 64-token tiles on grid.y, and the
+// projections start up to 512 threads per token, which a launch of less than 2^32 threads has room for.
+constexpr int64_t kPlainMaxTokens = 65535 * 64;
 
 struct TokenBlock { int32_t row0, nrows, task, rank_row0; };
 struct GradChunk  { int32_t tb_begin, tb_end, task, part_row0; };
