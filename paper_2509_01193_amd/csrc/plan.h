@@ -66,7 +66,11 @@ constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f;
 struct SegmentCost { float ktail, staged; };
 constexpr SegmentCost kSegmentCost = {1.5f, 1.0f};     // us per round and segment of a tile row beyond the first
 constexpr int32_t kGemmKTile = 64;
-constexpr int32_t kPersistentMinKTail = 520;   // an ordinary pair of K tiles, two pairs of the special kinds, and more
+// The persistent kernel's loop for such a K needs an ordinary pair of K tiles in front of the two special ones (K > 256).  It runs
+// from here on, where it is the better one for wide products (30000 x 520 x 1000 / 2048 / 7552, staged / persistent: 62 / 76,
+// 102 / 98, 336 / 329 us; the estimate tells them apart); below, it would lose at 264 (136 / 145 at 4096 columns), gain
+// nothing at 392 (165 / 167) and gain 5 .. 10 % at 456 and 504 (181 / 166).
+constexpr int32_t kPersistentMinKTail = 520;
 // Where a product has fewer tiles than compute units and a long K (decoding, narrow shards), K is split among up to eight
 // workgroups per tile, each of which writes its fp32 sums to scratch; a small kernel adds them in order (3 us, and the
 // sums' way to memory and back, mostly through the caches, at 6 TB/s: with a tile's time as above that puts 519 x 5504 x 1928
