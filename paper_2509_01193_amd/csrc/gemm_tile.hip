@@ -583,7 +583,8 @@ hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* 
     if (pd.T == 0) return hipSuccess;
     if (ldc == 0) ldc = N;
     if (!gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;   // (plan creation has checked already)
-    const GemmChoice choice = choose_gemm(pd.T, K, N, proj < 0 ? pd.dg : 0, P ? pd.nseg : 0, part ? std::min(part_bytes, kMaxPartBytes) : 0);
+    const GemmChoice choice = choose_gemm(pd.T, K, N, proj < 0 ? pd.dg : 0, P ? pd.nseg : 0, pd.r_max / nproj,
+                                          part ? std::min(part_bytes, kMaxPartBytes) : 0);
 #define LOBRA_TILE(...)                                                                                          \
     (transW ? launch_tile<false, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part)                 \
             : launch_tile<true, __VA_ARGS__>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, st, choice.splits, part))

@@ -330,12 +330,13 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             // narrow tiles do, and a long batch is better off with a launch per projection (45861 x 904 x 2 x 3392: 1171
             // against 732 us)
             p->fwd_group = 0;
-            const int32_t ns = ntb > 0 ? nseg : 0;
+            const int32_t ns = ntb > 0 ? nseg : 0, rk = p->r_max / p->n_proj;
             if (p->n_proj > 1 && p->dg % 64 == 0 &&
-                choose_gemm(T, d->d_in, d->d_out, p->dg, ns, 0).cost <= float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, ns, 0).cost + 3.f))
+                choose_gemm(T, d->d_in, d->d_out, p->dg, ns, rk, 0).cost <=
+                    float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, ns, rk, 0).cost + 3.f))
                 p->fwd_group = p->dg;
-            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns), 256);
-            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns), 256);
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk), 256);
+            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max), 256);
         }
         p->fwd_spart = spart_in;
         p->fwd_off_p = std::max(spart_in, p->fwd_part);
@@ -355,7 +356,7 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
     return LOBRA_OK;
 }
 
-GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, size_t part_bytes)
+GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, size_t part_bytes)
 {
     constexpr int64_t cus = 256;             // fixed, so that the choice does not depend on the device
     const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
@@ -375,7 +376,9 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
         // 99 us, 128 x 128 118, 128 x 64 145)
         if (group == 0 && N <= 256 && t.tn < N && int64_t(T) * K * 2 > (int64_t(256) << 20)) continue;
         float fixed = t.fixed;
-        if (i == kPersistentTile && ktail) fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kSegmentCost.ktail * segments;
+        if (i == kPersistentTile && ktail)
+            fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kKTailRank * std::max(0.f, float(rank - 32) / 32.f) +
+                    kSegmentCost.ktail * segments;
         if (i == kStagedTile) fixed += kSegmentCost.staged * segments;
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = cus * t.per_cu;
         for (int32_t s = 1; s <= kMaxSplits; ++s) {
@@ -393,9 +396,9 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
     return best;
 }
 
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg)
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank)
 {
-    const GemmChoice c = choose_gemm(T, K, N, group, nseg, kMaxPartBytes);
+    const GemmChoice c = choose_gemm(T, K, N, group, nseg, rank, kMaxPartBytes);
     return c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0;
 }
 

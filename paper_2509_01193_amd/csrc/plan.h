@@ -45,7 +45,9 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 // gives every compute unit one is the best; what remains is the count of rounds, which the choice estimates.
 // K that is no multiple of 128: the persistent kernel's form for it works its epilogue's addresses out anew per tile (kKTailFixed
 // for its `fixed`) and pays more again for rows of C that start inside a 64-byte sector (kKTailOddRows where N is no multiple
-// of 32: 20000 x 840 x 5240 268 us, the staged kernel 251; x 4096 154, 174).  Like the staged kernel, which has the largest tile
+// of 32: 20000 x 840 x 5240 268 us, the staged kernel 251; x 4096 154, 174) and for ranks above the 32 whose operands are copied
+// ahead (a round's cost beside its K tiles 9.6, 13.4 and 20.1 us at rank 32, 64 and 128, the staged kernel's 5.5, 7.2 and
+// 10.1: 47000 x 600 x 7232 485 against 550 us at rank 32, 804 against 700 at rank 128).  Like the staged kernel, which has the largest tile
 // and the shortest start, it does the up projection segment by segment, the tiled kernels by task (kSegmentCost).  Measured, us
 // per round of 256 tiles (N = 7552, 55000 tokens), and us in all for 12000 x 584 x 1000 in segments of n tokens, rank 16:
 //     K                 64    200   328   520   712   968   1376  2248      n = 400   20    4     1
@@ -55,14 +57,14 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed, once; };
 constexpr GemmTile kGemmTiles[] = {
     {256, 256, 1, 1.35f, 0.f, 5.f, 7.f},     // gemm_persistent_kernel
-    {128, 256, 1, 0.86f, 0.f, 6.f, 0.f},
-    {128, 128, 1, 0.48f, 0.f, 6.f, 0.f},
-    {128, 64, 2, 0.36f, 0.59f, 6.f, 0.f},
+    {128, 256, 1, 0.86f, 0.f, 6.5f, 0.f},
+    {128, 128, 1, 0.48f, 0.f, 7.f, 0.f},
+    {128, 64, 2, 0.36f, 0.59f, 7.f, 0.f},
     {64, 64, 2, 0.23f, 0.39f, 6.f, 0.f},
     {256, 256, 1, 2.0f, 0.f, 5.5f, 0.f},     // gemm_staged_kernel
 };
 constexpr int32_t kPersistentTile = 0, kStagedTile = 5;
-constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f;
+constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f, kKTailRank = 2.f;     // (kKTailRank: per 32 ranks beyond the first 32)
 struct SegmentCost { float ktail, staged; };
 constexpr SegmentCost kSegmentCost = {1.5f, 1.0f};     // us per round and segment of a tile row beyond the first
 constexpr int32_t kGemmKTile = 64;
@@ -82,10 +84,10 @@ constexpr int32_t kMaxSplits = 8, kMinSplitK = 1024;
 constexpr size_t kMaxPartBytes = size_t(12) << 20;
 struct GemmChoice { int32_t tile = -1, splits = 1; float cost = -1.f; };    // tile: of kGemmTiles, -1: none; cost: the estimate, us
 // The choice for C [T, N] = Z [T, K] op(W) given part_bytes of scratch.  group > 0: no tile may straddle a multiple of
-// `group` columns (a multiple of 64).  nseg: segments of the batch (0: no adapter).
-GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, size_t part_bytes);
+// `group` columns (a multiple of 64).  nseg: segments of the batch (0: no adapter); rank: the widest rank window.
+GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, size_t part_bytes);
 // The scratch that choice would like to have (0: none).
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg);
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank);
 
 // Byte offsets of the sub-buffers inside h_save and the workspaces.
 struct BufferLayout {
