@@ -71,8 +71,9 @@ __global__ __launch_bounds__(64 * NWV) void shrink_mfma_kernel(PlanDev pd, const
     }
     __shared__ float red[NWV][2][NRB][64][4];   // [wave][token half][rank block][lane][4]
     // (a launch order by rank is dealt round-robin: contiguous ranges of it would give one XCD all the expensive blocks)
-    const int32_t bi = pd.tb_order ? pd.tb_order[blockIdx.x]
-                                   : (LOBRA_SKINNY_XCD ? xcd_contiguous(blockIdx.x, gridDim.x) : int32_t(blockIdx.x));
+    const int32_t wi = int32_t(blockIdx.z * gridDim.x + blockIdx.x);
+    if (wi >= pd.ntb) return;
+    const int32_t bi = pd.tb_order ? pd.tb_order[wi] : (LOBRA_SKINNY_XCD ? xcd_contiguous(wi, pd.ntb) : wi);
     const TokenBlock b = pd.tb[bi];
     const int32_t r = (pd.rank_off[b.task + 1] - b.rank_row0) / nproj;
     const int32_t pofs = proj * r;               // first rank of the window inside the task's rows
@@ -751,7 +752,10 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                        hipStream_t st, const SlicedShape& sliced, float* part, const void* Hblk, float* partb)
 {
     if (pd.ntb == 0) return hipSuccess;
+    // (a grid dimension of 2^32 threads and more wraps without an error)
+    auto fits = [](int64_t workgroups) { return workgroups * 256 < (int64_t(1) << 32); };
     if (sliced.nsl > 0 && part && nproj == 1) {
+        if (!fits((int64_t(pd.ntb) + 1) / 2)) return hipErrorInvalidValue;
         hipError_t e = sliced_setup();
         if (e != hipSuccess) return e;
         // a fixed grid - one workgroup per compute unit of the chip this is written for - so that the split
@@ -773,6 +777,7 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
     const int nrb = (pd.r_max / nproj + 15) / 16;
     if (pd.shrink_group == 4 && nproj == 1 && ldz == D) {
         // ranks from about 24 up and a long batch: runs of four token blocks share the staged adapter rows
+        if (!fits(pd.nsb)) return hipErrorInvalidValue;
         if (nrb <= 2)
             shrink_lds_kernel<2, 2><<<pd.nsb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s,
                                                             (uint16_t*)P_tok, (uint16_t*)P_blk, D);
@@ -803,8 +808,10 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
             pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj, nrb);
         return hipGetLastError();
     }
+    // up to 2^23 blocks in a row of the grid
+    const int32_t rows = (pd.ntb - 1) / (1 << 23) + 1, row = rows > 1 ? 1 << 23 : pd.ntb;
 #define LOBRA_SHRINK(NRB, DEPTH)                                                                       \
-    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(pd.ntb, np), 256, 0, st>>>(                                           \
+    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(row, np, rows), 256, 0, st>>>(                                           \
         pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj)
     if (nrb <= 1) LOBRA_SHRINK(1, 3);
     else if (nrb <= 2) LOBRA_SHRINK(2, 2);

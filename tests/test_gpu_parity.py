@@ -509,6 +509,28 @@ def test_fp32_batch_of_two_million_token_blocks():
     check_problem(p, rows=np.unique(rows), tol=17200 * 2.0 ** -24, label="2M blocks")
 
 
+def test_bf16_batch_of_17_million_token_blocks():
+    """As many segments of one token as make the projection's launch, 256 threads per token block, exceed the 2^32 threads at which
+    a grid wraps (forward pass; the projected activations take 18 GB)."""
+    import torch
+    T = (1 << 24) + 100000
+    seg = np.arange(T + 1, dtype=np.int32)
+    plan = bd.Plan("bf16", T, 8, 8, [0, 1, 3], seg, seg[:T] % 2)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x, W = torch.randn(T, 8, device="cuda", generator=g).bfloat16(), torch.randn(8, 8, device="cuda", generator=g).bfloat16()
+    A, B = torch.randn(3, 8, device="cuda", generator=g).bfloat16(), torch.randn(3, 8, device="cuda", generator=g).bfloat16()
+    s, y = torch.tensor([1.0, -0.5], device="cuda"), torch.full((T, 8), 7.0, device="cuda", dtype=torch.bfloat16)
+    ws = torch.full((plan.fwd_ws_bytes,), 0x7f, dtype=torch.uint8, device="cuda")
+    bd.lobra_mlora_plan_fwd(plan, x, W, A, B, s, y, None, ws)
+    ref = torch.empty(T, 8, device="cuda")
+    x, W, A, B = x.float(), W.float(), A.float(), B.float()
+    for t, rows in ((0, slice(0, 1)), (1, slice(1, 3))):
+        ref[t::2] = x[t::2] @ W + s[t] * ((x[t::2] @ A[rows].t()) @ B[rows])
+    err = float(((y.float() - ref).abs().max(1).values / ref.abs().max()).max())
+    assert err <= TOL["bf16"], err
+    plan.close()
+
+
 def test_config3_reversed_rank_pairing():
     p = wl.make_config(3, "shuffled", d_in=192, d_out=344, reverse_ranks=True)
     check_problem(p)
