@@ -343,7 +343,6 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     const bool adapters = !p.tb.empty();
     const bool room = sliced && ws && ws_bytes >= (h_save ? p.fwd_part : p.fwd_ws_bytes);       // for a split product's sums
     void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (room ? p.fwd_off_p : (sliced ? p.fwd_spart : 0));
-    const SlicedShape sliced_in = sliced ? p.sliced_in : SlicedShape{};
     float* const part = room && p.fwd_part > 0 ? static_cast<float*>(ws) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const PlanDev pd = device_view(p);
@@ -366,8 +365,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     char* hb = static_cast<char*>(hbuf);
     if (adapters)   // all projections' down factors are stacked in A: one pass over x
         LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
-                     shrink_mfma(pd, x, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, pd.d_in, pd.d_in, 1, 0, st,
-                                 sliced_in, static_cast<float*>(ws)));
+                     shrink_mfma(pd, x, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, pd.d_in, pd.d_in, 1, 0, st));
     if (p.n_proj == 1) {
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                      gemm_mfma(pd, false, x, W, adapters ? hb + p.p_layout.p_tok : nullptr, B, y, pd.d_in,
@@ -482,8 +480,7 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
         if (!H) {
             char* Hr = wsb + p.bwd_off_h;
             LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
-                         shrink_mfma(pd, x, A, s, Hr + p.p_layout.p_tok, Hr + p.p_layout.p_blk, pd.d_in, pd.d_in, 1, 0, st,
-                                     p.sliced_in, spart));
+                         shrink_mfma(pd, x, A, s, Hr + p.p_layout.p_tok, Hr + p.p_layout.p_blk, pd.d_in, pd.d_in, 1, 0, st));
             H = Hr;
         }
         // G = s dy B^T; with fused projections every projection's column block of dy against its rows of the

@@ -94,6 +94,9 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                        void* P_tok, void* P_blk, int32_t D, int32_t ldz, int32_t nproj, int32_t proj,
                        hipStream_t st, const SlicedShape& sliced = SlicedShape{}, float* part = nullptr,
                        const void* Hblk = nullptr, float* partb = nullptr);
+// The same through an LDS ring (shrink_ring.hip), for ranks above 16.
+hipError_t shrink_ring(const PlanDev& pd, const void* Z, const void* M, const float* s, void* P_tok, void* P_blk, int32_t D,
+                       int32_t ldz, int32_t nproj, int32_t proj, hipStream_t st);
 
 // Stage 1 of dM_t = sum_i P_i^T Z_i from the block-transposed P; partial sums per reduction chunk.
 // (P = block-transposed bf16 copy; one launch for up to two gradients, jb.P == nullptr: only ja.)

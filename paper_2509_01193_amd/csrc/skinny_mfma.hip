@@ -1,7 +1,7 @@
-// HBM-bound rank-r kernels of the bf16 path (gfx950 MFMA, operands streamed straight from
-// global memory into MFMA registers: the skinny operand needs no LDS tile at all).
+// HBM-bound rank-r kernels of the bf16 path (gfx950 MFMA):
 //
-//   shrink_mfma      P = s_t Z M_t^T   (Z = x, M = A gives s_t A_t x_i; Z = dy, M = B gives s_t B_t dy_i)
+//   shrink_mfma      P = s_t Z M_t^T   (Z = x, M = A gives s_t A_t x_i; Z = dy, M = B gives s_t B_t dy_i): the K-sliced kernel that
+//                    accumulates dB in the same pass, else the ring (shrink_ring.hip)
 //   grad_mfma        stage 1 of dM_t = sum_i P_i^T Z_i over a reduction chunk (dB from P = s h,
 //                    Z = dy; dA from P = s g, Z = x), partial sums per chunk
 // (paper section 2.1: the two low-rank factors of X (down)(up) and their gradients; section 1:
@@ -13,9 +13,6 @@
 
 #ifndef LOBRA_GRAD_ORDER
 #define LOBRA_GRAD_ORDER 2      // reduction kernels: 2 column tile fastest, 0 chunk fastest, 1 column tile fastest and XCD-contiguous
-#endif
-#ifndef LOBRA_SKINNY_XCD
-#define LOBRA_SKINNY_XCD 1      // work items dealt to the XCDs in contiguous ranges (see xcd_contiguous)
 #endif
 
 namespace lobra {
@@ -29,8 +26,7 @@ namespace {
 // Load of data that is read once per launch and in whole cache lines (the gradient kernels' token
 // rows): marked non-temporal (STREAM), it does not displace the rank-r operand that every workgroup
 // re-reads.  Measured 7-11 % on the gradient kernels at ranks from 32 and on batches far larger than the
-// 256 MB infinity cache; a batch that fits that cache is better left in it for the kernels that follow
-// (the projection kernels, which read half lines per instruction, lose 15-20 % with the hint and never use it).
+// 256 MB infinity cache; a batch that fits that cache is better left in it for the kernels that follow.
 template <bool STREAM, typename V> __device__ __forceinline__ V stream_load(const V* p)
 {
     if constexpr (STREAM) return __builtin_nontemporal_load(p);
@@ -45,394 +41,13 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v)
 }  // namespace
 
 // -------------------------------------------------------------------------------------------------
-// shrink: one workgroup per token block (<= 32 tokens of one task), 4 waves split K.
-// v_mfma_f32_16x16x32_bf16 with the MFMA "A" operand = 16 rank rows of M_t and the "B" operand =
-// 16 token rows of Z, so a lane ends up with 4 consecutive ranks of one token.  K is walked in
-// slabs of 128 = 4 MFMA steps of 32: in step q lane (row, kg) loads the 8 elements
-// slab + 32 q + 8 kg .. + 7 of its row, so the four lanes of a row read one 64-byte sector per
-// load instruction and a whole 256-byte run per slab.  Rank blocks beyond the task's rank are
-// skipped.
-// -------------------------------------------------------------------------------------------------
-// NRB: rank blocks of 16 (r_t <= 16 NRB); NWV: waves; DEPTH: slabs in flight per wave
-template <int NRB, int NWV, int DEPTH>
-__global__ __launch_bounds__(64 * NWV) void shrink_mfma_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
-                                                          const uint16_t* __restrict__ M,
-                                                          const float* __restrict__ s,
-                                                          uint16_t* __restrict__ P_tok,
-                                                          uint16_t* __restrict__ P_blk, int32_t D,
-                                                          int32_t ldz, int32_t nproj, int32_t proj)
-{
-    // nproj > 1 (fused shared-input projections): a workgroup handles one projection only, `proj` or (proj < 0, Z is all of
-    // dy) the one in blockIdx.y - Z is that projection's column block of dy (row pitch ldz), M its rows of the compact
-    // up factors, and the task's rank rows it reads and writes are the window [proj r, (proj + 1) r).
-    if (proj < 0) {
-        proj = int32_t(blockIdx.y);
-        Z += size_t(proj) * D;
-    }
-    __shared__ float red[NWV][2][NRB][64][4];   // [wave][token half][rank block][lane][4]
-    // (a launch order by rank is dealt round-robin: contiguous ranges of it would give one XCD all the expensive blocks)
-    const int32_t wi = int32_t(blockIdx.z * gridDim.x + blockIdx.x);
-    if (wi >= pd.ntb) return;
-    const int32_t bi = pd.tb_order ? pd.tb_order[wi] : (LOBRA_SKINNY_XCD ? xcd_contiguous(wi, pd.ntb) : wi);
-    const TokenBlock b = pd.tb[bi];
-    const int32_t r = (pd.rank_off[b.task + 1] - b.rank_row0) / nproj;
-    const int32_t pofs = proj * r;               // first rank of the window inside the task's rows
-    const int32_t rank_row0 = b.rank_row0 + pofs;
-    const int32_t plim = proj == nproj - 1 ? pd.r_pad - pofs : r;   // ranks (and zero padding) stored by this launch
-    const int32_t nrb_t = (r + 15) >> 4;        // rank blocks this task needs (uniform)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = lane & 15, kg = lane >> 4;
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-    f32x4 acc[2][NRB];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) acc[h][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // rows beyond the block repeat its last row (their results are never stored)
-    const uint16_t* zrow[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-        zrow[h] = Z + size_t(b.row0 + min(16 * h + j, b.nrows - 1)) * ldz;
-    const uint16_t* mrow[NRB];
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) mrow[rb] = M + size_t(rank_row0 + min(16 * rb + j, r - 1)) * D;
-
-    // operands of one slab: 4 steps x (2 token halves of Z, NRB rank blocks of M).
-    // Rank rows beyond r_t and token rows beyond the block repeat a valid row: what they produce
-    // is dropped at the store, so the loads of a whole slab need no per-lane condition.
-    struct Slab { u32x4 zv[2][4], mv[NRB][4]; };
-    auto load = [&](Slab& sl, int32_t slab) {
-        const int32_t k = slab + 8 * kg;
-        if (slab + 128 <= D) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb)
-                    if (NRB == 1 || rb < nrb_t)
-                        sl.mv[rb][q] = *reinterpret_cast<const u32x4*>(mrow[rb] + k + 32 * q);
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    sl.zv[h][q] = *reinterpret_cast<const u32x4*>(zrow[h] + k + 32 * q);
-            }
-        } else {   // the last slab of a width that is not a multiple of 128: columns beyond D read as 0
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool kin = k + 32 * q < D;
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb)
-                    if (NRB == 1 || rb < nrb_t)
-                        sl.mv[rb][q] = kin ? *reinterpret_cast<const u32x4*>(mrow[rb] + k + 32 * q) : zero4;
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    sl.zv[h][q] = kin ? *reinterpret_cast<const u32x4*>(zrow[h] + k + 32 * q) : zero4;
-            }
-        }
-    };
-    auto mac = [&](const Slab& sl) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb)
-                    if (NRB == 1 || rb < nrb_t)
-                        acc[h][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf16x8(sl.mv[rb][q]), as_bf16x8(sl.zv[h][q]), acc[h][rb], 0, 0, 0);
-    };
-    const int32_t nsl = (D + 127) >> 7;
-    // DEPTH slabs in flight per wave: the loads of slab i + DEPTH - 1 are issued before the MFMAs
-    // of slab i (DEPTH = 1: load, then multiply).
-    Slab buf[DEPTH];
-#pragma unroll
-    for (int d = 0; d < DEPTH - 1; ++d)
-        if (wave + NWV * d < nsl) load(buf[d], (wave + NWV * d) << 7);
-    for (int32_t i = wave; i < nsl; i += NWV * DEPTH) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int32_t nx = i + NWV * (d + DEPTH - 1);
-            if (nx < nsl) load(buf[(d + DEPTH - 1) % DEPTH], nx << 7);
-            if (i + NWV * d < nsl) mac(buf[d]);
-        }
-    }
-    // cross-wave sum through LDS, then lane (token j, rank group kg) of wave 0/1 stores half h
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb)
-            if (rb < nrb_t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) red[wave][h][rb][lane][v] = acc[h][rb][v];
-    __syncthreads();
-    if (wave < 2) {
-        const int h = wave;
-        const int32_t tok = 16 * h + j;
-        const float st = s[b.task];
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
-            bf16x4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float sum = 0.f;
-                if (rb < nrb_t)
-#pragma unroll
-                    for (int w = 0; w < NWV; ++w) sum += red[w][h][rb][lane][v];   // fixed order
-                const int32_t p = 16 * rb + 4 * kg + v;
-                o[v] = (__bf16)((p < r && tok < b.nrows) ? st * sum : 0.f);
-            }
-            const int32_t p0 = 16 * rb + 4 * kg;
-            if (p0 < plim) {
-                if (tok < b.nrows)
-                    *reinterpret_cast<bf16x4*>(P_tok + size_t(b.row0 + tok) * pd.r_pad + pofs + p0) = o;
-                // block-transposed copy [block][rank][32 tokens]; tokens beyond the block hold 0
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    union { __bf16 b; uint16_t u; } c;
-                    c.b = o[v];
-                    P_blk[(size_t(bi) * pd.r_pad + pofs + p0 + v) * kTokenBlock + tok] = c.u;
-                }
-            }
-        }
-    }
-}
-
-// -------------------------------------------------------------------------------------------------
-// shrink for short batches (where: see the launcher below): one workgroup per half of a token block
-// and 16 ranks, 16 waves split K.  What bounds such a launch is the time a workgroup takes, which is a chain of memory
-// round trips: the kernel above walks eight slabs of 128 per wave at K = 4096 and all rank blocks with them, and takes 12-14 us
-// at rank 16 and 22 us at rank 64 whether it has 1 or 256 blocks; here a wave walks two, both in flight at once (10 and
-// 9 us).  Operands and sums as above; a half without tokens only clears its part of P_blk.
-// -------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void shrink_short_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
-                                                           const uint16_t* __restrict__ M, const float* __restrict__ s,
-                                                           uint16_t* __restrict__ P_tok, uint16_t* __restrict__ P_blk,
-                                                           int32_t D, int32_t ldz, int32_t nproj, int32_t proj, int32_t nrb)
-{
-    // nproj, proj: as in shrink_mfma_kernel.  blockIdx.y = rank block (of nrb) + nrb * projection of the launch
-    constexpr int NWV = 16, DEPTH = 2;
-    __shared__ f32x4 red[NWV][64];
-    const int32_t bi = int32_t(blockIdx.x >> 1), half = int32_t(blockIdx.x & 1);
-    const int32_t rb = int32_t(blockIdx.y) % nrb;
-    if (proj < 0) {
-        proj = int32_t(blockIdx.y) / nrb;
-        Z += size_t(proj) * D;
-    }
-    const TokenBlock b = pd.tb[bi];
-    const int32_t r = (pd.rank_off[b.task + 1] - b.rank_row0) / nproj;
-    const int32_t pofs = proj * r;
-    const int32_t plim = proj == nproj - 1 ? pd.r_pad - pofs : r;    // ranks (and zero padding) stored for this projection
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = lane & 15, kg = lane >> 4;
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    // (the last rank block also stores the padding beyond: with fused projections there can be more of it than 16)
-    const int32_t pbeg = 16 * rb, pend = rb == nrb - 1 ? plim : min(plim, pbeg + 16);
-    if (16 * half >= b.nrows) {
-        for (int32_t p = 2 * pbeg + int32_t(threadIdx.x); p < 2 * pend; p += 64 * NWV)
-            *reinterpret_cast<u32x4*>(P_blk + (size_t(bi) * pd.r_pad + pofs + (p >> 1)) * kTokenBlock + 16 + 8 * (p & 1)) = zero4;
-        return;
-    }
-    if (pbeg >= pend) return;
-    const int32_t tok = 16 * half + j;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (pbeg < r) {
-        const uint16_t* zrow = Z + size_t(b.row0 + min(tok, b.nrows - 1)) * ldz + 8 * kg;
-        const uint16_t* mrow = M + size_t(b.rank_row0 + pofs + min(pbeg + j, r - 1)) * D + 8 * kg;
-        struct Slab { u32x4 zv[4], mv[4]; };
-        auto load = [&](Slab& sl, int32_t k0) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int32_t k = k0 + 32 * q;
-                const bool in = k + 8 * kg < D;      // columns beyond D read as 0
-                sl.zv[q] = in ? *reinterpret_cast<const u32x4*>(zrow + k) : zero4;
-                sl.mv[q] = in ? *reinterpret_cast<const u32x4*>(mrow + k) : zero4;
-            }
-        };
-        auto mac = [&](const Slab& sl) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(sl.mv[q]), as_bf16x8(sl.zv[q]), acc, 0, 0, 0);
-        };
-        const int32_t nsl = (D + 127) >> 7;
-        Slab buf[DEPTH];
-#pragma unroll
-        for (int d = 0; d < DEPTH - 1; ++d)
-            if (wave + NWV * d < nsl) load(buf[d], (wave + NWV * d) << 7);
-        for (int32_t i = wave; i < nsl; i += NWV * DEPTH) {
-#pragma unroll
-            for (int d = 0; d < DEPTH; ++d) {
-                const int32_t nx = i + NWV * (d + DEPTH - 1);
-                if (nx < nsl) load(buf[(d + DEPTH - 1) % DEPTH], nx << 7);
-                if (i + NWV * d < nsl) mac(buf[d]);
-            }
-        }
-    }
-    red[wave][lane] = acc;
-    __syncthreads();
-    // wave 0 adds the sums in wave order and stores: lane (j, kg) ranks 4 kg .. 4 kg + 3 of the block, token j
-    if (wave > 0) return;
-    f32x4 sum = red[0][lane];
-#pragma unroll
-    for (int w = 1; w < NWV; ++w) sum = sum + red[w][lane];
-    const float st = s[b.task];
-    for (int32_t p0 = pbeg + 4 * kg; p0 < pend; p0 += 16) {          // (one turn, more only through padding)
-        bf16x4 o;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = (__bf16)((p0 < pbeg + 16 && p0 + v < r && tok < b.nrows) ? st * sum[v] : 0.f);
-        if (tok < b.nrows) *reinterpret_cast<bf16x4*>(P_tok + size_t(b.row0 + tok) * pd.r_pad + pofs + p0) = o;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            union { __bf16 b; uint16_t u; } c;
-            c.b = o[v];
-            P_blk[(size_t(bi) * pd.r_pad + pofs + p0 + v) * kTokenBlock + tok] = c.u;
-        }
-    }
-}
-
-// -------------------------------------------------------------------------------------------------
-// shrink for ranks from about 24 up (chosen by the plan for long batches): one workgroup per run of up to 4 token blocks of one task, wave w owns
-// block w over the whole of K.  The rank rows of a slab (16 NRB x 128 columns) are staged in LDS once
-// per workgroup and read by all four waves, so the adapter traffic is r_t rows per 128 token rows
-// instead of per 32; a wave's sums are complete when its loop ends (no cross-wave reduction).
-// LDS layout of a staged slab: [rank row][16 chunks of 16 bytes], chunk c of row R at c ^ (R & 15), so
-// that the 16 rank rows of one ds_read_b128 pass hit 16 different bank groups; two slabs are staged
-// alternately (one barrier per slab).
-// -------------------------------------------------------------------------------------------------
-template <int NRB, int DEPTH>
-__global__ __launch_bounds__(256) void shrink_lds_kernel(PlanDev pd, const uint16_t* __restrict__ Z,
-                                                      const uint16_t* __restrict__ M,
-                                                      const float* __restrict__ s,
-                                                      uint16_t* __restrict__ P_tok,
-                                                      uint16_t* __restrict__ P_blk, int32_t D)
-{
-    constexpr int ROWS = 16 * NRB;                       // staged rank rows
-    constexpr int CH = ROWS * 16;                        // 16-byte chunks per staged slab
-    constexpr int MLD = (CH + 255) / 256;                // chunks per thread
-    __shared__ __attribute__((aligned(16))) unsigned char ms[2][ROWS * 256];
-    const int32_t run = pd.sb_order ? pd.sb_order[blockIdx.x]
-                                    : (LOBRA_SKINNY_XCD ? xcd_contiguous(blockIdx.x, gridDim.x) : int32_t(blockIdx.x));
-    const int32_t tb0 = pd.sb_off[run];
-    const int32_t cnt = pd.sb_off[run + 1] - tb0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool active = wave < cnt;                      // wave-uniform: this wave has a token block
-    const TokenBlock b = pd.tb[tb0 + min(wave, cnt - 1)];
-    const int32_t r = pd.rank_off[b.task + 1] - b.rank_row0;
-    const int32_t nrb_t = (r + 15) >> 4;
-    const int j = lane & 15, kg = lane >> 4;
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-    f32x4 acc[2][NRB];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) acc[h][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t* zrow[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) zrow[h] = Z + size_t(b.row0 + min(16 * h + j, b.nrows - 1)) * D;
-
-    // staging: thread tid moves chunks tid, tid + 256, ...: chunk id = (rank row, 16-byte column chunk)
-    u32x4 mreg[MLD];
-    auto fetch_m = [&](int32_t slab) {
-#pragma unroll
-        for (int u = 0; u < MLD; ++u) {
-            const int ch = threadIdx.x + 256 * u, R = ch >> 4, c = ch & 15;
-            const int32_t k = slab + 8 * c;
-            mreg[u] = (ch < CH && R < 16 * nrb_t && k < D)
-                          ? *reinterpret_cast<const u32x4*>(M + size_t(b.rank_row0 + min(R, r - 1)) * D + k) : zero4;
-        }
-    };
-    auto stash_m = [&](int buf) {
-#pragma unroll
-        for (int u = 0; u < MLD; ++u) {
-            const int ch = threadIdx.x + 256 * u, R = ch >> 4, c = ch & 15;
-            if (ch < CH) *reinterpret_cast<u32x4*>(&ms[buf][R * 256 + ((c ^ (R & 15)) << 4)]) = mreg[u];
-        }
-    };
-    struct ZSlab { u32x4 zv[2][4]; };
-    auto load_z = [&](ZSlab& sl, int32_t slab) {
-        const int32_t k = slab + 8 * kg;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                sl.zv[h][q] = (slab + 128 <= D || k + 32 * q < D)
-                                  ? *reinterpret_cast<const u32x4*>(zrow[h] + min(k + 32 * q, D - 8)) : zero4;
-    };
-    auto mac = [&](const ZSlab& sl, int buf) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int rb = 0; rb < NRB; ++rb)
-                if (rb < nrb_t) {
-                    const int R = 16 * rb + j;
-                    const u32x4 mv = *reinterpret_cast<const u32x4*>(&ms[buf][R * 256 + (((4 * q + kg) ^ (R & 15)) << 4)]);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        acc[h][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(mv), as_bf16x8(sl.zv[h][q]),
-                                                                         acc[h][rb], 0, 0, 0);
-                }
-    };
-    const int32_t nsl = (D + 127) >> 7;
-    ZSlab zb[DEPTH];
-#pragma unroll
-    for (int d = 0; d < DEPTH - 1; ++d)
-        if (d < nsl && active) load_z(zb[d], d << 7);
-    fetch_m(0);
-    for (int32_t i = 0; i < nsl; i += DEPTH) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int32_t sl = i + d;
-            if (sl >= nsl) break;                            // uniform
-            stash_m(sl & 1);
-            __syncthreads();                                 // slab sl is staged; slab sl - 1 has been consumed
-            if (sl + 1 < nsl) fetch_m((sl + 1) << 7);
-            if (active) {
-                if (sl + DEPTH - 1 < nsl) load_z(zb[(d + DEPTH - 1) % DEPTH], (sl + DEPTH - 1) << 7);
-                mac(zb[d], sl & 1);
-            }
-        }
-    }
-    if (!active) return;
-    const float st = s[b.task];
-    const int32_t bi = tb0 + wave;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int32_t tok = 16 * h + j;
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
-            bf16x4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int32_t p = 16 * rb + 4 * kg + v;
-                o[v] = (__bf16)((p < r && tok < b.nrows) ? st * acc[h][rb][v] : 0.f);
-            }
-            const int32_t p0 = 16 * rb + 4 * kg;
-            if (p0 < pd.r_pad) {
-                if (tok < b.nrows)
-                    *reinterpret_cast<bf16x4*>(P_tok + size_t(b.row0 + tok) * pd.r_pad + p0) = o;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    union { __bf16 b; uint16_t u; } c;
-                    c.b = o[v];
-                    P_blk[(size_t(bi) * pd.r_pad + p0 + v) * kTokenBlock + tok] = c.u;
-                }
-            }
-        }
-    }
-}
-
-// -------------------------------------------------------------------------------------------------
-// shrink for ranks up to 16 on long batches: K is cut into slices of 512 columns, a work item is (token
+// shrink over dy for ranks up to 16 on long batches, with dB in the same pass: K is cut into slices of 512 columns, a work item is (token
 // block, slice), and one workgroup per compute unit walks a contiguous range of the items of its XCD's
-// token blocks in slice-major order.  What the one-block-per-workgroup kernel above loses on such a batch,
-// measured: (a) its workgroups all start, stream and finish in step, so the dependent loads at the start
-// and the reduction and stores at the end of a block are exposed once per launch with nothing behind them;
-// (b) a compute unit sustains about 20 GB/s of token rows however many workgroups it holds, so a launch of
-// 513 blocks on 256 compute units takes as long as one of 768 (one unit gets three blocks instead of two);
-// (c) the adapter rows are a third of what passes through the vector memory path.  Here a wave keeps the
-// adapter columns of its part of the slice in registers for as long as task and slice stay the same (they are
-// read once per dozen token blocks), the loads of the next three items are in flight while an item is
-// multiplied, reduced and stored, and the items are dealt to the workgroups to within one item.
+// token blocks in slice-major order.  A wave keeps the adapter columns of its part of the slice - and its dB sums - in registers for
+// as long as task and slice stay the same (a dozen token blocks), the loads of the next three items are in flight while an item is
+// multiplied, reduced and stored, and the items are dealt to the workgroups to within one item.  (The projection alone is faster
+// through the ring of shrink_ring.hip, 26.9 against 31.2 us with the finish at 16384 x 4096, which dB's saved pass over dy outweighs: 37.5 us
+// against 31.8 and 17 more for dB.  WITH_DB = false is left for batches whose tasks are so small that dB's sums would be too many.)
 // The eight waves of a workgroup share an item: wave (h, w) takes token half h (16 tokens) and the 128 columns
 // number w of the slice; the four waves of a half add their sums through LDS (fixed order) and wave (h, 0)
 // writes the fp32 partial projection part[slice][token][16]; the finish kernel below adds the slices in
@@ -752,72 +367,24 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                        hipStream_t st, const SlicedShape& sliced, float* part, const void* Hblk, float* partb)
 {
     if (pd.ntb == 0) return hipSuccess;
+    if (sliced.nsl == 0 || !part || nproj != 1) return shrink_ring(pd, Z, M, s, P_tok, P_blk, D, ldz, nproj, proj, st);
     // (a grid dimension of 2^32 threads and more wraps without an error)
-    auto fits = [](int64_t workgroups) { return workgroups * 256 < (int64_t(1) << 32); };
-    if (sliced.nsl > 0 && part && nproj == 1) {
-        if (!fits((int64_t(pd.ntb) + 1) / 2)) return hipErrorInvalidValue;
-        hipError_t e = sliced_setup();
-        if (e != hipSuccess) return e;
-        // a fixed grid - one workgroup per compute unit of the chip this is written for - so that the split
-        // of the items, and with it the order of every sum, does not depend on the device
-        if (Hblk && partb && pd.fb_run_row)
-            shrink_sliced_kernel<true><<<kSlicedGrid, 512, kSlicedLdsDb, st>>>(
-                pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
-                (const uint16_t*)Hblk, partb, pd.fb_wg_run_off, pd.fb_run_row);
-        else
-            shrink_sliced_kernel<false><<<kSlicedGrid, 512, kSlicedLds, st>>>(
-                pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
-                nullptr, nullptr, nullptr, nullptr);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        shrink_finish_kernel<<<(pd.ntb + 1) / 2, 256, 0, st>>>(pd, part, s, (uint16_t*)P_tok, (uint16_t*)P_blk, sliced.nsl);
-        return hipGetLastError();
-    }
-    // rank blocks of the widest window (nproj = 1: of the widest task)
-    const int nrb = (pd.r_max / nproj + 15) / 16;
-    if (pd.shrink_group == 4 && nproj == 1 && ldz == D) {
-        // ranks from about 24 up and a long batch: runs of four token blocks share the staged adapter rows
-        if (!fits(pd.nsb)) return hipErrorInvalidValue;
-        if (nrb <= 2)
-            shrink_lds_kernel<2, 2><<<pd.nsb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s,
-                                                            (uint16_t*)P_tok, (uint16_t*)P_blk, D);
-        else if (nrb <= 4)
-            shrink_lds_kernel<4, 2><<<pd.nsb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s,
-                                                            (uint16_t*)P_tok, (uint16_t*)P_blk, D);
-        else
-            shrink_lds_kernel<8, 2><<<pd.nsb, 256, 0, st>>>(pd, (const uint16_t*)Z, (const uint16_t*)M, s,
-                                                            (uint16_t*)P_tok, (uint16_t*)P_blk, D);
-        return hipGetLastError();
-    }
-    // Short batches: the kernel that splits K over 16 waves, rank blocks and token halves over workgroups, two of which fit a
-    // compute unit - faster as long as there are few of them, then slower than the kernel that keeps a token block's ranks
-    // together (us, that one / the short one):
-    //     ntb        D 256, rank 16   1024, 24     4096, 16      4096, 64      8192, 64      4096, 128
-    //     32          6.2 / 6.2       8.8 / 6.8    15.4 / 12.2   27.9 / 12.7   49.3 / 20.2   43.3 / 20.9
-    //     64          6.2 / 6.2       8.9 / 6.9    15.6 / 12.6   28.8 / 21.2   49.5 / 35.0   44.6 / 37.2
-    //     80          6.1 / 6.2       8.9 / 8.8    15.9 / 12.8   28.9 / 28.9   49.4 / 50.2   44.6 / 45.4
-    //     96          6.2 / 6.2       8.9 / 9.1    16.3 / 12.8   29.3 / 29.0   49.5 / 51.3   44.6 / 53.2
-    //     128         6.2 / 6.3       9.0 / 9.3    16.6 / 13.2   29.4 / 37.6   50.1 / 67.8   44.4 / 69.1
-    // With fused projections the other kernel has a workgroup per block and projection as well, and the line lies where the
-    // short one's are one per compute unit (dg 4096, rank 16 each: 2 projections, 64 / 80 blocks 16.4 / 13.7 and 16.5 / 21.4; 4
-    // projections, 32 / 48 blocks 16.3 / 13.4 and 16.8 / 20.8; rank 32 each, 2 projections, 32 / 48 blocks 23.1 / 13.1 and, at dg
-    // 512, 7.5 / 7.9).
-    const int32_t np = proj < 0 ? nproj : 1;
-    if (np > 1 ? 2 * int64_t(pd.ntb) * nrb * np <= 256 : pd.ntb <= (nrb <= 1 ? 128 : (nrb <= 2 ? 96 : 72))) {
-        shrink_short_kernel<<<dim3(2 * pd.ntb, nrb * np), 1024, 0, st>>>(
-            pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj, nrb);
-        return hipGetLastError();
-    }
-    // up to 2^23 blocks in a row of the grid
-    const int32_t rows = (pd.ntb - 1) / (1 << 23) + 1, row = rows > 1 ? 1 << 23 : pd.ntb;
-#define LOBRA_SHRINK(NRB, DEPTH)                                                                       \
-    shrink_mfma_kernel<NRB, 4, DEPTH><<<dim3(row, np, rows), 256, 0, st>>>(                                           \
-        pd, (const uint16_t*)Z, (const uint16_t*)M, s, (uint16_t*)P_tok, (uint16_t*)P_blk, D, ldz, nproj, proj)
-    if (nrb <= 1) LOBRA_SHRINK(1, 3);
-    else if (nrb <= 2) LOBRA_SHRINK(2, 2);
-    else if (nrb <= 4) LOBRA_SHRINK(4, 2);
-    else LOBRA_SHRINK(8, 1);
-#undef LOBRA_SHRINK
+    if ((int64_t(pd.ntb) + 1) / 2 * 256 >= (int64_t(1) << 32)) return hipErrorInvalidValue;
+    hipError_t e = sliced_setup();
+    if (e != hipSuccess) return e;
+    // a fixed grid - one workgroup per compute unit of the chip this is written for - so that the split
+    // of the items, and with it the order of every sum, does not depend on the device
+    if (Hblk && partb && pd.fb_run_row)
+        shrink_sliced_kernel<true><<<kSlicedGrid, 512, kSlicedLdsDb, st>>>(
+            pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
+            (const uint16_t*)Hblk, partb, pd.fb_wg_run_off, pd.fb_run_row);
+    else
+        shrink_sliced_kernel<false><<<kSlicedGrid, 512, kSlicedLds, st>>>(
+            pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
+            nullptr, nullptr, nullptr, nullptr);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    shrink_finish_kernel<<<(pd.ntb + 1) / 2, 256, 0, st>>>(pd, part, s, (uint16_t*)P_tok, (uint16_t*)P_blk, sliced.nsl);
     return hipGetLastError();
 }
 

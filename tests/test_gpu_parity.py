@@ -411,6 +411,32 @@ def test_projection_on_both_sides_of_the_short_batch_rule(blocks, ranks, n_proj)
     check_problem(p, label="%d blocks" % blocks)
 
 
+@pytest.mark.parametrize("d_in,d_out,ranks,blocks,n_proj", [
+    (8, 72, [16, 5], 3, 1),               # a slot of the ring that is hardly filled; a K tile and 8 of the next
+    (248, 264, [16, 24, 40], 70, 1),      # one slot short of 8, and 8 more; parts of 16 and of 32 ranks, padding beyond
+    (1288, 776, [128, 8], 40, 1),         # more slots than the ring has; one part has all of a task's ranks, seven have none
+    (520, 1032, [100, 64, 30], 300, 1),   # 128 ranks per workgroup, bodies for 2, 4 and 8 rank blocks
+    (136, 640, [64, 16], 1100, 1),        # long: four blocks a workgroup; mean rank above 24
+    (264, 384, [128, 96], 1100, 1),       #   128 ranks
+    (512, 2 * 136, [80, 16], 20, 2),      # rank windows of fused projections, in parts
+])
+def test_ring_projection_edges(d_in, d_out, ranks, blocks, n_proj):
+    """The rank-r projection at the edges of its slots, rank parts and token blocks, against the oracle; blocks of every length,
+    tasks of one token, and spans without adapter in between."""
+    lens, tasks, n = [], [], 0
+    rng = np.random.default_rng(d_in + blocks)
+    while n < blocks:
+        lens.append(int(rng.choice([1, 15, 17, 32, 33, 250])))
+        tasks.append(int(rng.integers(-1, len(ranks))))
+        n += (lens[-1] + 31) // 32 if tasks[-1] >= 0 else 0
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("ring-%dx%d" % (d_in, d_out), "bf16", d_in, d_out if n_proj == 1 else d_out // n_proj,
+                       ranks if n_proj == 1 else [r // n_proj for r in ranks], np.concatenate([[0], np.cumsum(lens)]), tasks, 41,
+                       s=np.linspace(-1, 2, len(ranks)).astype(np.float32), fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, rows=sample_rows(p, 300), label="ring")
+
+
 @pytest.mark.parametrize("n_proj", [1, 2])
 def test_persistent_gemm_up_projection_at_every_kind_of_rank(n_proj):
     """The GEMM's fused up projection takes the operands of a tile's first segment from a copy made ahead of the

@@ -266,3 +266,7 @@ def test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, source, l
         barriers += sum(l.startswith("s_barrier") for l in lines)
         assert not _lds_writes_pending_at_a_barrier(lines), (name, _lds_writes_pending_at_a_barrier(lines)[0])
     assert kernels >= least and barriers >= kernels, (kernels, barriers)
+
+
+def test_lds_writes_of_the_ring_projection_are_waited_for(tmp_path):
+    test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, "shrink_ring.hip", 6)
