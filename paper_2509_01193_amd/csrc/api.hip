@@ -499,26 +499,28 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
         // dB (from s h and dy) and dA (from s g and x) share one launch per stage
         GradJob jb{adapters ? H + p.p_layout.p_blk : nullptr, dy, part_b, dB, pd.dg};
         const GradJob ja{adapters ? G + p.p_layout.p_blk : nullptr, x, part_a, dA, pd.d_in};
+        // (tasks without tokens: stage 1 clears their rows if it writes all others' in place too)
+        const bool zero_empty = !fused_db && p.single_chunks && p.empty_tasks && !accumulate;
         if (fused_db) {
             const GradJob none{nullptr, nullptr, nullptr, nullptr, 0};
-            LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, ja, none, accumulate, st));
+            LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, ja, none, accumulate, zero_empty, st));
             jb.fcnt = pd.fb_cnt;
             jb.frow0 = pd.fb_task_row0;
             jb.fnsl = p.sliced_out.nsl;
         } else if (p.n_proj == 1) {
-            if (adapters) LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jb, ja, accumulate, st));
+            if (adapters) LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jb, ja, accumulate, zero_empty, st));
         } else if (adapters) {
             // dA over all stacked ranks in one pass over x; dB per projection (its column block of dy,
             // its rank window of H, its rows of the compact dB)
             const GradJob none{nullptr, nullptr, nullptr, nullptr, 0};
-            LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, ja, none, accumulate, st));
+            LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, ja, none, accumulate, zero_empty, st));
             if (pd.dg % 128 == 0) {     // no column tile straddles two projections: one pass over all of dy
                 GradJob jall = jb;
                 jall.D = pd.d_out;
                 jall.ldp = pd.dg;
                 jall.nproj = p.n_proj;
                 jall.proj = -1;
-                LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jall, none, accumulate, st));
+                LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jall, none, accumulate, zero_empty, st));
             } else
             for (int32_t j = 0; j < p.n_proj; ++j) {
                 GradJob jj = jb;
@@ -526,10 +528,10 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
                 jj.ldz = pd.d_out;
                 jj.nproj = p.n_proj;
                 jj.proj = j;
-                LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jj, none, accumulate, st));
+                LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_mfma(pd, jj, none, accumulate, zero_empty, st));
             }
         }
-        if (fused_db || !p.single_chunks)
+        if (fused_db || !p.single_chunks || !adapters)
             LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE2, reduce_partials(pd, jb, ja, accumulate, true, st));
     }
     return LOBRA_OK;

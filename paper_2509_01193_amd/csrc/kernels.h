@@ -100,8 +100,8 @@ hipError_t shrink_ring(const PlanDev& pd, const void* Z, const void* M, const fl
 
 // Stage 1 of dM_t = sum_i P_i^T Z_i from the block-transposed P; partial sums per reduction chunk.
 // (P = block-transposed bf16 copy; one launch for up to two gradients, jb.P == nullptr: only ja.)
-// accumulate: what goes to `out` directly is added to it.
-hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st);
+// accumulate: what goes to `out` directly is added to it.  zero_empty: the rows of tasks without tokens are cleared.
+hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, bool zero_empty, hipStream_t st);
 
 // Fused Adam over the stacked adapters A [R_tot, d_in] and B [R_tot, d_out] (one launch).
 struct AdamTensor {

@@ -345,7 +345,12 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJo
     const int32_t D = first ? ja.D : jb.D;
     const int32_t coltile = first ? int32_t(blockIdx.y) : int32_t(blockIdx.y) - tiles_a;
     const int32_t R = blockIdx.x;
-    int32_t t = 0;
+    int32_t t = 0, te = pd.n_tasks;                  // (by halves: a chain of table reads is most of what a workgroup takes)
+    while (te - t > 8) {
+        const int32_t m = (t + te) >> 1;
+        if (pd.rank_off[m] <= R) t = m;
+        else te = m;
+    }
     while (pd.rank_off[t + 1] <= R) ++t;
     const int32_t p = R - pd.rank_off[t];
     const int32_t col = coltile * 1024 + threadIdx.x * 4;

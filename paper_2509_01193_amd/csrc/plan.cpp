@@ -282,6 +282,20 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             else if (p->r_pad > 16 && rows * tiles < (p->n_proj > 1 ? 40960 : 12800)) limit = p->n_proj > 1 ? 10 : 12;
             if (most <= limit && active * tiles >= 192) cb = std::max(cb, most);
         }
+        // The higher the ranks the more the partial sums weigh, which stage 1 writes and stage 2 reads - r / 4 of the bytes of a chunk of one
+        // block -: on long batches chunks of at least 5 blocks per 16 ranks (of the mean over the blocks), if that leaves the largest task
+        // more than one (both stages, us, chunks as above / with this floor: rank 128, 42123 x 768 x 7168 541 / 315, 45263 x 2688 x
+        // 832 226 / 172, 8000 x 3072 x 5000 130 / 75; ranks 8 .. 64, 14378 x 1664 x 1080 44 / 36; twice the floor is no better)
+        if (p->mfma && !p->fused_db && !p->tb.empty()) {
+            int64_t most = 0, wsum = 0;
+            for (int32_t t = 0; t < n; ++t) {
+                const int64_t nb = p->task_tb_off[t + 1] - p->task_tb_off[t];
+                most = std::max(most, nb);
+                wsum += nb * (p->rank_off[t + 1] - p->rank_off[t]);
+            }
+            const int64_t least = wsum * 5 / (16 * int64_t(p->tb.size()));
+            if (5 * most > 6 * least) cb = std::max(cb, least);
+        }
         p->chunk_blocks = int32_t(cb);
         p->chunks.clear();
         p->task_chunk_off.assign(size_t(n) + 1, 0);
@@ -302,10 +316,16 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         }
 
         p->single_chunks = n > 0;
-        for (int32_t t = 0; t < n; ++t) p->single_chunks &= p->task_chunk_off[t + 1] - p->task_chunk_off[t] == 1;
+        p->empty_tasks = false;
+        for (int32_t t = 0; t < n; ++t) {
+            const int32_t c = p->task_chunk_off[t + 1] - p->task_chunk_off[t];
+            p->single_chunks &= c <= 1;
+            p->empty_tasks |= c == 0;
+        }
+        if (p->empty_tasks && n > kMaxClearedTasks) p->single_chunks = false;
 
         // (the reduction kernels put chunks x column tiles of at least 64 columns on grid.x)
-        if (int64_t(p->chunks.size()) * ((int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64) > 0x7fffffff)
+        if ((int64_t(p->chunks.size()) + kMaxClearedTasks) * ((int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64) > 0x7fffffff)
             return LOBRA_ERR_SHAPE;
 
         // 5. buffer sizes

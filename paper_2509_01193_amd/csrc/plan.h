@@ -13,6 +13,7 @@ constexpr int kTokenBlock = 32;   // tokens per token block (one MFMA K step of 
 constexpr int kRowBlock = 32;     // granularity of the row -> segment lookup table
 constexpr int kGemmTileRows = 256;    // token rows of a base-GEMM output tile
 constexpr int kGemmTileRec = 8;       // ints per record of Plan::gemm_tile_tab
+constexpr int kMaxClearedTasks = 4096;    // up to here stage 1 of the gradients clears the rows of tasks without tokens
 constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
 // Most tokens of an fp32 batch and of LOBRA_PLAN_PLAIN_KERNELS: the plain kernels put 64-token tiles on grid.y, and the
 // projections start up to 512 threads per token, which a launch of less than 2^32 threads has room for.
@@ -122,7 +123,9 @@ struct Plan {
     std::vector<int32_t> tb_order, sb_order;
     std::vector<GradChunk> chunks;      // grouped by task
     std::vector<int32_t> task_chunk_off;// [n_tasks+1]
-    bool single_chunks = false;         // every task has exactly one chunk: no partial sums to add
+    // no task has more than one chunk: no partial sums to add (tasks without tokens, which stage 1 then clears: only while
+    // there are few tasks, since it starts a workgroup for each of them and column tile)
+    bool single_chunks = false, empty_tasks = false;
     int32_t part_rows = 0;              // rows of the partial-sum buffer = sum over chunks of r_t
     int32_t chunk_blocks = 0;           // token blocks per reduction chunk
 

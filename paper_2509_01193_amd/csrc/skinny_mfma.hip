@@ -399,6 +399,19 @@ __device__ __forceinline__ GradRows grad_rows(const PlanDev& pd, const GradChunk
     return {job.part + size_t(ch.part_row0) * ldp, false};
 }
 
+// The gradient rows of a task without tokens, TW columns from col0 on, ranks [p0, p1) of the job's window: zeros.  They are
+// written by workgroups of stage 1 behind those of the chunks, so that a batch whose tasks have at most one chunk each needs no second
+// stage.  Kernels of their own (ZERO): with these stores in front the compiler no longer reads the tables with scalar loads, and a long
+// batch's stage 1 takes a tenth longer (290 -> 322 us at 49152 x 8192 x 8192, rank 64).  (366 tokens of 4 out of 16 tasks, rank 128, 1152 x 7680: 11 + 19 -> 15 us for both gradients).
+template <int TW> __device__ __forceinline__ void zero_task_rows(float* base, int32_t ldp, int32_t col, int32_t ncols, int32_t p0, int32_t p1)
+{
+    typedef float ovec __attribute__((ext_vector_type(4)));
+    const int32_t c = 4 * (int32_t(threadIdx.x) % (TW / 4));
+    if (c >= ncols) return;                              // (D is a multiple of 8)
+    for (int32_t p = p0 + int32_t(threadIdx.x) / (TW / 4); p < p1; p += 1024 / TW)
+        *reinterpret_cast<ovec*>(base + size_t(p) * ldp + col + c) = ovec{0.f, 0.f, 0.f, 0.f};
+}
+
 // -------------------------------------------------------------------------------------------------
 // grad stage 1: partial dM over one reduction chunk and 16 CW columns per workgroup of 4 waves
 // (CW = 8: 128 columns; CW = 4: 64 columns, for large ranks, where the accumulators of a
@@ -411,7 +424,7 @@ __device__ __forceinline__ GradRows grad_rows(const PlanDev& pd, const GradChunk
 // ends up with CW consecutive columns.  Rank blocks beyond the task's rank are skipped.
 // The four waves' sums are combined through LDS in two steps (fixed order: ((w0+w2)+(w1+w3))).
 // -------------------------------------------------------------------------------------------------
-template <int NRB, int CW, bool STREAM>
+template <int NRB, int CW, bool STREAM, bool ZERO>
 __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all, int32_t accumulate)
 {
     typedef uint32_t zvec __attribute__((ext_vector_type(CW / 2)));
@@ -441,6 +454,13 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
     const int32_t pcol0 = proj_in >= 0 ? 0 : proj * pd.dg;                      // its first column
     const int32_t ldp = (first ? ja.ldp : jb.ldp) ? (first ? ja.ldp : jb.ldp) : D;   // row pitch of part
     __shared__ float red[2][NRB][CW][64][4];
+    if (ZERO && chunk_x >= pd.nchunks) {                  // a task without tokens, perhaps
+        const int32_t t = chunk_x - pd.nchunks;
+        if (pd.task_chunk_off[t + 1] != pd.task_chunk_off[t]) return;
+        const int32_t rt = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, q0 = 16 * NRB * int32_t(blockIdx.y), c0 = coltile * (16 * CW);
+        zero_task_rows<16 * CW>((first ? ja : jb).out + size_t(pd.rank_off[t] + proj * rt) * ldp, ldp, c0 - pcol0, D - c0, q0, min(rt, q0 + 16 * NRB));
+        return;
+    }
     const GradChunk ch = pd.chunks[chunk_x];
     const int32_t r = (pd.rank_off[ch.task + 1] - pd.rank_off[ch.task]) / nproj;
     const int32_t pofs = proj * r;                        // first rank of the window inside the task's rows
@@ -544,7 +564,7 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
 }
 
 // -------------------------------------------------------------------------------------------------
-// grad stage 1 for ranks above 16 (NRB = 2: r_pad = 32, NRB = 4: r_pad >= 48, in passes of 64 ranks):
+// grad stage 1 for ranks above 16 (NRB = 2: r_pad = 32, NRB = 4: r_pad >= 48, in passes of 64 ranks, NRB = 8: up to 128 ranks in one):
 // partial dM over one reduction chunk and 256 columns per
 // workgroup.  Wave w owns the 64 columns 64 w .. of the tile for ALL token blocks of the chunk (so its
 // sums are final: no cross-wave reduction), and the P_blk tile of a token block ([16 NRB ranks][32
@@ -553,7 +573,7 @@ __global__ __launch_bounds__(256) void grad_mfma_kernel(PlanDev pd, GradJob ja, 
 // token block; the next block's Z rows and P tile are fetched before the current block is multiplied.
 // Operand layouts as in grad_mfma_kernel with CW = 4.
 // -------------------------------------------------------------------------------------------------
-template <int NRB>
+template <int NRB, bool ZERO>
 __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, GradJob jb, int32_t tiles_a, int32_t tiles_all, int32_t accumulate)
 {
     constexpr int CW = 4, TW = 4 * 16 * CW;     // rank blocks per pass, columns per lane, tile width
@@ -579,6 +599,13 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
     const int32_t proj = proj_in >= 0 ? proj_in : coltile * TW / pd.dg;   // pd.dg is a multiple of TW then
     const int32_t pcol0 = proj_in >= 0 ? 0 : proj * pd.dg;
     const int32_t ldp = (first ? ja.ldp : jb.ldp) ? (first ? ja.ldp : jb.ldp) : D;
+    if (ZERO && chunk_x >= pd.nchunks) {                  // a task without tokens, perhaps
+        const int32_t t = chunk_x - pd.nchunks;
+        if (pd.task_chunk_off[t + 1] != pd.task_chunk_off[t]) return;
+        const int32_t rt = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, q0 = 16 * NRB * int32_t(blockIdx.y), c0 = coltile * TW;
+        zero_task_rows<TW>((first ? ja : jb).out + size_t(pd.rank_off[t] + proj * rt) * ldp, ldp, c0 - pcol0, D - c0, q0, min(rt, q0 + 16 * NRB));
+        return;
+    }
     const GradChunk ch = pd.chunks[chunk_x];
     const int32_t r = (pd.rank_off[ch.task + 1] - pd.rank_off[ch.task]) / nproj;
     const int32_t pofs = proj * r;
@@ -596,11 +623,14 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
 #pragma unroll
         for (int jj = 0; jj < CW; ++jj) acc[rb][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // staging: thread tid moves 16 bytes: rank row tid / 4 of the pass, tokens 8 (tid % 4) ..
+    // staging: thread tid moves 16 bytes of rank row tid / 4 of the pass (NRB = 8: and of row tid / 4 + 64), tokens 8 (tid % 4) ..
     const int prow = min(int(threadIdx.x >> 2), 16 * NRB - 1), pchunk = threadIdx.x & 3;
-    const int32_t prank = min(pofs + 16 * rb0 + prow, pd.r_pad - 1);
+    const int32_t prank = min(pofs + 16 * rb0 + prow, pd.r_pad - 1), prank2 = min(pofs + 16 * rb0 + prow + 64, pd.r_pad - 1);
     auto fetch_p = [&](int32_t bi) {
         return *reinterpret_cast<const u32x4*>(P_blk + (size_t(bi) * pd.r_pad + prank) * kTokenBlock + 8 * pchunk);
+    };
+    auto fetch_p2 = [&](int32_t bi) {
+        return *reinterpret_cast<const u32x4*>(P_blk + (size_t(bi) * pd.r_pad + prank2) * kTokenBlock + 8 * pchunk);
     };
     auto load_z = [&](zvec (&zin)[8], int32_t bi) {
         const TokenBlock b = pd.tb[bi];
@@ -630,22 +660,27 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
     };
     const int32_t n = ch.tb_end - ch.tb_begin;
     zvec za[8], zb[8];
-    u32x4 preg = fetch_p(ch.tb_begin);
+    u32x4 preg = fetch_p(ch.tb_begin), preg2;
+    if constexpr (NRB > 4) preg2 = fetch_p2(ch.tb_begin);
     load_z(za, ch.tb_begin);
     for (int32_t i = 0; i < n; i += 2) {
         // block i (Z rows in za), then block i + 1 (zb): the buffers alternate without register copies
         *reinterpret_cast<u32x4*>(&ps[0][prow * 64 + 16 * pchunk]) = preg;
+        if constexpr (NRB > 4) *reinterpret_cast<u32x4*>(&ps[0][(prow + 64) * 64 + 16 * pchunk]) = preg2;
         __syncthreads();                                 // tile i is staged; tile i - 1 has been consumed
         if (i + 1 < n) {
             preg = fetch_p(ch.tb_begin + i + 1);
+            if constexpr (NRB > 4) preg2 = fetch_p2(ch.tb_begin + i + 1);
             load_z(zb, ch.tb_begin + i + 1);
         }
         mac(za, 0);
         if (i + 1 >= n) break;                           // uniform
         *reinterpret_cast<u32x4*>(&ps[1][prow * 64 + 16 * pchunk]) = preg;
+        if constexpr (NRB > 4) *reinterpret_cast<u32x4*>(&ps[1][(prow + 64) * 64 + 16 * pchunk]) = preg2;
         __syncthreads();
         if (i + 2 < n) {
             preg = fetch_p(ch.tb_begin + i + 2);
+            if constexpr (NRB > 4) preg2 = fetch_p2(ch.tb_begin + i + 2);
             load_z(za, ch.tb_begin + i + 2);
         }
         mac(zb, 1);
@@ -667,31 +702,44 @@ __global__ __launch_bounds__(256) void grad_lds_kernel(PlanDev pd, GradJob ja, G
         }
 }
 
-hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st)
+hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, bool zero_empty, hipStream_t st)
 {
     if (pd.nchunks == 0) return hipSuccess;
     // rank blocks of the widest window (both jobs of a launch have the same nproj)
     const int nrb = ja.nproj > 1 ? (pd.r_max / ja.nproj + 15) / 16 : pd.r_pad / 16;
     const int NRB = nrb <= 1 ? 1 : (nrb <= 2 ? 2 : 4);
+    const uint32_t items = uint32_t(pd.nchunks) + (zero_empty ? uint32_t(pd.n_tasks) : 0u);
     // ranks above 16: the kernel that stages P_blk in LDS (its 256-column tiles must not straddle projections)
     if (NRB >= 2 &&
         (ja.proj >= 0 || pd.dg % 256 == 0) && (!jb.P || jb.proj >= 0 || pd.dg % 256 == 0)) {
         const int32_t ta = (ja.D + 255) / 256, tb = jb.P ? (jb.D + 255) / 256 : 0;
-        const dim3 grid(uint32_t(pd.nchunks) * uint32_t(ta + tb), (nrb + 3) / 4);     // (plan creation bounds the product)
-        if (NRB == 2) grad_lds_kernel<2><<<dim3(grid.x, 1), 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);
-        else grad_lds_kernel<4><<<grid, 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);
+        const uint32_t wgs = items * uint32_t(ta + tb);                               // (plan creation bounds the product)
+        // Ranks above 64: in two passes over Z, which many workgroups hide better than the registers of one pass allow, or in one where
+        // all workgroups run at once (us, two passes / one: 42123 x 768 x 7168, 1116 workgroups 299 / 309; 45263 x 2688 x 832, 570
+        // 157 / 179; 8000 x 3072 x 5000, 256 68 / 59; 366 x 1152 x 7680 22 / 18)
+        const int one = nrb > 4 && pd.nchunks * (ta + tb) <= 512 ? 8 : 4, passes = nrb > one ? 2 : 1;
+#define LOBRA_GRAD(NRB_)                                                                       \
+    do {                                                                                       \
+        if (zero_empty) grad_lds_kernel<NRB_, true><<<dim3(wgs, passes), 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);  \
+        else grad_lds_kernel<NRB_, false><<<dim3(wgs, passes), 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);            \
+    } while (0)
+        if (nrb <= 2) LOBRA_GRAD(2);
+        else if (one == 4) LOBRA_GRAD(4);
+        else LOBRA_GRAD(8);
+#undef LOBRA_GRAD
         return hipGetLastError();
     }
     const int cw = NRB == 4 ? 4 : 8;
     const int32_t tw = 16 * cw;
     const int32_t tiles_a = (ja.D + tw - 1) / tw, tiles_b = jb.P ? (jb.D + tw - 1) / tw : 0;
-    const dim3 grid(uint32_t(pd.nchunks) * uint32_t(tiles_a + tiles_b), (nrb + NRB - 1) / NRB);
+    const dim3 grid(items * uint32_t(tiles_a + tiles_b), (nrb + NRB - 1) / NRB);
     // token rows that cannot stay in the 256 MB infinity cache anyway are streamed past the caches
     const bool stream = int64_t(pd.T) * (int64_t(ja.D) + (jb.P ? jb.D : 0)) * 2 > (int64_t(512) << 20);
 #define LOBRA_GRAD(NRB_, CW_)                                                                  \
     do {                                                                                       \
-        if (stream) grad_mfma_kernel<NRB_, CW_, true><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);  \
-        else grad_mfma_kernel<NRB_, CW_, false><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);        \
+        if (stream && !zero_empty) grad_mfma_kernel<NRB_, CW_, true, false><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);  \
+        else if (zero_empty) grad_mfma_kernel<NRB_, CW_, false, true><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);        \
+        else grad_mfma_kernel<NRB_, CW_, false, false><<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, tiles_a + tiles_b, accumulate ? 1 : 0);        \
     } while (0)
     if (NRB == 1) LOBRA_GRAD(1, 8);
     else if (NRB == 2) LOBRA_GRAD(2, 8);

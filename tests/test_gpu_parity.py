@@ -679,6 +679,40 @@ def test_gradients_of_tasks_with_a_single_chunk(ranks, n_proj, empty_task):
     assert torch.equal(dp.dA, first[0]) and torch.equal(dp.dB, first[1]) and dp.guards_intact()
 
 
+@pytest.mark.parametrize("d_in,d_out,ranks,n_proj,lens", [
+    (136, 264, [8, 16, 4, 16], 1, [60, 33]),          # 128-column kernel, ragged tiles
+    (520, 264, [24, 40, 32, 64], 1, [60, 33]),        # 256-column kernel, ranks in one pass of 64
+    (264, 1032, [100, 8, 128, 96], 1, [200, 33]),     # ranks above 64 in one pass
+    (2056, 4104, [128, 100, 72, 8], 1, [2600, 2600, 2600]),   # several chunks, many workgroups: two passes, a second stage
+    (136, 2 * 256, [16, 32, 80, 48], 2, [60, 33]),    # fused projections, one launch for dB
+    (136, 2 * 136, [16, 32, 80, 48], 2, [60, 33]),    #   one per projection
+])
+def test_gradients_of_tasks_without_tokens(d_in, d_out, ranks, n_proj, lens):
+    """The last task, and one between tasks with tokens, have none: their rows of dA and dB are cleared, or left alone where gradients
+    accumulate, with and without a second stage."""
+    import torch
+    tasks = [0, 2, 0][:len(lens)]
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("empty-%dx%d" % (d_in, d_out), "bf16", d_in, d_out // n_proj, [r // n_proj for r in ranks],
+                       np.concatenate([[0], np.cumsum(lens)]), tasks, 47, s=[2.0, -1.0, 0.5, 1.0], fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    dp, _ = check_problem(p, rows=sample_rows(p, 100), label="empty tasks")
+    first = [dp.dA.clone(), dp.dB.clone()]
+    empty = np.concatenate([np.arange(p.rank_off[t], p.rank_off[t + 1]) for t in (1, 3)])
+    idx = torch.from_numpy(empty).to(dp.dev)
+    assert all(bool((g.index_select(0, idx) == 0).all()) for g in first)
+    dp.dA.fill_(3.0)
+    dp.dB.fill_(float("nan"))
+    dp.bwd()
+    torch.cuda.synchronize()
+    assert torch.equal(dp.dA, first[0]) and torch.equal(dp.dB, first[1]) and dp.guards_intact()
+    dp.dA.fill_(1.0)
+    dp.dB.fill_(-2.0)
+    dp.bwd(flags=bd.FLAG_ACCUMULATE_GRADS)
+    torch.cuda.synchronize()
+    assert torch.equal(dp.dA, first[0] + 1.0) and torch.equal(dp.dB, first[1] - 2.0)       # one fp32 addition each
+
+
 def test_empty_batch_and_argument_errors():
     import torch
     p = wl.make_custom("empty", "bf16", 64, 64, [8], [0], [], 5)
