@@ -363,6 +363,13 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     }
     // bf16 MFMA path
     char* hb = static_cast<char*>(hbuf);
+    if (adapters && gemm_takes_projection(pd, pd.d_in, pd.d_out, part, p.fwd_part)) {     // few token blocks: one launch for both
+        LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK, hipSuccess);
+        LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
+                     gemm_mfma_beside(pd, false, x, W, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, B, y, pd.d_in, pd.d_out,
+                                      pd.d_out, st, part, p.fwd_part));
+        return LOBRA_OK;
+    }
     if (adapters)   // all projections' down factors are stacked in A: one pass over x
         LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
                      shrink_mfma(pd, x, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, pd.d_in, pd.d_in, 1, 0, st));
@@ -476,6 +483,8 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
     // dB in the same pass over dy as G = s dy B^T (then stage 1 below is dA alone)
     const bool fused_db = adapters && p.fused_db && p.R_tot > 0;
     const char* H = static_cast<const char*>(h_saved);
+    float* const split_part = ws && ws_bytes >= p.bwd_off_spart + p.bwd_part && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr;
+    const bool beside = adapters && want_dx && p.sliced_out.nsl == 0 && gemm_takes_projection(pd, pd.d_out, pd.d_in, split_part, p.bwd_part);
     if (adapters) {
         if (!H) {
             char* Hr = wsb + p.bwd_off_h;
@@ -486,15 +495,16 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
         // G = s dy B^T; with fused projections every projection's column block of dy against its rows of the
         // compact B, written into its rank window of G
         LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
+                     beside ? hipSuccess :
                      shrink_mfma(pd, dy, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, pd.dg, pd.d_out, p.n_proj,
                                  p.n_proj > 1 ? -1 : 0, st, p.sliced_out, spart, fused_db ? H + p.p_layout.p_blk : nullptr, part_b));
     }
     if (want_dx && p.desc.T > 0)
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
-                     gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,
-                               pd.d_in, pd.d_out, st, 0, 1, 0,
-                               ws && ws_bytes >= p.bwd_off_spart + p.bwd_part && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr,
-                               p.bwd_part));
+                     beside ? gemm_mfma_beside(pd, true, dy, W, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, A, dx, pd.d_out,
+                                               pd.d_in, pd.d_out, st, split_part, p.bwd_part)
+                            : gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,
+                                        pd.d_in, pd.d_out, st, 0, 1, 0, split_part, p.bwd_part));
     if (p.R_tot > 0) {
         // dB (from s h and dy) and dA (from s g and x) share one launch per stage
         GradJob jb{adapters ? H + p.p_layout.p_blk : nullptr, dy, part_b, dB, pd.dg};

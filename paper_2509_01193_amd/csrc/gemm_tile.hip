@@ -35,6 +35,7 @@
 
 #include "gemm_common.h"
 #include "kernels.h"
+#include "shrink_ring.h"
 
 namespace lobra {
 
@@ -97,19 +98,17 @@ template <int TM, int TN, int WN, int STAGES> constexpr int ring_bytes()
     return loop;
 }
 
-}  // namespace
-
-template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
-__global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4)
-void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
-                      const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
-                      uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t splits,
-                      float* __restrict__ part)
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES>
+__device__ __forceinline__
+void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
+               const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
+               uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+               int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t splits,
+               float* __restrict__ part, int32_t wg, unsigned char* lds)
 {
     // splits > 1: that many workgroups per tile share the K tiles, and one more has the adapter term (if P): in the time
     // that its chain of table reads, copies and products takes, the others are done with theirs.  Their fp32 sums go to
-    // part [splits (+ 1)][T][N]; gemm_add_kernel adds them and writes C.
+    // part [splits (+ 1)][T][N]; gemm_add_kernel adds them and writes C.  (C = NULL: also with one split.)
     // ldc: row pitch of C.  nproj > 1: this launch is projection `proj` of a fused shared-input
     // call: of every task's rank rows (in M) and rank columns (in P) only the window
     // [proj r, (proj + 1) r) takes part, r = the task's stacked rank / nproj.  proj < 0: the launch
@@ -125,7 +124,6 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     static_assert(ZC * 8 * NW == TM && WC * 8 * NW == TN && RPC * CR == 64, "whole copies");
     static_assert(STAGES > 2, "a K tile's copies are dealt over two K steps");
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -139,7 +137,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     int32_t row0, col0, split;
     {
         const int32_t per = splits + (splits > 1 && P ? 1 : 0);
-        const int32_t wid = xcd_contiguous(blockIdx.x, tiles_m * tiles_n * per);
+        const int32_t wid = xcd_contiguous(wg, tiles_m * tiles_n * per);
         const int32_t id = wid / per;
         split = wid - id * per;
         const int32_t group = id / (GM * tiles_n);
@@ -470,7 +468,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
             }
         }
     }
-    if (splits > 1) {                               // the sums as they are, 16 bytes per lane
+    if (splits > 1 || !C) {                         // the sums as they are, 16 bytes per lane
         float* dst = part + size_t(split) * T * N;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
@@ -514,27 +512,126 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
     }
 }
 
+}  // namespace
+
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4)
+void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
+                      const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
+                      uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t splits,
+                      float* __restrict__ part)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    tile_body<W_KN, TM, TN, WM, WN, STAGES>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, GM, splits, part,
+                                            int32_t(blockIdx.x), lds);
+}
+
+// A split product and the rank-r projection of the same Z in one launch: the first pwgs workgroups (a multiple of eight, so that the
+// others keep their XCDs) project, rparts * 2 columns of items as in shrink_ring_kernel<1, 1, 1, 256>, the others multiply.
+// Neither needs the other; gemm_add_up_kernel brings them together.  Small batches are bound by launches and memory round trips: 40
+// one-token requests to 8 adapters, 4096 x 4096, took 9.5 us for the projection, 12.5 for the product, whose adapter workgroups waited for
+// it, and 3.5 for the sum; together 22.3, now 15.0.
+constexpr int kBesideLds = 80 * 1024;
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES>
+__global__ __launch_bounds__(256, 2)
+void gemm_tile_beside_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W, int32_t K, int32_t N,
+                             int32_t ldw, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t splits, float* __restrict__ part,
+                             const uint16_t* __restrict__ D, const float* __restrict__ s, uint16_t* __restrict__ P_tok,
+                             uint16_t* __restrict__ P_blk, int32_t rparts, int32_t pwgs)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int32_t wg = int32_t(blockIdx.x);
+    if (wg < pwgs) {
+        if (wg < pd.ntb * 2 * rparts)
+            ring_item<1, 1, 1, 256, kBesideLds>(pd, Z, D, s, P_tok, P_blk, K, K, 1, 0, rparts, wg % pd.ntb, wg / pd.ntb, lds);
+        return;
+    }
+    tile_body<W_KN, TM, TN, WM, WN, STAGES>(pd, Z, W, nullptr, nullptr, nullptr, K, N, ldw, N, 1, 0, tiles_m, tiles_n, GM, splits, part,
+                                            wg - pwgs, lds);
+}
+
+// C = the splits' partial products, in split order, plus the adapter term P M_t, rounded once.  A wave has 256 columns of a row, so the
+// row's task and its projected activations are the same for all lanes; the rank rows go straight from memory into fp32 products, 16 of
+// them in flight.  (S splits as a template argument: under a condition of its own every load waited for the one before.)  What bounds it: three dependent reads of the tables and then the rank rows, out of the L2.
+template <int S>
+__global__ __launch_bounds__(256) void gemm_add_up_kernel(PlanDev pd, const float* __restrict__ part, const uint16_t* __restrict__ P,
+                                                          const uint16_t* __restrict__ M, uint16_t* __restrict__ C, int32_t N)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int32_t row = int32_t(blockIdx.x) * 4 + wave, col = int32_t(blockIdx.y) * 256 + 4 * lane;
+    if (row >= pd.T) return;
+    const int32_t c = min(col, N - 4);
+    f32x4 v[S];
+    const int64_t n = int64_t(pd.T) * N;
+#pragma unroll
+    for (int i = 0; i < S; ++i) v[i] = *reinterpret_cast<const f32x4*>(part + i * n + int64_t(row) * N + c);
+    // the row's segment: at most 32 begin in its block of 32 rows, and the table has the one of the block's first row
+    const int32_t k0 = pd.rowblk_seg[row / kRowBlock], k = k0 + 1 + lane;
+    const bool before = lane < kRowBlock && k < pd.nseg && pd.cseg_off[min(k, pd.nseg - 1)] <= row;
+    const int32_t t = pd.cseg_task[k0 + __builtin_popcountll(__ballot(before))];
+    f32x4 a = v[0];
+#pragma unroll
+    for (int i = 1; i < S; ++i) a = a + v[i];
+    if (t >= 0) {                                    // (uniform)
+        const int32_t r0 = __builtin_amdgcn_readfirstlane(pd.rank_off[t]), r = __builtin_amdgcn_readfirstlane(pd.rank_off[t + 1]) - r0;
+        f32x4 up = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int32_t p0 = 0; p0 < r; p0 += 16) {
+            const int32_t left = r - p0;             // ranks beyond r: zero times zero
+            const float pv = bf16_bits_to_float(P[size_t(row) * pd.r_pad + min(p0 + (lane & 15), r - 1)]);
+            uint64_t b[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) b[q] = *reinterpret_cast<const uint64_t*>(M + size_t(r0 + min(p0 + q, r - 1)) * N + uint32_t(c));
+            const float p = (lane & 15) < left ? pv : 0.f;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const float pq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), q));
+                const uint64_t m = b[q] & (q < left ? ~uint64_t(0) : uint64_t(0));
+                const uint32_t lo = uint32_t(m), hi = uint32_t(m >> 32);
+                up[0] += pq * __uint_as_float(lo << 16);
+                up[1] += pq * __uint_as_float(lo & 0xffff0000u);
+                up[2] += pq * __uint_as_float(hi << 16);
+                up[3] += pq * __uint_as_float(hi & 0xffff0000u);
+            }
+        }
+        a = a + up;
+    }
+    bf16x4 o;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = (__bf16)a[u];
+    if (col < N) *reinterpret_cast<bf16x4*>(C + size_t(row) * N + col) = o;
+}
+
 // C = the sum of the splits' partial products, in split order, rounded once: 8 columns per thread.
-__global__ __launch_bounds__(256) void gemm_add_kernel(const float* __restrict__ part, uint16_t* __restrict__ C, int32_t splits,
-                                                       int64_t n, int32_t N, int32_t ldc)
+template <int S>
+__global__ __launch_bounds__(256) void gemm_add_kernel(const float* __restrict__ part, uint16_t* __restrict__ C, int64_t n, int32_t N,
+                                                       int32_t ldc)
 {
     const int64_t i = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 8;
     if (i >= n) return;
-    f32x4 v[kMaxSplits + 1][2];
+    f32x4 v[S][2];
 #pragma unroll
-    for (int s = 0; s <= kMaxSplits; ++s)
-        if (s < splits) {
-            v[s][0] = *reinterpret_cast<const f32x4*>(part + s * n + i);
-            v[s][1] = *reinterpret_cast<const f32x4*>(part + s * n + i + 4);
-        }
+    for (int k = 0; k < S; ++k) {
+        v[k][0] = *reinterpret_cast<const f32x4*>(part + k * n + i);
+        v[k][1] = *reinterpret_cast<const f32x4*>(part + k * n + i + 4);
+    }
     f32x4 a = v[0][0], b = v[0][1];
 #pragma unroll
-    for (int s = 1; s <= kMaxSplits; ++s)
-        if (s < splits) a = a + v[s][0], b = b + v[s][1];
+    for (int k = 1; k < S; ++k) a = a + v[k][0], b = b + v[k][1];
     bf16x8 o;
 #pragma unroll
     for (int q = 0; q < 4; ++q) o[q] = (__bf16)a[q], o[4 + q] = (__bf16)b[q];
     *reinterpret_cast<bf16x8*>(C + size_t(i / N) * ldc + size_t(i % N)) = o;
+}
+
+// f(S) with S = n as a constant, 1 .. kMaxSplits + 1
+template <int S = 1, typename F> static void with_splits(int32_t n, F&& f)
+{
+    if constexpr (S <= kMaxSplits + 1) {
+        if (n == S) f(std::integral_constant<int, S>{});
+        else with_splits<S + 1>(n, f);
+    }
 }
 
 template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int OCC>
@@ -564,8 +661,66 @@ static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, c
     e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     const int64_t n = int64_t(pd.T) * N;             // (N is a multiple of 8)
-    gemm_add_kernel<<<dim3(uint32_t((n + 2047) / 2048)), 256, 0, st>>>(part, (uint16_t*)C, per, n, N, ldc);
+    with_splits(per, [&](auto s_c) {
+        gemm_add_kernel<decltype(s_c)::value><<<dim3(uint32_t((n + 2047) / 2048)), 256, 0, st>>>(part, (uint16_t*)C, n, N, ldc);
+    });
     return hipGetLastError();
+}
+
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES>
+static hipError_t launch_beside(const PlanDev& pd, const void* Z, const void* W, const void* D, const float* s, void* P_tok, void* P_blk,
+                                const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st, int32_t splits, float* part)
+{
+    static_assert(WM * WN == 4 && ring_bytes<TM, TN, WN, STAGES>() + int(sizeof(TileTable<TM>)) <= kBesideLds, "two workgroups per compute unit");
+    // the kernel needs more dynamic LDS than the default limit: raise it once per device
+    static std::atomic<uint64_t> raised{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = uint64_t(1) << (dev & 63);
+    if (!(raised.load(std::memory_order_acquire) & bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tile_beside_kernel<W_KN, TM, TN, WM, WN, STAGES>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kBesideLds);
+        if (e != hipSuccess) return e;
+        raised.fetch_or(bit, std::memory_order_release);
+    }
+    const int32_t tiles_m = (pd.T + TM - 1) / TM, tiles_n = (N + TN - 1) / TN, rparts = (pd.r_max + 15) / 16;
+    const int32_t pwgs = (pd.ntb * 2 * rparts + 7) / 8 * 8;
+    gemm_tile_beside_kernel<W_KN, TM, TN, WM, WN, STAGES><<<dim3(uint32_t(pwgs + tiles_m * tiles_n * splits)), 256, kBesideLds, st>>>(
+        pd, (const uint16_t*)Z, (const uint16_t*)W, K, N, ldw, tiles_m, tiles_n, 1024 / TM, splits, part, (const uint16_t*)D, s,
+        (uint16_t*)P_tok, (uint16_t*)P_blk, rparts, pwgs);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    with_splits(splits, [&](auto s_c) {
+        gemm_add_up_kernel<decltype(s_c)::value><<<dim3(uint32_t((pd.T + 3) / 4), uint32_t((N + 255) / 256)), 256, 0, st>>>(
+            pd, part, (const uint16_t*)P_tok, (const uint16_t*)M, (uint16_t*)C, N);
+    });
+    return hipGetLastError();
+}
+
+static GemmChoice beside_choice(const PlanDev& pd, int32_t K, int32_t N, const float* part, size_t part_bytes)
+{
+    if (!part || pd.T == 0 || pd.n_proj != 1) return GemmChoice{};
+    const GemmChoice c = choose_beside(pd.T, K, N, pd.nseg, pd.r_max, pd.ntb);
+    return size_t(c.splits) * size_t(pd.T) * size_t(N) * 4 <= part_bytes ? c : GemmChoice{};
+}
+
+bool gemm_takes_projection(const PlanDev& pd, int32_t K, int32_t N, const float* part, size_t part_bytes)
+{
+    return beside_choice(pd, K, N, part, part_bytes).tile >= 0;
+}
+
+hipError_t gemm_mfma_beside(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* D, const float* s, void* P_tok,
+                            void* P_blk, const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st, float* part,
+                            size_t part_bytes)
+{
+    const GemmChoice choice = beside_choice(pd, K, N, part, part_bytes);
+    if (choice.tile < 0 || !gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;
+#define LOBRA_BESIDE(...)                                                                                          \
+    (transW ? launch_beside<false, __VA_ARGS__>(pd, Z, W, D, s, P_tok, P_blk, M, C, K, N, ldw, st, choice.splits, part)   \
+            : launch_beside<true, __VA_ARGS__>(pd, Z, W, D, s, P_tok, P_blk, M, C, K, N, ldw, st, choice.splits, part))
+    return choice.tile == 3 ? LOBRA_BESIDE(128, 64, 2, 2, 3) : LOBRA_BESIDE(64, 64, 2, 2, 4);
+#undef LOBRA_BESIDE
 }
 
 bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw)

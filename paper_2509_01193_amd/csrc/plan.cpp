@@ -355,8 +355,8 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 choose_gemm(T, d->d_in, d->d_out, p->dg, ns, rk, 0).cost <=
                     float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, ns, rk, 0).cost + 3.f))
                 p->fwd_group = p->dg;
-            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk), 256);
-            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max), 256);
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk, p->n_proj == 1 ? int64_t(ntb) : 0), 256);
+            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max, p->n_proj == 1 && p->sliced_out.nsl == 0 ? int64_t(ntb) : 0), 256);
         }
         p->fwd_spart = spart_in;
         p->fwd_off_p = std::max(spart_in, p->fwd_part);
@@ -376,9 +376,18 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
     return LOBRA_OK;
 }
 
+constexpr int64_t cus = 256;                 // fixed, so that the choice does not depend on the device
+
+// The time of so many workgroups of a tile with so many K tiles each.
+static float rounds_cost(const GemmTile& t, int64_t wgs, int32_t kt, float fixed)
+{
+    const int64_t slots = cus * t.per_cu, full = wgs / slots, rest = wgs % slots;
+    const float per = float(kt), most = t.per_cu == 2 ? t.k2 : t.k1;
+    return float(full) * (most * per + fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + fixed : 0.f);
+}
+
 GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, size_t part_bytes)
 {
-    constexpr int64_t cus = 256;             // fixed, so that the choice does not depend on the device
     const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
     const bool ktail = K % (2 * kGemmKTile) != 0;
     const float segments = std::max(0.f, float(nseg) * kGemmTileRows / float(T) - 1.f);      // per tile row, beyond the first
@@ -406,9 +415,7 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
             if (s > 1 && (i == kPersistentTile || i == kStagedTile || K < kMinSplitK || kt < 4 * s || tiles * s > slots ||
                           uint64_t(bytes) > part_bytes))
                 break;
-            const int64_t full = tiles * s / slots, rest = tiles * s % slots;
-            const float per = float((kt + s - 1) / s), most = t.per_cu == 2 ? t.k2 : t.k1;
-            float cost = float(full) * (most * per + fixed) + (rest ? (rest <= cus ? t.k1 : most) * per + fixed : 0.f) + t.once;
+            float cost = rounds_cost(t, tiles * s, (kt + s - 1) / s, fixed) + t.once;
             if (s > 1) cost += 3.f + float(bytes) / 3e6f;
             if (least < 0.f || cost < least) best = GemmChoice{i, s, cost}, least = cost;
         }
@@ -416,10 +423,30 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
     return best;
 }
 
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank)
+GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb)
 {
-    const GemmChoice c = choose_gemm(T, K, N, group, nseg, rank, kMaxPartBytes);
-    return c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0;
+    GemmChoice best;
+    const int64_t items = ntb * ((rank + 15) / 16);
+    if (ntb == 0 || K < kMinSplitK || items > kMaxBesideItems || T * N * rank > kMaxBesideRankRows) return best;
+    const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
+    float least = choose_gemm(T, K, N, 0, nseg, rank, kMaxPartBytes).cost + kBesideGain;
+    for (int32_t i = 3; i <= 4; ++i) {               // (two workgroups of these, or of the projection, share a compute unit)
+        const GemmTile& t = kGemmTiles[i];
+        const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn);
+        for (int32_t s = 1; s <= kMaxSplits; ++s) {
+            const int64_t bytes = int64_t(s) * T * N * 4;
+            if (tiles * s > cus * t.per_cu || uint64_t(bytes) > kMaxPartBytes || (s > 1 && kt < 4 * s)) break;
+            const float cost = rounds_cost(t, tiles * s + items, (kt + s - 1) / s, t.fixed) + t.once + 3.f + float(bytes) / 3e6f;
+            if (cost < least) best = GemmChoice{i, s, cost}, least = cost;
+        }
+    }
+    return best;
+}
+
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, int64_t ntb)
+{
+    const GemmChoice c = choose_gemm(T, K, N, group, nseg, rank, kMaxPartBytes), b = choose_beside(T, K, N, nseg, rank, ntb);
+    return std::max(c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0, b.tile >= 0 ? size_t(b.splits) * size_t(T) * size_t(N) * 4 : 0);
 }
 
 SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D)

@@ -208,6 +208,36 @@ def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
                 assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5 * b.abs().max()).all()), T
 
 
+@pytest.mark.parametrize("T,d_in,d_out,ranks,longest", [
+    (1, 4096, 1032, [7], 1),                  # a single token; a rank below one rank block
+    (64, 2056, 264, [16, 17], 1),             # one-token segments: 64 blocks of two rank blocks, the most that goes in one launch
+    (65, 2056, 264, [16, 17], 1),             #   and one more
+    (33, 4096, 1088, [128, 16, 1], 5),        # eight rank blocks; a row's rank rows in eight loads of 16
+    (130, 3080, 136, [100, 24], 50),          # two tile rows, ranks beyond a multiple of 16, columns beyond one of 64
+    (300, 5504, 1032, [16, 8, 33], 90),       # blocks with a second half
+])
+def test_projection_beside_the_split_product(T, d_in, d_out, ranks, longest):
+    """Few token blocks and a split product: one launch projects and multiplies, the adapter term comes with the sum.  Both passes
+    against the oracle; the projected activations are those of a launch of their own (a forward pass without room for sums), bit
+    for bit.  Tokens without adapter among the others."""
+    import torch
+    rng = np.random.default_rng(T)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.integers(1, longest + 1)), T - sum(lens)))
+    tasks = [k % len(ranks) for k in range(len(lens))] if T in (64, 65) else rng.integers(-1 if T > 1 else 0, len(ranks), len(lens))
+    p = wl.make_custom("beside-%d" % T, "bf16", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]), tasks, 83,
+                       s=np.linspace(-1, 2, len(ranks)).astype(np.float32), std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, label="beside")
+    assert dp.plan.fwd_ws_bytes - dp.plan.h_save_bytes >= 2 * T * d_out * 4
+    h = dp.h_save.clone()
+    dp.h_save.fill_(7)
+    bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, dp.h_save, None)
+    torch.cuda.synchronize()
+    same = h == dp.h_save
+    assert bool((same | (dp.h_save == 7)).all()) and int(same.sum()) > 0
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [(1, 3072, 64, 1), (40, 4104, 136, 1), (70, 5128, 1032, 1), (33, 4096, 4096, 1),
                                                  (64, 5000, 192, 2)])
 def test_split_k_product_in_every_entry_point(T, d_in, d_out, n_proj):
