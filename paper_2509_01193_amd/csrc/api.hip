@@ -458,6 +458,11 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
             LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                          plain_gemm(pd, dt, true, dy, W, G, A, dx, pd.d_out, pd.d_in, pd.d_out, st));
         if (p.R_tot > 0) {
+            const GradJob jb{H, dy, part_b, dB, pd.dg}, ja{G, x, part_a, dA, pd.d_in};
+            if (adapters && p.grad_one) {
+                LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE1, grad_f32_one(pd, jb, ja, accumulate, st));
+                return LOBRA_OK;
+            }
             if (adapters) {
                 const size_t esz = dt == LOBRA_F32 ? 4 : 2;
                 if (p.n_proj == 1) {       // dB and dA in one launch
@@ -472,7 +477,6 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
                                  plain_grad_stage1(pd, dt, G, x, part_a, pd.d_in, st));
                 }
             }
-            const GradJob jb{H, dy, part_b, dB, pd.dg}, ja{G, x, part_a, dA, pd.d_in};
             LOBRA_LAUNCH(p, st, LOBRA_K_GRAD_STAGE2, reduce_partials(pd, jb, ja, accumulate, false, st));
         }
         return LOBRA_OK;

@@ -499,6 +499,103 @@ __global__ __launch_bounds__(256) void grad_f32_kernel(PlanDev pd, const float* 
     }
 }
 
+// -------------------------------------------------------------------------------------------
+// Both gradients of a batch whose tasks are short in one launch: one workgroup per (task, 64 columns), its NW waves take half blocks
+// of tokens in turn and add their sums through LDS in order.  What bounds it: a memory round trip per 16 tokens and wave, next to the
+// launch; the second stage that it saves was another launch and the partial sums' way to memory and back (618 tokens of 256 x 256,
+// two tasks of rank 8: 4.4 + 6.3 us; the step 29.4 -> 26.7).
+// -------------------------------------------------------------------------------------------
+template <int NRB, int NW, bool VEC>
+__global__ __launch_bounds__(64 * NW) void grad_f32_one_kernel(PlanDev pd, const float* __restrict__ P, const float* __restrict__ Z,
+                                                               float* __restrict__ out, int32_t D, int32_t tiles_a,
+                                                               const float* __restrict__ P2, const float* __restrict__ Z2,
+                                                               float* __restrict__ out2, int32_t D2, int accumulate)
+{
+    __shared__ __attribute__((aligned(16))) float red[NW][16][64];       // [wave][rank][column]
+    int32_t coltile = blockIdx.y;
+    if (coltile >= tiles_a) {
+        coltile -= tiles_a;
+        P = P2;
+        Z = Z2;
+        out = out2;
+        D = D2;
+    }
+    const int32_t t = blockIdx.x, tb0 = pd.task_tb_off[t], nb = pd.task_tb_off[t + 1] - tb0;
+    const int32_t r0 = pd.rank_off[t], r = pd.rank_off[t + 1] - r0;
+    if (nb == 0 && accumulate) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), i = lane & 15, kg = lane >> 4;
+    const int32_t col = coltile * 64 + 4 * i;
+    for (int32_t p0 = 0; p0 < r; p0 += 16 * NRB) {
+        f32x4 acc[NRB][4];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[rb][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int32_t nrb = min(NRB, (r - p0 + 15) >> 4);           // uniform
+        for (int32_t it = wave; it < 2 * nb; it += NW) {            // the first halves of all blocks, then the second ones
+            const int32_t h = it >= nb ? 16 : 0;
+            const TokenBlock b = pd.tb[tb0 + (it >= nb ? it - nb : it)];
+            if (h >= b.nrows) continue;              // uniform
+            f32x4 z[4];
+            float p[NRB][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {            // tokens beyond the block: zero in both operands
+                const int32_t tok = h + 4 * q + kg;
+                const size_t row = size_t(b.row0 + min(tok, b.nrows - 1));
+                z[q] = load4<VEC>(Z + row * D, tok < b.nrows ? col : D, D);
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb) {
+                    const int32_t k = p0 + 16 * rb + i;
+                    p[rb][q] = (rb < nrb && tok < b.nrows && k < r) ? P[row * pd.r_max + k] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb)
+                    if (rb < nrb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[rb][e] = mfma4(p[rb][q], z[q][e], acc[rb][e]);
+        }
+        // acc[rb][e][v]: rank p0 + 16 rb + 4 kg + v, column col + e
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            if (rb >= nrb) break;                    // uniform
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                *reinterpret_cast<f32x4*>(&red[wave][4 * kg + v][4 * i]) = f32x4{acc[rb][0][v], acc[rb][1][v], acc[rb][2][v], acc[rb][3][v]};
+            __syncthreads();
+            for (int e = threadIdx.x; e < 16 * 64; e += 64 * NW) {
+                const int32_t k = p0 + 16 * rb + e / 64, c = coltile * 64 + e % 64;
+                float sum = red[0][e / 64][e % 64];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum += red[w][e / 64][e % 64];
+                if (k >= r || c >= D) continue;
+                float* dst = out + size_t(r0 + k) * D + c;
+                *dst = accumulate ? *dst + sum : sum;
+            }
+        }
+    }
+}
+
+hipError_t grad_f32_one(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st)
+{
+    const int32_t tiles_a = (ja.D + 63) / 64, tiles_b = (jb.D + 63) / 64;
+    const dim3 grid(pd.n_tasks, tiles_a + tiles_b);
+    if (grid.y > 65535u) return hipErrorInvalidValue;
+    const bool vec = ((ja.D | jb.D) & 3) == 0;
+    const int nrb = (pd.r_max + 15) / 16;
+#define LOBRA_F32_ONE2(NRB, NW, VEC)                                                                                         \
+    grad_f32_one_kernel<NRB, NW, VEC><<<grid, 64 * NW, 0, st>>>(pd, (const float*)ja.P, (const float*)ja.Z, ja.out, ja.D, tiles_a, \
+                                                                (const float*)jb.P, (const float*)jb.Z, jb.out, jb.D, accumulate ? 1 : 0)
+#define LOBRA_F32_ONE(NRB, NW) do { if (vec) LOBRA_F32_ONE2(NRB, NW, true); else LOBRA_F32_ONE2(NRB, NW, false); } while (0)
+    if (nrb <= 1) LOBRA_F32_ONE(1, 16);
+    else if (nrb <= 2) LOBRA_F32_ONE(2, 16);
+    else LOBRA_F32_ONE(4, 8);
+    return hipGetLastError();
+}
+
 hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, float* part, int32_t D, int32_t ldz, int32_t nproj,
                            int32_t proj, const float* P2, const float* Z2, float* part2, int32_t D2, hipStream_t st)
 {

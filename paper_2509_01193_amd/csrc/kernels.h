@@ -58,6 +58,9 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
                     int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st);
 hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, float* part, int32_t D, int32_t ldz, int32_t nproj,
                            int32_t proj, const float* P2, const float* Z2, float* part2, int32_t D2, hipStream_t st);
+// Both gradients, final, of a plan with grad_one (n_proj = 1): no partial sums, no second stage; rows of tasks without tokens are
+// cleared (or, accumulating, left alone).
+hipError_t grad_f32_one(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st);
 // ---- bf16 MFMA kernels ------------------------------------------------------------------------
 // C[T, N] = Z[T, K] * op(W) + P * M_t with P bf16 [T][r_pad] (already scaled by s_t, zero beyond r_t).
 // ldc: row pitch of C (0: N).  nproj > 1: projection `proj` of a fused shared-input call - of every

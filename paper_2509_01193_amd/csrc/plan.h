@@ -143,6 +143,7 @@ struct Plan {
     // no task has more than one chunk: no partial sums to add (tasks without tokens, which stage 1 then clears: only while
     // there are few tasks, since it starts a workgroup for each of them and column tile)
     bool single_chunks = false, empty_tasks = false;
+    bool grad_one = false;      // fp32: both gradients without partial sums (grad_f32_one)
     int32_t part_rows = 0;              // rows of the partial-sum buffer = sum over chunks of r_t
     int32_t chunk_blocks = 0;           // token blocks per reduction chunk
 

@@ -709,6 +709,31 @@ def test_gradients_of_tasks_with_a_single_chunk(ranks, n_proj, empty_task):
     assert torch.equal(dp.dA, first[0]) and torch.equal(dp.dB, first[1]) and dp.guards_intact()
 
 
+@pytest.mark.parametrize("d_in,d_out,ranks,lens", [
+    (256, 64, [16, 8], [32 * 32, 500]),       # the longest task of one rank block: every wave two blocks
+    (256, 64, [16, 8], [32 * 32 + 1, 500]),   #   and one more, in two stages
+    (70, 33, [3, 16, 9], [1, 15, 17]),        # rows that start anywhere; single tokens, halves of blocks
+    (65, 260, [32, 17], [16 * 32, 33]),       # two rank blocks
+    (128, 96, [100, 1, 64], [4 * 32, 40, 7]), # eight in two passes over the tokens
+    (64, 8, [8, 24, 8], [40, 0, 16]),         # a task without tokens between others
+])
+def test_fp32_gradients_in_one_launch(d_in, d_out, ranks, lens):
+    """fp32 gradients without partial sums at the edges of their rule, tiles and rank passes, against the oracle; accumulating
+    twice the same gradients gives their double, bit for bit, and leaves the rows of a task without tokens alone."""
+    import torch
+    p = wl.make_custom("one-launch-%d" % d_in, "f32", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens + [9])]),
+                       list(range(len(lens))) + [-1], 37, s=np.linspace(-1, 2, len(ranks)).astype(np.float32), std_x=0.5, std_w=0.1,
+                       std_a=0.1, std_b=0.1)
+    dp, _ = check_problem(p, label="one launch")
+    want = [t.clone() for t in (dp.dA, dp.dB)]
+    bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, dp.h_save, dp.dx, dp.dA, dp.dB,
+                            bd.FLAG_ACCUMULATE_GRADS, dp.ws)
+    torch.cuda.synchronize()
+    for a, b in zip((dp.dA, dp.dB), want):
+        assert torch.equal(a, 2 * b)
+    assert dp.guards_intact()
+
+
 @pytest.mark.parametrize("d_in,d_out,ranks,n_proj,lens", [
     (136, 264, [8, 16, 4, 16], 1, [60, 33]),          # 128-column kernel, ragged tiles
     (520, 264, [24, 40, 32, 64], 1, [60, 33]),        # 256-column kernel, ranks in one pass of 64
