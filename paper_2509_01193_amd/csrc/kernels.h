@@ -103,7 +103,7 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                        void* P_tok, void* P_blk, int32_t D, int32_t ldz, int32_t nproj, int32_t proj,
                        hipStream_t st, const SlicedShape& sliced = SlicedShape{}, float* part = nullptr,
                        const void* Hblk = nullptr, float* partb = nullptr);
-// The same through an LDS ring (shrink_ring.hip), for ranks above 16.
+// The same through an LDS ring (shrink_ring.hip): every projection that does not accumulate dB.
 hipError_t shrink_ring(const PlanDev& pd, const void* Z, const void* M, const float* s, void* P_tok, void* P_blk, int32_t D,
                        int32_t ldz, int32_t nproj, int32_t proj, hipStream_t st);
 
