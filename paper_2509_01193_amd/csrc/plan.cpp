@@ -347,9 +347,11 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         }
         if (p->empty_tasks && n > kMaxClearedTasks) p->single_chunks = false;
 
-        // (the reduction kernels put chunks x column tiles of at least 64 columns on grid.x)
-        if ((int64_t(p->chunks.size()) + kMaxClearedTasks) * ((int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64) > 0x7fffffff)
-            return LOBRA_ERR_SHAPE;
+        // (the reduction kernels put chunks x column tiles of at least 64 columns on grid.x, and behind them the tasks whose rows stage 1
+        // clears, if there is room)
+        const int64_t red_tiles = (int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64;
+        if (int64_t(p->chunks.size()) * red_tiles > 0x7fffffff) return LOBRA_ERR_SHAPE;
+        if (p->empty_tasks && (int64_t(p->chunks.size()) + n) * red_tiles > 0x7fffffff) p->single_chunks = false;
 
         // 5. buffer sizes
         BufferLayout& L = p->p_layout;

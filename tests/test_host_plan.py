@@ -102,6 +102,21 @@ def test_shape_limits_are_reported_before_any_launch():
     assert bd.lib().lobra_mlora_plan_destroy(h) == 0
 
 
+def test_reduction_grid_limit_counts_what_a_batch_launches():
+    """Reduction chunks x 64-column tiles bound a batch, and nothing else does: not the workgroups that clear the rows of tasks without
+    tokens, of which this batch has none (130000 tasks of one token, 16385 tiles), and which go to the second stage where there is no
+    room for them."""
+    n, d_out = 130000, (1 << 20) - 8
+    for empty in (0, 1):
+        d, keep = bd.make_desc("bf16", n, 8, d_out, np.arange(n + empty + 1), np.arange(n + 1), np.arange(n))
+        h = ctypes.c_void_p()
+        assert bd.lib().lobra_mlora_plan_create(ctypes.byref(d), bd.PLAN_HOST_ONLY, ctypes.byref(h)) == 0
+        assert bd.lib().lobra_mlora_plan_destroy(h) == 0
+    n += 2000                                          # more chunks than the grid takes
+    d, keep = bd.make_desc("bf16", n, 8, d_out, np.arange(n + 1), np.arange(n + 1), np.arange(n))
+    assert bd.lib().lobra_mlora_plan_create(ctypes.byref(d), bd.PLAN_HOST_ONLY, ctypes.byref(h)) == -2
+
+
 def test_workspace_bytes_and_one_shot_argument_errors():
     """lobra_mlora_workspace_bytes is host only; the one-shot calls report descriptor and workspace errors
     before they touch the device (so all of this runs without a GPU)."""
