@@ -46,13 +46,12 @@ __device__ __forceinline__ void ring_body(const PlanDev& pd, const uint16_t* __r
     // ---- copies: rows beyond a block repeat its last one, rank rows beyond r_t the last one (what they produce is dropped)
     const unsigned char* zcur = reinterpret_cast<const unsigned char*>(Z + size_t(b.row0) * ldz);
     const unsigned char* mcur = reinterpret_cast<const unsigned char*>(M + size_t(b.rank_row0 + pofs) * D);
-    // (copy c of a wave: K tile zsub(c) of the slot, 8 rows that are the same for all c where G = 1)
-    auto zsub = [&](int c) { return G == 1 ? (wk + 4 * c) / (2 * H) : 0; };
     uint32_t zvo[ZC], avo[AC], zat[ZC], aat[AC];
     int32_t zk[ZC], ak[AC];                          // first k of the lane's chunk within the slot
 #pragma unroll
     for (int c = 0; c < ZC; ++c) {
-        const int sub = zsub(c), q = G == 1 ? wk % (2 * H) : c, row = 8 * q + lane / 8;
+        // (copy c of a wave: 8 rows that are the same for all c where G = 1, K tile sub of the slot)
+        const int sub = G == 1 ? (wk + 4 * c) / (2 * H) : 0, q = G == 1 ? wk % (2 * H) : c, row = 8 * q + lane / 8;
         zk[c] = 64 * sub + 8 * ((lane % 8) ^ swz_row(row));
         zvo[c] = (uint32_t(min(16 * half0 + row, b.nrows - 1)) * uint32_t(ldz) + uint32_t(zk[c])) * 2u;
         zat[c] = lds0 + sub * KTILE + (16 * H * blk + 8 * q) * 128;
@@ -69,13 +68,15 @@ __device__ __forceinline__ void ring_body(const PlanDev& pd, const uint16_t* __r
     const bool no_rows = G == 1 && 16 * half0 + 8 * (wk % (2 * H)) >= b.nrows;
     auto copy_slot = [&](int32_t i, uint32_t slot) __attribute__((always_inline)) {
         const uint32_t at = slot * SLOT;
-        if (ktail && i + 1 == n) {                   // (uniform) chunks beyond D repeat the last one, K tiles beyond D are left out
+        // (uniform) Chunks beyond D repeat the last one: with as many copies as the others the last slot is waited for by count like
+        // them (without, everything was waited for as soon as it was on its way: 1504 columns, 81 blocks of rank 64 10.0 -> 9.0 us,
+        // 141 one-token blocks of rank 16 7.7 -> 7.3; 4104, 81 blocks of rank 128 20.0 -> 19.4)
+        if (ktail && i + 1 == n) {
+            if (!no_rows)
 #pragma unroll
-            for (int c = 0; c < ZC; ++c)
-                if (!no_rows && zsub(c) * 64 < ktail) dma16(zat[c] + at, zcur, zvo[c] - 2u * uint32_t(max(zk[c] - (ktail - 8), 0)));
+                for (int c = 0; c < ZC; ++c) dma16(zat[c] + at, zcur, zvo[c] - 2u * uint32_t(max(zk[c] - (ktail - 8), 0)));
 #pragma unroll
-            for (int c = 0; c < AC; ++c)
-                if ((wave + 4 * c) % AP / (2 * NRB) * 64 < ktail) dma16(aat[c] + at, mcur, avo[c] - 2u * uint32_t(max(ak[c] - (ktail - 8), 0)));
+            for (int c = 0; c < AC; ++c) dma16(aat[c] + at, mcur, avo[c] - 2u * uint32_t(max(ak[c] - (ktail - 8), 0)));
         } else {
             if (!no_rows)
 #pragma unroll
@@ -121,7 +122,7 @@ __device__ __forceinline__ void ring_body(const PlanDev& pd, const uint16_t* __r
     uint32_t slot = 0, fill = STAGES - 1;
     for (int32_t i = 0; i < n; ++i) {
         // this slot's copies have landed
-        if (i + STAGES - 1 > n || (i + STAGES - 1 == n && ktail)) wait_vmcnt<0>();
+        if (i + STAGES - 1 > n) wait_vmcnt<0>();
         else if (no_rows) wait_vmcnt<(STAGES - 2) * AC>();
         else wait_vmcnt<(STAGES - 2) * CPW>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
