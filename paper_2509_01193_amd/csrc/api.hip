@@ -315,6 +315,11 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
         src = plan->fb_task_row0.data();
         n = plan->fb_task_row0.size();
         break;
+    case LOBRA_Q_BESIDE:
+        tmp = {plan->beside_fwd.tile >= 0 ? plan->beside_fwd.splits : 0, plan->beside_bwd.tile >= 0 ? plan->beside_bwd.splits : 0};
+        src = tmp.data();
+        n = tmp.size();
+        break;
     case LOBRA_Q_GEMM_TILE_ROWS:
         src = plan->gemm_tile_tab.data();
         n = plan->gemm_tile_tab.size();
@@ -363,11 +368,11 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     }
     // bf16 MFMA path
     char* hb = static_cast<char*>(hbuf);
-    if (adapters && gemm_takes_projection(pd, pd.d_in, pd.d_out, part, p.fwd_part)) {     // few token blocks: one launch for both
+    if (adapters && part && p.beside_fwd.tile >= 0) {     // few token blocks: one launch for both
         LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK, hipSuccess);
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
-                     gemm_mfma_beside(pd, false, x, W, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, B, y, pd.d_in, pd.d_out,
-                                      pd.d_out, st, part, p.fwd_part));
+                     gemm_mfma_beside(pd, p.beside_fwd, false, x, W, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, B, y, pd.d_in,
+                                      pd.d_out, pd.d_out, st, part, p.fwd_part));
         return LOBRA_OK;
     }
     if (adapters)   // all projections' down factors are stacked in A: one pass over x
@@ -488,7 +493,7 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
     const bool fused_db = adapters && p.fused_db && p.R_tot > 0;
     const char* H = static_cast<const char*>(h_saved);
     float* const split_part = ws && ws_bytes >= p.bwd_off_spart + p.bwd_part && p.bwd_part > 0 ? reinterpret_cast<float*>(wsb + p.bwd_off_spart) : nullptr;
-    const bool beside = adapters && want_dx && p.sliced_out.nsl == 0 && gemm_takes_projection(pd, pd.d_out, pd.d_in, split_part, p.bwd_part);
+    const bool beside = adapters && want_dx && split_part && p.beside_bwd.tile >= 0;
     if (adapters) {
         if (!H) {
             char* Hr = wsb + p.bwd_off_h;
@@ -505,8 +510,8 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
     }
     if (want_dx && p.desc.T > 0)
         LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
-                     beside ? gemm_mfma_beside(pd, true, dy, W, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, A, dx, pd.d_out,
-                                               pd.d_in, pd.d_out, st, split_part, p.bwd_part)
+                     beside ? gemm_mfma_beside(pd, p.beside_bwd, true, dy, W, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, A, dx,
+                                               pd.d_out, pd.d_in, pd.d_out, st, split_part, p.bwd_part)
                             : gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,
                                         pd.d_in, pd.d_out, st, 0, 1, 0, split_part, p.bwd_part));
     if (p.R_tot > 0) {

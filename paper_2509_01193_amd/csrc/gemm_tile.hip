@@ -698,24 +698,13 @@ static hipError_t launch_beside(const PlanDev& pd, const void* Z, const void* W,
     return hipGetLastError();
 }
 
-static GemmChoice beside_choice(const PlanDev& pd, int32_t K, int32_t N, const float* part, size_t part_bytes)
+hipError_t gemm_mfma_beside(const PlanDev& pd, const GemmChoice& choice, bool transW, const void* Z, const void* W, const void* D,
+                            const float* s, void* P_tok, void* P_blk, const void* M, void* C, int32_t K, int32_t N, int32_t ldw,
+                            hipStream_t st, float* part, size_t part_bytes)
 {
-    if (!part || pd.T == 0 || pd.n_proj != 1) return GemmChoice{};
-    const GemmChoice c = choose_beside(pd.T, K, N, pd.nseg, pd.r_max, pd.ntb);
-    return size_t(c.splits) * size_t(pd.T) * size_t(N) * 4 <= part_bytes ? c : GemmChoice{};
-}
-
-bool gemm_takes_projection(const PlanDev& pd, int32_t K, int32_t N, const float* part, size_t part_bytes)
-{
-    return beside_choice(pd, K, N, part, part_bytes).tile >= 0;
-}
-
-hipError_t gemm_mfma_beside(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* D, const float* s, void* P_tok,
-                            void* P_blk, const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st, float* part,
-                            size_t part_bytes)
-{
-    const GemmChoice choice = beside_choice(pd, K, N, part, part_bytes);
-    if (choice.tile < 0 || !gemm_mfma_shape_ok(pd.T, K, N, ldw)) return hipErrorInvalidValue;
+    if (choice.tile < 0 || pd.T == 0 || pd.n_proj != 1 || !part || size_t(choice.splits) * size_t(pd.T) * size_t(N) * 4 > part_bytes ||
+        !gemm_mfma_shape_ok(pd.T, K, N, ldw))
+        return hipErrorInvalidValue;
 #define LOBRA_BESIDE(...)                                                                                          \
     (transW ? launch_beside<false, __VA_ARGS__>(pd, Z, W, D, s, P_tok, P_blk, M, C, K, N, ldw, st, choice.splits, part)   \
             : launch_beside<true, __VA_ARGS__>(pd, Z, W, D, s, P_tok, P_blk, M, C, K, N, ldw, st, choice.splits, part))

@@ -69,13 +69,12 @@ hipError_t grad_f32_one(const PlanDev& pd, const GradJob& ja, const GradJob& jb,
 hipError_t gemm_mfma(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* P,
                      const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st,
                      int32_t ldc = 0, int32_t nproj = 1, int32_t proj = 0, float* part = nullptr, size_t part_bytes = 0);
-// The projection of Z by the down factors D and the product in one launch (and one that adds up), where the product is split and the
-// batch has few token blocks: gemm_takes_projection says whether; P_tok and P_blk are what shrink_mfma would have written.
-bool gemm_takes_projection(const PlanDev& pd, int32_t K, int32_t N, const float* part, size_t part_bytes);
-hipError_t gemm_mfma_beside(const PlanDev& pd, bool transW, const void* Z, const void* W, const void* D, const float* s, void* P_tok,
-                            void* P_blk, const void* M, void* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st, float* part,
-                            size_t part_bytes);
 // part, part_bytes: scratch for the sums of a product whose K is split (choose_gemm; NULL, 0: it is not split).
+// The projection of Z by the down factors D and the product in one launch (and one that adds up): what choose_beside chose for the
+// batch; P_tok and P_blk are what shrink_mfma would have written.
+hipError_t gemm_mfma_beside(const PlanDev& pd, const GemmChoice& choice, bool transW, const void* Z, const void* W, const void* D,
+                            const float* s, void* P_tok, void* P_blk, const void* M, void* C, int32_t K, int32_t N, int32_t ldw,
+                            hipStream_t st, float* part, size_t part_bytes);
 // The persistent direct-to-LDS kernel behind gemm_mfma for many output tiles (gemm_persistent.hip; T >= 256, N >= 256, K a
 // multiple of 128, or any multiple of 8 from kPersistentMinKTail on);
 // gm = tile rows per sweep of the tile order.  Everything else runs on the tiled kernels of gemm_tile.hip and the

@@ -380,8 +380,15 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 choose_gemm(T, d->d_in, d->d_out, p->dg, ns, rk, 0).cost <=
                     float(p->n_proj) * (choose_gemm(T, d->d_in, p->dg, 0, ns, rk, 0).cost + 3.f))
                 p->fwd_group = p->dg;
-            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk, p->n_proj == 1 ? int64_t(ntb) : 0), 256);
-            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max, p->n_proj == 1 && p->sliced_out.nsl == 0 ? int64_t(ntb) : 0), 256);
+            p->beside_fwd = p->beside_bwd = GemmChoice{};
+            if (p->n_proj == 1) {
+                int32_t halves = 1;
+                for (const TokenBlock& b : p->tb) halves = std::max(halves, (b.nrows + 15) / 16);
+                p->beside_fwd = choose_beside(T, d->d_in, d->d_out, ns, p->r_max, int64_t(ntb), halves);
+                if (p->sliced_out.nsl == 0) p->beside_bwd = choose_beside(T, d->d_out, d->d_in, ns, p->r_max, int64_t(ntb), halves);
+            }
+            p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk, p->beside_fwd), 256);
+            p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max, p->beside_bwd), 256);
         }
         p->fwd_spart = spart_in;
         p->fwd_off_p = std::max(spart_in, p->fwd_part);
@@ -448,7 +455,7 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
     return best;
 }
 
-GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb)
+GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb, int32_t halves)
 {
     GemmChoice best;
     const int64_t items = ntb * ((rank + 15) / 16);
@@ -460,7 +467,7 @@ GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t 
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn);
         for (int32_t s = 1; s <= kMaxSplits; ++s) {
             const int64_t bytes = int64_t(s) * T * N * 4;
-            if (tiles * s > cus * t.per_cu || uint64_t(bytes) > kMaxPartBytes || (s > 1 && kt < 4 * s)) break;
+            if (tiles * s + items * halves > cus * t.per_cu || uint64_t(bytes) > kMaxPartBytes || (s > 1 && kt < 4 * s)) break;
             const float cost = rounds_cost(t, tiles * s + items, (kt + s - 1) / s, t.fixed) + t.once + 3.f + float(bytes) / 3e6f;
             if (cost < least) best = GemmChoice{i, s, cost}, least = cost;
         }
@@ -468,10 +475,11 @@ GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t 
     return best;
 }
 
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, int64_t ntb)
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, const GemmChoice& beside)
 {
-    const GemmChoice c = choose_gemm(T, K, N, group, nseg, rank, kMaxPartBytes), b = choose_beside(T, K, N, nseg, rank, ntb);
-    return std::max(c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0, b.tile >= 0 ? size_t(b.splits) * size_t(T) * size_t(N) * 4 : 0);
+    const GemmChoice c = choose_gemm(T, K, N, group, nseg, rank, kMaxPartBytes);
+    return std::max(c.splits > 1 ? size_t(c.splits + 1) * size_t(T) * size_t(N) * 4 : 0,
+                    beside.tile >= 0 ? size_t(beside.splits) * size_t(T) * size_t(N) * 4 : 0);
 }
 
 SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D)

@@ -88,24 +88,28 @@ struct GemmChoice { int32_t tile = -1, splits = 1; float cost = -1.f; };    // t
 // `group` columns (a multiple of 64).  nseg: segments of the batch (0: no adapter); rank: the widest rank window.
 GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, size_t part_bytes);
 // The same where the projection runs in the product's launch and the adapter term comes with the sum of the splits, of which there may
-// be one (gemm_mfma_beside; ntb: token blocks): tile -1 where a projection of its own is better.  Given kMaxPartBytes of scratch.
+// be one (gemm_mfma_beside; ntb: token blocks; halves: 2 if one has more than 16 tokens, else 1): tile -1 where a projection of its own is better.  Given kMaxPartBytes of scratch.
 // Forward passes, a projection of its own / beside the product, us (K x N, rank, n one-token requests or tokens of segments of m):
 //     4096 x 4096    16   n = 1 20.7 / 13.0   40 22.3 / 15.0   100 28.1 / 17.9   150 29.9 / 22.4   128 of 40  25.7 / 17.8
 //                    128  n = 1 22.3 / 18.4   40 31.4 / 23.1
 //     8192 x 1024    64   n = 8 22.8 / 18.9   200 of 60  28.4 / 23.0   500 of 200  42.2 / 36.2
 //     4096 x 11008   16   n = 1 29.0 / 22.6   40 35.3 / 28.7   100 45.2 / 38.6   (one split)
 //     2048 x 2048    16   n = 40 18.2 / 11.6  300 of 100  18.6 / 15.8
-// The estimate counts a projection's workgroups (items: token blocks x rank blocks) with the product's, as if they took as long: without
+// The estimate counts a projection's items (token blocks x rank blocks) with the product's workgroups, as if they took as long: without
 // that, a product that filled the compute units by itself was split as far (100 of 4096 x 4096: 20.4; 1284 x 8160 x 768, both
-// passes: 108 where it is 97 now and 102 apart).  What is saved, a launch and the chain of tables and adapter copies behind
-// a tile, is kBesideGain.  The sum reads T N rank elements of the adapters: from 32 million on that takes the gain
+// passes: 108 where it is 97 now and 102 apart).  An item is a workgroup per half of its block, and all have to run at once: on one
+// that has to wait for another to end the launch waits too (apart / one too many, us: 600 x 1504 x 1536, rank 16 15.8 / 18.5; 800 x 1024 x
+// 1024, rank 32 13.7 / 17.0; 1100 x 2048 x 768, rank 32 18.3 / 21.7).  Halves without tokens end at once, but leave room on their own XCD
+// only, so they count unless all blocks are short.  What is saved, a launch and the chain of tables and adapter copies behind
+// a tile, is kBesideGain (apart / beside where that is all: 1100 x 1024 x 1024, estimates 4.5 apart, 14.9 / 15.7; 600 x 2048 x 2048, 4.2,
+// 20.8 / 19.5; 1500 x 2048 x 768, 4.0, 22.1 / 20.5).  The sum reads T N rank elements of the adapters: from 32 million on that takes the gain
 // (200 x 1024 x 3072 at rank 64, 39 million: 15.0 / 17.0; 700 x 8192 x 1024 39.2 / 44.8; 128 x 4096 x 4096 at rank 128 25.5 / 26.6).
 // Below K = kMinSplitK a token's result shall not depend on the size of its batch.
-constexpr float kBesideGain = 5.f;
+constexpr float kBesideGain = 4.4f;
 constexpr int64_t kMaxBesideItems = 256, kMaxBesideRankRows = int64_t(32) << 20;
-GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb);
-// The scratch that these choices would like to have (0: none; ntb = 0: without the second).
-size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, int64_t ntb);
+GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb, int32_t halves);
+// The scratch that these choices would like to have (0: none).
+size_t gemm_part_bytes(int64_t T, int32_t K, int32_t N, int32_t group, int32_t nseg, int32_t rank, const GemmChoice& beside);
 
 // Byte offsets of the sub-buffers inside h_save and the workspaces.
 struct BufferLayout {
@@ -161,6 +165,7 @@ struct Plan {
     // (fwd_group: fused projections' forward products run as one launch whose tiles do not straddle multiples of this
     // many columns; 0: one launch per projection)
     int32_t fwd_group = 0;
+    GemmChoice beside_fwd, beside_bwd;  // the projection in the launch of its product, given scratch for it (tile -1: not)
     size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0, bwd_need = 0;
     // dB fused into the sliced projection of dy (one pass over dy for s_t B_t dy_i and for dB): a workgroup
     // keeps the dB sums of the (task, slice) it is working on and writes them out - 16 rank rows x 512

@@ -208,6 +208,28 @@ def test_reduction_chunks_of_high_ranks_leave_enough_workgroups(T, d_in, d_out, 
     plan.close()
 
 
+@pytest.mark.parametrize("lens,d_in,d_out,rank,beside", [
+    ([1] * 40, 4096, 4096, 16, (7, 7)),
+    ([1] * 128, 2056, 264, 32, (7, 0)),               # 128 blocks x 2 rank blocks are taken (backward: K below kMinSplitK),
+    ([1] * 129, 2056, 264, 32, (0, 0)),               #   129 are not
+    ([150] * 4, 1504, 1536, 16, (0, 0)),              # 480 tiles and a workgroup per half of 20 blocks: more than run at once
+    ([200] * 4, 1024, 1024, 32, (0, 0)),
+    ([300, 300], 2048, 768, 64, (2, 0)),              # three splits and 160 halves would be too many, two are not
+    ([100, 100], 1024, 3072, 64, (0, 3)),             # the sum would read 39 million elements of the adapters
+])
+def test_projection_beside_the_product_where_all_workgroups_run_at_once(lens, d_in, d_out, rank, beside):
+    """Segments of two alternating tasks.  The projection shares its product's launch only while the product's workgroups and one per half
+    of a token block and rank block (all blocks short: per block) find room on 256 compute units, two each."""
+    off = np.concatenate([[0], np.cumsum(lens)])
+    plan = bd.Plan("bf16", off[-1], d_in, d_out, [0, rank, 2 * rank], off, np.arange(len(lens)) % 2, bd.PLAN_HOST_ONLY)
+    assert tuple(plan.query(bd.Q_BESIDE).tolist()) == beside
+    items = len(plan.query(bd.Q_TOKEN_BLOCKS)) // 4 * (-(-rank // 16)) * (2 if max(lens) > 16 else 1)
+    for splits, n in zip(beside, (d_out, d_in)):
+        least = -(-int(off[-1]) // 128) * -(-n // 64) * splits               # with the largest of its tiles
+        assert splits == 0 or least + items <= 512
+    plan.close()
+
+
 def split_k_floor(plan, rank_off):
     """Least (forward without h_save, backward) workspace of a short MFMA batch: the projected activations, once and twice,
     and the reduction's partial sums (a split product's sums are not needed)."""
