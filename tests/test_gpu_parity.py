@@ -208,34 +208,58 @@ def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
                 assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5 * b.abs().max()).all()), T
 
 
-@pytest.mark.parametrize("T,d_in,d_out,ranks,longest", [
-    (1, 4096, 1032, [7], 1),                  # a single token; a rank below one rank block
-    (64, 2056, 264, [16, 17], 1),             # one-token segments: 64 blocks of two rank blocks, the most that goes in one launch
-    (65, 2056, 264, [16, 17], 1),             #   and one more
-    (33, 4096, 1088, [128, 16, 1], 5),        # eight rank blocks; a row's rank rows in eight loads of 16
-    (130, 3080, 136, [100, 24], 50),          # two tile rows, ranks beyond a multiple of 16, columns beyond one of 64
-    (300, 5504, 1032, [16, 8, 33], 90),       # blocks with a second half
+@pytest.mark.parametrize("T,d_in,d_out,ranks,longest,beside", [
+    (1, 4096, 1032, [7], 1, (True, True)),                  # a single token; a rank below one rank block
+    (128, 2056, 264, [16, 17], 1, (True, False)),           # one-token segments: 128 blocks of two rank blocks, the most that goes in one launch
+    (129, 2056, 264, [16, 17], 1, (False, False)),          #   and one more
+    (128, 264, 2056, [16, 17], 1, (False, True)),           #   the same in the other direction
+    (129, 264, 2056, [16, 17], 1, (False, False)),
+    (33, 4096, 1088, [128, 16, 1], 5, (True, True)),        # eight rank blocks; a row's rank rows in eight loads of 16
+    (130, 3080, 136, [100, 24], 50, (True, False)),         # two tile rows, ranks beyond a multiple of 16, columns beyond one of 64
+    (300, 5504, 1032, [16, 8, 33], 90, (True, False)),      # blocks with a second half; backward, too many rank rows for the sum
+    (600, 1504, 1536, [16, 8], 25, (False, False)),         # more workgroups than run at once
 ])
-def test_projection_beside_the_split_product(T, d_in, d_out, ranks, longest):
-    """Few token blocks and a split product: one launch projects and multiplies, the adapter term comes with the sum.  Both passes
-    against the oracle; the projected activations are those of a launch of their own (a forward pass without room for sums), bit
-    for bit.  Tokens without adapter among the others."""
+def test_projection_beside_the_split_product(T, d_in, d_out, ranks, longest, beside):
+    """Few token blocks and room for sums: one launch projects and multiplies, the adapter term comes with the sum.  Both passes
+    against the oracle; the projected activations are those of a launch of their own (a pass without room for sums), bit
+    for bit, whatever their buffer held.  Tokens without adapter among the others."""
     import torch
     rng = np.random.default_rng(T)
     lens = []
     while sum(lens) < T:
         lens.append(min(int(rng.integers(1, longest + 1)), T - sum(lens)))
-    tasks = [k % len(ranks) for k in range(len(lens))] if T in (64, 65) else rng.integers(-1 if T > 1 else 0, len(ranks), len(lens))
+    tasks = [k % len(ranks) for k in range(len(lens))] if longest == 1 else rng.integers(-1, len(ranks), len(lens))
     p = wl.make_custom("beside-%d" % T, "bf16", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]), tasks, 83,
                        s=np.linspace(-1, 2, len(ranks)).astype(np.float32), std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
     dp, _ = check_problem(p, label="beside")
-    assert dp.plan.fwd_ws_bytes - dp.plan.h_save_bytes >= 2 * T * d_out * 4
-    h = dp.h_save.clone()
-    dp.h_save.fill_(7)
-    bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, dp.h_save, None)
-    torch.cuda.synchronize()
-    same = h == dp.h_save
-    assert bool((same | (dp.h_save == 7)).all()) and int(same.sum()) > 0
+    assert tuple(v > 0 for v in dp.plan.query(bd.Q_BESIDE).tolist()) == beside
+    r_pad, ntb = (max(ranks) + 15) // 16 * 16, len(dp.plan.query(bd.Q_TOKEN_BLOCKS)) // 4
+    up = lambda n: (n + 255) // 256 * 256
+    blk = up(T * r_pad * 2)
+    mine = torch.from_numpy(oracle.token_task(T, p.seg_off, p.seg_task, p.n_tasks) >= 0).to(dp.dev)
+
+    def projected(buf):
+        """The token-major rows of adapter tokens and the block-transposed copy."""
+        return (buf[: T * r_pad * 2].view(torch.int16).view(T, r_pad)[mine].clone(),
+                buf[blk: blk + ntb * r_pad * 64].view(torch.int16).clone())
+
+    rows = int(np.diff(p.rank_off)[dp.plan.query(bd.Q_GRAD_CHUNKS).reshape(-1, 4)[:, 2]].sum())
+    bare = dp.ws[: 2 * dp.plan.h_save_bytes + up(rows * d_out * 4) + up(rows * d_in * 4)]      # no room for sums
+    h, g = [], []
+    for fill, roomy in ((7, True), (0xA5, True), (7, False)):
+        dp.h_save.fill_(fill)
+        bd.lobra_mlora_plan_fwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.y, dp.h_save, dp.ws if roomy else None)
+        torch.cuda.synchronize()
+        h.append(projected(dp.h_save))
+        dp.ws.fill_(fill)
+        bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, dp.h_save, dp.dx, dp.dA, dp.dB, 0,
+                                dp.ws if roomy else bare)
+        torch.cuda.synchronize()
+        g.append(projected(dp.ws))
+    for runs in (h, g):
+        for other in runs[1:]:
+            assert torch.equal(runs[0][0], other[0]) and torch.equal(runs[0][1], other[1])
+    assert dp.guards_intact()
 
 
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [(1, 3072, 64, 1), (40, 4104, 136, 1), (70, 5128, 1032, 1), (33, 4096, 4096, 1),
