@@ -178,11 +178,11 @@ LOBRA_API lobra_status lobra_mlora_plan_sizes(const lobra_mlora_plan *plan, size
  *   LOBRA_Q_BLOCK_ORDER  order in which the token blocks are handed to the down-projection's
  *   LOBRA_Q_RUN_ORDER    workgroups, and the same for the runs: a permutation by descending rank
  *                        (stable), or empty when that is the stored order (e.g. equal ranks)
- *   LOBRA_Q_SLICED       {slices_in, slices_out, fused_db, fused_rows, workgroups}: long batches of ranks up
- *                        to 16 are projected by a fixed grid of `workgroups` workgroups that walk (token block,
- *                        512-column slice) items (slices_* = number of slices of d_in / d_out, 0 = the
- *                        one-block-per-workgroup kernels are used for that direction); fused_db = 1: the backward
- *                        projection of dy accumulates dB in the same pass, its sums in fused_rows rows
+ *   LOBRA_Q_SLICED       {0, slices_out, fused_db, fused_rows, workgroups}: dy of long batches of ranks up
+ *                        to 16 is projected by a fixed grid of `workgroups` workgroups that walk (token block,
+ *                        512-column slice) items (slices_out = number of slices of d_out, 0 = a workgroup per token
+ *                        block or run of them, as x always is); fused_db = 1: this projection
+ *                        accumulates dB in the same pass, its sums in fused_rows rows
  *   LOBRA_Q_FUSED_WG_RUNS  [workgroups + 1]: the runs of items of one (task, slice) that workgroup g meets are
  *                        number wg_runs[g] .. wg_runs[g + 1] - 1 (all four lists are empty unless fused_db)
  *   LOBRA_Q_FUSED_RUN_ROW  per run: first of its 16 rows in the array of dB sums
@@ -208,10 +208,8 @@ LOBRA_API lobra_status lobra_mlora_plan_query(const lobra_mlora_plan *plan, int3
  *   h_save        : device, h_save_bytes, or NULL.  When given, bwd can reuse the
  *                   down-projected activations instead of recomputing them
  *   ws, ws_bytes  : device scratch of at least fwd_ws_bytes.  With h_save given only its first
- *                   fwd_ws_bytes - h_save_bytes bytes are used: the partial sums of the K-sliced down
- *                   projection that long batches of ranks up to 16 take, and those of a base product whose K is
- *                   split.  Only the former are needed and checked (see lobra_mlora_plan_sizes), so that with h_save ws
- *                   may be NULL for every batch that is not long
+ *                   fwd_ws_bytes - h_save_bytes bytes are used, for the partial sums of a base product whose K is
+ *                   split.  They are not needed (see lobra_mlora_plan_sizes), so that with h_save ws may be NULL
  *   hip_stream    : hipStream_t (NULL = default stream); work is enqueued, not awaited
  * x, W, A, B, s are read only; y and h_save are overwritten. */
 LOBRA_API lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan *plan, const void *x, const void *W,
@@ -224,7 +222,7 @@ LOBRA_API lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan *plan, const 
  * own device image instead of a caller buffer.  Arguments as for lobra_mlora_plan_fwd.  Makes no allocation
  * of any kind and does not synchronise.  LOBRA_ERR_WORKSPACE when the projected activations (h_save_bytes)
  * exceed LOBRA_STATIC_WS_BYTES (nothing is launched); a plan whose fwd_ws_bytes exceed the array only because of
- * partial sums (K-sliced projection, split product) runs without them here (same result up to the order of the sums).  Each GPU has ONE such array, which keeps the last
+ * a split product's partial sums runs without them here (same result up to the order of the sums).  Each GPU has ONE such array, which keeps the last
  * call's contents: two calls of this function (or of lobra_token_task_map, which parks its tables there)
  * that overlap in time on the same GPU (different streams, or different threads) race on it and must be
  * ordered by the caller; the saved activations are not available to bwd (pass h_saved = NULL there). */

@@ -88,7 +88,7 @@ lobra_status runnable(const lobra_mlora_plan* plan)
 
 // Argument checks of a forward call on plan p (everything except the plan itself): host only.
 lobra_status fwd_check(const Plan& p, const void* x, const void* W, const void* A, const void* B, const float* s,
-                       const void* y, const void* h_save, const void* ws, size_t ws_bytes, bool sliced = true)
+                       const void* y, const void* h_save, const void* ws, size_t ws_bytes)
 {
     const bool adapters = !p.tb.empty();
     if (!x || !W || !y) return LOBRA_ERR_NULL;
@@ -96,9 +96,8 @@ lobra_status fwd_check(const Plan& p, const void* x, const void* W, const void* 
     if (!aligned16(x) || !aligned16(W) || !aligned16(y) || !aligned16(A) || !aligned16(B) ||
         !aligned16(h_save) || !aligned16(ws))
         return LOBRA_ERR_ALIGN;
-    // the workspace holds the sliced projection's partial sums (if the plan uses it), then, if there is room, those of a
-    // split base product in the same place, and, without h_save, the projected activations behind them
-    const size_t need = (sliced ? p.fwd_spart : 0) + (h_save ? 0 : p.p_layout.total);
+    // the workspace holds, without h_save, the projected activations, and in front of them, if there is room, a split base product's sums
+    const size_t need = h_save ? 0 : p.p_layout.total;
     if (adapters && need > 0 && (!ws || ws_bytes < need)) return LOBRA_ERR_WORKSPACE;
     return LOBRA_OK;
 }
@@ -295,7 +294,7 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
         n = plan->sb_order.size();
         break;
     case LOBRA_Q_SLICED:
-        tmp = {plan->sliced_in.nsl, plan->sliced_out.nsl, plan->fused_db ? 1 : 0, plan->fb_rows, kSlicedGrid};
+        tmp = {0, plan->sliced_out.nsl, plan->fused_db ? 1 : 0, plan->fb_rows, kSlicedGrid};
         src = tmp.data();
         n = tmp.size();
         break;
@@ -333,21 +332,20 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
 }
 
 namespace {
-// The forward pass.  A workspace without room for the partial sums of a split base product goes without the split; sliced =
-// false: without the K-sliced projection either, even where the plan would take it (its partial sums are most of what the
-// workspace must hold then): the projected activations then start at ws itself.
+// The forward pass.  A workspace without room for the partial sums of a split base product goes without the split: the projected
+// activations then start at ws itself.
 lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W, const void* A, const void* B,
-                      const float* s, void* y, void* h_save, void* ws, size_t ws_bytes, void* hip_stream, bool sliced)
+                      const float* s, void* y, void* h_save, void* ws, size_t ws_bytes, void* hip_stream)
 {
     lobra_status rs = runnable(plan);
     if (rs != LOBRA_OK) return rs;
     const Plan& p = *plan;
     if (p.desc.T == 0) return LOBRA_OK;
-    rs = fwd_check(p, x, W, A, B, s, y, h_save, ws, ws_bytes, sliced);
+    rs = fwd_check(p, x, W, A, B, s, y, h_save, ws, ws_bytes);
     if (rs != LOBRA_OK) return rs;
     const bool adapters = !p.tb.empty();
-    const bool room = sliced && ws && ws_bytes >= (h_save ? p.fwd_part : p.fwd_ws_bytes);       // for a split product's sums
-    void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (room ? p.fwd_off_p : (sliced ? p.fwd_spart : 0));
+    const bool room = ws && ws_bytes >= (h_save ? p.fwd_part : p.fwd_ws_bytes);       // for a split product's sums
+    void* hbuf = h_save ? h_save : static_cast<char*>(ws) + (room ? p.fwd_part : 0);
     float* const part = room && p.fwd_part > 0 ? static_cast<float*>(ws) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const PlanDev pd = device_view(p);
@@ -408,7 +406,7 @@ lobra_status lobra_mlora_plan_fwd(const lobra_mlora_plan* plan, const void* x, c
                              const void* A, const void* B, const float* s, void* y,
                              void* h_save, void* ws, size_t ws_bytes, void* hip_stream)
 {
-    return plan_fwd(plan, x, W, A, B, s, y, h_save, ws, ws_bytes, hip_stream, true);
+    return plan_fwd(plan, x, W, A, B, s, y, h_save, ws, ws_bytes, hip_stream);
 }
 
 lobra_status lobra_mlora_fwd_static_ws(const lobra_mlora_plan* plan, const void* x, const void* W,
@@ -417,12 +415,9 @@ lobra_status lobra_mlora_fwd_static_ws(const lobra_mlora_plan* plan, const void*
 {
     lobra_status rs = runnable(plan);
     if (rs != LOBRA_OK) return rs;
-    // a batch whose K-sliced projection needs more than the array for its partial sums goes without it: the
-    // one-block-per-workgroup projection needs the projected activations only
-    const bool sliced = plan->fwd_spart + plan->p_layout.total <= size_t(LOBRA_STATIC_WS_BYTES);
-    if (!sliced && plan->p_layout.total > size_t(LOBRA_STATIC_WS_BYTES)) return LOBRA_ERR_WORKSPACE;
+    if (plan->p_layout.total > size_t(LOBRA_STATIC_WS_BYTES)) return LOBRA_ERR_WORKSPACE;
     // the kernels get the array's device address, looked up when the plan was created on this device
-    return plan_fwd(plan, x, W, A, B, s, y, nullptr, plan->static_ws, size_t(LOBRA_STATIC_WS_BYTES), hip_stream, sliced);
+    return plan_fwd(plan, x, W, A, B, s, y, nullptr, plan->static_ws, size_t(LOBRA_STATIC_WS_BYTES), hip_stream);
 }
 
 lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, const void* W,
@@ -651,7 +646,7 @@ lobra_status lobra_mlora_fwd(const lobra_mlora_desc* desc, const void* x, const 
     const size_t img = align256(p->blob_bytes);
     char* rest = static_cast<char*>(ws) + img;
     if (p->desc.T == 0) st = LOBRA_OK;
-    else if (!ws || ws_bytes < img + p->fwd_spart + (h_save ? 0 : p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
+    else if (!ws || ws_bytes < img + (h_save ? 0 : p->p_layout.total)) st = LOBRA_ERR_WORKSPACE;
     else if (!aligned16(ws)) st = LOBRA_ERR_ALIGN;
     else if ((st = fwd_check(*p, x, W, A, B, s, y, h_save, rest, ws_bytes - img)) == LOBRA_OK &&
              (st = upload_oneshot(p, ws, stream)) == LOBRA_OK) {

@@ -176,12 +176,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             by_rank(p->sb_off.size() - 1, [&](int32_t i) { return p->tb[size_t(p->sb_off[size_t(i)])].task; }, p->sb_order);
         }
 
-        // 3d. the K-sliced projection (long batches, ranks up to 16) and whether dB rides with its pass over dy
-        p->sliced_in = p->sliced_out = SlicedShape{};
-        if (p->mfma && !p->tb.empty()) {
-            p->sliced_in = sliced_shrink_shape(int64_t(p->tb.size()), p->r_pad, d->d_in);
-            if (p->n_proj == 1) p->sliced_out = sliced_shrink_shape(int64_t(p->tb.size()), p->r_pad, d->d_out);
-        }
+        // 3d. the K-sliced projection of dy (long batches, ranks up to 16) and whether dB rides with its pass over dy
+        p->sliced_out = SlicedShape{};
+        if (p->mfma && !p->tb.empty() && p->n_proj == 1) p->sliced_out = sliced_shrink_shape(int64_t(p->tb.size()), p->r_pad, d->d_out);
         // dB fused into the sliced projection of dy: the runs of (task, slice) that every workgroup meets, by
         // the same split of the items as the kernel's (shrink_sliced_kernel)
         p->fused_db = false;
@@ -367,8 +364,7 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             L.p_blk = 0;
             L.total = align_up(size_t(T) * p->r_max * 4, 256);
         }
-        const size_t spart_in = align_up(size_t(p->sliced_in.nsl) * size_t(T) * 64, 256);
-        const size_t spart_out = align_up(size_t(p->sliced_out.nsl) * size_t(T) * 64, 256);
+        const size_t spart = align_up(size_t(p->sliced_out.nsl) * size_t(T) * 64, 256);
         p->h_save_bytes = L.total;
         if (p->mfma && T > 0) {
             // fused projections: one launch over all of them if its tiles fit their widths - at a width like 53 x 64 only
@@ -390,9 +386,7 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             p->fwd_part = align_up(gemm_part_bytes(T, d->d_in, p->n_proj > 1 && !p->fwd_group ? p->dg : d->d_out, p->fwd_group, ns, rk, p->beside_fwd), 256);
             p->bwd_part = align_up(gemm_part_bytes(T, d->d_out, d->d_in, 0, ns, p->r_max, p->beside_bwd), 256);
         }
-        p->fwd_spart = spart_in;
-        p->fwd_off_p = std::max(spart_in, p->fwd_part);
-        p->fwd_ws_bytes = p->fwd_off_p + L.total;
+        p->fwd_ws_bytes = p->fwd_part + L.total;
         p->bwd_off_g = 0;
         p->bwd_off_h = L.total;
         p->bwd_off_part_b = 2 * L.total;
@@ -400,7 +394,7 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         p->bwd_off_part_a = p->bwd_off_part_b +
                             align_up(size_t(p->fused_db ? p->fb_rows : p->part_rows) * size_t(d->d_out) * 4, 256);
         p->bwd_off_spart = p->bwd_off_part_a + align_up(size_t(p->part_rows) * size_t(d->d_in) * 4, 256);
-        p->bwd_need = p->bwd_off_spart + std::max(spart_in, spart_out);
+        p->bwd_need = p->bwd_off_spart + spart;
         p->bwd_ws_bytes = std::max(p->bwd_need, p->bwd_off_spart + p->bwd_part);
     } catch (const std::bad_alloc&) {
         return LOBRA_ERR_NOMEM;

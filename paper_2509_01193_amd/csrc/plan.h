@@ -154,19 +154,18 @@ struct Plan {
     BufferLayout p_layout;              // layout of h_save (and of the G buffer in bwd)
     size_t h_save_bytes = 0, fwd_ws_bytes = 0, bwd_ws_bytes = 0;
     size_t bwd_off_g = 0, bwd_off_h = 0, bwd_off_part_b = 0, bwd_off_part_a = 0;
-    // K-sliced projection: its shape for the projection from d_in (x, A) and from d_out (dy, B), and where its
-    // fp32 partial projections [nsl][T][16] go: at the start of the forward workspace (the projected
-    // activations follow at fwd_off_p unless the caller gives h_save), at bwd_off_spart in the backward one
-    SlicedShape sliced_in, sliced_out;
-    // The same scratch then takes the split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm): the
+    // K-sliced projection of dy: its shape, and where its fp32 partial projections [nsl][T][16] go: at bwd_off_spart in the workspace
+    SlicedShape sliced_out;
+    // A split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm) go to the start of the forward workspace, in front
+    // of the projected activations (which the caller may have elsewhere: h_save), and in the backward one to bwd_off_spart, where the
     // projection is done by that time.  They are welcome and not needed: fwd_ws_bytes and bwd_ws_bytes have room for them, but
-    // a call is refused only below what it cannot do without - fwd_spart, and without h_save the projected activations
-    // (then at fwd_spart), in a forward call, bwd_need in a backward one.
+    // a call is refused only below what it cannot do without - without h_save the projected activations in a forward call (then at
+    // the start), bwd_need in a backward one.
     // (fwd_group: fused projections' forward products run as one launch whose tiles do not straddle multiples of this
     // many columns; 0: one launch per projection)
     int32_t fwd_group = 0;
     GemmChoice beside_fwd, beside_bwd;  // the projection in the launch of its product, given scratch for it (tile -1: not)
-    size_t fwd_off_p = 0, bwd_off_spart = 0, fwd_spart = 0, fwd_part = 0, bwd_part = 0, bwd_need = 0;
+    size_t bwd_off_spart = 0, fwd_part = 0, bwd_part = 0, bwd_need = 0;
     // dB fused into the sliced projection of dy (one pass over dy for s_t B_t dy_i and for dB): a workgroup
     // keeps the dB sums of the (task, slice) it is working on and writes them out - 16 rank rows x 512
     // columns - whenever task or slice changes.  These tables say where: the runs of workgroup g are

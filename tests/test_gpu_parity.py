@@ -936,7 +936,7 @@ def test_fwd_bwd_under_hip_graph_capture(kernels):
     else:
         p = wl.make_config(4, "shuffled", d_in=1024, d_out=1024)
         q = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY).query(bd.Q_SLICED)
-        assert q[0] > 0 and q[1] > 0 and q[2] == 1, q      # the plan does take the sliced kernels here
+        assert q[1] > 0 and q[2] == 1, q                    # the plan does take the sliced kernel here
     dp = bd.DeviceProblem(p)
     dp.step()                                     # warm-up outside capture (first-call attribute set-up)
     torch.cuda.synchronize()
@@ -1287,9 +1287,9 @@ def test_sliced_projection_with_and_without_fused_db(name, fused):
     import torch
     p = _sliced_case(name, 0)
     plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
-    nsl_in, nsl_out, is_fused = plan.query(bd.Q_SLICED)[:3].tolist()
+    nsl_out, is_fused = plan.query(bd.Q_SLICED)[1:3].tolist()
     plan.close()
-    assert nsl_in == p.d_in // 512 and nsl_out == p.d_out // 512 and bool(is_fused) == fused
+    assert nsl_out == p.d_out // 512 and bool(is_fused) == fused
     dp, _ = check_problem(p, rows=sample_rows(p, 400), label="sliced")
     # the same results on the next call (nothing of a call survives in the partial sums), with accumulation, and
     # with the down-projected activations recomputed by bwd
@@ -1323,7 +1323,7 @@ def test_sliced_projection_with_and_without_fused_db(name, fused):
 
 @pytest.mark.parametrize("seed", range(6))
 def test_random_long_batches_at_ranks_up_to_16(seed):
-    """Random long batches that the plan hands to the sliced projection in one or both directions (widths from
+    """Random long batches, whose dy the plan hands to the sliced projection unless it is narrow (widths from
     512 to 4096, one to 33 tasks of ranks 1 to 16, segments from 1 token to 9000, spans without an adapter):
     sampled rows of y and dx, dA and dB in full, and bit-identical results over repeated steps."""
     import torch
@@ -1344,7 +1344,7 @@ def test_random_long_batches_at_ranks_up_to_16(seed):
     plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
     q = plan.query(bd.Q_SLICED).tolist()
     plan.close()
-    assert q[0] > 0 or q[1] > 0
+    assert q[1] > 0 or d_out == 512
     dp, _ = check_problem(p, rows=sample_rows(p, 300, seed=seed), label="T=%d slices=%s" % (p.T, q[:4]))
     first = {k: getattr(dp, k).clone() for k in ("y", "dx", "dA", "dB")}
     for _ in range(3):

@@ -257,6 +257,21 @@ def test_one_shot_workspace_without_room_for_a_split_products_sums(tasks):
     assert L.lobra_mlora_bwd(ctypes.byref(d), one, one, one, one, one, one, None, one, one, one, 0, odd, img + bwd - 1, None) == -7
 
 
+def test_long_forward_needs_its_projected_activations_only():
+    """A long batch of rank 16: no scratch beside the projected activations, none at all where the caller keeps those (a
+    misaligned workspace is refused as such, not for its size), and one byte less than them is too small."""
+    T, rank_off, seg_off, seg_task = 16384, [0, 16, 32], [0, 8000, 16384], [0, 1]
+    plan = bd.Plan("bf16", T, 4096, 4096, rank_off, seg_off, seg_task, bd.PLAN_HOST_ONLY)
+    assert plan.query(bd.Q_SLICED).tolist()[:3] == [0, 8, 1] and plan.fwd_ws_bytes == plan.h_save_bytes
+    d, keep = bd.make_desc("bf16", T, 4096, 4096, rank_off, seg_off, seg_task)
+    img = (bd.plan_device_bytes(d) + 255) // 256 * 256
+    L, one, odd = bd.lib(), ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004)       # never dereferenced
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, one, odd, img, None) == -8
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, None, odd, img + plan.h_save_bytes, None) == -8
+    assert L.lobra_mlora_fwd(ctypes.byref(d), one, one, one, one, one, one, None, odd, img + plan.h_save_bytes - 1, None) == -7
+    plan.close()
+
+
 def test_plan_init_argument_errors():
     """The errors of lobra_mlora_plan_init that precede its first HIP call."""
     p = wl.make_config(1, fill=False)
@@ -385,19 +400,20 @@ def check_sliced_tables(p):
     over every item of every workgroup by the rule the kernel itself follows (the items of an XCD's token blocks,
     slice-major, split evenly over its workgroups)."""
     plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
-    nsl_in, nsl_out, fused, rows, G = plan.query(bd.Q_SLICED).tolist()
+    zero, nsl_out, fused, rows, G = plan.query(bd.Q_SLICED).tolist()
     tb = plan.query(bd.Q_TOKEN_BLOCKS).reshape(-1, 4)
     ntb = len(tb)
     ranks = np.asarray(p.ranks)
     r_pad = (int(ranks.max()) + 15) // 16 * 16 if len(ranks) else 0
     n_proj = getattr(p, "n_proj", 1)
-    for nsl, D, ok in ((nsl_in, p.d_in, True), (nsl_out, p.d_out, n_proj == 1)):
-        want = D // 512 if (p.dtype == "bf16" and ok and r_pad == 16 and D % 512 == 0 and ntb * (D // 512) >= 3072) else 0
-        assert nsl == want, (p.name, nsl, want)
+    D = p.d_out
+    want = D // 512 if (p.dtype == "bf16" and n_proj == 1 and r_pad == 16 and D % 512 == 0 and ntb * (D // 512) >= 3072) else 0
+    assert zero == 0 and nsl_out == want, (p.name, nsl_out, want)
     assert G == 256
-    # the workspaces hold the fp32 partial projections [slices][T][16]
-    assert plan.fwd_ws_bytes >= plan.h_save_bytes + nsl_in * p.T * 64
-    assert plan.bwd_ws_bytes >= max(nsl_in, nsl_out) * p.T * 64
+    # the backward workspace holds the fp32 partial projections [slices][T][16], the forward one nothing of the kind
+    assert plan.bwd_ws_bytes >= nsl_out * p.T * 64
+    if p.T >= 16384:
+        assert plan.fwd_ws_bytes == plan.h_save_bytes
     wg_runs, run_row = plan.query(bd.Q_FUSED_WG_RUNS), plan.query(bd.Q_FUSED_RUN_ROW)
     cnt, task_row = plan.query(bd.Q_FUSED_COUNT), plan.query(bd.Q_FUSED_TASK_ROW)
     if not fused:
