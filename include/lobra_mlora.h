@@ -178,11 +178,11 @@ LOBRA_API lobra_status lobra_mlora_plan_sizes(const lobra_mlora_plan *plan, size
  *   LOBRA_Q_BLOCK_ORDER  order in which the token blocks are handed to the down-projection's
  *   LOBRA_Q_RUN_ORDER    workgroups, and the same for the runs: a permutation by descending rank
  *                        (stable), or empty when that is the stored order (e.g. equal ranks)
- *   LOBRA_Q_SLICED       {0, slices_out, fused_db, fused_rows, workgroups}: dy of long batches of ranks up
+ *   LOBRA_Q_SLICED       {0, slices_out, fused_db, fused_rows, workgroups}: fused_db = 1: dy of a long batch of ranks up
  *                        to 16 is projected by a fixed grid of `workgroups` workgroups that walk (token block,
- *                        512-column slice) items (slices_out = number of slices of d_out, 0 = a workgroup per token
- *                        block or run of them, as x always is); fused_db = 1: this projection
- *                        accumulates dB in the same pass, its sums in fused_rows rows
+ *                        512-column slice) items (slices_out = number of slices of d_out) and accumulate dB in the same
+ *                        pass, their sums in fused_rows rows; else slices_out = 0 and a projection has a workgroup per token
+ *                        block or run of them, as x always has
  *   LOBRA_Q_FUSED_WG_RUNS  [workgroups + 1]: the runs of items of one (task, slice) that workgroup g meets are
  *                        number wg_runs[g] .. wg_runs[g + 1] - 1 (all four lists are empty unless fused_db)
  *   LOBRA_Q_FUSED_RUN_ROW  per run: first of its 16 rows in the array of dB sums

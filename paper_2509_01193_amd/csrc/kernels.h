@@ -93,11 +93,9 @@ bool gemm_mfma_shape_ok(int64_t T, int32_t K, int32_t N, int32_t ldw);
 // P = s_t Z M_t^T in bf16, written token-major [T][r_pad] and block-transposed [ntb][r_pad][32].
 // (ldz: row pitch of Z; nproj > 1: projection `proj` of a fused call - rank window, see the kernel; proj < 0: all of
 //  them in one launch, Z with nproj * D columns)
-// sliced.nsl > 0 (chosen by the plan, see sliced_shrink_shape) and part != nullptr: the K-sliced kernel with its
-// fp32 partial projections in part [nsl][T][16], followed by the finish kernel.  Hblk, partb (and a plan with
-// fused_db): the same pass also accumulates sum_i Hblk_i^T Z_i (dB when Z = dy and Hblk = the block-transposed
-// s_t h) into partb [fb_rows][D], to be added up by reduce_partials (GradJob::fcnt).
-
+// sliced.nsl > 0 (a plan with fused_db): the K-sliced kernel with its fp32 partial projections in part [nsl][T][16], followed by the
+// finish kernel; the same pass accumulates sum_i Hblk_i^T Z_i (dB: Z = dy and Hblk = the block-transposed s_t h) into
+// partb [fb_rows][D], to be added up by reduce_partials (GradJob::fcnt).
 hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const float* s,
                        void* P_tok, void* P_blk, int32_t D, int32_t ldz, int32_t nproj, int32_t proj,
                        hipStream_t st, const SlicedShape& sliced = SlicedShape{}, float* part = nullptr,

@@ -227,7 +227,8 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 p->fb_run_row.resize(run_task.size());
                 for (size_t i = 0; i < run_task.size(); ++i)
                     p->fb_run_row[i] = p->fb_task_row0[run_task[i]] + 16 * run_k[i];
-            } else {
+            } else {                         // (shrink_sliced_kernel says why the projection goes without slices then)
+                p->sliced_out = SlicedShape{};
                 p->fb_wg_run_off.clear();
                 p->fb_cnt.clear();
                 p->fb_task_row0.clear();
@@ -484,7 +485,7 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D)
     const int64_t nsl = D / 512;
     const int64_t items = ntb * nsl;
     if (items < 3072 || items >= 0x7fffffff) return none;
-    return SlicedShape{1, int32_t(nsl)};
+    return SlicedShape{int32_t(nsl)};
 }
 
 std::vector<int32_t> pack_blob(Plan* p)

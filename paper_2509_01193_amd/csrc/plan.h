@@ -22,10 +22,10 @@ constexpr int64_t kPlainMaxTokens = 65535 * 64;
 struct TokenBlock { int32_t row0, nrows, task, rank_row0; };
 struct GradChunk  { int32_t tb_begin, tb_end, task, part_row0; };
 
-// The rank-r projection of a long batch of ranks up to 16 cuts K into slices of 512 columns and lets one
-// workgroup per compute unit walk (token block, slice) items (shrink_sliced_kernel).  nsl = slices; nsl = 0: the
-// one-block-per-workgroup kernels are used.  (m = slabs of 128 columns per wave and item: always 1.)
-struct SlicedShape { int32_t m = 0, nsl = 0; };
+// The pass over dy that projects it and accumulates dB, for long batches of ranks up to 16, cuts K into slices of 512 columns and lets one
+// workgroup per compute unit walk (token block, slice) items (shrink_sliced_kernel).  nsl = slices; nsl = 0: dB is left to the
+// reduction kernels.
+struct SlicedShape { int32_t nsl = 0; };
 constexpr int kSlicedGrid = 256;      // its workgroups: 8 XCDs x 32 compute units
 // The shape for ntb token blocks projected from width D, or none: widths that are not a multiple of the slice,
 // other ranks, too few items to keep every compute unit busy.
@@ -154,7 +154,7 @@ struct Plan {
     BufferLayout p_layout;              // layout of h_save (and of the G buffer in bwd)
     size_t h_save_bytes = 0, fwd_ws_bytes = 0, bwd_ws_bytes = 0;
     size_t bwd_off_g = 0, bwd_off_h = 0, bwd_off_part_b = 0, bwd_off_part_a = 0;
-    // K-sliced projection of dy: its shape, and where its fp32 partial projections [nsl][T][16] go: at bwd_off_spart in the workspace
+    // K-sliced projection of dy (fused_db): its shape, and where its fp32 partial projections [nsl][T][16] go: at bwd_off_spart in the workspace
     SlicedShape sliced_out;
     // A split base product's partial sums (fwd_part / bwd_part bytes, see choose_gemm) go to the start of the forward workspace, in front
     // of the projected activations (which the caller may have elsewhere: h_save), and in the backward one to bwd_off_spart, where the

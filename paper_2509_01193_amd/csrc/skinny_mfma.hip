@@ -47,7 +47,10 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v)
 // as long as task and slice stay the same (a dozen token blocks), the loads of the next three items are in flight while an item is
 // multiplied, reduced and stored, and the items are dealt to the workgroups to within one item.  (The projection alone is faster
 // through the ring of shrink_ring.hip, 26.9 against 31.2 us with the finish at 16384 x 4096, which dB's saved pass over dy outweighs: 37.5 us
-// against 31.8 and 17 more for dB.  WITH_DB = false is left for batches whose tasks are so small that dB's sums would be too many.)
+// against 31.8 and 17 more for dB.  Batches whose tasks are so small that dB's sums would be too many take the ring: projection and
+// backward pass of d_in = 1024, us, this kernel without dB / the ring: 3000 one-token segments x 4096 columns 57.8 / 43.6 and 208 / 188,
+// 16384 tokens of 200 tasks x 4096 57.4 / 36.5 and 273 / 266, 40000 of 800 x 8192 193 / 172 and 1079 / 1057, 4000 of 60 x 28672
+// 74 / 63 and 398 / 404.)
 // The eight waves of a workgroup share an item: wave (h, w) takes token half h (16 tokens) and the 128 columns
 // number w of the slice; the four waves of a half add their sums through LDS (fixed order) and wave (h, 0)
 // writes the fp32 partial projection part[slice][token][16]; the finish kernel below adds the slices in
@@ -60,7 +63,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v)
 // s_barrier (no fence), and the tables are restrict-qualified arguments of their own rather than members of
 // the plan structure: only then are they read with scalar loads, which vmcnt does not count.
 //
-// WITH_DB (the backward pass over dy): the same pass also accumulates dB_t = sum_i (s_t h_i)^T dy_i (section 2.1:
+// The pass also accumulates dB_t = sum_i (s_t h_i)^T dy_i (section 2.1:
 // the gradient of the up factor), so that dy is read once for both.  The block-transposed s_t h of an item
 // (P_blk: 16 ranks x 32 tokens, 1 KiB) comes in with one more copy of wave 0 and is read by all waves behind
 // the item's barrier (one such copy per wave measured 4 us slower at workload 2); the dy
@@ -72,12 +75,11 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v)
 // -------------------------------------------------------------------------------------------------
 constexpr int kSlicedRing = 4;                                     // ring slots per wave
 constexpr int kSlicedRedOff = 8 * kSlicedRing * 4096;              // the two reduction buffers (also the dB exchange)
-constexpr int kSlicedHOff = kSlicedRedOff + 2 * 8 * 64 * 16;       // WITH_DB: ring of the items' s_t h blocks, 1 KiB per slot
-constexpr int kSlicedLds = kSlicedHOff, kSlicedLdsDb = kSlicedHOff + (kSlicedRing + 1) * 1024;
+constexpr int kSlicedHOff = kSlicedRedOff + 2 * 8 * 64 * 16;       // ring of the items' s_t h blocks, 1 KiB per slot
+constexpr int kSlicedLds = kSlicedHOff + (kSlicedRing + 1) * 1024;
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-template <bool WITH_DB>
 __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __restrict__ tbs,
                                                            const int32_t* __restrict__ rank_off, int32_t ntb,
                                                            int32_t T, const uint16_t* __restrict__ Z,
@@ -98,7 +100,7 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
     unsigned char* ring = lds + wave * (R * 4096);                 // this wave's ring
     const uint32_t ring_addr = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)ring));
     float* red = reinterpret_cast<float*>(lds + kSlicedRedOff);    // [item parity][wave][lane][4]
-    unsigned char* hring = lds + kSlicedHOff;                      // WITH_DB: [slot][16 ranks][32 tokens] bf16
+    unsigned char* hring = lds + kSlicedHOff;                      // [slot][16 ranks][32 tokens] bf16
     const uint32_t hring_addr = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)hring));
 
     // consecutive workgroup ids run on different XCDs: XCD x takes the token blocks [bx0, bx1) - a
@@ -131,68 +133,62 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
         const uint32_t voff = (uint32_t(min(16 * h + j, b.nrows - 1)) * uint32_t(ldz) + 8u * kg) * 2u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) gemm::dma16(ring_addr + c.slot * 4096 + q * 1024, base + q * 64, voff);
-        if constexpr (WITH_DB) {
-            // the item's block of s_t h (1 KiB, as stored) for the whole workgroup: one more copy of wave 0,
-            // which the other waves read behind the item's barrier
-            if (wave == 0)
-                gemm::dma16(hring_addr + c.hslot * 1024,
-                            reinterpret_cast<const unsigned char*>(Hblk) + size_t(bx0 + c.bo) * (16 * kTokenBlock * 2),
-                            uint32_t(lane) * 16u);
-        }
+        // the item's block of s_t h (1 KiB, as stored) for the whole workgroup: one more copy of wave 0,
+        // which the other waves read behind the item's barrier
+        if (wave == 0)
+            gemm::dma16(hring_addr + c.hslot * 1024,
+                        reinterpret_cast<const unsigned char*>(Hblk) + size_t(bx0 + c.bo) * (16 * kTokenBlock * 2),
+                        uint32_t(lane) * 16u);
     };
     // vector memory operations complete in order: with the copies of y younger items behind it, an item has
     // landed when at most y times the copies per item are outstanding (wave (h, 0)'s stores also count: they
     // only make the wait stricter)
     auto wait_item = [&](auto younger) {
         constexpr int y = decltype(younger)::value;
-        if (WITH_DB && wave == 0) gemm::wait_vmcnt<5 * y>();
+        if (wave == 0) gemm::wait_vmcnt<5 * y>();
         else gemm::wait_vmcnt<4 * y>();
     };
 
-    // WITH_DB: this wave's dB sums, 8 column tiles of 16: lane (n, kg) holds ranks 4 kg .. 4 kg + 3 of column n
-    f32x4 dbacc[WITH_DB ? 8 : 1];
+    // this wave's dB sums, 8 column tiles of 16: lane (n, kg) holds ranks 4 kg .. 4 kg + 3 of column n
+    f32x4 dbacc[8];
     int32_t run_idx = -1;                        // runs of (task, slice) this workgroup has met so far, minus 1
-    if constexpr (WITH_DB) {
 #pragma unroll
-        for (int tl = 0; tl < 8; ++tl) dbacc[tl] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int tl = 0; tl < 8; ++tl) dbacc[tl] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the run's sums go out: the halves are added through LDS (h = 0 plus h = 1, four column tiles at a time:
     // the exchange memory is the two reduction buffers), wave (0, w) stores its 128 columns
     auto flush_db = [&](int32_t sl) {
-        if constexpr (WITH_DB) {
-            const int32_t row0 = run_row[wg_run_off[blockIdx.x] + run_idx];
-            float* ex = red + (w * 4 * 64) * 4;      // [tile of the round][lane][4]
-            float* dst = partb + size_t(row0 + 4 * kg) * D + sl * 512 + w * 128 + j;
+        const int32_t row0 = run_row[wg_run_off[blockIdx.x] + run_idx];
+        float* ex = red + (w * 4 * 64) * 4;      // [tile of the round][lane][4]
+        float* dst = partb + size_t(row0 + 4 * kg) * D + sl * 512 + w * 128 + j;
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                // (first round: wave (h, 0) has read the last item's sums out of this memory; second: the
-                //  first round's reads are done)
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                if (h == 1) {
+        for (int half = 0; half < 2; ++half) {
+            // (first round: wave (h, 0) has read the last item's sums out of this memory; second: the
+            //  first round's reads are done)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (h == 1) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) *reinterpret_cast<f32x4*>(ex + (u * 64 + lane) * 4) = dbacc[4 * half + u];
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                if (h == 0) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int tl = 4 * half + u;
-                        const f32x4 o = dbacc[tl] + *reinterpret_cast<const f32x4*>(ex + (u * 64 + lane) * 4);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) dst[size_t(v) * D + tl * 16] = o[v];
-                    }
-                }
+                for (int u = 0; u < 4; ++u) *reinterpret_cast<f32x4*>(ex + (u * 64 + lane) * 4) = dbacc[4 * half + u];
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();        // the memory is free for the next item's sums
+            __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
+            if (h == 0) {
 #pragma unroll
-            for (int tl = 0; tl < 8; ++tl) dbacc[tl] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int u = 0; u < 4; ++u) {
+                    const int tl = 4 * half + u;
+                    const f32x4 o = dbacc[tl] + *reinterpret_cast<const f32x4*>(ex + (u * 64 + lane) * 4);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) dst[size_t(v) * D + tl * 16] = o[v];
+                }
+            }
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();        // the memory is free for the next item's sums
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int tl = 0; tl < 8; ++tl) dbacc[tl] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
 
     u32x4 av[4];                                 // the adapter columns of this wave's part of the slice
@@ -200,7 +196,7 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
     auto consume = [&](const Cursor& c, int32_t it) {
         const TokenBlock b = tbs[bx0 + c.bo];
         if (b.task != cur_task || c.sl != cur_sl) {          // uniform; once per dozen items
-            if (WITH_DB && run_idx >= 0) flush_db(cur_sl);
+            if (run_idx >= 0) flush_db(cur_sl);
             ++run_idx;
             const int32_t r = rank_off[b.task + 1] - b.rank_row0;
             // rank rows beyond r_t repeat a valid row; the finish kernel drops what they produce
@@ -220,20 +216,18 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
             const u32x4 zv = *reinterpret_cast<const u32x4*>(ring + c.slot * 4096 + q * 1024 + lane * 16);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(av[q]), as_bf16x8(zv), acc, 0, 0, 0);
         }
-        // WITH_DB: the dy operands of the dB product are gathered here, in front of the barrier, whose wait then
+        // The dy operands of the dB product are gathered here, in front of the barrier, whose wait then
         // covers their latency.  "B" operand of column tile tl: lane (n, kg) needs tokens 4 kg .. 4 kg + 3 of column
         // 16 tl + n.  A transposing read of a 16-lane group takes 8 bytes (4 columns) from each lane's address and
         // hands lane 4 g + e element e of what the lanes 4 kr + g, kr = 0 .. 3, supplied: so lane j supplies token
         // 4 kg + (j >> 2), columns 16 tl + 4 (j & 3) .. + 3.  In the ring, column c of token t lies in copy c / 32
         // at lane t + 16 ((c / 8) & 3), 2 (c & 7) bytes in.
-        s16x4 bv[WITH_DB ? 8 : 1];
-        if constexpr (WITH_DB) {
-            const unsigned char* zb = ring + c.slot * 4096 + ((4 * kg + (j >> 2)) + 16 * ((j & 3) >> 1)) * 16 + (j & 1) * 8;
+        s16x4 bv[8];
+        const unsigned char* zb = ring + c.slot * 4096 + ((4 * kg + (j >> 2)) + 16 * ((j & 3) >> 1)) * 16 + (j & 1) * 8;
 #pragma unroll
-            for (int tl = 0; tl < 8; ++tl)
-                bv[tl] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (s16x4 __attribute__((address_space(3)))*)(zb + (tl >> 1) * 1024 + (tl & 1) * 512));
-        }
+        for (int tl = 0; tl < 8; ++tl)
+            bv[tl] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (s16x4 __attribute__((address_space(3)))*)(zb + (tl >> 1) * 1024 + (tl & 1) * 512));
         float* rbuf = red + (it & 1) * (8 * 64 * 4);
         *reinterpret_cast<f32x4*>(rbuf + (wave * 64 + lane) * 4) = acc;
         // one barrier per item: the next write to this half of red follows the next item's barrier,
@@ -250,15 +244,13 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
             if (tok < b.nrows)     // lane (j, kg): ranks 4 kg .. 4 kg + 3 of token j
                 *reinterpret_cast<f32x4*>(part + (size_t(c.sl) * T + b.row0 + tok) * 16 + 4 * kg) = ((s0 + s1) + s2) + s3;
         }
-        if constexpr (WITH_DB) {
-            // (behind the barrier: wave 0 has seen the block of s_t h land before it came here)
-            // "A" operand: s_t h transposed, lane (i, kg): rank i, tokens 16 h + 4 kg .. + 3 of the block
-            union { uint64_t u; s16x4 v; } hv;
-            hv.u = *reinterpret_cast<const uint64_t*>(hring + c.hslot * 1024 + (j * kTokenBlock + 16 * h + 4 * kg) * 2);
+        // (behind the barrier: wave 0 has seen the block of s_t h land before it came here)
+        // "A" operand: s_t h transposed, lane (i, kg): rank i, tokens 16 h + 4 kg .. + 3 of the block
+        union { uint64_t u; s16x4 v; } hv;
+        hv.u = *reinterpret_cast<const uint64_t*>(hring + c.hslot * 1024 + (j * kTokenBlock + 16 * h + 4 * kg) * 2);
 #pragma unroll
-            for (int tl = 0; tl < 8; ++tl)
-                dbacc[tl] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hv.v, bv[tl], dbacc[tl], 0, 0, 0);
-        }
+        for (int tl = 0; tl < 8; ++tl)
+            dbacc[tl] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hv.v, bv[tl], dbacc[tl], 0, 0, 0);
     };
 
     Cursor pc, cc;                               // next item to fetch, next item to consume
@@ -295,7 +287,7 @@ __global__ __launch_bounds__(512) void shrink_sliced_kernel(const TokenBlock* __
             advance(cc);
         }
     }
-    if (WITH_DB) flush_db(cur_sl);
+    flush_db(cur_sl);
 }
 
 // Second pass of the sliced projection: P = s_t * (sum of the slices' partial projections, in slice order),
@@ -350,11 +342,8 @@ hipError_t sliced_setup()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev].load(std::memory_order_acquire) == 0) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_sliced_kernel<false>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_sliced_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSlicedLds);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_sliced_kernel<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSlicedLdsDb);
         if (e != hipSuccess) return e;
         done[dev].store(1, std::memory_order_release);
     }
@@ -367,21 +356,16 @@ hipError_t shrink_mfma(const PlanDev& pd, const void* Z, const void* M, const fl
                        hipStream_t st, const SlicedShape& sliced, float* part, const void* Hblk, float* partb)
 {
     if (pd.ntb == 0) return hipSuccess;
-    if (sliced.nsl == 0 || !part || nproj != 1) return shrink_ring(pd, Z, M, s, P_tok, P_blk, D, ldz, nproj, proj, st);
+    if (sliced.nsl == 0) return shrink_ring(pd, Z, M, s, P_tok, P_blk, D, ldz, nproj, proj, st);
+    if (!part || !Hblk || !partb || !pd.fb_run_row || nproj != 1) return hipErrorInvalidValue;
     // (a grid dimension of 2^32 threads and more wraps without an error)
     if ((int64_t(pd.ntb) + 1) / 2 * 256 >= (int64_t(1) << 32)) return hipErrorInvalidValue;
     hipError_t e = sliced_setup();
     if (e != hipSuccess) return e;
     // a fixed grid - one workgroup per compute unit of the chip this is written for - so that the split
     // of the items, and with it the order of every sum, does not depend on the device
-    if (Hblk && partb && pd.fb_run_row)
-        shrink_sliced_kernel<true><<<kSlicedGrid, 512, kSlicedLdsDb, st>>>(
-            pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
-            (const uint16_t*)Hblk, partb, pd.fb_wg_run_off, pd.fb_run_row);
-    else
-        shrink_sliced_kernel<false><<<kSlicedGrid, 512, kSlicedLds, st>>>(
-            pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D, ldz, sliced.nsl,
-            nullptr, nullptr, nullptr, nullptr);
+    shrink_sliced_kernel<<<kSlicedGrid, 512, kSlicedLds, st>>>(pd.tb, pd.rank_off, pd.ntb, pd.T, (const uint16_t*)Z, (const uint16_t*)M, part, D,
+                                                               ldz, sliced.nsl, (const uint16_t*)Hblk, partb, pd.fb_wg_run_off, pd.fb_run_row);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     shrink_finish_kernel<<<(pd.ntb + 1) / 2, 256, 0, st>>>(pd, part, s, (uint16_t*)P_tok, (uint16_t*)P_blk, sliced.nsl);

@@ -1270,7 +1270,7 @@ def _sliced_case(name, seed):
     elif name == "one-task-one-segment":
         n_tasks, ranks, d_in, d_out = 1, [16], 2048, 1024
         lens, seg_task = np.asarray([50001]), np.asarray([0])
-    else:   # "tiny-tasks": more rows of dB sums than the fused pass is worth: sliced projection, dB by the reduction kernels
+    else:   # "tiny-tasks": more rows of dB sums than the fused pass is worth: the ring projects, dB by the reduction kernels
         n_tasks, d_in, d_out = 750, 1024, 1024
         ranks = np.full(n_tasks, 16)
         lens = np.full(3000, 33)
@@ -1289,7 +1289,7 @@ def test_sliced_projection_with_and_without_fused_db(name, fused):
     plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
     nsl_out, is_fused = plan.query(bd.Q_SLICED)[1:3].tolist()
     plan.close()
-    assert nsl_out == p.d_out // 512 and bool(is_fused) == fused
+    assert nsl_out == (p.d_out // 512 if fused else 0) and bool(is_fused) == fused
     dp, _ = check_problem(p, rows=sample_rows(p, 400), label="sliced")
     # the same results on the next call (nothing of a call survives in the partial sums), with accumulation, and
     # with the down-projected activations recomputed by bwd

@@ -168,24 +168,22 @@ def sliced_kernels(tmp_path_factory):
         code = [l.split(";")[0].strip() for l in body[:end].split("\n")]
         code = [l for l in code if l and not l.startswith(".")]
         ks.append((parts[i], code, body[end:end + 3000]))
-    assert len(ks) == 2, [k[0] for k in ks]      # projection alone, projection with dB
+    assert len(ks) == 1, [k[0] for k in ks]      # projection with dB
     return ks
 
 
 def test_sliced_kernel_waits_for_its_copies_by_count(sliced_kernels):
     for name, code, tail in sliced_kernels:
-        fused = "ILb1E" in name
         assert re.search(r"; ScratchSize: 0\b", tail), name
         copies = [i for i, l in enumerate(code) if l.startswith("global_load_lds_dwordx4")]
         assert len(copies) >= 16, (name, len(copies))
         for c in copies:            # M0 is written inside the copy's own asm statement
             assert any(re.match(r"s_mov_b32 m0,", code[k]) for k in range(max(0, c - 2), c)), (name, code[c - 3:c + 1])
-        # the steady-state wait leaves the copies of three younger items in flight (wave 0 of the fused form
-        # has a fifth copy per item), the drain at the end counts down
+        # the steady-state wait leaves the copies of three younger items in flight (wave 0 has a fifth copy per item), the
+        # drain at the end counts down
         waits = {int(m.group(1)) for l in code for m in [re.match(r"s_waitcnt vmcnt\((\d+)\)$", l)] if m}
         assert {12, 8, 4} <= waits, (name, sorted(waits))
-        if fused:
-            assert {15, 10, 5} <= waits, (name, sorted(waits))
+        assert {15, 10, 5} <= waits, (name, sorted(waits))
         # ordinary vector loads: only the adapter rows (16 bytes per lane), never the tables
         plain = [l for l in code if re.match(r"global_load_(dword|dwordx2|dwordx3|ubyte|ushort|sbyte|sshort)\b", l)]
         assert not plain, (name, plain[:4])
