@@ -332,13 +332,14 @@ LOBRA_API lobra_status lobra_padded_segments(int64_t n_seq, const int32_t *padde
 /* Profiling aid (bench, tests).  While a trace is attached, every kernel that fwd / bwd /
  * token_task_map launch through this plan is bracketed by hipEventRecord on the call's stream:
  * the i-th launch since the trace was attached records events[2i] before and events[2i+1]
- * after it and stores which kernel it was in kernel_ids[i] (LOBRA_K_*); launches beyond
+ * after it and stores which kernel it was in kernel_ids[i] (LOBRA_K_*; a projection and its product that run in one
+ * launch are one, LOBRA_K_SHRINK_GEMM; the kernel that adds up a split product's sums belongs to the product); launches beyond
  * n_pairs are not bracketed.  events are hipEvent_t created by the caller with timing
  * enabled; events and kernel_ids are HOST arrays that must outlive the trace.  *n_launched
  * (host, may be NULL) counts the launches seen.  n_pairs = 0 or events = NULL detaches.
  * A plan with a trace attached must not be used from two threads at once. */
 enum { LOBRA_K_SHRINK = 1, LOBRA_K_GEMM = 2, LOBRA_K_GRAD_STAGE1 = 3, LOBRA_K_GRAD_STAGE2 = 4,
-       LOBRA_K_TOKEN_TASK = 5, LOBRA_K_ADAM = 6 };
+       LOBRA_K_TOKEN_TASK = 5, LOBRA_K_ADAM = 6, LOBRA_K_SHRINK_GEMM = 7 };
 LOBRA_API lobra_status lobra_mlora_plan_set_trace(lobra_mlora_plan *plan, void *const *events,
                                         int32_t n_pairs, int32_t *kernel_ids,
                                         int32_t *n_launched);

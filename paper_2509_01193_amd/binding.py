@@ -443,7 +443,7 @@ class DeviceProblem:
 # ---------------------------------------------------------------------------------------------
 # launch trace: per-kernel durations from HIP events recorded on the stream the kernels run on
 # ---------------------------------------------------------------------------------------------
-KERNEL_NAMES = {1: "shrink", 2: "gemm", 3: "grad_stage1", 4: "grad_stage2", 5: "token_task", 6: "adam"}
+KERNEL_NAMES = {1: "shrink", 2: "gemm", 3: "grad_stage1", 4: "grad_stage2", 5: "token_task", 6: "adam", 7: "shrink_gemm"}
 
 
 class LaunchTrace:

@@ -367,8 +367,7 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     // bf16 MFMA path
     char* hb = static_cast<char*>(hbuf);
     if (adapters && part && p.beside_fwd.tile >= 0) {     // few token blocks: one launch for both
-        LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK, hipSuccess);
-        LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
+        LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK_GEMM,
                      gemm_mfma_beside(pd, p.beside_fwd, false, x, W, A, s, hb + p.p_layout.p_tok, hb + p.p_layout.p_blk, B, y, pd.d_in,
                                       pd.d_out, pd.d_out, st, part, p.fwd_part));
         return LOBRA_OK;
@@ -497,14 +496,14 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
             H = Hr;
         }
         // G = s dy B^T; with fused projections every projection's column block of dy against its rows of the
-        // compact B, written into its rank window of G
-        LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
-                     beside ? hipSuccess :
-                     shrink_mfma(pd, dy, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, pd.dg, pd.d_out, p.n_proj,
-                                 p.n_proj > 1 ? -1 : 0, st, p.sliced_out, spart, fused_db ? H + p.p_layout.p_blk : nullptr, part_b));
+        // compact B, written into its rank window of G (few token blocks: in the product's launch)
+        if (!beside)
+            LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
+                         shrink_mfma(pd, dy, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, pd.dg, pd.d_out, p.n_proj,
+                                     p.n_proj > 1 ? -1 : 0, st, p.sliced_out, spart, fused_db ? H + p.p_layout.p_blk : nullptr, part_b));
     }
     if (want_dx && p.desc.T > 0)
-        LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
+        LOBRA_LAUNCH(p, st, beside ? LOBRA_K_SHRINK_GEMM : LOBRA_K_GEMM,
                      beside ? gemm_mfma_beside(pd, p.beside_bwd, true, dy, W, B, s, G + p.p_layout.p_tok, G + p.p_layout.p_blk, A, dx,
                                                pd.d_out, pd.d_in, pd.d_out, st, split_part, p.bwd_part)
                             : gemm_mfma(pd, true, dy, W, adapters ? G + p.p_layout.p_tok : nullptr, A, dx, pd.d_out,

@@ -262,6 +262,26 @@ def test_projection_beside_the_split_product(T, d_in, d_out, ranks, longest, bes
     assert dp.guards_intact()
 
 
+@pytest.mark.parametrize("T,launches", [
+    (40, ["shrink_gemm", "shrink_gemm", "grad_stage1", "grad_stage2"]),              # 40 one-token blocks: projection and product in one launch
+    (300, ["shrink", "gemm", "shrink", "gemm", "grad_stage1", "grad_stage2"]),       # too many of them
+])
+def test_trace_has_an_entry_for_what_is_launched(T, launches):
+    """One event pair per launch, none around nothing: a step whose projections run in their products' launches, and one where
+    they do not."""
+    import torch
+    p = wl.make_custom("trace-%d" % T, "bf16", 2048, 2048, [16, 16], np.arange(T + 1), np.arange(T) % 2, 31)
+    dp = bd.DeviceProblem(p)
+    dp.step()
+    tr = bd.LaunchTrace(dp.plan, 8)
+    tr.attach()
+    dp.step()
+    torch.cuda.synchronize()
+    got = tr.durations()
+    tr.close()
+    assert [name for name, _ in got] == launches and all(ms > 0 for _, ms in got)
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [(1, 3072, 64, 1), (40, 4104, 136, 1), (70, 5128, 1032, 1), (33, 4096, 4096, 1),
                                                  (64, 5000, 192, 2)])
 def test_split_k_product_in_every_entry_point(T, d_in, d_out, n_proj):
