@@ -625,12 +625,12 @@ __global__ __launch_bounds__(256) void gemm_add_kernel(const float* __restrict__
     *reinterpret_cast<bf16x8*>(C + size_t(i / N) * ldc + size_t(i % N)) = o;
 }
 
-// f(S) with S = n as a constant, 1 .. kMaxSplits + 1
-template <int S = 1, typename F> static void with_splits(int32_t n, F&& f)
+// f(S) with S = n as a constant, S .. LAST
+template <int S, int LAST, typename F> static void with_splits(int32_t n, F&& f)
 {
-    if constexpr (S <= kMaxSplits + 1) {
+    if constexpr (S <= LAST) {
         if (n == S) f(std::integral_constant<int, S>{});
-        else with_splits<S + 1>(n, f);
+        else with_splits<S + 1, LAST>(n, f);
     }
 }
 
@@ -661,7 +661,7 @@ static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, c
     e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     const int64_t n = int64_t(pd.T) * N;             // (N is a multiple of 8)
-    with_splits(per, [&](auto s_c) {
+    with_splits<2, kMaxSplits + 1>(per, [&](auto s_c) {
         gemm_add_kernel<decltype(s_c)::value><<<dim3(uint32_t((n + 2047) / 2048)), 256, 0, st>>>(part, (uint16_t*)C, n, N, ldc);
     });
     return hipGetLastError();
@@ -691,7 +691,7 @@ static hipError_t launch_beside(const PlanDev& pd, const void* Z, const void* W,
         (uint16_t*)P_tok, (uint16_t*)P_blk, rparts, pwgs);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    with_splits(splits, [&](auto s_c) {
+    with_splits<1, kMaxSplits>(splits, [&](auto s_c) {
         gemm_add_up_kernel<decltype(s_c)::value><<<dim3(uint32_t((pd.T + 3) / 4), uint32_t((N + 255) / 256)), 256, 0, st>>>(
             pd, part, (const uint16_t*)P_tok, (const uint16_t*)M, (uint16_t*)C, N);
     });

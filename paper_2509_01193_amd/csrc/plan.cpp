@@ -250,6 +250,18 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         // (the MFMA kernel gives each of its four waves a token block of the chunk at a time; the plain
         //  kernel walks a chunk's tokens one after the other, so small batches want short chunks there)
         cb = std::max<int64_t>(p->mfma ? 4 : 1, std::min<int64_t>(64, cb));
+        // fp32, short tasks: no partial sums and no second stage (grad_f32_one), while a task's blocks times the rank blocks are few: a
+        // launch lasts as long as its longest chain of them.  Training steps, two stages / one, us, with n blocks in the largest task:
+        //   rank 16   256 x 256, n = 13 29.4 / 26.7, 30 35.7 / 32.7, 39 64.7 / 62.3, 53 41.8 / 42.8; 1024 x 1024, n = 13 69.2 / 64.7, 31 107.5 /
+        //             105.2, 57 161.6 / 162.2; 1999 x 500, n = 30 129.7 / 121.5
+        //   rank 32   256 x 256, n = 10 34.9 / 32.3, 30 40.0 / 42.3;  rank 64  n = 4 39.9 / 36.7, 22 50.7 / 56.7;  rank 128  n = 13 64.1 / 69.6
+        // (tasks and column tiles within what the grid takes)
+        p->grad_one = false;
+        if (d->dtype == LOBRA_F32 && p->n_proj == 1 && n <= 65536 && (int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64 <= 65535) {
+            int64_t most = 0;
+            for (int32_t t = 0; t < n; ++t) most = std::max<int64_t>(most, p->task_tb_off[t + 1] - p->task_tb_off[t]);
+            p->grad_one = most > 0 && most * ((p->r_max + 15) / 16) <= 32;
+        }
         // Small batches: one chunk per task where that is the faster way to the gradients: the sums are then final and there
         // is no second stage (6 us and the partial sums' way to memory and back), but a launch lasts as long as its longest chain
         // of blocks.  Both stages, several chunks per task against one, with n blocks in the largest task (us):
@@ -265,18 +277,6 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         //     49.5 and 61.5 / 53.1); where dB takes a launch per projection, up to n = 6 (P = 3, 2048 x 3192, 8 tasks of stacked rank
         //     24 and 96: n = 6 35.0 / 33.2 and 48.4 / 46.4, n = 8 37.2 / 36.4 and 51.6 / 53.0)
         // In every case only with a workgroup for most compute units.
-        // fp32, short tasks: no partial sums and no second stage (grad_f32_one), while a task's blocks times the rank blocks are few: a
-        // launch lasts as long as its longest chain of them.  Training steps, two stages / one, us, with n blocks in the largest task:
-        //   rank 16   256 x 256, n = 13 29.4 / 26.7, 30 35.7 / 32.7, 39 64.7 / 62.3, 53 41.8 / 42.8; 1024 x 1024, n = 13 69.2 / 64.7, 31 107.5 /
-        //             105.2, 57 161.6 / 162.2; 1999 x 500, n = 30 129.7 / 121.5
-        //   rank 32   256 x 256, n = 10 34.9 / 32.3, 30 40.0 / 42.3;  rank 64  n = 4 39.9 / 36.7, 22 50.7 / 56.7;  rank 128  n = 13 64.1 / 69.6
-        // (tasks and column tiles within what the grid takes)
-        p->grad_one = false;
-        if (d->dtype == LOBRA_F32 && p->n_proj == 1 && n <= 65536 && (int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64 <= 65535) {
-            int64_t most = 0;
-            for (int32_t t = 0; t < n; ++t) most = std::max<int64_t>(most, p->task_tb_off[t + 1] - p->task_tb_off[t]);
-            p->grad_one = most > 0 && most * ((p->r_max + 15) / 16) <= 32;
-        }
         if (p->mfma && !p->fused_db) {
             int64_t most = 0, active = 0, rows = 0;
             for (int32_t t = 0; t < n; ++t) {
