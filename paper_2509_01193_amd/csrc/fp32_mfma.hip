@@ -512,7 +512,9 @@ __global__ __launch_bounds__(64 * NW) void grad_f32_one_kernel(PlanDev pd, const
                                                                float* __restrict__ out2, int32_t D2, int accumulate)
 {
     __shared__ __attribute__((aligned(16))) float red[NW][16][64];       // [wave][rank][column]
-    int32_t coltile = blockIdx.y;
+    // (column tile fastest: workgroups are dealt to the XCDs in turn, and with the task fastest all of one task's would share an XCD where
+    //  their number is a multiple of eight: 1316 x 348 x 780, one of 16 tasks with tokens, gradients 24 us, like this 15)
+    int32_t coltile = blockIdx.x;
     if (coltile >= tiles_a) {
         coltile -= tiles_a;
         P = P2;
@@ -520,7 +522,7 @@ __global__ __launch_bounds__(64 * NW) void grad_f32_one_kernel(PlanDev pd, const
         out = out2;
         D = D2;
     }
-    const int32_t t = blockIdx.x, tb0 = pd.task_tb_off[t], nb = pd.task_tb_off[t + 1] - tb0;
+    const int32_t t = blockIdx.y, tb0 = pd.task_tb_off[t], nb = pd.task_tb_off[t + 1] - tb0;
     const int32_t r0 = pd.rank_off[t], r = pd.rank_off[t + 1] - r0;
     if (nb == 0 && accumulate) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), i = lane & 15, kg = lane >> 4;
@@ -582,7 +584,7 @@ __global__ __launch_bounds__(64 * NW) void grad_f32_one_kernel(PlanDev pd, const
 hipError_t grad_f32_one(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, hipStream_t st)
 {
     const int32_t tiles_a = (ja.D + 63) / 64, tiles_b = (jb.D + 63) / 64;
-    const dim3 grid(pd.n_tasks, tiles_a + tiles_b);
+    const dim3 grid(tiles_a + tiles_b, pd.n_tasks);
     if (grid.y > 65535u) return hipErrorInvalidValue;
     const bool vec = ((ja.D | jb.D) & 3) == 0;
     const int nrb = (pd.r_max + 15) / 16;

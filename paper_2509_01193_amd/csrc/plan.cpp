@@ -255,9 +255,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         //   rank 16   256 x 256, n = 13 29.4 / 26.7, 30 35.7 / 32.7, 39 64.7 / 62.3, 53 41.8 / 42.8; 1024 x 1024, n = 13 69.2 / 64.7, 31 107.5 /
         //             105.2, 57 161.6 / 162.2; 1999 x 500, n = 30 129.7 / 121.5
         //   rank 32   256 x 256, n = 10 34.9 / 32.3, 30 40.0 / 42.3;  rank 64  n = 4 39.9 / 36.7, 22 50.7 / 56.7;  rank 128  n = 13 64.1 / 69.6
-        // (tasks and column tiles within what the grid takes)
+        // (tasks within what the grid takes)
         p->grad_one = false;
-        if (d->dtype == LOBRA_F32 && p->n_proj == 1 && n <= 65536 && (int64_t(d->d_in) + 63) / 64 + (int64_t(d->d_out) + 63) / 64 <= 65535) {
+        if (d->dtype == LOBRA_F32 && p->n_proj == 1 && n <= 65535) {
             int64_t most = 0;
             for (int32_t t = 0; t < n; ++t) most = std::max<int64_t>(most, p->task_tb_off[t + 1] - p->task_tb_off[t]);
             p->grad_one = most > 0 && most * ((p->r_max + 15) / 16) <= 32;

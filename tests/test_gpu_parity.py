@@ -760,6 +760,7 @@ def test_gradients_of_tasks_with_a_single_chunk(ranks, n_proj, empty_task):
     (65, 260, [32, 17], [16 * 32, 33]),       # two rank blocks
     (128, 96, [100, 1, 64], [4 * 32, 40, 7]), # eight in two passes over the tokens
     (64, 8, [8, 24, 8], [40, 0, 16]),         # a task without tokens between others
+    (96, 136, [8, 4, 16] * 3, [0, 500, 0, 0, 70, 0, 0, 0, 0]),    # most tasks without
 ])
 def test_fp32_gradients_in_one_launch(d_in, d_out, ranks, lens):
     """fp32 gradients without partial sums at the edges of their rule, tiles and rank passes, against the oracle; accumulating
