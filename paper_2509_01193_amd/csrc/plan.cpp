@@ -456,9 +456,11 @@ GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t 
     const int64_t items = ntb * ((rank + 15) / 16);
     if (ntb == 0 || K < kMinSplitK || items > kMaxBesideItems || T * N * rank > kMaxBesideRankRows) return best;
     const int32_t kt = (K + kGemmKTile - 1) / kGemmKTile;
-    float least = choose_gemm(T, K, N, 0, nseg, rank, kMaxPartBytes).cost + kBesideGain;
+    float least = choose_gemm(T, K, N, 0, nseg, rank, kMaxPartBytes).cost + beside_gain(K);
+    const float spread = 1.f + 0.3f * std::max(0.f, float(T) * float(K) / 5e6f - 1.f);
     for (int32_t i = 3; i <= 4; ++i) {               // (two workgroups of these, or of the projection, share a compute unit)
-        const GemmTile& t = kGemmTiles[i];
+        GemmTile t = kGemmTiles[i];
+        t.k2 *= spread;
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn);
         for (int32_t s = 1; s <= kMaxSplits; ++s) {
             const int64_t bytes = int64_t(s) * T * N * 4;

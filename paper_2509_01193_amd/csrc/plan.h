@@ -100,12 +100,15 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
 // passes: 108 where it is 97 now and 102 apart).  An item is a workgroup per half of its block, and all have to run at once: on one
 // that has to wait for another to end the launch waits too (apart / one too many, us: 600 x 1504 x 1536, rank 16 15.8 / 18.5; 800 x 1024 x
 // 1024, rank 32 13.7 / 17.0; 1100 x 2048 x 768, rank 32 18.3 / 21.7).  Halves without tokens end at once, but leave room on their own XCD
-// only, so they count unless all blocks are short.  What is saved, a launch and the chain of tables and adapter copies behind
-// a tile, is kBesideGain (apart / beside where that is all: 1100 x 1024 x 1024, estimates 4.5 apart, 14.9 / 15.7; 600 x 2048 x 2048, 4.2,
-// 20.8 / 19.5; 1500 x 2048 x 768, 4.0, 22.1 / 20.5).  The sum reads T N rank elements of the adapters: from 32 million on that takes the gain
+// only, so they count unless all blocks are short.  Where two workgroups share a compute unit the splits of a Z of more than 5 million
+// elements find less of it in the L2 than the table's k2 says (per K tile of 128 x 64: 0.59 us at 1500 x 4096, 0.76 at 1800 x 5504, 0.93
+// at 1500 x 11008, where a product beside took 93 us and one apart 72).  What is saved, a launch and the chain of tables and adapter copies behind
+// a tile, is beside_gain, and more with a longer K, which a projection of its own takes longer for (apart / beside where the estimates differ
+// by about that: 1100 x 1024 x 1024, 4.5 us, 14.9 / 15.7; 600 x 2048 x 2048, 4.2, 20.8 / 19.5; 1500 x 2048 x 768, 4.0, 22.1 / 20.5; both passes
+// of 158 x 3456 x 8576, 4.8, 67.9 / 64.3).  The sum reads T N rank elements of the adapters: from 32 million on that takes the gain
 // (200 x 1024 x 3072 at rank 64, 39 million: 15.0 / 17.0; 700 x 8192 x 1024 39.2 / 44.8; 128 x 4096 x 4096 at rank 128 25.5 / 26.6).
 // Below K = kMinSplitK a token's result shall not depend on the size of its batch.
-constexpr float kBesideGain = 4.4f;
+inline float beside_gain(int32_t K) { return K < 3414 ? 3.5f + 0.45f * float(K) / 1024.f : 5.f; }
 constexpr int64_t kMaxBesideItems = 256, kMaxBesideRankRows = int64_t(32) << 20;
 GemmChoice choose_beside(int64_t T, int32_t K, int32_t N, int32_t nseg, int32_t rank, int64_t ntb, int32_t halves);
 // The scratch that these choices would like to have (0: none).
