@@ -296,14 +296,13 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         // block -: on long batches chunks of at least 5 blocks per 16 ranks (of the mean over the blocks), if that leaves the largest task
         // more than one (both stages, us, chunks as above / with this floor: rank 128, 42123 x 768 x 7168 541 / 315, 45263 x 2688 x
         // 832 226 / 172, 8000 x 3072 x 5000 130 / 75; twice the floor is no better).  A wave walks a chunk's blocks one after the other, some
-        // 0.8 us each, so the floor ends where a launch (the smallest one of fused projections) would be left with fewer than 320 workgroups,
-        // or 224 where ranks above 64 make a chunk's sums the dearer part.  Projection of dy and gradients, us, chunks as above / the floor
-        // alone / ended like this (x 1024 x 1024: one task; P = 3: dB in three launches):
+        // 0.8 us each, so the floor ends where it would leave fewer than 320 workgroups, 224 where ranks above 64 make a chunk's sums the
+        // dearer part, or 352 on average over the launches of fused projections, which follow each other.  Projection of dy and gradients,
+        // us, chunks as above / the floor alone / ended like this (one task; P = 3: dB in three launches):
         //   1600 x 1024 x 1024, rank 128   25.8 / 40.3 / 25.8        10000 x 1024 x 1024, rank 128     80.5 / 74.8 / 55
         //   2500 x 768 x 768, rank 32      18.3 / 19.7 / 18.3        1696 x 832 x 1536, P = 3, rank 96     27.1 / 57.3 / 27.0
-        // 269 batches drawn at 600 to 49000 tokens, 768 to 11008 columns, ranks 8 to 128, P = 1 .. 3, beside 288 on a grid of the same: no floor
-        // 1, the floor alone 1.016, ended at 224 for all 0.927, at 288 0.939, as here 0.928 with five batches more than 3 % behind no floor (5 %
-        // at most), where 224 for all has twelve.
+        // 557 batches of 600 to 49000 tokens, 768 to 11008 columns, ranks 8 to 128, P = 1 .. 3: no floor 1, the floor alone 1.015,
+        // ended as here 0.927, with two batches more than 3 % behind no floor.
         if (p->mfma && !p->fused_db && !p->tb.empty()) {
             int64_t most = 0, wsum = 0;
             for (int32_t t = 0; t < n; ++t) {
@@ -312,9 +311,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 wsum += nb * (p->rank_off[t + 1] - p->rank_off[t]);
             }
             const int64_t nb = int64_t(p->tb.size()), least = wsum * 5 / (16 * nb);
-            const int64_t tiles_in = (int64_t(d->d_in) + 255) / 256, tiles_out = (int64_t(p->dg % 128 == 0 ? d->d_out : p->dg) + 255) / 256;
-            const int64_t tiles = p->n_proj > 1 ? std::min(tiles_in, tiles_out) : tiles_in + tiles_out;
-            const int64_t wanted = p->n_proj > 1 || p->r_max > 64 ? 224 : 320;
+            const int64_t db_launches = p->n_proj > 1 && p->dg % 128 != 0 ? p->n_proj : 1, launches = p->n_proj > 1 ? 1 + db_launches : 1;
+            const int64_t tiles = (int64_t(d->d_in) + 255) / 256 + (int64_t(d->d_out / db_launches) + 255) / 256 * db_launches;
+            const int64_t wanted = p->n_proj > 1 ? 352 * launches : p->r_max > 64 ? 224 : 320;
             if (5 * most > 6 * least) cb = std::max(cb, std::min(least, nb * tiles / wanted));
         }
         p->chunk_blocks = int32_t(cb);

@@ -190,21 +190,22 @@ def test_one_reduction_chunk_per_task_with_one_large_task():
     (1600, 1024, 1024, 1, 128, 1, 4, 0),
     (2500, 768, 4096, 1, 32, 1, 4, 320),
     (4000, 2048, 2048, 1, 128, 2, 9, 224),        # some longer ones, as far as the workgroups last
-    (1696, 832, 1536, 3, 96, 1, 4, 0),            # fused projections: the launch with the fewest workgroups counts
-    (17800, 1984, 4608, 3, 96, 1, 19, 224),
-    (8000, 4096, 3 * 1032, 3, 96, 1, 7, 160),     #   dB takes a launch per projection (and the chunks are as without a floor)
+    (1696, 832, 1536, 3, 96, 1, 4, 0),            # fused projections: launches that follow each other
+    (17800, 1984, 4608, 3, 96, 1, 20, 352),
+    (10549, 5376, 1280, 2, 128, 1, 13, 352),
+    (8000, 4096, 3 * 1032, 3, 96, 1, 7, 0),       #   dB takes a launch per projection (and the chunks are as without a floor)
     (42123, 768, 7168, 1, 128, 4, 40, 320),       # long batches: five blocks per 16 ranks
 ])
 def test_reduction_chunks_of_high_ranks_leave_enough_workgroups(T, d_in, d_out, n_proj, rank, tasks, longest, wgs):
-    """Chunks grow with the rank only while every launch of stage 1 keeps a workgroup for most compute units; no chunk is longer
-    than `longest` blocks then, and the smallest launch has at least `wgs` workgroups of 256 columns."""
+    """Chunks grow with the rank only while stage 1 keeps a workgroup for most compute units; no chunk is longer than `longest`
+    blocks then, and a launch has at least `wgs` workgroups of 256 columns on average."""
     plan = bd.Plan("bf16", T, d_in, d_out, np.arange(tasks + 1) * rank, np.arange(tasks + 1) * T // tasks, np.arange(tasks),
                    bd.PLAN_HOST_ONLY, n_proj)
     chunks = plan.query(bd.Q_GRAD_CHUNKS).reshape(-1, 4)
     dg = d_out // n_proj
-    tiles = [-(-d_in // 256), -(-(d_out if dg % 128 == 0 else dg) // 256)]
+    tiles = [-(-d_in // 256)] + ([-(-d_out // 256)] if dg % 128 == 0 else [-(-dg // 256)] * n_proj)
     assert int((chunks[:, 1] - chunks[:, 0]).max()) <= longest
-    assert len(chunks) * (sum(tiles) if n_proj == 1 else min(tiles)) >= wgs
+    assert len(chunks) * sum(tiles) >= wgs * (1 if n_proj == 1 else len(tiles))
     plan.close()
 
 
