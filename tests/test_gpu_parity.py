@@ -469,17 +469,19 @@ def test_gemm_k_beyond_the_last_whole_tile(T, d_in, d_out):
 
 
 @pytest.mark.parametrize("blocks,ranks,n_proj", [
-    (128, [16, 8], 1), (129, [16, 8], 1), (96, [32, 17], 1), (97, [32, 17], 1), (72, [40, 128], 1), (73, [40, 128], 1),
-    (64, [8, 16], 2), (65, [8, 16], 2), (21, [8, 32], 3), (22, [8, 32], 3),
+    (128, [16, 8], 1), (129, [16, 8], 1), (64, [32, 17], 1), (65, [32, 17], 1), (16, [40, 128], 1), (17, [40, 128], 1),    # halves of blocks
+    (96, [32, 17], 1), (97, [32, 17], 1), (48, [64, 8], 1), (49, [64, 8], 1),         # 16 ranks a workgroup
+    (64, [40, 128], 1), (65, [40, 128], 1),                                           # 32 ranks
+    (72, [40, 128], 1), (128, [40, 128], 1), (129, [40, 128], 1),                     # 64 and 128 ranks
+    (64, [8, 16], 2), (65, [8, 16], 2), (21, [8, 32], 3), (22, [8, 32], 3),           # fused projections
 ])
-def test_projection_on_both_sides_of_the_short_batch_rule(blocks, ranks, n_proj):
-    """The last batch (in token blocks) that the kernel for short batches takes and the first that it leaves to the other (ranks per
-    projection), in
-    both directions, at one, two and more rank blocks and with fused projections."""
+def test_projection_on_both_sides_of_its_rules(blocks, ranks, n_proj):
+    """The last batch (in token blocks) of a workgroup shape of the ring projection and the first of the next (ranks per
+    projection), in both directions, at one, two and more rank blocks and with fused projections."""
     T = 32 * blocks - 5
     cut = 32 * (blocks // 3)
     kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
-    p = wl.make_custom("short-rule-%d" % blocks, "bf16", 136, 72, ranks, [0, cut, 2 * cut, T], [0, 1, 0], 91, s=[2.0, -1.0],
+    p = wl.make_custom("ring-rule-%d" % blocks, "bf16", 136, 72, ranks, [0, cut, 2 * cut, T], [0, 1, 0], 91, s=[2.0, -1.0],
                        fill=(n_proj == 1), **kw)
     p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
     check_problem(p, label="%d blocks" % blocks)
