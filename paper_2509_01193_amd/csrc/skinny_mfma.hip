@@ -699,12 +699,12 @@ hipError_t grad_mfma(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bo
         const int32_t ta = (ja.D + 255) / 256, tb = jb.P ? (jb.D + 255) / 256 : 0;
         const uint32_t wgs = items * uint32_t(ta + tb);                               // (plan creation bounds the product)
         // Ranks above 64: in one pass over Z, whose registers leave room for one workgroup per compute unit, or in two, which hide
-        // each other's waits.  One is better on chunks of some blocks where its rounds of 256 workgroups are nearly full (us, two / one:
-        // 225 workgroups, chunks of 36 blocks, 0.94 of two; 250 of 18 0.93; 280 of 28 1.17; 348 of 18 1.03; 414 of 22 0.90; 476 of 21 0.87; 128
-        // of 16 at 3072 x 5000, rank 128 26.6 / 28.5 us; 256 of 4 at 4096 x 4096 24.6 / 25.1, of 16 44.0 / 42.8; 32 of 4 13.8 / 16.4).  Long
-        // batches: 42123 x 768 x 7168, 1116 workgroups 299 / 309; 45263 x 2688 x 832, 570 157 / 179.
+        // each other's waits.  One is better where its rounds of 256 workgroups are nearly full (one / two, mean of 329 training steps, by
+        // workgroups: up to 64 1.18, to 130 1.14, to 197 1.05, to 256 0.93, to 384 1.17, to 512 0.92), and where two would start twice as
+        // many workgroups that only clear rows (more than 256 with them: 0.89; up to 80 1.3).
         const int64_t one_wgs = int64_t(pd.nchunks) * (ta + tb), rounds = (one_wgs + 255) / 256;
-        const int one = nrb > 4 && rounds <= 2 && one_wgs * 13 >= rounds * 256 * 10 && pd.ntb >= 5 * int64_t(pd.nchunks) ? 8 : 4, passes = nrb > one ? 2 : 1;
+        const bool fits = zero_empty ? wgs > 256 : rounds <= 2 && one_wgs * 13 >= rounds * 256 * 10;
+        const int one = nrb > 4 && fits ? 8 : 4, passes = nrb > one ? 2 : 1;
 #define LOBRA_GRAD(NRB_)                                                                       \
     do {                                                                                       \
         if (zero_empty) grad_lds_kernel<NRB_, true><<<dim3(wgs, passes), 256, 0, st>>>(pd, ja, jb, ta, ta + tb, accumulate ? 1 : 0);  \
