@@ -297,7 +297,8 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         // more than one (both stages, us, chunks as above / with this floor: rank 128, 42123 x 768 x 7168 541 / 315, 45263 x 2688 x
         // 832 226 / 172, 8000 x 3072 x 5000 130 / 75; twice the floor is no better).  A wave walks a chunk's blocks one after the other, some
         // 0.8 us each, so the floor ends where it would leave fewer than 320 workgroups, 224 where ranks above 64 make a chunk's sums the
-        // dearer part, or 352 on average over the launches of fused projections, which follow each other.  Projection of dy and gradients,
+        // dearer part, or 352 on average over the launches of fused projections, which follow each other (the kernel of ranks up to 16 has
+        // tiles of 128 columns: 6390 x 1024 x 768 keeps chunks of 5 blocks).  Projection of dy and gradients,
         // us, chunks as above / the floor alone / ended like this (one task; P = 3: dB in three launches):
         //   1600 x 1024 x 1024, rank 128   25.8 / 40.3 / 25.8        10000 x 1024 x 1024, rank 128     80.5 / 74.8 / 55
         //   2500 x 768 x 768, rank 32      18.3 / 19.7 / 18.3        1696 x 832 x 1536, P = 3, rank 96     27.1 / 57.3 / 27.0
@@ -312,7 +313,8 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             }
             const int64_t nb = int64_t(p->tb.size()), least = wsum * 5 / (16 * nb);
             const int64_t db_launches = p->n_proj > 1 && p->dg % 128 != 0 ? p->n_proj : 1, launches = p->n_proj > 1 ? 1 + db_launches : 1;
-            const int64_t tiles = (int64_t(d->d_in) + 255) / 256 + (int64_t(d->d_out / db_launches) + 255) / 256 * db_launches;
+            const int64_t tw = p->r_pad <= 16 ? 128 : 256;
+            const int64_t tiles = (d->d_in + tw - 1) / tw + (d->d_out / db_launches + tw - 1) / tw * db_launches;
             const int64_t wanted = p->n_proj > 1 ? 352 * launches : p->r_max > 64 ? 224 : 320;
             if (5 * most > 6 * least) cb = std::max(cb, std::min(least, nb * tiles / wanted));
         }

@@ -209,6 +209,14 @@ def test_reduction_chunks_of_high_ranks_leave_enough_workgroups(T, d_in, d_out, 
     plan.close()
 
 
+def test_reduction_chunks_of_rank_16_count_their_own_tiles():
+    """Ranks up to 16 have column tiles of 128: 200 blocks in chunks of 5 still make 560 workgroups."""
+    plan = bd.Plan("bf16", 6390, 1024, 768, [0, 16, 32], [0, 3200, 6390], [0, 1], bd.PLAN_HOST_ONLY)
+    chunks = plan.query(bd.Q_GRAD_CHUNKS).reshape(-1, 4)
+    assert len(chunks) == 40 and (chunks[:, 1] - chunks[:, 0] == 5).all()
+    plan.close()
+
+
 @pytest.mark.parametrize("lens,d_in,d_out,rank,beside", [
     ([1] * 40, 4096, 4096, 16, (7, 7)),
     ([1] * 128, 2056, 264, 32, (7, 0)),               # 128 blocks x 2 rank blocks are taken (backward: K below kMinSplitK),
