@@ -36,7 +36,7 @@ PlanDev device_view(const Plan& p)
     d.fb_run_row = p.fused_db ? b + p.o_fb_run : nullptr;
     d.fb_cnt = p.fused_db ? b + p.o_fb_cnt : nullptr;
     d.fb_task_row0 = p.fused_db ? b + p.o_fb_row0 : nullptr;
-    d.gemm_tile_tab = b + p.o_tile_tab;
+    d.gemm_tile_seg = b + p.o_tile_seg;
     d.T = int32_t(p.desc.T);
     d.d_in = p.desc.d_in;
     d.d_out = p.desc.d_out;

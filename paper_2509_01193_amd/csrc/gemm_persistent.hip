@@ -73,14 +73,13 @@ constexpr int TM = BM / WM, TN = BN / WN;            // wave tile 128 x 128
 constexpr int MB = TM / 16, NB = TN / 16;            // 16 x 16 blocks per wave
 constexpr int ZT_BYTES = BM * BK * 2;                // one operand tile: 32 KiB
 constexpr int STAGE_BYTES = 2 * ZT_BYTES;            // Z tile + W tile
-constexpr int MROWS = 64;                            // rank rows of the adapter slice staged at a time
-constexpr int MSLICE_OFF = 2 * STAGE_BYTES, MSLICE_BYTES = MROWS * BN * 2;
+constexpr int RSTEP = 32;                            // ranks per step of the up projection
+constexpr int MSLICE_OFF = 2 * STAGE_BYTES;          // adapter region: RSTEP rank rows of M_t's 256 columns,
+constexpr int P_OFF = RSTEP * BN * 2;                // then RSTEP ranks of the tile's 256 rows of P
+constexpr int MSLICE_BYTES = P_OFF + BM * RSTEP * 2;
 constexpr int LDS_BYTES = MSLICE_OFF + MSLICE_BYTES; // 160 KiB
-constexpr int PRE_RANKS = 32;                        // rank windows up to this are copied ahead of the epilogue
-constexpr int PRE_P_OFF = PRE_RANKS * BN * 2;        // where the P rows land in the adapter region
-constexpr int PRE_COPIES = 8;                        // 1 KiB copies per wave: half for the M_t slice, half for P
-static_assert(PRE_P_OFF + BM * PRE_RANKS * 2 <= MSLICE_BYTES && PRE_COPIES / 2 * NW * 1024 == PRE_P_OFF,
-              "the copied-ahead operands fill the adapter region");
+constexpr int RCOPIES = 4;                           // 1 KiB copies per wave and step for each of the two
+static_assert(RCOPIES * NW * 1024 == P_OFF && 2 * P_OFF == MSLICE_BYTES, "a step's operands fill the adapter region");
 constexpr int NBZ = (BK / 2) / NW;                   // 1 KiB copy blocks per wave, for Z and for W each
 constexpr int NU = MB + NB;                          // fragments per K step of 32 = sections per K step
 static_assert(NW == 4 && MB == 8 && NB == 8 && MB * NB == 4 * NU && 2 * NBZ == NU && BK == 64,
@@ -108,7 +107,7 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
                      const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
                      uint16_t* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
                      int32_t nproj, int32_t proj, int32_t tiles_m, int32_t tiles_n, int32_t GM, int32_t cpx,
-                     int32_t TPW, const int32_t* __restrict__ tile_tab, const int32_t* __restrict__ cseg_off,
+                     int32_t TPW, const int32_t* __restrict__ tile_seg, const int32_t* __restrict__ cseg_off,
                      const int32_t* __restrict__ cseg_task, const int32_t* __restrict__ rank_off)
 {
     constexpr bool KTAIL = LOBRA_GP_KTAIL;
@@ -116,7 +115,7 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
     // its second tile perhaps wholly, beyond K: their copies repeat the last valid chunk, and both operands' fragments
     // are cleared in registers in front of the K steps that reach beyond K.  A kernel of its own, so that whole K tiles
     // do not pay for it.
-    // tile_tab, cseg_off, cseg_task, rank_off: pd's tables of those names once more, as arguments of their own that
+    // tile_seg, cseg_off, cseg_task, rank_off: pd's tables of those names once more, as arguments of their own that
     // promise not to alias anything the kernel writes: their entries are the same for every lane, and with the
     // promise the compiler fetches them with scalar loads, which no vector memory operation in flight - copies,
     // stores - has to be waited for first.
@@ -347,62 +346,119 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
     using step_copy = std::integral_constant<int, STEP_COPY>;
     using step_copy_tail = std::integral_constant<int, STEP_COPY_TAIL>;
 
-    // ---- epilogue of the tile at (row0, col0): fused up projection, then fp32 -> bf16 and the stores.
-    //      tab_*: the table entries of the first segment that crosses the tile, read when the tile's main loop
-    //      began (a chain of dependent loads that would otherwise sit in front of the epilogue).
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    int32_t tab_sg = 0, tab_lo = 0, tab_hi = 0, tab_task = -1, tab_r0 = 0, tab_r1 = 0, tab_pcol = 0;
-    bool tab_pre = false;                            // the first segment's operands are copied ahead (prefetch_adapter)
+    // ---- fused up projection: for every segment with an adapter that crosses the tile, its ranks are further K steps of 32:
+    //      acc += M_t^T[:, cols] * P[rows, :]^T, rows outside the segment and ranks beyond r_t cleared in registers.  A step has
+    //      two halves of 16 ranks: the two of one segment's window of 32, or, where a window has at most 16 ranks left, those
+    //      and all of the next segment's, if it has at most 16.  (A window of more is never divided between steps, so a row's
+    //      sum does not depend on what else is in its tile.)
+    //      Both operands are copied into the adapter region, M_t in the [k][256 n] layout (rows beyond a half's last repeat it),
+    //      P 64 bytes a row (chunks beyond repeat the half's first): the first step's while the tile's last K tile is multiplied,
+    //      and every other's behind the reads of the one before, under its MFMAs.  What a step costs beyond its 64 MFMAs per wave
+    //      is what is left of one round trip to memory.  (With each segment's slice passing through registers behind its own
+    //      chain of table reads, five round trips at rank 64, a step of 49152 x 8192 x 8192, 32 tasks of rank 64, took 9955 us, with
+    //      this 9823; 8190 x 1376 x 4096, rank 16, 235.8 -> 232.2, its products 95 -> 89 each; the forward product of 47000 x 600 x
+    //      7232 at rank 128 804 -> 625, of 12000 x 584 x 1000 in segments of four tokens 151 -> 91.)
+    //      tile_seg's record of the tile row, read when the tile's main loop begins: scalar registers.
     auto rfl = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
-    auto load_table = [&](int32_t row0, int32_t col0) {
-        if (!P) return;
-        // the record of this tile row (the last tile row may start above a multiple of the tile height)
-        const int32_t* rec = tile_tab + size_t((row0 + BM - 1) / BM) * kGemmTileRec;
-        tab_sg = rec[0];
-        tab_lo = rec[1];
-        tab_hi = rec[2];
-        tab_task = rec[3];
-        const int32_t pj = proj >= 0 ? proj : col0 / pd.dg;
-        const int32_t rw = rec[5] / nproj;
-        tab_r0 = rec[4] + pj * rw;
-        tab_r1 = tab_r0 + rw;
-        tab_pcol = pj * rw;
-        tab_pre = tab_task >= 0 && rw > 0 && rw <= PRE_RANKS;
+    int32_t rec[kGemmTileSegRec];
+    int32_t u_e, u_sg, u_lo, u_hi, u_m, u_r, u_k;    // the walk: entry, next segment to look at, the segment, its window, next rank of it
+    int32_t u_pc = 0, u_mcol0 = 0, u_mpitch = 0, u_pj = 0;
+    struct Half { int32_t lo, hi, m, n, pc; };       // rows, first row of M, ranks (0: none), first column of P
+    Half ha, hb;                                     // the step that is in the region, or on its way
+    auto window = [&](int32_t lo, int32_t hi, int32_t r0, int32_t stacked) __attribute__((always_inline)) {
+        u_lo = lo;
+        u_hi = hi;
+        u_r = nproj == 1 ? stacked : rfl(stacked / nproj);
+        u_pc = u_pj * u_r;
+        u_m = r0 + u_pc;
+        u_k = 0;
     };
-    // ---- the up projection's operands for the first segment of the tile at (row0, col0), copied into the adapter
-    //      region while the tile's last K tiles are multiplied, when that segment's rank window fits one rank step:
-    //      k rows 0 .. 31 of the M_t slice in the [k][256 n] layout (16 KiB; rows from r_t on repeat row r_t - 1),
-    //      then the tile's 256 rows of P, 64 bytes each (16 KiB; chunks from r_t on repeat chunk 0).  What lies
-    //      beyond r_t is masked in registers, so only the addresses have to be valid.  Always PRE_COPIES copies
-    //      per wave, whatever the rank.
-    auto prefetch_adapter = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
-        if (!tab_pre) return;                        // uniform
-        const int32_t r = tab_r1 - tab_r0;
-        const int32_t mcol0 = proj >= 0 ? 0 : (col0 / pd.dg) * pd.dg;
-        const int32_t mpitch = proj >= 0 ? N : pd.dg;
-        const unsigned char* mbase = reinterpret_cast<const unsigned char*>(M + size_t(tab_r0) * mpitch + (col0 - mcol0));
-        const unsigned char* pbase = reinterpret_cast<const unsigned char*>(P + size_t(row0) * pd.r_pad + tab_pcol);
-        // (opaque to the optimiser: the per-lane offsets are worked out here, once per output tile, instead of
-        //  living in eight loop-invariant registers through the main loop)
+    auto next_segment = [&](int32_t row_end) __attribute__((always_inline)) {     // u_r = 0: there is none
+        ++u_e;
+        if (u_e < kGemmTileSegs) {
+            const bool one = u_e == 1;
+            window(one ? rec[4] : rec[8], one ? rec[5] : rec[9], one ? rec[6] : rec[10], one ? rec[7] : rec[11]);
+            return;
+        }
+        u_r = 0;
+        for (; u_sg < pd.nseg; ++u_sg) {
+            const int32_t lo = rfl(cseg_off[u_sg]);
+            if (lo >= row_end) return;
+            const int32_t t = rfl(cseg_task[u_sg]);
+            if (t < 0) continue;
+            const int32_t r0 = rfl(rank_off[t]);
+            window(lo, rfl(cseg_off[u_sg + 1]), r0, rfl(rank_off[t + 1]) - r0);
+            ++u_sg;
+            return;
+        }
+    };
+    auto load_table = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+        if (!P) return;
+        // (the last tile row may start above a multiple of the tile height)
+        const int32_t* src = tile_seg + size_t((row0 + BM - 1) / BM) * kGemmTileSegRec;
+#pragma unroll
+        for (int i = 0; i < 4 * kGemmTileSegs + 1; ++i) rec[i] = src[i];
+        u_pj = proj >= 0 ? proj : rfl(col0 / pd.dg);                 // this tile's projection,
+        u_mcol0 = proj >= 0 ? 0 : u_pj * pd.dg;                      // its first column
+        u_mpitch = proj >= 0 ? N : pd.dg;                            // and the row pitch of M
+    };
+    auto first_segment = [&]() __attribute__((always_inline)) {
+        u_e = 0;
+        u_sg = rec[4 * kGemmTileSegs];
+        window(rec[0], rec[1], rec[2], rec[3]);
+    };
+    // the next step into (ha, hb); false: there is none
+    auto next_step = [&](int32_t row_end) __attribute__((always_inline)) {
+        if (u_r == 0) return false;
+        const int32_t left = u_r - u_k;
+        ha = Half{u_lo, u_hi, u_m + u_k, min(left, 16), u_pc + u_k};
+        hb = Half{u_lo, u_hi, ha.m, 0, ha.pc};
+        if (left > 16) {
+            hb.m += 16;
+            hb.n = min(left - 16, 16);
+            hb.pc += 16;
+        }
+        u_k += 32;
+        if (u_k >= u_r) {
+            next_segment(row_end);
+            if (left <= 16 && u_r > 0 && u_r <= 16) {
+                hb = Half{u_lo, u_hi, u_m, u_r, u_pc};
+                next_segment(row_end);
+            }
+        }
+        return true;
+    };
+    // copies a step's operands for the tile at (row0, col0): 2 RCOPIES copies per wave
+    auto copy_step = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+        // (opaque to the optimiser: the per-lane offsets are worked out here instead of living in loop-invariant registers
+        //  through the main loop)
         int ln = lane;
         asm volatile("" : "+v"(ln));
 #pragma unroll
-        for (int c = 0; c < PRE_COPIES / 2; ++c) {
-            const int blk = wave_u + NW * c;
-            const int krow = 2 * blk + (ln >> 5);
-            const int chn = (ln & 31) ^ kn_swz2(krow);
-            dma16(lds0 + MSLICE_OFF + (wave_u + NW * c) * 1024, mbase,
-                  (uint32_t(min(krow, r - 1)) * uint32_t(mpitch) + 8u * chn) * 2u);
+        for (int c = 0; c < RCOPIES; ++c) {
+            const int krow = 2 * (wave_u + NW * c) + (ln >> 5);      // half c / 2
+            const int32_t m = c < RCOPIES / 2 ? ha.m : hb.m, n = c < RCOPIES / 2 ? ha.n : hb.n;
+            dma16(lds0 + MSLICE_OFF + (wave_u + NW * c) * 1024,
+                  reinterpret_cast<const unsigned char*>(M + size_t(m) * u_mpitch + (col0 - u_mcol0)),
+                  (uint32_t(min(krow & 15, max(n - 1, 0))) * uint32_t(u_mpitch) + 8u * ((ln & 31) ^ kn_swz2(krow))) * 2u);
         }
+        const int ch = ln & 3, k = 8 * (ch & 1);
+        const int32_t pcol = ch < 2 ? ha.pc + (k < ha.n ? k : 0) : hb.pc + (k < hb.n ? k : 0);
 #pragma unroll
-        for (int c = 0; c < PRE_COPIES / 2; ++c) {
-            const int blk = wave_u + NW * c;
-            const int row = 16 * blk + (ln >> 2), ch = ln & 3;
-            dma16(lds0 + MSLICE_OFF + PRE_P_OFF + (wave_u + NW * c) * 1024, pbase,
-                  (uint32_t(row) * uint32_t(pd.r_pad) + (8 * ch < r ? 8u * ch : 0u)) * 2u);
-        }
+        for (int c = 0; c < RCOPIES; ++c)
+            dma16(lds0 + MSLICE_OFF + P_OFF + (wave_u + NW * c) * 1024, reinterpret_cast<const unsigned char*>(P + size_t(row0) * pd.r_pad),
+                  (uint32_t(16 * (wave_u + NW * c) + (ln >> 2)) * uint32_t(pd.r_pad) + uint32_t(pcol)) * 2u);
     };
-    const int main_tid = tid, main_lane = lane, main_j = j, main_kg = kg;
+    bool up = false;                                 // the tile has an up projection, and its first step is on its way
+    auto prefetch_adapter = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+        if (!P) return;                              // uniform
+        first_segment();
+        up = next_step(min(row0 + BM, T));
+        if (up) copy_step(row0, col0);
+    };
+    // ---- epilogue of the tile at (row0, col0): fused up projection, then fp32 -> bf16 and the stores.
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+    const int main_lane = lane, main_j = j, main_kg = kg;
     auto epilogue = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
         // (KTAIL: counted anew and opaque to the optimiser, so that the epilogue's addresses are worked out here, once per
         //  output tile: kept through the main loop they would be spilled, and every reload waits for the copies in flight)
@@ -411,139 +467,71 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
             lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
             asm volatile("" : "+v"(lane));
         }
-        const int tid = KTAIL ? wave_u * 64 + lane : main_tid;
         const int j = KTAIL ? lane & 15 : main_j, kg = KTAIL ? lane >> 4 : main_kg;
         // the loop's MFMAs are asm statements, so the compiler does not know that the accumulators come out of
         // the matrix pipeline: keep the first read of them the documented number of wait states away
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         const int32_t row_end = min(row0 + BM, T);
         const int32_t wrow0 = row0 + wm * TM;        // the wave's rows are wrow0 .. wrow0 + TM - 1
-        // ---- fused up projection: for every adapter segment that crosses this tile, ceil(r_t / 32) extra
-        //      K steps acc += M_t^T[:, cols] * P[rows, :]^T with the rows outside the segment masked to zero.
-        //      The M_t slice [r_t][256 cols] is staged in its own LDS region, MROWS rank rows at a time, in the
-        //      [k][n] layout (rank rows up to the next multiple of 32 zero) and gathered with the transpose
-        //      read; P comes straight from global memory, 16 bytes per lane.
-        //      The segment loop and its barriers are uniform over the workgroup.
-        if (P) {
-            unsigned char* ml = lds + MSLICE_OFF;
-            const int32_t pj = proj >= 0 ? proj : col0 / pd.dg;          // this tile's projection
-            const int32_t mcol0 = proj >= 0 ? 0 : pj * pd.dg;            // first column of that projection
-            const int32_t mpitch = proj >= 0 ? N : pd.dg;                // row pitch of M
-            int32_t sg_first = tab_sg;
-            if (tab_pre) {                           // uniform: the first segment's operands are in the region already
-                sg_first = tab_sg + 1;
-                const int32_t lo = max(tab_lo, row0), hi = min(tab_hi, row_end);
-                if (hi > wrow0 && lo < wrow0 + TM) { // wave-uniform: the segment crosses this wave's rows
-                    // lane (j, kg) holds ranks 8 kg .. 8 kg + 7 in both operands: those from r_t on are cleared
-                    const int nv = min(max(tab_r1 - tab_r0 - 8 * kg, 0), 8);
-                    u32x4 km;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
-                    const unsigned char* pl = ml + PRE_P_OFF + (wm * TM + j) * (PRE_RANKS * 2) + kg * 16;
-                    u32x4 pv[MB];
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        const int32_t row = wrow0 + mb * 16 + j;
-                        const u32x4 v = *reinterpret_cast<const u32x4*>(pl + mb * 16 * (PRE_RANKS * 2));
-                        pv[mb] = (row >= lo && row < hi) ? (v & km) : zero4;
-                    }
-                    bf16x8 mf[NB];
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        union { bf16x8 b; u32x4 u; } cv;
-                        cv.b = read_kn(ml, 0, nb, j, kg);
-                        cv.u &= km;
-                        mf[nb] = cv.b;
-                    }
-                    // The MFMAs are asm statements, which the compiler's hazard pass does not look into: an MFMA
-                    // must not read a register in the two wait states after a vector ALU instruction has
-                    // written it, and the masking above is such a write (operands that come straight from a
-                    // load need nothing).  The statements below order the masking before the wait states and
-                    // the MFMAs behind them.
-                    asm volatile("s_nop 1" : "+v"(mf[0]), "+v"(mf[1]), "+v"(mf[2]), "+v"(mf[3]), "+v"(mf[4]), "+v"(mf[5]),
-                                 "+v"(mf[6]), "+v"(mf[7]));
-                    static_for<0, MB>([&](auto mb_c) {
-                        constexpr int mb = decltype(mb_c)::value;
-                        const int32_t rb = wrow0 + mb * 16;
-                        if (hi <= rb || lo >= rb + 16) return;          // wave-uniform
-                        bf16x8 pf = as_bf16x8(pv[mb]);
-                        asm volatile("s_nop 1" : "+v"(pf));
-                        static_for<0, NB>([&](auto nb_c) { mfma_acc<acc_reg(mb, decltype(nb_c)::value)>(mf[decltype(nb_c)::value], pf); });
-                    });
-                }
+        // ---- the up projection's steps (uniform over the workgroup, the barriers too)
+        for (bool first = true; up; first = false) {
+            const unsigned char* ml = lds + MSLICE_OFF;
+            if (!first) {                            // (the first step was waited for at the last K tile's barrier)
+                wait_vmcnt<0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
             }
-            for (int32_t sg = sg_first; sg < pd.nseg; ++sg) {
-                const bool cached = sg == tab_sg;
-                const int32_t seg_lo = cached ? tab_lo : rfl(cseg_off[sg]);
-                if (seg_lo >= row_end) break;
-                const int32_t t = cached ? tab_task : rfl(cseg_task[sg]);
-                if (t < 0) continue;
-                const int32_t seg_hi = cached ? tab_hi : rfl(cseg_off[sg + 1]);
-                const int32_t lo = max(seg_lo, row0), hi = min(seg_hi, row_end);
-                const int32_t r = cached ? tab_r1 - tab_r0 : rfl(rank_off[t + 1] - rank_off[t]) / nproj;
-                const int32_t r0 = cached ? tab_r0 : rfl(rank_off[t]) + pj * r;
-                const int32_t rp = (r + 31) & ~31;
-                const bool mine = hi > wrow0 && lo < wrow0 + TM;   // wave-uniform: the segment crosses this wave's rows
-                // the P fragments of a rank step: lane (j, kg) holds the ranks kk + 8 kg .. + 7 of token row j of
-                // each 16-row block; groups that start beyond r_t hold padding, or another projection's ranks,
-                // and are not read
-                u32x4 pv[MB];
-                auto load_p = [&](int32_t kk) {
+            // lane (j, kg) holds ranks 8 (kg % 2) .. + 7 of half kg / 2 in both operands
+            const Half h = Half{kg < 2 ? ha.lo : hb.lo, kg < 2 ? ha.hi : hb.hi, 0, kg < 2 ? ha.n : hb.n, 0};
+            const int32_t any_lo = hb.n > 0 ? min(ha.lo, hb.lo) : ha.lo, any_hi = hb.n > 0 ? max(ha.hi, hb.hi) : ha.hi;
+            const bool mine = any_hi > wrow0 && any_lo < wrow0 + TM;     // wave-uniform: the step has rows of this wave
+            const unsigned char* pl = ml + P_OFF + (wm * TM + j) * (RSTEP * 2) + kg * 16;
+            u32x4 pv[MB];
+            bf16x8 mf[NB];
+            if (mine) {
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        const int32_t row = wrow0 + mb * 16 + j;
-                        pv[mb] = (mine && kk + 8 * kg < r && row >= lo && row < hi)
-                                     ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * r + kk + 8 * kg) : zero4;
-                    }
-                };
-                for (int32_t k0 = 0; k0 < rp; k0 += MROWS) {           // rank rows k0 .. k0 + rows - 1 of the slice
-                    const int32_t rows = min(rp - k0, MROWS);
-                    load_p(k0);
-                    // the slice is rows * 32 chunks of 16 bytes; the first MCH * 256 of them are fetched before
-                    // the barrier that frees the region and written after it
-                    constexpr int MCH = 2, NT = 64 * NW;
-                    u32x4 mreg[MCH];
-                    auto fetch_m = [&](int32_t base) {
+                for (int mb = 0; mb < MB; ++mb) pv[mb] = *reinterpret_cast<const u32x4*>(pl + mb * 16 * (RSTEP * 2));
 #pragma unroll
-                        for (int q = 0; q < MCH; ++q) {
-                            const int32_t ch = base + tid + q * NT, kr = k0 + (ch >> 5), n = col0 + 8 * (ch & 31);
-                            mreg[q] = (ch < rows * 32 && kr < r && n < N)
-                                          ? *reinterpret_cast<const u32x4*>(M + size_t(r0 + kr) * mpitch + (n - mcol0)) : zero4;
-                        }
-                    };
-                    auto store_m = [&](int32_t base) {
-#pragma unroll
-                        for (int q = 0; q < MCH; ++q) {
-                            const int32_t ch = base + tid + q * NT, kr = ch >> 5, c = ch & 31;
-                            if (ch < rows * 32) *reinterpret_cast<u32x4*>(ml + kr * 512 + ((c ^ kn_swz2(kr)) << 4)) = mreg[q];
-                        }
-                    };
-                    fetch_m(0);
-                    __syncthreads();                    // everybody is done with what the region held before
-                    store_m(0);
-                    for (int32_t base = MCH * NT; base < rows * 32; base += MCH * NT) {
-                        fetch_m(base);
-                        store_m(base);
-                    }
-                    __syncthreads();
-                    if (!mine) continue;                // wave-uniform; the barriers are above
-                    for (int32_t kk = 0; kk < rows; kk += 32) {
-                        if (kk > 0) load_p(k0 + kk);
-                        bf16x8 mf[NB];
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, kk, nb, j, kg);
-                        static_for<0, MB>([&](auto mb_c) {
-                            constexpr int mb = decltype(mb_c)::value;
-                            const int32_t rb = wrow0 + mb * 16;
-                            if (hi <= rb || lo >= rb + 16) return;          // wave-uniform
-                            const bf16x8 pf = as_bf16x8(pv[mb]);
-                            static_for<0, NB>([&](auto nb_c) { mfma_acc<acc_reg(mb, decltype(nb_c)::value)>(mf[decltype(nb_c)::value], pf); });
-                        });
-                    }
-                }
+                for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, 0, nb, j, kg);
             }
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();            // everybody has read the step: the region is free
+            asm volatile("" ::: "memory");
+            up = next_step(row_end);
+            if (up) copy_step(row0, col0);
+            if (!mine) continue;
+            const int nv = min(max(h.n - 8 * (kg & 1), 0), 8);
+            u32x4 km;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const int32_t row = wrow0 + mb * 16 + j;
+                pv[mb] = (row >= h.lo && row < h.hi) ? (pv[mb] & km) : zero4;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                union { bf16x8 b; u32x4 u; } cv;
+                cv.b = mf[nb];
+                cv.u &= km;
+                mf[nb] = cv.b;
+            }
+            // The MFMAs are asm statements, which the compiler's hazard pass does not look into: an MFMA must not read a
+            // register in the two wait states after a vector ALU instruction has written it, and the masking above is such a
+            // write (operands that come straight from a load need nothing).  The statements below order the masking before the
+            // wait states and the MFMAs behind them.
+            asm volatile("s_nop 1" : "+v"(mf[0]), "+v"(mf[1]), "+v"(mf[2]), "+v"(mf[3]), "+v"(mf[4]), "+v"(mf[5]),
+                         "+v"(mf[6]), "+v"(mf[7]));
+            static_for<0, MB>([&](auto mb_c) {
+                constexpr int mb = decltype(mb_c)::value;
+                const int32_t rb = wrow0 + mb * 16;
+                if (any_hi <= rb || any_lo >= rb + 16) return;          // wave-uniform
+                bf16x8 pf = as_bf16x8(pv[mb]);
+                asm volatile("s_nop 1" : "+v"(pf));
+                static_for<0, NB>([&](auto nb_c) { mfma_acc<acc_reg(mb, decltype(nb_c)::value)>(mf[decltype(nb_c)::value], pf); });
+            });
         }
+        if (P) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         // (block_col: a lane with odd kg holds its high four columns in block 2 p and its low four in block 2 p + 1)
         auto pair_order = [&](bf16x8 o) {
             union { bf16x8 b; uint64_t h[2]; } u, v;
@@ -578,7 +566,7 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
         //      time the result costs 40 % more write requests between L2 and memory.  Rows of a block are 128 bytes
         //      apart in LDS, 16-byte chunk c of row r stored at c ^ ((r >> 1) & 7); a wave's LDS operations are
         //      carried out in order, so the reads of a block need no wait for its writes.
-        if (P) __syncthreads();                      // other waves may still read the adapter slice
+        //      (Nobody reads the adapter region any more: the last step's reads are behind a barrier.)
         unsigned char* cs = lds + MSLICE_OFF + wave * 8192;
         static_for<0, 4>([&](auto b_c) {
             constexpr int hm = decltype(b_c)::value / 2, hn = decltype(b_c)::value % 2;
@@ -741,7 +729,7 @@ hipError_t launch_persistent(const PlanDev& pd, const void* Z, const void* W, co
     const int64_t wgs = ntiles <= 8 * int64_t(cpx) ? ntiles : 8 * rounds * cpx;   // few tiles: one workgroup each
     LOBRA_GP_KERNEL<W_KN><<<dim3(uint32_t(wgs)), 64 * NW, LDS_BYTES, st>>>(
         pd, (const uint16_t*)Z, (const uint16_t*)W, (const uint16_t*)P, (const uint16_t*)M, (uint16_t*)C,
-        K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, cpx, tpw, pd.gemm_tile_tab, pd.cseg_off, pd.cseg_task, pd.rank_off);
+        K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, gm, cpx, tpw, pd.gemm_tile_seg, pd.cseg_off, pd.cseg_task, pd.rank_off);
     return hipGetLastError();
 }
 }  // namespace

@@ -105,6 +105,7 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         {
             const int32_t ntr = (T + kGemmTileRows - 1) / kGemmTileRows;
             p->gemm_tile_tab.assign(size_t(ntr) * kGemmTileRec, 0);
+            p->gemm_tile_seg.assign(size_t(ntr) * kGemmTileSegRec, 0);
             for (int32_t i = 0, k = 0; i < ntr; ++i) {
                 const int32_t row0 = std::max(0, std::min(i * kGemmTileRows, T - kGemmTileRows));
                 while (p->cseg_off[k + 1] <= row0) ++k;      // row0 does not decrease with i
@@ -116,6 +117,19 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
                 rec[3] = t;
                 rec[4] = t >= 0 ? p->rank_off[t] : 0;
                 rec[5] = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
+                int32_t* seg = &p->gemm_tile_seg[size_t(i) * kGemmTileSegRec];
+                const int32_t row_end = std::min(row0 + kGemmTileRows, T);
+                int32_t g = k, found = 0;
+                for (; g < nseg && p->cseg_off[g] < row_end && found < kGemmTileSegs; ++g) {
+                    const int32_t gt = p->cseg_task[g];
+                    if (gt < 0) continue;
+                    int32_t* e = seg + 4 * found++;
+                    e[0] = p->cseg_off[g];
+                    e[1] = p->cseg_off[g + 1];
+                    e[2] = p->rank_off[gt];
+                    e[3] = p->rank_off[gt + 1] - p->rank_off[gt];
+                }
+                seg[4 * kGemmTileSegs] = g;
             }
         }
 
@@ -434,8 +448,8 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
         if (group == 0 && N <= 256 && t.tn < N && int64_t(T) * K * 2 > (int64_t(256) << 20)) continue;
         float fixed = t.fixed;
         if (i == kPersistentTile && ktail)
-            fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kKTailRank * std::max(0.f, float(rank - 32) / 32.f) +
-                    kSegmentCost.ktail * segments;
+            fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kKTailRank * std::max(0.f, float(rank - 32) / 32.f);
+        if (i == kPersistentTile) fixed += (rank <= 16 ? kSegmentCost.persistent16 : kSegmentCost.persistent) * segments;
         if (i == kStagedTile) fixed += kSegmentCost.staged * segments;
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = cus * t.per_cu;
         for (int32_t s = 1; s <= kMaxSplits; ++s) {
@@ -516,7 +530,7 @@ std::vector<int32_t> pack_blob(Plan* p)
     p->o_fb_run = put(p->fb_run_row.data(), p->fb_run_row.size());
     p->o_fb_cnt = put(p->fb_cnt.data(), p->fb_cnt.size());
     p->o_fb_row0 = put(p->fb_task_row0.data(), p->fb_task_row0.size());
-    p->o_tile_tab = put(p->gemm_tile_tab.data(), p->gemm_tile_tab.size());
+    p->o_tile_seg = put(p->gemm_tile_seg.data(), p->gemm_tile_seg.size());
     while (blob.size() % 4) blob.push_back(0);
     return blob;
 }

@@ -13,6 +13,7 @@ constexpr int kTokenBlock = 32;   // tokens per token block (one MFMA K step of 
 constexpr int kRowBlock = 32;     // granularity of the row -> segment lookup table
 constexpr int kGemmTileRows = 256;    // token rows of a base-GEMM output tile
 constexpr int kGemmTileRec = 8;       // ints per record of Plan::gemm_tile_tab
+constexpr int kGemmTileSegs = 3, kGemmTileSegRec = 16;     // adapter segments and ints per record of Plan::gemm_tile_seg
 constexpr int kMaxClearedTasks = 4096;    // up to here stage 1 of the gradients clears the rows of tasks without tokens
 constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
 // Most tokens of an fp32 batch and of LOBRA_PLAN_PLAIN_KERNELS: the plain kernels put 64-token tiles on grid.y, and the
@@ -46,15 +47,15 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 // gives every compute unit one is the best; what remains is the count of rounds, which the choice estimates.
 // K that is no multiple of 128: the persistent kernel's form for it works its epilogue's addresses out anew per tile (kKTailFixed
 // for its `fixed`) and pays more again for rows of C that start inside a 64-byte sector (kKTailOddRows where N is no multiple
-// of 32: 20000 x 840 x 5240 268 us, the staged kernel 251; x 4096 154, 174) and for ranks above the 32 whose operands are copied
-// ahead (a round's cost beside its K tiles 9.6, 13.4 and 20.1 us at rank 32, 64 and 128, the staged kernel's 5.5, 7.2 and
-// 10.1: 47000 x 600 x 7232 485 against 550 us at rank 32, 804 against 700 at rank 128).  Like the staged kernel, which has the largest tile
-// and the shortest start, it does the up projection segment by segment, the tiled kernels by task (kSegmentCost).  Measured, us
-// per round of 256 tiles (N = 7552, 55000 tokens), and us in all for 12000 x 584 x 1000 in segments of n tokens, rank 16:
-//     K                 64    200   328   520   712   968   1376  2248      n = 400   20    4     1
-//     persistent                          23.6  26.9  33.7  41.6  65.5      35        63    151   391
-//     staged            9.3   15.0  18.6  25.1  31.0  38.6  48.6  75.8      33        49    102   240
-//     128 x 256 (x 2)   14.8  21    24    29    35    42    50    73        36        39    42    45
+// of 32: 20000 x 840 x 5240 268 us, the staged kernel 251; x 4096 154, 174) and for ranks above 32, a step of the up projection each
+// (kKTailRank; 47000 x 600 x 7232 at rank 32, 64 and 128, this kernel / the staged one: 579, 560 and 625 / 621, 613 and 646 us).
+// The persistent and the staged kernel do the up projection segment by segment - the persistent one two segments of up to 16
+// ranks in one step -, the tiled kernels by task (kSegmentCost).  Measured, us per round of 256 tiles (N = 7552, 55000 tokens),
+// and us in all for 12000 x 584 x 1000 and 12000 x 1024 x 1024 in segments of n tokens, rank 16:
+//     K                 64    200   328   520   712   968   1376  2248      n = 400   20    4     n = 400   20    4
+//     persistent                          23.6  26.9  33.7  41.6  65.5      35        42    91        32    45    92
+//     staged            9.3   15.0  18.6  25.1  31.0  38.6  48.6  75.8      30        46    103       42    58    113
+//     128 x 256 (x 2)   14.8  21    24    29    35    42    50    73        38        41    47        43    46    51
 struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed, once; };
 constexpr GemmTile kGemmTiles[] = {
     {256, 256, 1, 1.35f, 0.f, 5.f, 7.f},     // gemm_persistent_kernel
@@ -65,9 +66,10 @@ constexpr GemmTile kGemmTiles[] = {
     {256, 256, 1, 2.0f, 0.f, 5.5f, 0.f},     // gemm_staged_kernel
 };
 constexpr int32_t kPersistentTile = 0, kStagedTile = 5;
-constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f, kKTailRank = 2.f;     // (kKTailRank: per 32 ranks beyond the first 32)
-struct SegmentCost { float ktail, staged; };
-constexpr SegmentCost kSegmentCost = {1.5f, 1.0f};     // us per round and segment of a tile row beyond the first
+constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f, kKTailRank = 0.75f;  // (kKTailRank: per 32 ranks beyond the first 32)
+// us per round and segment of a tile row beyond the first (persistent kernel: ranks up to 16, above)
+struct SegmentCost { float persistent16, persistent, staged; };
+constexpr SegmentCost kSegmentCost = {0.8f, 1.4f, 1.0f};
 constexpr int32_t kGemmKTile = 64;
 // The persistent kernel's loop for such a K needs an ordinary pair of K tiles in front of the two special ones (K > 256).  It runs
 // from here on, where it is the better one for wide products (30000 x 520 x 1000 / 2048 / 7552, staged / persistent: 62 / 76,
@@ -135,9 +137,12 @@ struct Plan {
     // One record of kGemmTileRec ints per tile row of the base GEMM (tile row i starts at token
     // min(i kGemmTileRows, T - kGemmTileRows), never below 0): the compacted segment that holds that token, its
     // first and last + 1 token, its task (-1: none), and that task's first rank row and stacked rank
-    // (0, 0 without a task); the rest is padding.  One 32-byte read tells a GEMM workgroup what the fused
-    // up projection of a tile starts with.
+    // (0, 0 without a task); the rest is padding.  (For lobra_mlora_plan_query; the kernels read the next table.)
     std::vector<int32_t> gemm_tile_tab; // [ceil(T/kGemmTileRows)][kGemmTileRec]
+    // One record of kGemmTileSegRec ints per tile row, which one 64-byte read brings to a GEMM workgroup: the first kGemmTileSegs
+    // segments with an adapter that cross it - first token, last + 1, the task's first rank row and stacked rank (0 where there
+    // is no such segment) - and the compacted segment at which to look for further ones.
+    std::vector<int32_t> gemm_tile_seg; // [ceil(T/kGemmTileRows)][kGemmTileSegRec]
     std::vector<TokenBlock> tb;         // grouped by task, token order inside a task
     std::vector<int32_t> task_tb_off;   // [n_tasks+1]
     std::vector<int32_t> sb_off;        // [nsb+1] runs of <= shrink_group token blocks of one task
@@ -197,7 +202,7 @@ struct Plan {
     // offsets (in int32 units) of the lists inside the blob
     size_t o_cseg_off = 0, o_cseg_task = 0, o_rowblk = 0, o_tb = 0, o_chunks = 0,
            o_task_chunk = 0, o_rank_off = 0, o_task_tb = 0, o_sb = 0, o_tb_order = 0, o_sb_order = 0,
-           o_fb_wg = 0, o_fb_run = 0, o_fb_cnt = 0, o_fb_row0 = 0, o_tile_tab = 0;
+           o_fb_wg = 0, o_fb_run = 0, o_fb_cnt = 0, o_fb_row0 = 0, o_tile_seg = 0;
 };
 
 lobra_status validate(const lobra_mlora_desc* d);

@@ -166,6 +166,24 @@ def test_persistent_gemm_tile_edges_and_round_remainders(T, d_in, d_out):
     check_problem(p, rows=rows, label="edges")
 
 
+@pytest.mark.parametrize("d_in,d_out,n_proj", [(2048, 2048, 1), (2056, 2048, 1), (2048, 4096, 2)])
+def test_persistent_gemm_up_projection_of_many_segments(d_in, d_out, n_proj):
+    """Tiles that up to a dozen segments cross, with and without adapter: more than the table holds, windows of 16 ranks and fewer
+    that share a step with the next segment's, or cannot because that one has more, and windows of several steps.  (22 tile
+    rows of 8 columns: products of the persistent kernel, whole K tiles and not.)"""
+    T, ranks = 5632 + 13, [16, 8, 40, 16, 24, 128] if n_proj == 1 else [16, 8, 40, 56]
+    rng = np.random.default_rng(d_in)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.choice([1, 3, 17, 60, 90, 400])), T - sum(lens)))
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("up-%d-%d" % (d_in, d_out), "bf16", d_in, d_out // n_proj, ranks, np.concatenate([[0], np.cumsum(lens)]),
+                       rng.integers(-1, len(ranks), len(lens)), 37, s=np.linspace(-1, 2, len(ranks)).astype(np.float32),
+                       fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    check_problem(p, rows=sample_rows(p, 100)[::3], label="up")
+
+
 @pytest.mark.parametrize("d_in,d_out", [
     (72, 4104),       # a whole K tile and 8 of the next; backward: 65 K tiles, the last of 8, on two narrow column tiles
     (8, 4000),        # K shorter than a K tile
