@@ -573,8 +573,8 @@ inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 struct UploadPiece { int32_t v[1008]; };      // with the other arguments just below the 4 KiB of a launch
 // A piece takes 2.3 us of stream time; a copy from pageable memory and the host callback that releases it take 55 to 62 us
 // (73 to 166 KB of tables, with the host ahead of the stream; some 180 us a call where it is not: padded chunks of 3072
-// tokens, four calls, 730 -> 173 us).  So 25 pieces are worth it; up to 17 are sent, 64 KiB (some 35000 tokens in segments of 20).
-constexpr size_t kUploadByArgument = 64 * 1024;
+// tokens, four calls, 730 -> 173 us).  So 25 pieces are worth it; up to 21 are sent, 80 KiB (some 35000 tokens in segments of 20).
+constexpr size_t kUploadByArgument = 80 * 1024;
 
 __global__ __launch_bounds__(256) void upload_kernel(int32_t* __restrict__ dst, int32_t n, UploadPiece piece)
 {

@@ -10,7 +10,7 @@ namespace lobra {
 // Device pointers into the plan blob, passed to kernels by value.
 struct PlanDev {
     const int32_t* cseg_off;       // [nseg+1]
-    const int32_t* cseg_task;      // [nseg]
+    const int32_t* cseg_task;      // [3][nseg]: the segments' tasks (-1: none), these tasks' first rank rows, their stacked ranks
     const int32_t* rowblk_seg;     // [ceil(T/32)]
     const TokenBlock* tb;          // [ntb]
     const GradChunk* chunks;       // [nchunks]

@@ -32,6 +32,7 @@
 //   C staging in the epilogue: per wave [rows][cols + 8] bf16, written back with non-temporal stores.
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
 
 #include "gemm_common.h"
 #include "kernels.h"
@@ -56,10 +57,10 @@ template <int TN> __device__ __forceinline__ int swz_kn(int k)
 }
 
 // What a tile's rows belong to, in LDS behind the ring: the segments that cross the tile (at most one per row), each with
-// its first token, task, rank window and the first of them that has the same task; which of them are such firsts; and
-// per row the first segment of its task (-1: no adapter).
+// its first token, task and rank window; which of them are the first of their task; and per row the first segment of its
+// task (-1: no adapter).
 template <int TM> struct alignas(16) TileTable {
-    int32_t lo[TM], task[TM], r0[TM], r[TM], first[TM], row[TM];
+    int32_t lo[TM], task[TM], r0[TM], r[TM], row[TM];
     uint64_t firsts[(TM + 63) / 64];
 };
 
@@ -98,7 +99,14 @@ template <int TM, int TN, int WN, int STAGES> constexpr int ring_bytes()
     return loop;
 }
 
-template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES>
+// Rank rows (whole groups of eight) of adapter slices that fit behind ring and table, with OCC workgroups on a compute unit: up to 96.
+template <int TM, int TN, int WN, int STAGES, int OCC> constexpr int ahead_rows()
+{
+    const int left = 160 * 1024 / OCC - ring_bytes<TM, TN, WN, STAGES>() - int(sizeof(TileTable<TM>));
+    return std::min(left / (TN * 2) / 8 * 8, 96);
+}
+
+template <bool W_KN, int TM, int TN, int WM, int WN, int STAGES, int AHEAD>
 __device__ __forceinline__
 void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t* __restrict__ W,
                const uint16_t* __restrict__ P, const uint16_t* __restrict__ M,
@@ -150,6 +158,7 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
 
     // ---- copies.  Block b (1 KiB) of a [rows][64 k] tile holds rows 8 b .. 8 b + 7, of a [k][n] tile the k rows
     //      RPC b ..; wave w moves blocks w, w + NW, ...; the swizzle is applied to the address a lane fetches from.
+    const int32_t sg0 = P ? pd.rowblk_seg[row0 / kRowBlock] : 0;     // (in front of the copies: a scalar load)
     const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)lds));
     const unsigned char* zbase = reinterpret_cast<const unsigned char*>(Z + size_t(row0) * K);
     const unsigned char* wbase = reinterpret_cast<const unsigned char*>(W_KN ? W + col0 : W + size_t(col0) * ldw);
@@ -210,13 +219,13 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
         const int row = wm * WTM + mb * 16 + j;
         return *reinterpret_cast<const bf16x8*>(st + row * (BK * 2) + (((4 * ks + kg) ^ swz_row(j)) << 4));
     };
-    auto read_kn = [&](const unsigned char* base, int krow0, int nb) __attribute__((always_inline)) {
+    auto read_kn = [&](const unsigned char* base, int krow0, int nb, int kg) __attribute__((always_inline)) {
         const int krow = krow0 + 8 * kg + (j >> 2);
         const int n = wn * WTN + nb * 16 + 4 * (j & 3);
         return tr_pair(base + krow * (TN * 2) + (((n >> 3) ^ swz_kn<TN>(krow)) << 4) + (n & 7) * 2, TN * 2);
     };
     auto read_w = [&](const unsigned char* st, int ks, int nb) __attribute__((always_inline)) {
-        if (W_KN) return read_kn(st + ZT, 32 * ks, nb);
+        if (W_KN) return read_kn(st + ZT, 32 * ks, nb, kg);
         const int row = wn * WTN + nb * 16 + j;
         return *reinterpret_cast<const bf16x8*>(st + ZT + row * (BK * 2) + (((4 * ks + kg) ^ swz_row(j)) << 4));
     };
@@ -282,54 +291,132 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * STAGE); });
         else if (s < KT) copy_tail(la0 + s * STAGE);
         next_copy_tile();
-    }
-    // What this tile's rows belong to, worked out while the first copies are on their way.  (A batch of decoding requests has
-    // a segment per token; one chain of table reads and one staging of adapter rows per segment, behind the main loop, took
-    // longer than the product: 39 us where this takes 24, 40 one-token segments of eight tasks, K = N = 4096.)
-    if (P) {
-        const int32_t sg = pd.rowblk_seg[row0 / kRowBlock] + tid;    // (the segment of the tile's first row, and those behind it)
-        const bool in = tid < TM && sg < pd.nseg && pd.cseg_off[min(sg, pd.nseg - 1)] < min(row0 + TM, T);
-        int32_t t = -1;
-        if (tid < TM) {
-            t = in ? pd.cseg_task[sg] : -1;
-            const int32_t r0 = t >= 0 ? pd.rank_off[t] : 0, r = t >= 0 ? (pd.rank_off[t + 1] - r0) / nproj : 0;
-            tab.lo[tid] = in ? pd.cseg_off[sg] : 0x7fffffff;
-            tab.task[tid] = t;
-            tab.r0[tid] = r0 + pj * r;
-            tab.r[tid] = r;
-        }
-        lds_barrier();
-        int32_t first = tid;
-        if (tid < TM) {
-            // (eight at a time: one LDS latency per eight; what lies beyond the last segment has task -1)
-            for (int32_t i = 0; i < TM && tab.lo[i] != 0x7fffffff; i += 8) {         // (uniform)
-                const int4 a = *reinterpret_cast<const int4*>(&tab.task[i]), b = *reinterpret_cast<const int4*>(&tab.task[i + 4]);
-                const int32_t e[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-                for (int u = 7; u >= 0; --u)
-                    if (e[u] == t) first = min(first, i + u);
-            }
-            tab.first[tid] = first;
-        }
-        const uint64_t firsts = __ballot(t >= 0 && first == tid);
-        if (wave < (TM + 63) / 64 && lane == 0) tab.firsts[wave] = firsts;
-        lds_barrier();
-        if (tid < TM) {
-            int32_t a = 0, b = TM;                   // the last segment that starts at or before the row
-            while (b - a > 1) {
-                const int32_t m = (a + b) >> 1;
-                if (tab.lo[m] <= row0 + tid) a = m;
-                else b = m;
-            }
-            tab.row[tid] = (row0 + tid < T && tab.task[a] >= 0) ? tab.first[a] : -1;
+        // the segments from the tile's first row on, one a lane, behind the first K tile's copies: the chain of reads through
+        // registers in front of them or behind all of them kept the main loop waiting for one or the other
+        if (s == 0 && P && wave < TM / 64) {
+            const uint32_t to = lds0 + STAGES * STAGE + wave * 256, at = 4u * uint32_t(min(sg0 + wave * 64 + lane, pd.nseg - 1));
+            dma4(to + offsetof(TileTable<TM>, lo), pd.cseg_off, at);
+            dma4(to + offsetof(TileTable<TM>, task), pd.cseg_task, at);
+            dma4(to + offsetof(TileTable<TM>, r0), pd.cseg_task + pd.nseg, at);
+            dma4(to + offsetof(TileTable<TM>, r), pd.cseg_task + 2 * size_t(pd.nseg), at);
         }
     }
     bf16x8 za[MB], wa[NB], zb[MB], wb[NB];
     if (KT >= STAGES) wait_vmcnt<(STAGES - 1) * CPW>();
     else wait_vmcnt<0>();
-    // (the barrier does not wait for LDS, and with a single K tile, or none - the adapter term's workgroup of a split
-    //  product -, it is the last one in front of the epilogue's reads of tab.row)
     lds_barrier();
+    // What this tile's rows belong to, worked out while further K tiles are on their way.  (A batch of decoding requests has a
+    // segment per token; one chain of table reads and one staging of adapter rows per segment, behind the main loop, took
+    // longer than the product: 39 us where this takes 24, 40 one-token segments of eight tasks, K = N = 4096.)
+    if (P) {
+        const int32_t sg = sg0 + tid;
+        int32_t t = -1;
+        if (tid < TM) {
+            const int32_t lo = tab.lo[tid];
+            const bool in = sg < pd.nseg && lo < min(row0 + TM, T);
+            t = in ? tab.task[tid] : -1;
+            const int32_t r = t >= 0 ? (nproj == 1 ? tab.r[tid] : tab.r[tid] / nproj) : 0;
+            if (!in) tab.lo[tid] = 0x7fffffff;
+            tab.task[tid] = t;
+            tab.r0[tid] += pj * r;
+            tab.r[tid] = r;
+        }
+        lds_barrier();
+        // the task of thread's row, then the first segment of that task, and whether the thread's own segment is such a first (the
+        // table is read eight segments at a time, all threads the same; what lies beyond the last segment has task -1)
+        int32_t row_task = -1, row_first = TM, first = TM;
+        auto segments = [&](auto&& f) __attribute__((always_inline)) {
+            for (int32_t i = 0; i < TM && tab.lo[i] != 0x7fffffff; i += 8) {         // (uniform)
+                const int4 a = *reinterpret_cast<const int4*>(&tab.task[i]), b = *reinterpret_cast<const int4*>(&tab.task[i + 4]);
+                const int32_t e[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                f(i, e);
+            }
+        };
+        if (tid < TM) {
+            segments([&](int32_t i, const int32_t (&e)[8]) {
+                const int4 a = *reinterpret_cast<const int4*>(&tab.lo[i]), b = *reinterpret_cast<const int4*>(&tab.lo[i + 4]);
+                const int32_t lo[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (lo[u] <= row0 + tid) row_task = e[u];
+            });
+            segments([&](int32_t i, const int32_t (&e)[8]) {
+#pragma unroll
+                for (int u = 7; u >= 0; --u) {
+                    if (e[u] == t) first = min(first, i + u);
+                    if (e[u] == row_task) row_first = min(row_first, i + u);
+                }
+            });
+            tab.row[tid] = (row0 + tid < T && row_task >= 0) ? row_first : -1;
+        }
+        const uint64_t firsts = __ballot(t >= 0 && first == tid);
+        if (wave < (TM + 63) / 64 && lane == 0) tab.firsts[wave] = firsts;
+        lds_barrier();
+    }
+    // ---- fused up projection: for every task with rows in this tile, ceil(r_t / 32) extra K steps
+    //      acc += M_t^T[:, cols] * P[rows, :]^T with the rows of other tasks masked to zero.  The M_t slices [r_t][TN cols] are
+    //      copied to LDS in the [k][n] layout and gathered with the transpose read; rows of a slice from r_t up to the next
+    //      multiple of 8 repeat row r_t - 1, and what lies beyond r_t is cleared in registers.  P comes straight from global
+    //      memory, 16 bytes per lane and rank step.  The first step's P and the slices of as many tasks as fit AHEAD rank rows
+    //      behind the table are fetched some K tiles before the main loop ends (prepare_up); further slices go into the ring
+    //      behind it, as many at a time as fit.
+    //      The loops over tasks and their barriers are uniform over the workgroup.
+    //      (With the table's chain of reads waiting for all of the first copies, and slices and P fetched behind the main loop,
+    //      x [1000, 4096] times W [4096, 4096] with four tasks of rank 16 took 41.4 us, 5 more than without adapters, like this
+    //      39.0; x [1108, 1088] W [1088, 6400] with its projection 26.2 -> 25.2.)
+    constexpr int ROWS = STAGES * STAGE / (TN * 2);
+    constexpr int AHEAD_TILES = AHEAD ? 4 : 0;       // (with the ring's: so many K tiles in front of the end)
+    unsigned char* const ahead = lds + STAGES * STAGE + int(sizeof(TileTable<TM>));
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+    int32_t of[MB], rw[MB];                          // first segment and rank of the row's task
+    u32x4 pv[MB], pn[MB];                            // this rank step's P fragments and the next one's
+    // the P fragments of rank step s: lane (j, kg) holds the ranks 32 s + 8 kg .. + 7 of token row j of each 16-row
+    // block; groups that start beyond r_t hold padding, or another projection's ranks, and are not read
+    auto load_p = [&](int32_t s) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int32_t row = min(row0 + wm * WTM + mb * 16 + j, T - 1), k = 32 * s + 8 * kg;
+            pn[mb] = k < rw[mb] ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * rw[mb] + k) : zero4;
+        }
+    };
+    // rank and first rank row of segment i, out of the lanes' registers
+    constexpr int SEGW = (TM + 63) / 64;
+    int32_t lane_r[SEGW], lane_r0[SEGW];
+    auto of_segment = [&](const int32_t (&v)[SEGW], int32_t i) __attribute__((always_inline)) {
+        return __builtin_amdgcn_readlane(v[SEGW > 1 && i >= 64 ? SEGW - 1 : 0], i & 63);
+    };
+    TaskSet<TM> left, batch;                         // the tasks whose slices are still to be copied; those copied last
+    auto copy_slices = [&](uint32_t to, int32_t room) {              // of as many of those left as fit
+        batch = left;
+        int32_t rows = 0;
+        for (int32_t i = left.lowest(); i >= 0; i = left.lowest()) {
+            const int32_t r = of_segment(lane_r, i), rp = (r + 7) & ~7;
+            if (rows + rp > room) break;
+            const unsigned char* mbase = reinterpret_cast<const unsigned char*>(M + size_t(of_segment(lane_r0, i)) * mpitch + (col0 - mcol0));
+            for (int32_t c = wave; c < rp / RPC; c += NW) {
+                const int krow = RPC * c + lane / CR;
+                dma16(to + rows * (TN * 2) + c * 1024, mbase,
+                      (uint32_t(min(krow, r - 1)) * uint32_t(mpitch) + uint32_t(min(8 * ((lane % CR) ^ swz_kn<TN>(krow)), N - 8 - col0))) * 2u);
+            }
+            rows += rp;
+            left.remove_lowest();
+        }
+        batch.remove(left);
+    };
+    auto prepare_up = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            of[mb] = tab.row[wm * WTM + mb * 16 + j];
+            rw[mb] = of[mb] >= 0 ? tab.r[of[mb]] : 0;
+        }
+        load_p(0);
+#pragma unroll
+        for (int w = 0; w < SEGW; ++w) lane_r[w] = tab.r[64 * w + lane % TM], lane_r0[w] = tab.r0[64 * w + lane % TM];
+        left.load(tab.firsts);
+        // (vector memory operations complete in order, so the main loop's counted waits, which are about copies issued before
+        //  or after these, wait for no less than they did)
+        copy_slices(lds0 + STAGES * STAGE + int(sizeof(TileTable<TM>)), AHEAD);
+    };
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) wa[nb] = read_w(lds, 0, nb);
 #pragma unroll
@@ -351,8 +438,11 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
     };
     if (steady > 0) {
         body(none{});
-        for (kt = 1; kt < steady; ++kt) body(half1{});
+        for (kt = 1; kt < steady - AHEAD_TILES; ++kt) body(half1{});
     }
+    if (P) prepare_up();
+    if constexpr (AHEAD > 0)
+        for (; kt < steady; ++kt) body(half1{});
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;           // uniform
         if (tail) clear_tail(0, za, wa);
@@ -377,95 +467,64 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
         slot = ns;
     }
 
-    // ---- fused up projection: for every task with rows in this tile, ceil(r_t / 32) extra K steps
-    //      acc += M_t^T[:, cols] * P[rows, :]^T with the rows of other tasks masked to zero.  The M_t slices [r_t][TN cols] are
-    //      copied into the ring (free now) in the [k][n] layout, as many tasks at a time as fit, and gathered with the
-    //      transpose read; rows of a slice from r_t up to the next multiple of 32 repeat row r_t - 1 and are cleared in
-    //      registers.  P comes straight from global memory, 16 bytes per lane and rank step.
-    //      The loops over tasks and their barriers are uniform over the workgroup.
+    // ---- the up projection's steps
     if (P) {
-        constexpr int ROWS = STAGES * STAGE / (TN * 2);
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
-        auto rfl = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
-        // the P fragments of rank step s: lane (j, kg) holds the ranks 32 s + 8 kg .. + 7 of token row j of each 16-row
-        // block; groups that start beyond r_t hold padding, or another projection's ranks, and are not read
         const int32_t nks = (pd.r_max / nproj + 31) >> 5;            // rank steps of the widest window (uniform)
-        int32_t of[MB], rw[MB];                      // first segment and rank of the row's task
-        u32x4 pv[MB], pn[MB];                        // this rank step's and the next one's
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            of[mb] = tab.row[wm * WTM + mb * 16 + j];
-            rw[mb] = of[mb] >= 0 ? tab.r[of[mb]] : 0;
-        }
-        auto load_p = [&](int32_t s) {
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int32_t row = min(row0 + wm * WTM + mb * 16 + j, T - 1), k = 32 * s + 8 * kg;
-                pn[mb] = k < rw[mb] ? *reinterpret_cast<const u32x4*>(P + size_t(row) * pd.r_pad + pj * rw[mb] + k) : zero4;
-            }
-        };
-        load_p(0);
-        TaskSet<TM> left;
-        left.load(tab.firsts);
-        while (!left.empty()) {
-            lds_barrier();                           // everybody is done with what the LDS held before
-            TaskSet<TM> batch = left;                // the tasks staged now: as many of those left as fit
-            int32_t rows = 0;
-            for (int32_t i = left.lowest(); i >= 0; i = left.lowest()) {
-                const int32_t r = rfl(tab.r[i]), rp = (r + 31) & ~31;
-                if (rows + rp > ROWS) break;
-                const unsigned char* mbase = reinterpret_cast<const unsigned char*>(M + size_t(rfl(tab.r0[i])) * mpitch + (col0 - mcol0));
-                for (int32_t c = wave; c < rp / RPC; c += NW) {
-                    const int krow = RPC * c + lane / CR;
-                    dma16(lds0 + rows * (TN * 2) + c * 1024, mbase,
-                          (uint32_t(min(krow, r - 1)) * uint32_t(mpitch) + uint32_t(min(8 * ((lane % CR) ^ swz_kn<TN>(krow)), N - 8 - col0))) * 2u);
-                }
-                rows += rp;
-                left.remove_lowest();
-            }
-            batch.remove(left);
+        const unsigned char* at = ahead;
+        // (with two K tiles and more the last barrier is behind a wait for all that was copied ahead)
+        if (KT < 2) {
             wait_vmcnt<0>();
             lds_barrier();
-            for (int32_t s = 0; s < nks; ++s) {
+        }
+        for (;;) {
+            if (!batch.empty())
+                for (int32_t s = 0; s < nks; ++s) {
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) pv[mb] = pn[mb];
-                if (nks > 1) load_p(s + 1 < nks ? s + 1 : 0);
-                const unsigned char* slice = lds;
-                TaskSet<TM> todo = batch;
-                for (int32_t i = todo.lowest(); i >= 0; i = todo.lowest()) {
-                    todo.remove_lowest();
-                    const int32_t r = rfl(tab.r[i]);
-                    bool mine[MB], some = false;     // wave-uniform: a row of this block is the task's
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        mine[mb] = __ballot(of[mb] == i) != 0;
-                        some |= mine[mb];
-                    }
-                    if (some && 32 * s < r) {
-                        const int nv = min(max(r - 32 * s - 8 * kg, 0), 8);
-                        u32x4 km;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
-                        bf16x8 wf[NB];
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) {
-                            union { bf16x8 b; u32x4 u; } cv;
-                            cv.b = read_kn(slice, 32 * s, nb);
-                            cv.u &= km;
-                            wf[nb] = cv.b;
-                        }
+                    for (int mb = 0; mb < MB; ++mb) pv[mb] = pn[mb];
+                    if (nks > 1) load_p(s + 1 < nks ? s + 1 : 0);
+                    const unsigned char* slice = at;
+                    TaskSet<TM> todo = batch;
+                    for (int32_t i = todo.lowest(); i >= 0; i = todo.lowest()) {
+                        todo.remove_lowest();
+                        const int32_t r = of_segment(lane_r, i);
+                        bool mine[MB], some = false; // wave-uniform: a row of this block is the task's
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb) {
-                            if (!mine[mb]) continue;
-                            const bf16x8 pf = as_bf16x8(of[mb] == i ? pv[mb] : zero4);
-#pragma unroll
-                            for (int nb = 0; nb < NB; ++nb)
-                                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf, acc[mb][nb], 0, 0, 0);
+                            mine[mb] = __ballot(of[mb] == i) != 0;
+                            some |= mine[mb];
                         }
+                        if (some && 32 * s < r) {
+                            const int nv = min(max(r - 32 * s - 8 * kg, 0), 8);
+                            const int kgs = min(kg, ((r - 32 * s + 7) >> 3) - 1);      // (groups beyond the slice read its last one)
+                            u32x4 km;
+#pragma unroll
+                            for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
+                            bf16x8 wf[NB];
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb) {
+                                union { bf16x8 b; u32x4 u; } cv;
+                                cv.b = read_kn(slice, 32 * s, nb, kgs);
+                                cv.u &= km;
+                                wf[nb] = cv.b;
+                            }
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb) {
+                                if (!mine[mb]) continue;
+                                const bf16x8 pf = as_bf16x8(of[mb] == i ? pv[mb] : zero4);
+#pragma unroll
+                                for (int nb = 0; nb < NB; ++nb)
+                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf, acc[mb][nb], 0, 0, 0);
+                            }
+                        }
+                        slice += ((r + 7) & ~7) * (TN * 2);
                     }
-                    slice += ((r + 31) & ~31) * (TN * 2);
                 }
-            }
+            if (left.empty()) break;
+            lds_barrier();                           // everybody is done with what the ring held before
+            copy_slices(lds0, ROWS);
+            at = lds;
+            wait_vmcnt<0>();
+            lds_barrier();
         }
     }
     if (splits > 1 || !C) {                         // the sums as they are, 16 bytes per lane
@@ -523,7 +582,7 @@ void gemm_tile_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t
                       float* __restrict__ part)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    tile_body<W_KN, TM, TN, WM, WN, STAGES>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, GM, splits, part,
+    tile_body<W_KN, TM, TN, WM, WN, STAGES, ahead_rows<TM, TN, WN, STAGES, OCC>()>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_m, tiles_n, GM, splits, part,
                                             int32_t(blockIdx.x), lds);
 }
 
@@ -547,7 +606,7 @@ void gemm_tile_beside_kernel(PlanDev pd, const uint16_t* __restrict__ Z, const u
             ring_item<1, 1, 1, 256, kBesideLds>(pd, Z, D, s, P_tok, P_blk, K, K, 1, 0, rparts, wg % pd.ntb, wg / pd.ntb, lds);
         return;
     }
-    tile_body<W_KN, TM, TN, WM, WN, STAGES>(pd, Z, W, nullptr, nullptr, nullptr, K, N, ldw, N, 1, 0, tiles_m, tiles_n, GM, splits, part,
+    tile_body<W_KN, TM, TN, WM, WN, STAGES, 0>(pd, Z, W, nullptr, nullptr, nullptr, K, N, ldw, N, 1, 0, tiles_m, tiles_n, GM, splits, part,
                                             wg - pwgs, lds);
 }
 
@@ -639,8 +698,8 @@ static hipError_t launch_tile(const PlanDev& pd, const void* Z, const void* W, c
                               const void* M, void* C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
                               int32_t nproj, int32_t proj, hipStream_t st, int32_t splits, float* part)
 {
-    constexpr int bytes = ring_bytes<TM, TN, WN, STAGES>() + int(sizeof(TileTable<TM>));
-    static_assert(bytes * OCC <= 160 * 1024, "LDS budget");
+    constexpr int bytes = ring_bytes<TM, TN, WN, STAGES>() + int(sizeof(TileTable<TM>)) + ahead_rows<TM, TN, WN, STAGES, OCC>() * TN * 2;
+    static_assert(bytes * OCC <= 160 * 1024 && ahead_rows<TM, TN, WN, STAGES, OCC>() >= 16, "LDS budget");
     // the kernel needs more dynamic LDS than the default limit: raise it once per device
     static std::atomic<uint64_t> raised{0};
     int dev = 0;

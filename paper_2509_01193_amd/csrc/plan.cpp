@@ -516,7 +516,17 @@ std::vector<int32_t> pack_blob(Plan* p)
         return off;
     };
     p->o_cseg_off = put(p->cseg_off.data(), p->cseg_off.size());
-    p->o_cseg_task = put(p->cseg_task.data(), p->cseg_task.size());
+    {
+        const size_t nseg = p->cseg_task.size();
+        std::vector<int32_t> rows(3 * nseg, 0);
+        for (size_t k = 0; k < nseg; ++k) {
+            const int32_t t = rows[k] = p->cseg_task[k];
+            if (t < 0) continue;
+            rows[nseg + k] = p->rank_off[t];
+            rows[2 * nseg + k] = p->rank_off[t + 1] - p->rank_off[t];
+        }
+        p->o_cseg_task = put(rows.data(), rows.size());
+    }
     p->o_rowblk = put(p->rowblk_seg.data(), p->rowblk_seg.size());
     p->o_tb = put(reinterpret_cast<const int32_t*>(p->tb.data()), p->tb.size() * 4);
     p->o_chunks = put(reinterpret_cast<const int32_t*>(p->chunks.data()), p->chunks.size() * 4);

@@ -226,6 +226,25 @@ def test_tiled_gemm_every_tile_size_and_ring_remainder(d_in, d_out):
                 assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5 * b.abs().max()).all()), T
 
 
+@pytest.mark.parametrize("T,d_in,d_out,ranks,longest", [
+    (200, 48, 520, [16] * 24, 1),               # a single K tile; two dozen tasks in every tile: their slices in several batches
+    (200, 520, 48, [128, 100, 8], 9),           # slices of more rank rows than fit ahead, and one that fits
+    (1300, 328, 2056, [16, 5, 40, 96, 1], 60),  # 128-row tiles; ranks that are no multiple of 8
+    (900, 4096, 2048, [16, 24], 300),           # the main loop long enough for the copies to go out inside it
+    (2100, 712, 4096, [24, 16, 8], 40),         # 128 x 256: room for 24 rank rows
+])
+def test_tiled_gemm_up_projection_slices_ahead(T, d_in, d_out, ranks, longest):
+    """Adapter slices that are copied while the tiled product runs, those that are not, and both in one tile."""
+    rng = np.random.default_rng(T + d_in)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.integers(1, longest + 1)), T - sum(lens)))
+    p = wl.make_custom("ahead-%dx%dx%d" % (T, d_in, d_out), "bf16", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]),
+                       rng.integers(-1, len(ranks), len(lens)), 41, s=np.linspace(-1, 2, len(ranks)).astype(np.float32),
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    check_problem(p, rows=sample_rows(p, 100)[:: 1 + T // 500], label="ahead")
+
+
 @pytest.mark.parametrize("T,d_in,d_out,ranks,longest,beside", [
     (1, 4096, 1032, [7], 1, (True, True)),                  # a single token; a rank below one rank block
     (128, 2056, 264, [16, 17], 1, (True, False)),           # one-token segments: 128 blocks of two rank blocks, the most that goes in one launch
