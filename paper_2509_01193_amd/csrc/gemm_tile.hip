@@ -297,8 +297,8 @@ void tile_body(const PlanDev& pd, const uint16_t* __restrict__ Z, const uint16_t
             const uint32_t to = lds0 + STAGES * STAGE + wave * 256, at = 4u * uint32_t(min(sg0 + wave * 64 + lane, pd.nseg - 1));
             dma4(to + offsetof(TileTable<TM>, lo), pd.cseg_off, at);
             dma4(to + offsetof(TileTable<TM>, task), pd.cseg_task, at);
-            dma4(to + offsetof(TileTable<TM>, r0), pd.cseg_task + pd.nseg, at);
-            dma4(to + offsetof(TileTable<TM>, r), pd.cseg_task + 2 * size_t(pd.nseg), at);
+            dma4(to + offsetof(TileTable<TM>, r0), cseg_rank(pd), at);
+            dma4(to + offsetof(TileTable<TM>, r), cseg_rank(pd) + pd.nseg, at);
         }
     }
     bf16x8 za[MB], wa[NB], zb[MB], wb[NB];

@@ -516,17 +516,7 @@ std::vector<int32_t> pack_blob(Plan* p)
         return off;
     };
     p->o_cseg_off = put(p->cseg_off.data(), p->cseg_off.size());
-    {
-        const size_t nseg = p->cseg_task.size();
-        std::vector<int32_t> rows(3 * nseg, 0);
-        for (size_t k = 0; k < nseg; ++k) {
-            const int32_t t = rows[k] = p->cseg_task[k];
-            if (t < 0) continue;
-            rows[nseg + k] = p->rank_off[t];
-            rows[2 * nseg + k] = p->rank_off[t + 1] - p->rank_off[t];
-        }
-        p->o_cseg_task = put(rows.data(), rows.size());
-    }
+    p->o_cseg_task = put(p->cseg_task.data(), p->cseg_task.size());
     p->o_rowblk = put(p->rowblk_seg.data(), p->rowblk_seg.size());
     p->o_tb = put(reinterpret_cast<const int32_t*>(p->tb.data()), p->tb.size() * 4);
     p->o_chunks = put(reinterpret_cast<const int32_t*>(p->chunks.data()), p->chunks.size() * 4);
@@ -540,7 +530,19 @@ std::vector<int32_t> pack_blob(Plan* p)
     p->o_fb_run = put(p->fb_run_row.data(), p->fb_run_row.size());
     p->o_fb_cnt = put(p->fb_cnt.data(), p->fb_cnt.size());
     p->o_fb_row0 = put(p->fb_task_row0.data(), p->fb_task_row0.size());
-    p->o_tile_seg = put(p->gemm_tile_seg.data(), p->gemm_tile_seg.size());
+    {
+        // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
+        const size_t nseg = p->cseg_task.size(), at = p->gemm_tile_seg.size();
+        std::vector<int32_t> list(p->gemm_tile_seg);
+        list.resize(at + 2 * nseg, 0);
+        for (size_t k = 0; k < nseg; ++k) {
+            const int32_t t = p->cseg_task[k];
+            if (t < 0) continue;
+            list[at + k] = p->rank_off[t];
+            list[at + nseg + k] = p->rank_off[t + 1] - p->rank_off[t];
+        }
+        p->o_tile_seg = put(list.data(), list.size());
+    }
     while (blob.size() % 4) blob.push_back(0);
     return blob;
 }

@@ -132,8 +132,7 @@ struct Plan {
     int32_t dg = 0;                     // d_out / n_proj: width of B and dB
     std::vector<int32_t> rank_off;      // [n_tasks+1]
     std::vector<int32_t> seg_off_in, seg_task_in;   // the caller's table, as given
-    std::vector<int32_t> cseg_off, cseg_task;       // compacted table (on the device cseg_task is [3][segments]: the segments'
-                                        // tasks, then these tasks' first rank rows, then their stacked ranks)
+    std::vector<int32_t> cseg_off, cseg_task;       // compacted table
     std::vector<int32_t> rowblk_seg;    // [ceil(T/32)]
     // One record of kGemmTileRec ints per tile row of the base GEMM (tile row i starts at token
     // min(i kGemmTileRows, T - kGemmTileRows), never below 0): the compacted segment that holds that token, its
