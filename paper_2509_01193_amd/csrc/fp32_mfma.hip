@@ -12,6 +12,7 @@
 //
 // VEC: rows start on 16-byte boundaries and end on them (widths that are multiples of 4).  Other widths take the same
 // kernels with loads at any element and guards at the rows' ends.
+#include "gemm_common.h"
 #include "kernels.h"
 
 namespace lobra {
@@ -42,9 +43,8 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __bui
 }  // namespace
 
 // -------------------------------------------------------------------------------------------
-// gemm: TM x TN per workgroup of 2 x 2 waves, K step FBK, global -> registers -> LDS one K step ahead.  Bound by the matrix
-// cores: a K step of a 64 x 64 tile is 1024 cycles of MFMAs and a quarter of that in LDS reads (8192 x 2048 x 2048: 120
-// TFLOP/s, without the global loads 127, of 157).  The adapter term is further K steps per segment, with the rows
+// gemm: TM x TN per workgroup of 2 x 2 waves, K step FBK, global -> registers -> LDS one K step ahead: for tiles of 32, and for rows that
+// start anywhere (gemm_f32_ring_kernel has the rest).  Bound by the matrix cores and the barriers around the way to LDS.  The adapter term is further K steps per segment, with the rows
 // outside the segment masked; where more than kFewSegments segments cross the tile, per task that has rows in it (8000
 // one-token segments of 8 tasks of rank 128, 10 x 1373: 4820 -> 290 us; 10119 tokens in segments of 3, rank 8, 64 x 1920: 390 -> 112).
 // -------------------------------------------------------------------------------------------
@@ -298,25 +298,376 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* 
     }
 }
 
+// -------------------------------------------------------------------------------------------
+// The same for rows on 16-byte boundaries and many tiles: K tiles of 32 come through a ring of STAGES LDS slots that direct global -> LDS
+// copies fill, one counted wait and one barrier each; the fragments of 16 k are read while the ones before are multiplied, every
+// read and copy behind an MFMA (pinned by sched_barrier).  Bound by the matrix cores (a K tile of 64 x 64 is 1024 cycles of MFMAs, its
+// copies 16 KiB and its fragment reads 20): through registers, with the wait for all loads and a barrier around their way to
+// LDS, the products of 3000 x 1024 x 1024 took 76 us, like this
+// 61 and 63 (with neither reads nor copies in the loop 52: the rate of the MFMAs at the clock the chip keeps), of 8192 x 2048 x 2048 627
+// and 600, like this 559 and 563; the steps 162.8 -> 135 and 1326 -> 1220.
+//
+// LDS: [rows][32 k], 128 bytes per row, 16-byte chunk c of a row at c ^ swz_row(row), for Z and, where K is fastest, W; else W as
+// [32 k][TN n], and the MFMA columns are dealt so that a lane reads the NB columns of its NB blocks at once: column NB i of the
+// wave tile and the ones behind it, for row i of the "A" operand.  (TN = 64: the k rows of odd lane groups lie 128 bytes further
+// on, so that two groups' reads fall into different banks.)
+// -------------------------------------------------------------------------------------------
+template <bool TRANSW, int TM, int TN, int STAGES, int OCC>
+__global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
+                                                               const float* __restrict__ P, const float* __restrict__ M,
+                                                               float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
+                                                               int32_t nproj, int32_t proj, int32_t tiles_n)
+{
+    using gemm::dma16;
+    using gemm::static_for;
+    using gemm::swz_row;
+    using gemm::wait_vmcnt;
+    constexpr int FK = 32, WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
+    constexpr int ZT = TM * FK * 4, SLOT = ZT + TN * FK * 4;
+    constexpr int ZC = TM / 32, WC = TN / 32, CPW = ZC + WC;     // 1 KiB copies per wave and K tile
+    constexpr int CR = TN / 4, RPC = 64 / CR;                    // [k][n] tile: 16-byte chunks per k row, k rows per copy
+    constexpr int FPITCH = 20, NPITCH = TN + 4;                  // adapter step of 16 ranks: [rows][k] and [k][n] in front of the ring
+    constexpr int ROW_TASK = (TM * FPITCH + 16 * NPITCH) * 4;    // behind it: the rows' tasks, and which rows are the first of one
+    static_assert(ROW_TASK + TM * 4 + 16 <= STAGES * SLOT && ROW_TASK % 16 == 0, "the adapter term fits the ring");
+    static_assert(TM <= 128 && (NB == 2 || NB == 4), "two words of firsts; reads of 8 or 16 bytes");
+    __shared__ __attribute__((aligned(16))) unsigned char lds[STAGES * SLOT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
+    const int32_t id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int32_t row0 = id / tiles_n * TM, col0 = id % tiles_n * TN;
+    const int32_t T = pd.T, row_end = min(row0 + TM, T);
+
+    // ---- copies: rows beyond T and columns beyond N repeat the last one (what they produce is not stored), chunks beyond K too (the
+    //      fragments are cleared)
+    const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)lds)), la0 = lds0 + wave * 1024;
+    const unsigned char* zcur = reinterpret_cast<const unsigned char*>(Z + size_t(row0) * K);
+    const unsigned char* wcur = reinterpret_cast<const unsigned char*>(TRANSW ? W + size_t(col0) * ldw : W + col0);
+    const size_t wstep = TRANSW ? size_t(FK) * 4 : size_t(FK) * ldw * 4;
+    auto swz_k = [](int k) { return TN == 64 ? ((k >> 2) & 1) << 3 : 0; };
+    auto z_off = [&](int c, int32_t left) {          // of copy c, with `left` k in the K tile
+        const int row = 8 * (wave + 4 * c) + lane / 8;
+        return (uint32_t(min(row, T - 1 - row0)) * uint32_t(K) + uint32_t(min(4 * ((lane % 8) ^ swz_row(row)), left - 4))) * 4u;
+    };
+    auto w_off = [&](int c, int32_t left) {
+        if (TRANSW) {
+            const int row = 8 * (wave + 4 * c) + lane / 8;
+            return (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + uint32_t(min(4 * ((lane % 8) ^ swz_row(row)), left - 4))) * 4u;
+        }
+        const int k = RPC * (wave + 4 * c) + lane / CR;
+        return (uint32_t(min(k, left - 1)) * uint32_t(ldw) + uint32_t(min(4 * ((lane % CR) ^ swz_k(k)), N - 4 - col0))) * 4u;
+    };
+    uint32_t zvo[ZC], wvo[WC];
+#pragma unroll
+    for (int c = 0; c < ZC; ++c) zvo[c] = z_off(c, FK);
+#pragma unroll
+    for (int c = 0; c < WC; ++c) wvo[c] = w_off(c, FK);
+    auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {
+        constexpr int c = decltype(c_c)::value;
+        if constexpr (c < ZC) dma16(la + 4 * c * 1024, zcur, zvo[c]);
+        else dma16(la + ZT + 4 * (c - ZC) * 1024, wcur, wvo[c - ZC]);
+    };
+    auto next_copy_tile = [&]() __attribute__((always_inline)) { zcur += FK * 4, wcur += wstep; };
+    const int32_t KT = (K + FK - 1) / FK, ktail = K % FK, KF = K / FK;
+    auto copy_tail = [&](uint32_t la) {
+#pragma unroll
+        for (int c = 0; c < ZC; ++c) dma16(la + 4 * c * 1024, zcur, z_off(c, ktail));
+#pragma unroll
+        for (int c = 0; c < WC; ++c) dma16(la + ZT + 4 * c * 1024, wcur, w_off(c, ktail));
+    };
+    for (int s = 0; s < STAGES; ++s) {
+        if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * SLOT); });
+        else if (s < KT) copy_tail(la0 + s * SLOT);
+        next_copy_tile();
+    }
+
+    // ---- the adapter term's first step - the first segment's first 16 ranks - is fetched inside the main loop, early, and at another
+    //      K tile in each of the workgroups that share a compute unit: they multiply while one of them waits for its chain of
+    //      table reads and loads (in front of the loop that chain stood alone, 4 us of 62 at 3000 x 1024 x 1024)
+    constexpr int ZA = TM * 16 / 256, WA = TN * 16 / 256;
+    float pa[ZA], ma[WA];
+    int32_t sf = 0, sf_task = -1, s0 = 0;            // the first segment with an adapter and its task; the segment of the tile's first row
+    bool many = false;
+    // (mine(u, row): whether the row of piece u is the segment's, or the task's)
+    auto load_adapter_of = [&](auto mine, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) {
+            const int e = tid + 256 * u, kk = e & 15, row = row0 + (e >> 4);
+            pa[u] = (mine(u, row) && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < WA; ++u) {
+            const int e = tid + 256 * u, n = col0 + e % TN, kk = e / TN;
+            ma[u] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
+        }
+    };
+    auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
+        load_adapter_of([&](int, int32_t row) { return row >= lo && row < hi; }, r, pofs, r0, c0);
+    };
+    auto fetch_adapter = [&]() __attribute__((always_inline)) {
+        sf = s0 = pd.rowblk_seg[row0 / kRowBlock];
+        many = s0 + kFewSegments < pd.nseg && pd.cseg_off[s0 + kFewSegments] < row_end;      // (uniform)
+        if (many) return;
+        while (sf < pd.nseg && pd.cseg_task[sf] < 0 && pd.cseg_off[sf + 1] < row_end) ++sf;  // (uniform)
+        sf_task = sf < pd.nseg ? pd.cseg_task[sf] : -1;
+        if (sf_task < 0) return;
+        const int32_t r = (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj;
+        load_adapter(max(pd.cseg_off[sf], row0), min(pd.cseg_off[sf + 1], row_end), r, proj * r, pd.rank_off[sf_task] + proj * r, 0);
+    };
+
+    // ---- fragments and the steps of 16 k
+    struct Frags {
+        f32x4 z[MB];
+        float w[NB][4];                              // [block][q]
+    };
+    constexpr int NR = MB + (TRANSW ? NB : 4);       // reads of a step
+    auto read = [&](auto i_c, Frags& f, const unsigned char* slot, int ks) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        constexpr int NW = TRANSW ? NB : 4;
+        const int ch = (4 * ks + kg) ^ swz_row(j);
+        if constexpr (i >= NW) {
+            f.z[i - NW] = *reinterpret_cast<const f32x4*>(slot + (wm * WTM + (i - NW) * 16 + j) * 128 + ch * 16);
+        } else if constexpr (TRANSW) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(slot + ZT + (wn * WTN + i * 16 + j) * 128 + ch * 16);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f.w[i][q] = v[q];
+        } else {
+            typedef float row_t __attribute__((ext_vector_type(NB)));
+            const int k = 16 * ks + 4 * kg + i, n = wn * WTN + NB * j;
+            const row_t v = *reinterpret_cast<const row_t*>(slot + ZT + k * (TN * 4) + (((n >> 2) ^ swz_k(k)) << 4) + (n & 3) * 4);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) f.w[nb][i] = v[nb];
+        }
+    };
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the 4 MB NB MFMAs on `f`, with the reads of the next step's fragments and (COPY) a K tile's copies dealt evenly behind them
+    auto kstep = [&](auto read_c, auto copy_c, const Frags& f, Frags& next, const unsigned char* slot, int ks, uint32_t la) __attribute__((always_inline)) {
+        constexpr int NM = 4 * MB * NB, R = decltype(read_c)::value ? NR : 0, CC = decltype(copy_c)::value ? CPW : 0;
+        static_for<0, NM>([&](auto m_c) {
+            constexpr int m = decltype(m_c)::value, q = m / (MB * NB), mb = m / NB % MB, nb = m % NB;
+            acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+            static_for<m * R / NM, (m + 1) * R / NM>([&](auto i_c) { read(i_c, next, slot, ks); });
+            static_for<m * CC / NM, (m + 1) * CC / NM>([&](auto c_c) { copy(c_c, la); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto clear_tail = [&](Frags& f, int ks) __attribute__((always_inline)) {       // lane group kg holds k 16 ks + 4 kg .. + 3
+        const bool in = 16 * ks + 4 * kg < ktail;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) f.z[mb] = in ? f.z[mb] : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f.w[nb][q] = in ? f.w[nb][q] : 0.f;
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    auto barrier = []() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    if (KT >= STAGES) wait_vmcnt<(STAGES - 1) * CPW>();
+    else wait_vmcnt<0>();
+    barrier();
+    Frags fa, fb;
+    static_for<0, NR>([&](auto i_c) { read(i_c, fa, lds, 0); });
+    int32_t kt = 0, slot = 0;
+    auto ktile = [&]() __attribute__((always_inline)) {              // a whole K tile is still to be copied
+        const unsigned char* cur = lds + slot * SLOT;
+        kstep(yes{}, no{}, fa, fb, cur, 1, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_vmcnt<(STAGES - 2) * CPW>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const uint32_t la = la0 + slot * SLOT;
+        slot = slot + 1 == STAGES ? 0 : slot + 1;
+        kstep(yes{}, yes{}, fb, fa, lds + slot * SLOT, 0, la);
+        next_copy_tile();
+    };
+    const int32_t steady = KF - STAGES, at = min(2 + 4 * int32_t(blockIdx.x >> 8 & 3), steady);
+    for (; kt < at; ++kt) ktile();
+    if (P) fetch_adapter();
+    for (; kt < steady; ++kt) ktile();
+    for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
+        const bool tail = ktail != 0 && kt + 1 == KT;            // uniform
+        if (tail) clear_tail(fa, 0);
+        kstep(yes{}, no{}, fa, fb, lds + slot * SLOT, 1, 0);
+        if (tail) clear_tail(fb, 1);
+        if (kt + 1 < KT) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (kt + STAGES < KT) copy_tail(la0 + slot * SLOT);
+            slot = slot + 1 == STAGES ? 0 : slot + 1;
+            kstep(yes{}, no{}, fb, fa, lds + slot * SLOT, 0, 0);
+        } else {
+            kstep(no{}, no{}, fb, fa, lds, 0, 0);
+        }
+    }
+
+    // ---- adapter term: 16 ranks at a time are further k of the same tile product, rows outside the segment and ranks beyond r_t zero (the
+    //      loops are uniform over the workgroup): as in gemm_f32_kernel
+    float *const zs = reinterpret_cast<float*>(lds), *const ws = zs + TM * FPITCH;
+    auto stash_adapter = [&]() {
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) zs[((tid + 256 * u) >> 4) * FPITCH + (tid & 15)] = pa[u];
+#pragma unroll
+        for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
+    };
+    auto col_of = [&](int nb, int i) { return wn * WTN + (TRANSW ? nb * 16 + i : NB * i + nb); };    // of result row i of block nb
+    auto mac = [&]() {
+        Frags f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) f.z[mb] = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + 4 * kg);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f.w[nb][q] = ws[(4 * kg + q) * NPITCH + col_of(nb, j)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+    };
+    if (sf_task >= 0 || many) __syncthreads();       // everybody is done with the ring
+    if (sf_task >= 0) {
+        for (int32_t sg = sf; sg < pd.nseg; ++sg) {
+            const int32_t seg_lo = pd.cseg_off[sg];
+            if (seg_lo >= row_end) break;
+            const int32_t t = pd.cseg_task[sg];
+            if (t < 0) continue;
+            const int32_t lo = max(seg_lo, row0), hi = min(pd.cseg_off[sg + 1], row_end);
+            const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
+            const int32_t r0 = pd.rank_off[t] + pofs;
+            for (int32_t c0 = 0; c0 < r; c0 += 16) {
+                if (sg != sf || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
+                stash_adapter();
+                __syncthreads();
+                mac();
+                __syncthreads();
+            }
+        }
+    }
+    if (many) {
+        int32_t* const row_task = reinterpret_cast<int32_t*>(lds + ROW_TASK);
+        uint64_t* const firsts = reinterpret_cast<uint64_t*>(lds + ROW_TASK + TM * 4);
+        if (tid < TM) {
+            const int32_t sg = s0 + tid;             // (at most one segment per row)
+            if (sg < pd.nseg && pd.cseg_off[sg] < row_end) {
+                const int32_t t = pd.cseg_task[sg], hi = min(pd.cseg_off[sg + 1], row_end) - row0;
+                for (int32_t i = max(pd.cseg_off[sg], row0) - row0; i < hi; ++i) row_task[i] = t;
+            }
+            if (row0 + tid >= row_end) row_task[tid] = -1;
+        }
+        __syncthreads();
+        const int32_t own = tid < TM ? row_task[tid] : -1;
+        bool first = own >= 0;
+        for (int i = 0; i < TM; i += 4) {
+            const int4 a = *reinterpret_cast<const int4*>(&row_task[i]);
+            first &= !((a.x == own && i < tid) || (a.y == own && i + 1 < tid) || (a.z == own && i + 2 < tid) || (a.w == own && i + 3 < tid));
+        }
+        const uint64_t word = __ballot(first);
+        if (wave < 2 && lane == 0) firsts[wave] = word;
+        int32_t rt[ZA];                              // tasks of this thread's rows
+#pragma unroll
+        for (int u = 0; u < ZA; ++u) rt[u] = row_task[(tid + 256 * u) >> 4];
+        __syncthreads();
+        auto uniform = [](uint64_t v) {
+            return (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32)))) << 32) |
+                   uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v)));
+        };
+        uint64_t left[2] = {uniform(firsts[0]), uniform(firsts[1])};
+        int32_t t = -1, r = 0, c0 = 0;
+        auto next = [&]() {                          // moves to the next 16 ranks, of the next task at a task's end
+            c0 += 16;
+            if (c0 < r) return true;
+            const int w = left[0] ? 0 : 1;
+            if (!left[w]) return false;
+            t = __builtin_amdgcn_readfirstlane(row_task[64 * w + __builtin_ctzll(left[w])]);
+            left[w] &= left[w] - 1;
+            r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj;
+            c0 = 0;
+            return true;
+        };
+        auto load = [&]() { load_adapter_of([&](int u, int32_t) { return rt[u] == t; }, r, proj * r, pd.rank_off[t] + proj * r, c0); };
+        bool more = next();
+        if (more) load();
+        while (more) {
+            stash_adapter();
+            __syncthreads();
+            more = next();
+            if (more) load();
+            mac();
+            __syncthreads();
+        }
+    }
+    // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column col_of(nb, 4 kg + v)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int32_t row = row0 + wm * WTM + mb * 16 + j;
+        if (row >= T) continue;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {               // 16 bytes at a time
+            const int32_t col = col0 + wn * WTN + (TRANSW ? 16 * u + 4 * kg : 4 * NB * kg + 4 * u);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = TRANSW ? acc[mb][u][e] : acc[mb][(4 * u + e) % NB][(4 * u + e) / NB];
+            if (col < N) *reinterpret_cast<f32x4*>(C + size_t(row) * ldc + col) = v;
+        }
+    }
+}
+
 hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,
                     int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st)
 {
     const bool vec = ((K | N | ldw | ldc) & 3) == 0;
-    // The larger the tile the fewer loads and LDS writes per MFMA, as long as every compute unit has work (us per product;
-    // 8192 x 2048 x 2048: 775 with tiles of 32, 627 of 64, 571 of 128; 3000 x 1024 x 1024: 85, 75, 96; 2000 x 363 x 517: 29, 33, 54; the vector-ALU kernel that
-    // stood here before took 119 for the latter).  Tiles of 32 run where there are few of them, so a workgroup has its compute
-    // unit almost to itself and what counts is the number of round trips to memory: K steps of 128 and loads
-    // that cover whole lines at odd widths, 43 -> 30 us at 148 x 1676 x 1357.
+    // The larger the tile the fewer loads per MFMA, as long as every compute unit has work: tiles of 32 where they are few, so that a
+    // workgroup has its compute unit almost to itself and what counts is the number of round trips to memory (K steps of 128).
+    // Rows on 16-byte boundaries: by an estimate of rounds of workgroups (us; three of 64, two of 128 to a compute unit), tiles of 32 /
+    // 64 / 128 measured:
+    //     500 x 1024 x 1024  22 / 25 / 69      1000 x 1024 x 1024  34 / 27 / 74     4000 x 1024 x 1024  113 / 88 / 79
+    //     2000 x 512 x 512  20 / 16 / 43       3000 x 2048 x 256  45 / 48 / 133     8000 x 128 x 1024  50 / 36 / 37
+    // Other rows: 2000 x 363 x 517 29 / 33 / 54 (the vector-ALU kernel that stood here before took 119), 148 x 1676 x 1357 30 in tiles
+    // of 32 with loads that cover whole lines.
     auto tiles = [&](int32_t t) { return int64_t((pd.T + t - 1) / t) * ((N + t - 1) / t); };
-    const int32_t tm = tiles(128) >= 384 ? 128 : (tiles(64) >= 512 ? 64 : 32), tiles_n = (N + tm - 1) / tm;
+    auto estimate = [&](int32_t t) {
+        const float k = float(K) / 1024.f;
+        const int64_t n = tiles(t), per = t == 64 ? 768 : 512, full = n / per, rest = n % per;
+        if (t == 32) return 7.f + k + float(n) * (0.026f * k + 0.0015f);
+        if (t == 64) return float(full) * (6.f + 47.f * k) + (rest == 0 ? 4.f : rest <= 256 ? 7.f + 18.5f * k : rest <= 512 ? 10.f + 32.f * k : 10.f + 47.f * k);
+        return float(full) * (20.f + 127.f * k) + (rest == 0 ? 0.f : rest <= 256 ? 15.f + 65.f * k : 20.f + 127.f * k);
+    };
+    int32_t tm = tiles(128) >= 384 ? 128 : (tiles(64) >= 512 ? 64 : 32);
+    if (vec) {
+        tm = estimate(64) < estimate(32) ? 64 : 32;
+        if (estimate(128) < estimate(tm)) tm = 128;
+    }
+    const int32_t tiles_n = (N + tm - 1) / tm;
     const dim3 grid(uint32_t((pd.T + tm - 1) / tm) * uint32_t(tiles_n));
 #define LOBRA_F32_GEMM(TR, TILE, VEC) \
     gemm_f32_kernel<TR, TILE, TILE, (TILE == 32 ? 128 : 32), (TILE == 32 ? 1 : 2), VEC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
-#define LOBRA_F32_GEMM2(TR, TILE) do { if (vec) LOBRA_F32_GEMM(TR, TILE, true); else LOBRA_F32_GEMM(TR, TILE, false); } while (0)
-#define LOBRA_F32_GEMM3(TILE) do { if (transW) LOBRA_F32_GEMM2(true, TILE); else LOBRA_F32_GEMM2(false, TILE); } while (0)
-    if (tm == 128) LOBRA_F32_GEMM3(128);
-    else if (tm == 64) LOBRA_F32_GEMM3(64);
-    else LOBRA_F32_GEMM3(32);
+#define LOBRA_F32_RING(TR, TILE, STAGES, OCC) \
+    gemm_f32_ring_kernel<TR, TILE, TILE, STAGES, OCC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
+#define LOBRA_F32_GEMM2(TR) \
+    do { \
+        if (tm == 32 && vec) LOBRA_F32_GEMM(TR, 32, true); \
+        else if (tm == 32) LOBRA_F32_GEMM(TR, 32, false); \
+        else if (tm == 64 && vec) LOBRA_F32_RING(TR, 64, 3, 3); \
+        else if (tm == 64) LOBRA_F32_GEMM(TR, 64, false); \
+        else if (vec) LOBRA_F32_RING(TR, 128, 2, 2); \
+        else LOBRA_F32_GEMM(TR, 128, false); \
+    } while (0)
+    if (transW) LOBRA_F32_GEMM2(true);
+    else LOBRA_F32_GEMM2(false);
+#undef LOBRA_F32_GEMM
+#undef LOBRA_F32_RING
+#undef LOBRA_F32_GEMM2
     return hipGetLastError();
 }
 

@@ -601,6 +601,30 @@ def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
     assert bool(torch.isnan(dp.y[bad]).all()) and not bool(torch.isfinite(dp.dx[bad]).any())
 
 
+@pytest.mark.parametrize("T,d_in,d_out,n_proj,longest", [
+    (3001, 4, 2052, 1, 400),        # 64 x 64 tiles of one K tile of 4, a last row tile of 57 and a last column tile of 4
+    (3001, 96, 1028, 1, 400),       # as many K tiles as the ring has slots
+    (3001, 100, 1028, 1, 9),        # and a partial one; segments by the dozen in a tile
+    (3000, 1028, 1060, 1, 90),      # both directions, the copies inside the main loop
+    (2000, 640, 2064, 2, 200),      # two projections: row pitches of their own
+    (8200, 1028, 1036, 1, 300),     # 128 x 128 tiles, a partial K tile
+    (8200, 64, 2048, 1, 5),         # as many K tiles as their ring has slots
+])
+def test_fp32_products_through_the_ring(T, d_in, d_out, n_proj, longest):
+    """Edges of tiles, of the ring and of K of the fp32 products whose rows start on 16-byte boundaries."""
+    ranks = [16, 7, 40] if n_proj == 1 else [8, 24, 16]
+    rng = np.random.default_rng(T + d_in)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.integers(1, longest + 1)), T - sum(lens)))
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("ring-%dx%dx%d" % (T, d_in, d_out), "f32", d_in, d_out // n_proj, ranks, np.concatenate([[0], np.cumsum(lens)]),
+                       rng.integers(-1, 3, len(lens)), 61, s=[2.0, -1.0, 0.5], fill=(n_proj == 1), **kw)
+    p = p if n_proj == 1 else wl.fuse_projections(p, n_proj, **kw)
+    rows = np.unique(np.concatenate([rng.integers(0, T, 400), np.arange(0, 70), np.arange(T - 70, T)]))
+    check_problem(p, rows=rows, label="ring")
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [
     (33, 40, 64, 1), (300, 100, 36, 1), (2100, 48, 1028, 1), (2100, 31, 1025, 1), (6200, 20, 1028, 1), (6200, 23, 1031, 1), (6200, 16, 1032, 2),
 ])
