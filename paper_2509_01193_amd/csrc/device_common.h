@@ -37,6 +37,10 @@ __device__ __forceinline__ const int32_t* cseg_rank(const PlanDev& pd)
     return pd.gemm_tile_seg + size_t((pd.T + kGemmTileRows - 1) / kGemmTileRows) * kGemmTileSegRec;
 }
 
+// [T][2], in plans with a projection beside its product and at most kRowTableTokens tokens: first rank row and rank of every row's task
+// (0, 0: none).
+__device__ __forceinline__ const int32_t* row_rank(const PlanDev& pd) { return cseg_rank(pd) + 2 * size_t(pd.nseg); }
+
 // Index of the compacted segment that holds `row` (0 <= row < T): start from the table entry
 // of the row's 32-row block and walk forward.
 __device__ __forceinline__ int32_t segment_of_row(const PlanDev& pd, int32_t row)

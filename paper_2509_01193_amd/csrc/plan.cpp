@@ -541,6 +541,10 @@ std::vector<int32_t> pack_blob(Plan* p)
             list[at + k] = p->rank_off[t];
             list[at + nseg + k] = p->rank_off[t + 1] - p->rank_off[t];
         }
+        // and, where the sum of a split product adds the adapter term, the same for every row (see row_rank)
+        if ((p->beside_fwd.tile >= 0 || p->beside_bwd.tile >= 0) && p->desc.T <= kRowTableTokens)
+            for (size_t k = 0; k < nseg; ++k)
+                for (int32_t i = p->cseg_off[k]; i < p->cseg_off[k + 1]; ++i) list.insert(list.end(), {list[at + k], list[at + nseg + k]});
         p->o_tile_seg = put(list.data(), list.size());
     }
     while (blob.size() % 4) blob.push_back(0);

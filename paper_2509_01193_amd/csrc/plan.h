@@ -13,6 +13,7 @@ constexpr int kTokenBlock = 32;   // tokens per token block (one MFMA K step of 
 constexpr int kRowBlock = 32;     // granularity of the row -> segment lookup table
 constexpr int kGemmTileRows = 256;    // token rows of a base-GEMM output tile
 constexpr int kGemmTileRec = 8;       // ints per record of Plan::gemm_tile_tab
+constexpr int32_t kRowTableTokens = 256;  // batches that get a table of rows: 2 KiB of tables at most
 constexpr int kGemmTileSegs = 3, kGemmTileSegRec = 16;     // adapter segments and ints per record of Plan::gemm_tile_seg
 constexpr int kMaxClearedTasks = 4096;    // up to here stage 1 of the gradients clears the rows of tasks without tokens
 constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
