@@ -43,293 +43,37 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __bui
 }  // namespace
 
 // -------------------------------------------------------------------------------------------
-// gemm: TM x TN per workgroup of 2 x 2 waves, K step FBK, global -> registers -> LDS one K step ahead: for tiles of 32, and for rows that
-// start anywhere (gemm_f32_ring_kernel has the rest).  Bound by the matrix cores and the barriers around the way to LDS.  The adapter term is further K steps per segment, with the rows
-// outside the segment masked; where more than kFewSegments segments cross the tile, per task that has rows in it (8000
-// one-token segments of 8 tasks of rank 128, 10 x 1373: 4820 -> 290 us; 10119 tokens in segments of 3, rank 8, 64 x 1920: 390 -> 112).
-// -------------------------------------------------------------------------------------------
-constexpr int kFewSegments = 4;
-
-template <bool TRANSW, int TM, int TN, int FBK, int NBUF, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
-                                                       const float* __restrict__ P, const float* __restrict__ M,
-                                                       float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                                                       int32_t nproj, int32_t proj, int32_t tiles_n)
-{
-    // ldc: row pitch of C.  nproj > 1: projection `proj` of a fused shared-input call - of every task's
-    // ranks only the window [proj r, (proj + 1) r) takes part (columns of P, rows of M; M pitch N)
-    constexpr int WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
-    constexpr int ZL = TM * (FBK / 4) / 256, WL = TN * (FBK / 4) / 256;     // 16-byte pieces per thread and K step
-    constexpr int FPITCH = FBK + 4;      // [rows][k] tile: 16 rows' 16-byte pieces fall into 16 bank groups
-    constexpr int NPITCH = TN + 4;       // [k][n] tile: k rows 4 apart start 16 banks apart
-    constexpr int ZS = TM * FPITCH, WS = TRANSW ? TN * FPITCH : FBK * NPITCH;
-    __shared__ __attribute__((aligned(16))) float lds[NBUF][ZS + WS];
-    static_assert(16 * NPITCH <= WS, "the adapter's rank rows fit the W tile");
-    static_assert(TM <= 128, "two words of firsts");
-    __shared__ __attribute__((aligned(16))) int32_t row_task[TM];    // (see the adapter term of many segments)
-    __shared__ uint64_t firsts[2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
-    const int32_t id = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int32_t row0 = id / tiles_n * TM, col0 = id % tiles_n * TN;
-    const int32_t T = pd.T;
-
-    f32x4 acc[MB][NB];                   // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column nb 16 + 4 kg + v
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // rows beyond T and columns beyond N repeat the last one (what they produce is not stored); k beyond K reads as 0
-    f32x4 zr[ZL], wr[WL];
-    auto fetch = [&](int32_t k0) {
-#pragma unroll
-        for (int u = 0; u < ZL; ++u) {
-            const int c = tid + 256 * u, row = c / (FBK / 4), k = k0 + 4 * (c % (FBK / 4));
-            zr[u] = load4<VEC>(Z + size_t(min(row0 + row, T - 1)) * K, k, K);
-        }
-#pragma unroll
-        for (int u = 0; u < WL; ++u) {
-            const int c = tid + 256 * u;
-            if (TRANSW) {                // op(W)[k][n] = W[n*ldw + k]
-                const int row = c / (FBK / 4), k = k0 + 4 * (c % (FBK / 4));
-                wr[u] = load4<VEC>(W + size_t(min(col0 + row, N - 1)) * ldw, k, K);
-            } else if (!VEC) {           // op(W)[k][n] = W[k*ldw + n], an element per lane: whole lines of rows that start anywhere
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int ce = tid + 256 * (4 * u + e), k = k0 + ce / TN, n = col0 + ce % TN;
-                    wr[u][e] = k < K && n < N ? W[size_t(k) * ldw + n] : 0.f;
-                }
-            } else {
-                const int k = k0 + c / (TN / 4), n = col0 + 4 * (c % (TN / 4));
-                wr[u] = load4<VEC>(W + size_t(min(k, K - 1)) * ldw, k < K ? n : N, N);
-            }
-        }
-    };
-    auto stash = [&](float* zs) {
-#pragma unroll
-        for (int u = 0; u < ZL; ++u) {
-            const int c = tid + 256 * u;
-            *reinterpret_cast<f32x4*>(zs + c / (FBK / 4) * FPITCH + 4 * (c % (FBK / 4))) = zr[u];
-        }
-#pragma unroll
-        for (int u = 0; u < WL; ++u) {
-            const int c = tid + 256 * u;
-            if (TRANSW) *reinterpret_cast<f32x4*>(zs + ZS + c / (FBK / 4) * FPITCH + 4 * (c % (FBK / 4))) = wr[u];
-            else if (VEC) *reinterpret_cast<f32x4*>(zs + ZS + c / (TN / 4) * NPITCH + 4 * (c % (TN / 4))) = wr[u];
-            else
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int ce = tid + 256 * (4 * u + e);
-                    zs[ZS + ce / TN * NPITCH + ce % TN] = wr[u][e];
-                }
-        }
-    };
-    // 16 k from k0 on of the tiles at zs / ws
-    auto mac = [&](const float* zs, const float* ws, int k0, auto trans) {
-        f32x4 zf[MB], wf[NB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) zf[mb] = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + k0 + 4 * kg);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int n = wn * WTN + nb * 16 + j;
-            if constexpr (decltype(trans)::value) {
-                wf[nb] = *reinterpret_cast<const f32x4*>(ws + n * FPITCH + k0 + 4 * kg);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) wf[nb][q] = ws[(k0 + 4 * kg + q) * NPITCH + n];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(wf[nb][q], zf[mb][q], acc[mb][nb]);
-    };
-    using trans_c = std::integral_constant<bool, TRANSW>;
-
-    // The adapter term's first step - the first segment's first 16 ranks - is fetched in front of the main loop: behind
-    // it, its chain of table reads and loads would stand alone (3 us of 8 at K = 256).
-    constexpr int ZA = TM * 16 / 256, WA = TN * 16 / 256;
-    float pa[ZA], ma[WA];
-    const int32_t row_end = min(row0 + TM, T);
-    int32_t sf = pd.rowblk_seg[row0 / kRowBlock];
-    const int32_t s0 = sf;                               // the segment of the tile's first row
-    const bool many = P && s0 + kFewSegments < pd.nseg && pd.cseg_off[s0 + kFewSegments] < row_end;    // (uniform)
-    if (P && !many)
-        while (sf < pd.nseg && pd.cseg_task[sf] < 0 && pd.cseg_off[sf + 1] < row_end) ++sf;      // (uniform)
-    const int32_t sf_task = P && !many && sf < pd.nseg ? pd.cseg_task[sf] : -1;
-    // (mine(u, row): whether the row of piece u is the segment's, or the task's)
-    auto load_adapter_of = [&](auto mine, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
-#pragma unroll
-        for (int u = 0; u < ZA; ++u) {
-            const int e = tid + 256 * u, kk = e & 15, row = row0 + (e >> 4);
-            pa[u] = (mine(u, row) && c0 + kk < r) ? P[size_t(row) * pd.r_max + pofs + c0 + kk] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < WA; ++u) {
-            const int e = tid + 256 * u, n = col0 + e % TN, kk = e / TN;
-            ma[u] = (c0 + kk < r && n < N) ? M[size_t(r0 + c0 + kk) * N + n] : 0.f;
-        }
-    };
-    auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
-        load_adapter_of([&](int, int32_t row) { return row >= lo && row < hi; }, r, pofs, r0, c0);
-    };
-    auto stash_adapter = [&](float* zs, float* ws) {
-#pragma unroll
-        for (int u = 0; u < ZA; ++u) zs[((tid + 256 * u) >> 4) * FPITCH + (tid & 15)] = pa[u];
-#pragma unroll
-        for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
-    };
-    if (sf_task >= 0) {
-        const int32_t r = (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj;
-        load_adapter(max(pd.cseg_off[sf], row0), min(pd.cseg_off[sf + 1], row_end), r, proj * r, pd.rank_off[sf_task] + proj * r, 0);
-    }
-
-    fetch(0);
-    stash(lds[0]);
-    __syncthreads();
-    int buf = 0;
-    for (int32_t k0 = 0; k0 < K; k0 += FBK) {
-        const bool more = k0 + FBK < K;
-        if (more) fetch(k0 + FBK);
-#pragma unroll
-        for (int k = 0; k < FBK; k += 16)
-            if (k0 + k < K) mac(lds[buf], lds[buf] + ZS, k, trans_c{});         // (uniform)
-        if (NBUF == 1) __syncthreads();
-        else buf ^= 1;                   // (its last readers are behind the previous barrier)
-        if (more) stash(lds[buf]);
-        __syncthreads();
-    }
-    // adapter term: for every adapter segment that crosses the tile, the task's ranks are further k of the same tile
-    // product, 16 at a time: acc += P[rows, ranks] M_t[ranks, cols], rows outside the segment and ranks beyond r_t zero
-    // (the loops are uniform over the workgroup)
-    if (sf_task >= 0) {
-        float *zs = lds[0], *ws = lds[0] + ZS;           // (everybody is done with the last K step)
-        for (int32_t sg = sf; sg < pd.nseg; ++sg) {
-            const int32_t seg_lo = pd.cseg_off[sg];
-            if (seg_lo >= row_end) break;
-            const int32_t t = pd.cseg_task[sg];
-            if (t < 0) continue;
-            const int32_t lo = max(seg_lo, row0), hi = min(pd.cseg_off[sg + 1], row_end);
-            const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
-            const int32_t r0 = pd.rank_off[t] + pofs;
-            for (int32_t c0 = 0; c0 < r; c0 += 16) {
-                if (sg != sf || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
-                stash_adapter(zs, ws);
-                __syncthreads();
-                mac(zs, ws, 0, std::false_type{});
-                __syncthreads();
-            }
-        }
-    }
-    // many segments: the same steps, once per task with rows in the tile (in the order of their first rows), each with all of the
-    // task's rows; the next step's pieces are fetched while one is multiplied
-    if (many) {
-        if (tid < TM) {
-            const int32_t sg = s0 + tid;                 // (at most one segment per row)
-            if (sg < pd.nseg && pd.cseg_off[sg] < row_end) {
-                const int32_t t = pd.cseg_task[sg], hi = min(pd.cseg_off[sg + 1], row_end) - row0;
-                for (int32_t i = max(pd.cseg_off[sg], row0) - row0; i < hi; ++i) row_task[i] = t;
-            }
-            if (row0 + tid >= row_end) row_task[tid] = -1;
-        }
-        __syncthreads();
-        const int32_t own = tid < TM ? row_task[tid] : -1;
-        bool first = own >= 0;
-        for (int i = 0; i < TM; i += 4) {
-            const int4 a = *reinterpret_cast<const int4*>(&row_task[i]);
-            first &= !((a.x == own && i < tid) || (a.y == own && i + 1 < tid) || (a.z == own && i + 2 < tid) || (a.w == own && i + 3 < tid));
-        }
-        const uint64_t word = __ballot(first);
-        if (wave < 2 && lane == 0) firsts[wave] = word;
-        int32_t rt[ZA];                                  // tasks of this thread's rows
-#pragma unroll
-        for (int u = 0; u < ZA; ++u) rt[u] = row_task[(tid + 256 * u) >> 4];
-        __syncthreads();
-        auto uniform = [](uint64_t v) {
-            return (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32)))) << 32) |
-                   uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v)));
-        };
-        uint64_t left[2] = {uniform(firsts[0]), uniform(firsts[1])};
-        int32_t t = -1, r = 0, c0 = 0;
-        auto next = [&]() {                              // moves to the next 16 ranks, of the next task at a task's end
-            c0 += 16;
-            if (c0 < r) return true;
-            const int w = left[0] ? 0 : 1;
-            if (!left[w]) return false;
-            t = __builtin_amdgcn_readfirstlane(row_task[64 * w + __builtin_ctzll(left[w])]);
-            left[w] &= left[w] - 1;
-            r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj;
-            c0 = 0;
-            return true;
-        };
-        auto load = [&]() { load_adapter_of([&](int u, int32_t) { return rt[u] == t; }, r, proj * r, pd.rank_off[t] + proj * r, c0); };
-        bool more = next();
-        if (more) load();
-        while (more) {
-            stash_adapter(lds[0], lds[0] + ZS);
-            __syncthreads();
-            more = next();
-            if (more) load();
-            mac(lds[0], lds[0] + ZS, 0, std::false_type{});
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int32_t row = row0 + wm * WTM + mb * 16 + j;
-        if (row >= T) continue;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int32_t col = col0 + wn * WTN + nb * 16 + 4 * kg;
-            float* c = C + size_t(row) * ldc + col;
-            if (VEC && col < N) {
-                *reinterpret_cast<f32x4*>(c) = acc[mb][nb];
-            } else if (!VEC && col + 4 <= N) {
-                *reinterpret_cast<f32x4_any*>(c) = acc[mb][nb];
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (col + v < N) c[v] = acc[mb][nb][v];
-            }
-        }
-    }
-}
-
-// -------------------------------------------------------------------------------------------
-// The same for rows on 16-byte boundaries and many tiles: K tiles of 32 come through a ring of STAGES LDS slots that direct global -> LDS
-// copies fill, one counted wait and one barrier each; the fragments of 16 k are read while the ones before are multiplied, every
-// read and copy behind an MFMA (pinned by sched_barrier).  Bound by the matrix cores (a K tile of 64 x 64 is 1024 cycles of MFMAs, its
-// copies 16 KiB and its fragment reads 20): through registers, with the wait for all loads and a barrier around their way to
-// LDS, the products of 3000 x 1024 x 1024 took 76 us, like this
-// 61 and 63 (with neither reads nor copies in the loop 52: the rate of the MFMAs at the clock the chip keeps), of 8192 x 2048 x 2048 627
-// and 600, like this 559 and 563; the steps 162.8 -> 135 and 1326 -> 1220.
+// gemm: TM x TN per workgroup of 2 x 2 waves; K tiles of 32 come through a ring of STAGES LDS slots that direct global -> LDS copies
+// fill (16 bytes a lane, or 4 where rows start anywhere), one counted wait and one barrier each; the fragments of 16 k are read
+// while the ones before are multiplied, every read and copy behind an MFMA (pinned by sched_barrier).  Bound by the matrix cores (a K tile
+// of 64 x 64 is 1024 cycles of MFMAs, its copies 16 KiB and its fragment reads 20), tiles of 32 by the barriers.  Through registers, with the
+// wait for all loads and a barrier around their way to LDS, the products of 3000 x 1024 x 1024 took 76 us, like this 61 and 63 (with
+// neither reads nor copies in the loop 52: the rate of the MFMAs at the clock the chip keeps), of 8192 x 2048 x 2048 627 and 600, like
+// this 559 and 563, of 1500 x 700 x 333 25 and 21, like this 18 and 19; the step of the first 162.8 -> 134.
 //
 // LDS: [rows][32 k], 128 bytes per row, 16-byte chunk c of a row at c ^ swz_row(row), for Z and, where K is fastest, W; else W as
 // [32 k][TN n], and the MFMA columns are dealt so that a lane reads the NB columns of its NB blocks at once: column NB i of the
-// wave tile and the ones behind it, for row i of the "A" operand.  (TN = 64: the k rows of odd lane groups lie 128 bytes further
-// on, so that two groups' reads fall into different banks.)
+// wave tile and the ones behind it, for row i of the "A" operand.  (TN = 64 and 32: the chunks of odd lane groups' k rows are
+// exchanged half a row apart, so that two groups' reads fall into different banks.)
 // -------------------------------------------------------------------------------------------
-template <bool TRANSW, int TM, int TN, int STAGES, int OCC>
-__global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
+template <bool TRANSW, int TM, int TN, int STAGES, int OCC, bool VEC>
+__global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
                                                                const float* __restrict__ P, const float* __restrict__ M,
                                                                float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
                                                                int32_t nproj, int32_t proj, int32_t tiles_n)
 {
-    using gemm::dma16;
     using gemm::static_for;
     using gemm::swz_row;
     using gemm::wait_vmcnt;
     constexpr int FK = 32, WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
     constexpr int ZT = TM * FK * 4, SLOT = ZT + TN * FK * 4;
-    constexpr int ZC = TM / 32, WC = TN / 32, CPW = ZC + WC;     // 1 KiB copies per wave and K tile
-    constexpr int CR = TN / 4, RPC = 64 / CR;                    // [k][n] tile: 16-byte chunks per k row, k rows per copy
+    constexpr int E = VEC ? 4 : 1, LB = 64 * E * 4;              // elements per lane and bytes of a copy
+    constexpr int ZC = ZT / LB / 4, WC = TN * FK * 4 / LB / 4, CPW = ZC + WC;    // copies per wave and K tile
+    constexpr int ZL = FK / E, CR = TN / E;                      // lanes of a copy per row of 32 k, per k row of n
     constexpr int FPITCH = 20, NPITCH = TN + 4;                  // adapter step of 16 ranks: [rows][k] and [k][n] in front of the ring
     constexpr int ROW_TASK = (TM * FPITCH + 16 * NPITCH) * 4;    // behind it: the rows' tasks, and which rows are the first of one
     static_assert(ROW_TASK + TM * 4 + 16 <= STAGES * SLOT && ROW_TASK % 16 == 0, "the adapter term fits the ring");
-    static_assert(TM <= 128 && (NB == 2 || NB == 4), "two words of firsts; reads of 8 or 16 bytes");
+    static_assert(TM <= 128 && NB <= 4 && (STAGES - 1) * CPW < 64, "two words of firsts; reads of up to 16 bytes; what vmcnt can count");
     __shared__ __attribute__((aligned(16))) unsigned char lds[STAGES * SLOT];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
@@ -337,24 +81,34 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
     const int32_t row0 = id / tiles_n * TM, col0 = id % tiles_n * TN;
     const int32_t T = pd.T, row_end = min(row0 + TM, T);
 
+    const F32BlockRec rec = P ? f32_block_rec(pd)[row0 / kRowBlock] : F32BlockRec{};     // (in front of the copies: a scalar load)
+    const bool many = P && rec.fifth < row_end;      // more than kFewSegments segments in the tile
+
     // ---- copies: rows beyond T and columns beyond N repeat the last one (what they produce is not stored), chunks beyond K too (the
     //      fragments are cleared)
-    const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)lds)), la0 = lds0 + wave * 1024;
+    const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)lds)), la0 = lds0 + wave * LB;
     const unsigned char* zcur = reinterpret_cast<const unsigned char*>(Z + size_t(row0) * K);
     const unsigned char* wcur = reinterpret_cast<const unsigned char*>(TRANSW ? W + size_t(col0) * ldw : W + col0);
     const size_t wstep = TRANSW ? size_t(FK) * 4 : size_t(FK) * ldw * 4;
-    auto swz_k = [](int k) { return TN == 64 ? ((k >> 2) & 1) << 3 : 0; };
+    auto dma = [](uint32_t to, const unsigned char* from, uint32_t off) __attribute__((always_inline)) {
+        if constexpr (VEC) gemm::dma16(to, from, off);
+        else gemm::dma4(to, from, off);
+    };
+    auto swz_k = [](int k) { return TN == 128 ? 0 : ((k >> 2) & 1) << (TN == 64 ? 3 : 2); };
+    // (element e of a row lies at swizzled(e, s): its chunk of 16 bytes exchanged)
+    auto swizzled = [](int e, int s) { return (((e >> 2) ^ s) << 2) | (e & 3); };
     auto z_off = [&](int c, int32_t left) {          // of copy c, with `left` k in the K tile
-        const int row = 8 * (wave + 4 * c) + lane / 8;
-        return (uint32_t(min(row, T - 1 - row0)) * uint32_t(K) + uint32_t(min(4 * ((lane % 8) ^ swz_row(row)), left - 4))) * 4u;
+        const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
+        return (uint32_t(min(row, T - 1 - row0)) * uint32_t(K) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
     };
     auto w_off = [&](int c, int32_t left) {
         if (TRANSW) {
-            const int row = 8 * (wave + 4 * c) + lane / 8;
-            return (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + uint32_t(min(4 * ((lane % 8) ^ swz_row(row)), left - 4))) * 4u;
+            const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
+            return (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
         }
-        const int k = RPC * (wave + 4 * c) + lane / CR;
-        return (uint32_t(min(k, left - 1)) * uint32_t(ldw) + uint32_t(min(4 * ((lane % CR) ^ swz_k(k)), N - 4 - col0))) * 4u;
+        // (a copy has several k rows, or half of one: TN = 128, four bytes a lane)
+        const int at = 64 * (wave + 4 * c) + lane, k = at / CR;
+        return (uint32_t(min(k, left - 1)) * uint32_t(ldw) + uint32_t(min(swizzled(E * (at % CR), swz_k(k)), N - E - col0))) * 4u;
     };
     uint32_t zvo[ZC], wvo[WC];
 #pragma unroll
@@ -363,16 +117,16 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
     for (int c = 0; c < WC; ++c) wvo[c] = w_off(c, FK);
     auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {
         constexpr int c = decltype(c_c)::value;
-        if constexpr (c < ZC) dma16(la + 4 * c * 1024, zcur, zvo[c]);
-        else dma16(la + ZT + 4 * (c - ZC) * 1024, wcur, wvo[c - ZC]);
+        if constexpr (c < ZC) dma(la + 4 * c * LB, zcur, zvo[c]);
+        else dma(la + ZT + 4 * (c - ZC) * LB, wcur, wvo[c - ZC]);
     };
     auto next_copy_tile = [&]() __attribute__((always_inline)) { zcur += FK * 4, wcur += wstep; };
     const int32_t KT = (K + FK - 1) / FK, ktail = K % FK, KF = K / FK;
     auto copy_tail = [&](uint32_t la) {
 #pragma unroll
-        for (int c = 0; c < ZC; ++c) dma16(la + 4 * c * 1024, zcur, z_off(c, ktail));
+        for (int c = 0; c < ZC; ++c) dma(la + 4 * c * LB, zcur, z_off(c, ktail));
 #pragma unroll
-        for (int c = 0; c < WC; ++c) dma16(la + ZT + 4 * c * 1024, wcur, w_off(c, ktail));
+        for (int c = 0; c < WC; ++c) dma(la + ZT + 4 * c * LB, wcur, w_off(c, ktail));
     };
     for (int s = 0; s < STAGES; ++s) {
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * SLOT); });
@@ -380,13 +134,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
         next_copy_tile();
     }
 
-    // ---- the adapter term's first step - the first segment's first 16 ranks - is fetched inside the main loop, early, and at another
-    //      K tile in each of the workgroups that share a compute unit: they multiply while one of them waits for its chain of
-    //      table reads and loads (in front of the loop that chain stood alone, 4 us of 62 at 3000 x 1024 x 1024)
+    // ---- the adapter term's first step - the first segment's first 16 ranks - is fetched in front of the main loop, behind its first
+    //      copies, with what the row block's record says (through the segments' tables, a chain of four reads: 4 us of 62 at 3000 x
+    //      1024 x 1024)
     constexpr int ZA = TM * 16 / 256, WA = TN * 16 / 256;
     float pa[ZA], ma[WA];
-    int32_t sf = 0, sf_task = -1, s0 = 0;            // the first segment with an adapter and its task; the segment of the tile's first row
-    bool many = false;
     // (mine(u, row): whether the row of piece u is the segment's, or the task's)
     auto load_adapter_of = [&](auto mine, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
 #pragma unroll
@@ -403,16 +155,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
     auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
         load_adapter_of([&](int, int32_t row) { return row >= lo && row < hi; }, r, pofs, r0, c0);
     };
-    auto fetch_adapter = [&]() __attribute__((always_inline)) {
-        sf = s0 = pd.rowblk_seg[row0 / kRowBlock];
-        many = s0 + kFewSegments < pd.nseg && pd.cseg_off[s0 + kFewSegments] < row_end;      // (uniform)
-        if (many) return;
-        while (sf < pd.nseg && pd.cseg_task[sf] < 0 && pd.cseg_off[sf + 1] < row_end) ++sf;  // (uniform)
-        sf_task = sf < pd.nseg ? pd.cseg_task[sf] : -1;
-        if (sf_task < 0) return;
-        const int32_t r = (pd.rank_off[sf_task + 1] - pd.rank_off[sf_task]) / nproj;
-        load_adapter(max(pd.cseg_off[sf], row0), min(pd.cseg_off[sf + 1], row_end), r, proj * r, pd.rank_off[sf_task] + proj * r, 0);
-    };
+    const bool some = P && !many && rec.lo < row_end;
+    if (some) {
+        const int32_t r = rec.rank / nproj;
+        load_adapter(max(rec.lo, row0), min(rec.hi, row_end), r, proj * r, rec.rank0 + proj * r, 0);
+    }
 
     // ---- fragments and the steps of 16 k
     struct Frags {
@@ -431,11 +178,16 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
 #pragma unroll
             for (int q = 0; q < 4; ++q) f.w[i][q] = v[q];
         } else {
-            typedef float row_t __attribute__((ext_vector_type(NB)));
             const int k = 16 * ks + 4 * kg + i, n = wn * WTN + NB * j;
-            const row_t v = *reinterpret_cast<const row_t*>(slot + ZT + k * (TN * 4) + (((n >> 2) ^ swz_k(k)) << 4) + (n & 3) * 4);
+            const unsigned char* at = slot + ZT + k * (TN * 4) + swizzled(n, swz_k(k)) * 4;
+            if constexpr (NB == 1) {
+                f.w[0][i] = *reinterpret_cast<const float*>(at);
+            } else {
+                typedef float row_t __attribute__((ext_vector_type(NB)));
+                const row_t v = *reinterpret_cast<const row_t*>(at);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) f.w[nb][i] = v[nb];
+                for (int nb = 0; nb < NB; ++nb) f.w[nb][i] = v[nb];
+            }
         }
     };
     f32x4 acc[MB][NB];
@@ -455,13 +207,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
         });
     };
     auto clear_tail = [&](Frags& f, int ks) __attribute__((always_inline)) {       // lane group kg holds k 16 ks + 4 kg .. + 3
-        const bool in = 16 * ks + 4 * kg < ktail;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) f.z[mb] = in ? f.z[mb] : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 4; ++q) {
+            const bool in = 16 * ks + 4 * kg + q < ktail;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+            for (int mb = 0; mb < MB; ++mb) f.z[mb][q] = in ? f.z[mb][q] : 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) f.w[nb][q] = in ? f.w[nb][q] : 0.f;
+            for (int nb = 0; nb < NB; ++nb) f.w[nb][q] = in ? f.w[nb][q] : 0.f;
+        }
     };
     using yes = std::true_type;
     using no = std::false_type;
@@ -488,10 +241,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
         kstep(yes{}, yes{}, fb, fa, lds + slot * SLOT, 0, la);
         next_copy_tile();
     };
-    const int32_t steady = KF - STAGES, at = min(2 + 4 * int32_t(blockIdx.x >> 8 & 3), steady);
-    for (; kt < at; ++kt) ktile();
-    if (P) fetch_adapter();
-    for (; kt < steady; ++kt) ktile();
+    for (; kt < KF - STAGES; ++kt) ktile();
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;            // uniform
         if (tail) clear_tail(fa, 0);
@@ -535,9 +285,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
     };
-    if (sf_task >= 0 || many) __syncthreads();       // everybody is done with the ring
-    if (sf_task >= 0) {
-        for (int32_t sg = sf; sg < pd.nseg; ++sg) {
+    if (some || many) __syncthreads();               // everybody is done with the ring
+    if (some) {
+        for (int32_t sg = rec.first; sg < pd.nseg; ++sg) {
             const int32_t seg_lo = pd.cseg_off[sg];
             if (seg_lo >= row_end) break;
             const int32_t t = pd.cseg_task[sg];
@@ -546,7 +296,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
             const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
             const int32_t r0 = pd.rank_off[t] + pofs;
             for (int32_t c0 = 0; c0 < r; c0 += 16) {
-                if (sg != sf || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
+                if (sg != rec.first || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
                 stash_adapter();
                 __syncthreads();
                 mac();
@@ -558,7 +308,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
         int32_t* const row_task = reinterpret_cast<int32_t*>(lds + ROW_TASK);
         uint64_t* const firsts = reinterpret_cast<uint64_t*>(lds + ROW_TASK + TM * 4);
         if (tid < TM) {
-            const int32_t sg = s0 + tid;             // (at most one segment per row)
+            const int32_t sg = rec.own + tid;        // (at most one segment per row)
             if (sg < pd.nseg && pd.cseg_off[sg] < row_end) {
                 const int32_t t = pd.cseg_task[sg], hi = min(pd.cseg_off[sg + 1], row_end) - row0;
                 for (int32_t i = max(pd.cseg_off[sg], row0) - row0; i < hi; ++i) row_task[i] = t;
@@ -618,7 +368,16 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
             f32x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = TRANSW ? acc[mb][u][e] : acc[mb][(4 * u + e) % NB][(4 * u + e) / NB];
-            if (col < N) *reinterpret_cast<f32x4*>(C + size_t(row) * ldc + col) = v;
+            float* c = C + size_t(row) * ldc + col;
+            if (VEC && col < N) {
+                *reinterpret_cast<f32x4*>(c) = v;
+            } else if (!VEC && col + 4 <= N) {
+                *reinterpret_cast<f32x4_any*>(c) = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < N) c[e] = v[e];
+            }
         }
     }
 }
@@ -626,47 +385,36 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_ring_kernel(PlanDev pd, con
 hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,
                     int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st)
 {
+    // The larger the tile the fewer loads per MFMA, as long as every compute unit has work: by an estimate of rounds of workgroups
+    // (us; four of 32, three of 64, two of 128 to a compute unit).  Tiles of 32 / 64 / 128, rows on 16-byte boundaries and not:
+    //     600 x 1024 x 1024  23 / 25 / 70      1000 x 1024 x 1024  30 / 27 / 74     4000 x 1024 x 1024  104 / 92 / 80
+    //     2000 x 512 x 512  17 / 16 / 43       4000 x 96 x 512  16 / 12 / 20        8000 x 128 x 1024  50 / 36 / 37
+    //     600 x 1357 x 1676  40 / 51 / 149     2000 x 1357 x 1676  130 / 104 / 157  4000 x 1357 x 1676  262 / 187 / 262
+    // (128 four bytes a lane: behind the others everywhere, the addresses of 32 copies a K tile do not fit the registers)
     const bool vec = ((K | N | ldw | ldc) & 3) == 0;
-    // The larger the tile the fewer loads per MFMA, as long as every compute unit has work: tiles of 32 where they are few, so that a
-    // workgroup has its compute unit almost to itself and what counts is the number of round trips to memory (K steps of 128).
-    // Rows on 16-byte boundaries: by an estimate of rounds of workgroups (us; three of 64, two of 128 to a compute unit), tiles of 32 /
-    // 64 / 128 measured:
-    //     500 x 1024 x 1024  22 / 25 / 69      1000 x 1024 x 1024  34 / 27 / 74     4000 x 1024 x 1024  113 / 88 / 79
-    //     2000 x 512 x 512  20 / 16 / 43       3000 x 2048 x 256  45 / 48 / 133     8000 x 128 x 1024  50 / 36 / 37
-    // Other rows: 2000 x 363 x 517 29 / 33 / 54 (the vector-ALU kernel that stood here before took 119), 148 x 1676 x 1357 30 in tiles
-    // of 32 with loads that cover whole lines.
     auto tiles = [&](int32_t t) { return int64_t((pd.T + t - 1) / t) * ((N + t - 1) / t); };
     auto estimate = [&](int32_t t) {
         const float k = float(K) / 1024.f;
         const int64_t n = tiles(t), per = t == 64 ? 768 : 512, full = n / per, rest = n % per;
-        if (t == 32) return 7.f + k + float(n) * (0.026f * k + 0.0015f);
+        if (t == 32) return 6.f + k + float(n) * (0.0205f * k + 0.003f);
         if (t == 64) return float(full) * (6.f + 47.f * k) + (rest == 0 ? 4.f : rest <= 256 ? 7.f + 18.5f * k : rest <= 512 ? 10.f + 32.f * k : 10.f + 47.f * k);
         return float(full) * (20.f + 127.f * k) + (rest == 0 ? 0.f : rest <= 256 ? 15.f + 65.f * k : 20.f + 127.f * k);
     };
-    int32_t tm = tiles(128) >= 384 ? 128 : (tiles(64) >= 512 ? 64 : 32);
-    if (vec) {
-        tm = estimate(64) < estimate(32) ? 64 : 32;
-        if (estimate(128) < estimate(tm)) tm = 128;
-    }
+    int32_t tm = estimate(64) < estimate(32) ? 64 : 32;
+    if (vec && estimate(128) < estimate(tm)) tm = 128;
     const int32_t tiles_n = (N + tm - 1) / tm;
     const dim3 grid(uint32_t((pd.T + tm - 1) / tm) * uint32_t(tiles_n));
-#define LOBRA_F32_GEMM(TR, TILE, VEC) \
-    gemm_f32_kernel<TR, TILE, TILE, (TILE == 32 ? 128 : 32), (TILE == 32 ? 1 : 2), VEC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
-#define LOBRA_F32_RING(TR, TILE, STAGES, OCC) \
-    gemm_f32_ring_kernel<TR, TILE, TILE, STAGES, OCC><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
+#define LOBRA_F32_GEMM(TR, TILE, STAGES, OCC) \
+    (vec ? gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, true> : gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, false>)<<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
 #define LOBRA_F32_GEMM2(TR) \
     do { \
-        if (tm == 32 && vec) LOBRA_F32_GEMM(TR, 32, true); \
-        else if (tm == 32) LOBRA_F32_GEMM(TR, 32, false); \
-        else if (tm == 64 && vec) LOBRA_F32_RING(TR, 64, 3, 3); \
-        else if (tm == 64) LOBRA_F32_GEMM(TR, 64, false); \
-        else if (vec) LOBRA_F32_RING(TR, 128, 2, 2); \
-        else LOBRA_F32_GEMM(TR, 128, false); \
+        if (tm == 32) LOBRA_F32_GEMM(TR, 32, 5, 4); \
+        else if (tm == 64) LOBRA_F32_GEMM(TR, 64, 3, 3); \
+        else gemm_f32_kernel<TR, 128, 128, 2, 2, true><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n); \
     } while (0)
     if (transW) LOBRA_F32_GEMM2(true);
     else LOBRA_F32_GEMM2(false);
 #undef LOBRA_F32_GEMM
-#undef LOBRA_F32_RING
 #undef LOBRA_F32_GEMM2
     return hipGetLastError();
 }

@@ -530,7 +530,26 @@ std::vector<int32_t> pack_blob(Plan* p)
     p->o_fb_run = put(p->fb_run_row.data(), p->fb_run_row.size());
     p->o_fb_cnt = put(p->fb_cnt.data(), p->fb_cnt.size());
     p->o_fb_row0 = put(p->fb_task_row0.data(), p->fb_task_row0.size());
-    {
+    if (p->desc.dtype == LOBRA_F32) {
+        const int32_t nseg = int32_t(p->cseg_task.size());
+        std::vector<F32BlockRec> rec(p->rowblk_seg.size());
+        int32_t first = nseg;                        // of the blocks from the last to the first, so that each step looks at few segments
+        for (size_t b = rec.size(), seen = size_t(nseg); b-- > 0;) {
+            F32BlockRec& r = rec[b];
+            r.own = p->rowblk_seg[b];
+            for (; seen > size_t(r.own); --seen)
+                if (p->cseg_task[seen - 1] >= 0) first = int32_t(seen - 1);
+            const int32_t t = first < nseg ? p->cseg_task[size_t(first)] : -1;
+            r.fifth = r.own + kFewSegments < nseg ? p->cseg_off[size_t(r.own + kFewSegments)] : INT32_MAX;
+            r.first = first;
+            r.lo = t >= 0 ? p->cseg_off[size_t(first)] : INT32_MAX;
+            r.hi = t >= 0 ? p->cseg_off[size_t(first) + 1] : INT32_MAX;
+            r.rank0 = t >= 0 ? p->rank_off[t] : 0;
+            r.rank = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
+            r.pad = 0;
+        }
+        p->o_tile_seg = put(reinterpret_cast<const int32_t*>(rec.data()), rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
+    } else {
         // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
         const size_t nseg = p->cseg_task.size(), at = p->gemm_tile_seg.size();
         std::vector<int32_t> list(p->gemm_tile_seg);

@@ -21,6 +21,12 @@ constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
 // projections start up to 512 threads per token, which a launch of less than 2^32 threads has room for.
 constexpr int64_t kPlainMaxTokens = 65535 * 64;
 
+// fp32: what a 32-row block says about the tiles that start with it - the segment of its first row, where the segment
+// kFewSegments further on starts, and the first segment from there on that has an adapter: its index, tokens, and its task's first rank
+// row and stacked rank (first tokens INT32_MAX: none)
+constexpr int kFewSegments = 4;
+struct F32BlockRec { int32_t own, fifth, first, lo, hi, rank0, rank, pad; };
+
 struct TokenBlock { int32_t row0, nrows, task, rank_row0; };
 struct GradChunk  { int32_t tb_begin, tb_end, task, part_row0; };
 

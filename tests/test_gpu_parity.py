@@ -602,13 +602,16 @@ def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
 
 
 @pytest.mark.parametrize("T,d_in,d_out,n_proj,longest", [
-    (3001, 4, 2052, 1, 400),        # 64 x 64 tiles of one K tile of 4, a last row tile of 57 and a last column tile of 4
+    (3001, 4, 2052, 1, 400),        # a K tile of 4, a last row tile of 57 (of 64) and a last column tile of 4
     (3001, 96, 1028, 1, 400),       # as many K tiles as the ring has slots
     (3001, 100, 1028, 1, 9),        # and a partial one; segments by the dozen in a tile
     (3000, 1028, 1060, 1, 90),      # both directions, the copies inside the main loop
     (2000, 640, 2064, 2, 200),      # two projections: row pitches of their own
     (8200, 1028, 1036, 1, 300),     # 128 x 128 tiles, a partial K tile
     (8200, 64, 2048, 1, 5),         # as many K tiles as their ring has slots
+    (700, 163, 131, 1, 60),         # 32 x 32 tiles, four bytes a lane: one K tile more than the ring has slots, of 3
+    (333, 160, 256, 1, 3),          # as many as slots; 16 bytes a lane
+    (3001, 99, 1030, 1, 400),       # 64 x 64 tiles, four bytes a lane, a K tile of 3
 ])
 def test_fp32_products_through_the_ring(T, d_in, d_out, n_proj, longest):
     """Edges of tiles, of the ring and of K of the fp32 products whose rows start on 16-byte boundaries."""
