@@ -8,6 +8,7 @@
 //   shrink      P = s_t Z M_t^T            (Z = x, M = A: s_t A_t x_i;  Z = dy, M = B: s_t B_t dy_i)
 //   gemm        C = Z op(W) + P M_t        (y = x W + P B_t;  dx = dy W^T + P A_t)
 //   gradreduce  dM_t = sum_i P_i^T Z_i     (dB_t from P = s h, Z = dy;  dA_t from P = s g, Z = x)
+#include <type_traits>
 #include "kernels.h"
 
 namespace lobra {
@@ -335,83 +336,70 @@ __global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const
 }
 
 // stage 2: out[R, col] (+)= sum over the chunks of task(R), in chunk order.  One workgroup per
-// (rank row, 1024 columns), one float4 per thread, four chunk loads in flight.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(PlanDev pd, GradJob ja, GradJob jb,
+// (rank row, 1024 columns), one float4 per thread, up to eight chunk loads in flight.  What bounds it where the sums are few: the chain of
+// reads in front of them - the row's task, its first chunk, that chunk's first row; a task's chunks follow each
+// other in the partial sums, r_t rows each.  (With a search one task at a time and a table read per chunk / like this, us: 8190 x 1376 x 4096
+// 7.7 / 6.3; fp32 3000 x 1024 x 1024 5.7 / 4.7, 1500 x 700 x 333 15.1 / 6.7; 49152 x 8192 x 8192 at rank 64, 32768 workgroups
+// most of which find one chunk and have nothing to add, 42 / 46.)  Registers for eight waves on a SIMD.
+__global__ __launch_bounds__(256, 8) void reduce_partials_kernel(PlanDev pd, GradJob ja, GradJob jb,
                                                               int32_t tiles_a, int accumulate, int skip_single)
 {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));        // (rows start anywhere outside the bf16 MFMA path)
     const bool first = int32_t(blockIdx.y) < tiles_a;
     const float* __restrict__ part = first ? ja.part : jb.part;
     float* __restrict__ out = first ? ja.out : jb.out;
     const int32_t D = first ? ja.D : jb.D;
     const int32_t coltile = first ? int32_t(blockIdx.y) : int32_t(blockIdx.y) - tiles_a;
     const int32_t R = blockIdx.x;
-    int32_t t = 0, te = pd.n_tasks;                  // (by halves: a chain of table reads is most of what a workgroup takes)
+    int32_t t = 0, te = pd.n_tasks;                  // the row's task is one of t .. te - 1
     while (te - t > 8) {
         const int32_t m = (t + te) >> 1;
         if (pd.rank_off[m] <= R) t = m;
         else te = m;
     }
-    while (pd.rank_off[t + 1] <= R) ++t;
-    const int32_t p = R - pd.rank_off[t];
+    int32_t off[8], behind = 0;                      // (scalar loads, all at once)
+#pragma unroll
+    for (int k = 1; k < 8; ++k) off[k] = pd.rank_off[min(t + k, te)];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) behind += int(t + k < te) & int(off[k] <= R);
+    t += behind;
+    const int32_t r0 = pd.rank_off[t], r = pd.rank_off[t + 1] - r0;
     const int32_t col = coltile * 1024 + threadIdx.x * 4;
     if (col >= D) return;
     // the partial sums of a task: one per reduction chunk, or (fcnt) one per run of the fused pass that covers
     // this thread's 512-column slice
     const int32_t* fcnt = first ? ja.fcnt : jb.fcnt;
-    const int32_t c0 = fcnt ? 0 : pd.task_chunk_off[t];
-    const int32_t c1 = fcnt ? fcnt[t * (first ? ja.fnsl : jb.fnsl) + (col >> 9)] : pd.task_chunk_off[t + 1];
-    if (skip_single && !fcnt && c1 - c0 == 1) return;
-    const int32_t frow = fcnt ? (first ? ja.frow0 : jb.frow0)[t] + p : 0;
-    const int nv = min(4, D - col);                 // D need not be a multiple of 4 outside the bf16 MFMA path
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    auto row_ptr = [&](int32_t c) {
-        return part + size_t(fcnt ? frow + 16 * c : pd.chunks[c].part_row0 + p) * D + col;
-    };
-    if (nv == 4 && (D & 3) == 0) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        int32_t c = c0;
-        for (; c + 8 <= c1; c += 8) {            // eight loads in flight, added in order
-            f4 v[8];
+    const int32_t c0 = pd.task_chunk_off[t], nc = pd.task_chunk_off[t + 1] - c0;
+    const int32_t n = fcnt ? fcnt[t * (first ? ja.fnsl : jb.fnsl) + (col >> 9)] : nc;
+    if (skip_single && !fcnt && n == 1) return;
+    const int32_t row0 = (fcnt ? (first ? ja.frow0 : jb.frow0)[t] : nc > 0 ? pd.chunks[c0].part_row0 : 0) + (R - r0);
+    const size_t step = size_t(fcnt ? 16 : r) * D;   // from a chunk's (run's) sums to the next one's
+    const float* src = part + size_t(row0) * D;
+    float* o = out + size_t(R) * D + col;
+    if (col + 4 <= D) {
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+        int32_t c = 0;
+        auto some = [&](auto n_c) __attribute__((always_inline)) {           // so many loads in flight, added in order
+            constexpr int U = decltype(n_c)::value;
+            for (; c + U <= n; c += U, src += U * step) {
+                f4 v[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f4*>(row_ptr(c + u));
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f4*>(src + u * step + uint32_t(col));
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] += v[u][q];
-        }
-        for (; c + 4 <= c1; c += 4) {
-            const f4 v0 = *reinterpret_cast<const f4*>(row_ptr(c));
-            const f4 v1 = *reinterpret_cast<const f4*>(row_ptr(c + 1));
-            const f4 v2 = *reinterpret_cast<const f4*>(row_ptr(c + 2));
-            const f4 v3 = *reinterpret_cast<const f4*>(row_ptr(c + 3));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q] = (((acc[q] + v0[q]) + v1[q]) + v2[q]) + v3[q];
-        }
-        for (; c < c1; ++c) {
-            const f4 v = *reinterpret_cast<const f4*>(row_ptr(c));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q] += v[q];
-        }
-        float* o = out + size_t(R) * D + col;
-        f4 res;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) res[q] = accumulate ? o[q] + acc[q] : acc[q];
-        *reinterpret_cast<f4*>(o) = res;
+                for (int u = 0; u < U; ++u) acc = acc + v[u];
+            }
+        };
+        some(std::integral_constant<int, 8>{});
+        some(std::integral_constant<int, 4>{});
+        some(std::integral_constant<int, 1>{});
+        *reinterpret_cast<f4*>(o) = accumulate ? *reinterpret_cast<f4*>(o) + acc : acc;
     } else {
-        for (int32_t c = c0; c < c1; c += 8) {   // (the same for rows that do not start on 16-byte boundaries)
-            float v[8][4];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[u][q] = (c + u < c1 && q < nv) ? row_ptr(c + u)[q] : 0.f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (c + u < c1)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[q] += v[u][q];
+        for (int q = 0; q < D - col; ++q) {          // (the last columns of a width that is no multiple of 4)
+            float acc = 0.f;
+#pragma unroll 8
+            for (int32_t c = 0; c < n; ++c) acc += src[c * step + uint32_t(col + q)];
+            o[q] = accumulate ? o[q] + acc : acc;
         }
-        float* o = out + size_t(R) * D + col;
-        for (int q = 0; q < nv; ++q) o[q] = accumulate ? o[q] + acc[q] : acc[q];
     }
 }
 
