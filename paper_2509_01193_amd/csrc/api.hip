@@ -351,6 +351,12 @@ lobra_status plan_fwd(const lobra_mlora_plan* plan, const void* x, const void* W
     const PlanDev pd = device_view(p);
     const int dt = p.desc.dtype;
     if (!p.mfma) {
+        if (adapters && p.fused_fwd) {
+            LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK_GEMM,
+                         gemm_f32_fused(pd, p.f32_items, false, static_cast<const float*>(x), static_cast<const float*>(W), static_cast<const float*>(A), s,
+                                        static_cast<float*>(hbuf), static_cast<const float*>(B), static_cast<float*>(y), pd.d_in, pd.d_out, pd.d_out, st));
+            return LOBRA_OK;
+        }
         if (adapters)
             LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
                          plain_shrink(pd, dt, x, A, s, static_cast<float*>(hbuf), pd.d_in, st));
@@ -444,16 +450,24 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
         if (adapters) {
             if (!H) {
                 float* Hr = reinterpret_cast<float*>(wsb + p.bwd_off_h);
-                LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK, plain_shrink(pd, dt, x, A, s, Hr, pd.d_in, st));
+                LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
+                             p.fused_fwd ? gemm_f32_fused(pd, p.f32_items, false, static_cast<const float*>(x), static_cast<const float*>(W),
+                                                          static_cast<const float*>(A), s, Hr, static_cast<const float*>(B), nullptr, pd.d_in, pd.d_out,
+                                                          pd.d_out, st)
+                                         : plain_shrink(pd, dt, x, A, s, Hr, pd.d_in, st));
                 H = Hr;
             }
             const size_t esz = dt == LOBRA_F32 ? 4 : 2;
-            for (int32_t j = 0; j < p.n_proj; ++j)
+            for (int32_t j = 0; !p.fused_bwd && j < p.n_proj; ++j)
                 LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
                              plain_shrink(pd, dt, static_cast<const char*>(dy) + size_t(j) * pd.dg * esz, B, s, G,
                                           pd.dg, st, pd.d_out, p.n_proj, j));
         }
-        if (want_dx && p.desc.T > 0)
+        if (adapters && p.fused_bwd)                 // (without dx: the projection alone)
+            LOBRA_LAUNCH(p, st, want_dx ? LOBRA_K_SHRINK_GEMM : LOBRA_K_SHRINK,
+                         gemm_f32_fused(pd, p.f32_items, true, static_cast<const float*>(dy), static_cast<const float*>(W), static_cast<const float*>(B), s, G,
+                                        static_cast<const float*>(A), want_dx ? static_cast<float*>(dx) : nullptr, pd.d_out, pd.d_in, pd.d_out, st));
+        else if (want_dx && p.desc.T > 0)
             LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                          plain_gemm(pd, dt, true, dy, W, G, A, dx, pd.d_out, pd.d_in, pd.d_out, st));
         if (p.R_tot > 0) {

@@ -40,6 +40,12 @@ __device__ __forceinline__ const int32_t* cseg_rank(const PlanDev& pd)
 // [ceil(T/32)], in plans of fp32 batches, where the MFMA kernels' records would be
 __device__ __forceinline__ const F32BlockRec* f32_block_rec(const PlanDev& pd) { return reinterpret_cast<const F32BlockRec*>(pd.gemm_tile_seg); }
 
+// [ceil(T/32)][Plan::f32_items], behind them
+__device__ __forceinline__ const F32Item* f32_items(const PlanDev& pd)
+{
+    return reinterpret_cast<const F32Item*>(f32_block_rec(pd) + (pd.T + kRowBlock - 1) / kRowBlock);
+}
+
 // [T][2], in plans with a projection beside its product and at most kRowTableTokens tokens: first rank row and rank of every row's task
 // (0, 0: none).
 __device__ __forceinline__ const int32_t* row_rank(const PlanDev& pd) { return cseg_rank(pd) + 2 * size_t(pd.nseg); }

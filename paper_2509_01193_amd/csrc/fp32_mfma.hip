@@ -56,24 +56,31 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __bui
 // wave tile and the ones behind it, for row i of the "A" operand.  (TN = 64 and 32: the chunks of odd lane groups' k rows are
 // exchanged half a row apart, so that two groups' reads fall into different banks.)
 // -------------------------------------------------------------------------------------------
-template <bool TRANSW, int TM, int TN, int STAGES, int OCC, bool VEC>
+template <bool TRANSW, int TM, int TN, int STAGES, int OCC, bool VEC, int NI = 0>
 __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ W,
                                                                const float* __restrict__ P, const float* __restrict__ M,
                                                                float* __restrict__ C, int32_t K, int32_t N, int32_t ldw, int32_t ldc,
-                                                               int32_t nproj, int32_t proj, int32_t tiles_n)
+                                                               int32_t nproj, int32_t proj, int32_t tiles_n,
+                                                               const float* __restrict__ D, const float* __restrict__ s,
+                                                               float* __restrict__ Pout)
 {
+    // NI > 0 (P = NULL): the tile projects its own rows.  The up to NI blocks of 16 ranks that its row block meets (F32Item) are further
+    // rows of the ring, their products with the tile's rows of Z further MFMAs of the waves, and the workgroups of the first
+    // column tile store the projected activations.
     using gemm::static_for;
     using gemm::swz_row;
     using gemm::wait_vmcnt;
     constexpr int FK = 32, WTM = TM / 2, WTN = TN / 2, MB = WTM / 16, NB = WTN / 16;
-    constexpr int ZT = TM * FK * 4, SLOT = ZT + TN * FK * 4;
+    constexpr int ZT = TM * FK * 4, AOFF = ZT + TN * FK * 4, SLOT = AOFF + NI * 16 * FK * 4;
     constexpr int E = VEC ? 4 : 1, LB = 64 * E * 4;              // elements per lane and bytes of a copy
-    constexpr int ZC = ZT / LB / 4, WC = TN * FK * 4 / LB / 4, CPW = ZC + WC;    // copies per wave and K tile
+    constexpr int ZC = ZT / LB / 4, WC = TN * FK * 4 / LB / 4, AC = NI * 16 * FK * 4 / LB / 4;
+    constexpr int CPW = ZC + WC + AC;                            // copies per wave and K tile
     constexpr int ZL = FK / E, CR = TN / E;                      // lanes of a copy per row of 32 k, per k row of n
     constexpr int FPITCH = 20, NPITCH = TN + 4;                  // adapter step of 16 ranks: [rows][k] and [k][n] in front of the ring
     constexpr int ROW_TASK = (TM * FPITCH + 16 * NPITCH) * 4;    // behind it: the rows' tasks, and which rows are the first of one
     static_assert(ROW_TASK + TM * 4 + 16 <= STAGES * SLOT && ROW_TASK % 16 == 0, "the adapter term fits the ring");
     static_assert(TM <= 128 && NB <= 4 && (STAGES - 1) * CPW < 64, "two words of firsts; reads of up to 16 bytes; what vmcnt can count");
+    static_assert(NI == 0 || (TM == 32 && TN == 32 && NI % 2 == 0), "a wave has every second block of ranks for its half of the rows");
     __shared__ __attribute__((aligned(16))) unsigned char lds[STAGES * SLOT];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, j = lane & 15, kg = lane >> 4;
@@ -83,6 +90,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
 
     const F32BlockRec rec = P ? f32_block_rec(pd)[row0 / kRowBlock] : F32BlockRec{};     // (in front of the copies: a scalar load)
     const bool many = P && rec.fifth < row_end;      // more than kFewSegments segments in the tile
+    F32Item item[NI > 0 ? NI : 1];
+    if constexpr (NI > 0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) item[i] = f32_items(pd)[size_t(row0 / kRowBlock) * NI + i];
+    }
 
     // ---- copies: rows beyond T and columns beyond N repeat the last one (what they produce is not stored), chunks beyond K too (the
     //      fragments are cleared)
@@ -115,18 +127,42 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     for (int c = 0; c < ZC; ++c) zvo[c] = z_off(c, FK);
 #pragma unroll
     for (int c = 0; c < WC; ++c) wvo[c] = w_off(c, FK);
+    // (rank rows: a copy has rows of one block; those beyond its last repeat it)
+    const unsigned char* abase[AC > 0 ? AC : 1];
+    int32_t an[AC > 0 ? AC : 1];
+    uint32_t avo[AC > 0 ? AC : 1];
+    size_t aat = 0;
+    auto a_off = [&](int c, int32_t left) {
+        const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
+        return (uint32_t(min(row & 15, max(an[c] - 1, 0))) * uint32_t(K) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
+    };
+    if constexpr (NI > 0) {
+#pragma unroll
+        for (int c = 0; c < AC; ++c) {
+            int32_t row = item[0].row;
+            an[c] = item[0].n;
+#pragma unroll
+            for (int i = 1; i < NI; ++i)
+                if ((64 / ZL * (wave + 4 * c)) >> 4 == i) row = item[i].row, an[c] = item[i].n;
+            abase[c] = reinterpret_cast<const unsigned char*>(D + size_t(row) * K);
+            avo[c] = a_off(c, FK);
+        }
+    }
     auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {
         constexpr int c = decltype(c_c)::value;
         if constexpr (c < ZC) dma(la + 4 * c * LB, zcur, zvo[c]);
-        else dma(la + ZT + 4 * (c - ZC) * LB, wcur, wvo[c - ZC]);
+        else if constexpr (c < ZC + WC) dma(la + ZT + 4 * (c - ZC) * LB, wcur, wvo[c - ZC]);
+        else dma(la + AOFF + 4 * (c - ZC - WC) * LB, abase[c - ZC - WC] + aat, avo[c - ZC - WC]);
     };
-    auto next_copy_tile = [&]() __attribute__((always_inline)) { zcur += FK * 4, wcur += wstep; };
+    auto next_copy_tile = [&]() __attribute__((always_inline)) { zcur += FK * 4, wcur += wstep, aat += FK * 4; };
     const int32_t KT = (K + FK - 1) / FK, ktail = K % FK, KF = K / FK;
     auto copy_tail = [&](uint32_t la) {
 #pragma unroll
         for (int c = 0; c < ZC; ++c) dma(la + 4 * c * LB, zcur, z_off(c, ktail));
 #pragma unroll
         for (int c = 0; c < WC; ++c) dma(la + ZT + 4 * c * LB, wcur, w_off(c, ktail));
+#pragma unroll
+        for (int c = 0; c < AC; ++c) dma(la + AOFF + 4 * c * LB, abase[c] + aat, a_off(c, ktail));
     };
     for (int s = 0; s < STAGES; ++s) {
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * SLOT); });
@@ -161,17 +197,34 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         load_adapter(max(rec.lo, row0), min(rec.hi, row_end), r, proj * r, rec.rank0 + proj * r, 0);
     }
 
+    float mi[NI > 0 ? NI : 1][WA], scale[NI > 0 ? NI / 2 : 1];       // the up factors' rows of the blocks; the scales of this wave's
+    if constexpr (NI > 0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int u = 0; u < WA; ++u) {
+                const int e = tid + 256 * u, n = col0 + e % TN, kk = e / TN;
+                mi[i][u] = kk < item[i].n && n < N ? M[size_t(item[i].row + kk) * N + n] : 0.f;
+            }
+#pragma unroll
+        for (int b = 0; b < NI / 2; ++b) scale[b] = s[wn ? item[2 * b + 1].task : item[2 * b].task];
+    }
+
     // ---- fragments and the steps of 16 k
+    constexpr int HB = NI / 2;                       // this wave's blocks of ranks: wn, wn + 2, ...
     struct Frags {
         f32x4 z[MB];
         float w[NB][4];                              // [block][q]
+        f32x4 a[HB > 0 ? HB : 1];
     };
-    constexpr int NR = MB + (TRANSW ? NB : 4);       // reads of a step
+    constexpr int NR = MB + (TRANSW ? NB : 4) + HB;  // reads of a step
     auto read = [&](auto i_c, Frags& f, const unsigned char* slot, int ks) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value;
         constexpr int NW = TRANSW ? NB : 4;
         const int ch = (4 * ks + kg) ^ swz_row(j);
-        if constexpr (i >= NW) {
+        if constexpr (i >= NW + MB) {
+            f.a[i - NW - MB] = *reinterpret_cast<const f32x4*>(slot + AOFF + ((wn + 2 * (i - NW - MB)) * 16 + j) * 128 + ch * 16);
+        } else if constexpr (i >= NW) {
             f.z[i - NW] = *reinterpret_cast<const f32x4*>(slot + (wm * WTM + (i - NW) * 16 + j) * 128 + ch * 16);
         } else if constexpr (TRANSW) {
             const f32x4 v = *reinterpret_cast<const f32x4*>(slot + ZT + (wn * WTN + i * 16 + j) * 128 + ch * 16);
@@ -195,12 +248,18 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the 4 MB NB MFMAs on `f`, with the reads of the next step's fragments and (COPY) a K tile's copies dealt evenly behind them
-    auto kstep = [&](auto read_c, auto copy_c, const Frags& f, Frags& next, const unsigned char* slot, int ks, uint32_t la) __attribute__((always_inline)) {
-        constexpr int NM = 4 * MB * NB, R = decltype(read_c)::value ? NR : 0, CC = decltype(copy_c)::value ? CPW : 0;
+    f32x4 hacc[HB > 0 ? HB : 1][2];                  // the projections, first and second K steps of a K tile apart
+#pragma unroll
+    for (int b = 0; b < HB; ++b) hacc[b][0] = hacc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the MFMAs on `f`, fragments of K step ks ^ 1, with the reads of the next step's fragments (ks) and (COPY) a K tile's copies dealt
+    // evenly behind them
+    auto kstep = [&](auto read_c, auto copy_c, const Frags& f, Frags& next, const unsigned char* slot, auto ks_c, uint32_t la) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_c)::value, PQ = MB * NB + HB;
+        constexpr int NM = 4 * PQ, R = decltype(read_c)::value ? NR : 0, CC = decltype(copy_c)::value ? CPW : 0;
         static_for<0, NM>([&](auto m_c) {
-            constexpr int m = decltype(m_c)::value, q = m / (MB * NB), mb = m / NB % MB, nb = m % NB;
-            acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+            constexpr int m = decltype(m_c)::value, q = m / PQ, mb = m % PQ / NB, nb = m % PQ % NB;
+            if constexpr (m % PQ < MB * NB) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+            else hacc[m % PQ - MB * NB][ks ^ 1] = mfma4(f.a[m % PQ - MB * NB][q], f.z[0][q], hacc[m % PQ - MB * NB][ks ^ 1]);
             static_for<m * R / NM, (m + 1) * R / NM>([&](auto i_c) { read(i_c, next, slot, ks); });
             static_for<m * CC / NM, (m + 1) * CC / NM>([&](auto c_c) { copy(c_c, la); });
             __builtin_amdgcn_sched_barrier(0);
@@ -214,8 +273,12 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             for (int mb = 0; mb < MB; ++mb) f.z[mb][q] = in ? f.z[mb][q] : 0.f;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) f.w[nb][q] = in ? f.w[nb][q] : 0.f;
+#pragma unroll
+            for (int b = 0; b < HB; ++b) f.a[b][q] = in ? f.a[b][q] : 0.f;
         }
     };
+    using step0 = std::integral_constant<int, 0>;
+    using step1 = std::integral_constant<int, 1>;
     using yes = std::true_type;
     using no = std::false_type;
     auto barrier = []() __attribute__((always_inline)) {
@@ -231,21 +294,21 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     int32_t kt = 0, slot = 0;
     auto ktile = [&]() __attribute__((always_inline)) {              // a whole K tile is still to be copied
         const unsigned char* cur = lds + slot * SLOT;
-        kstep(yes{}, no{}, fa, fb, cur, 1, 0);
+        kstep(yes{}, no{}, fa, fb, cur, step1{}, 0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wait_vmcnt<(STAGES - 2) * CPW>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const uint32_t la = la0 + slot * SLOT;
         slot = slot + 1 == STAGES ? 0 : slot + 1;
-        kstep(yes{}, yes{}, fb, fa, lds + slot * SLOT, 0, la);
+        kstep(yes{}, yes{}, fb, fa, lds + slot * SLOT, step0{}, la);
         next_copy_tile();
     };
     for (; kt < KF - STAGES; ++kt) ktile();
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;            // uniform
         if (tail) clear_tail(fa, 0);
-        kstep(yes{}, no{}, fa, fb, lds + slot * SLOT, 1, 0);
+        kstep(yes{}, no{}, fa, fb, lds + slot * SLOT, step1{}, 0);
         if (tail) clear_tail(fb, 1);
         if (kt + 1 < KT) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -254,14 +317,16 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             asm volatile("" ::: "memory");
             if (kt + STAGES < KT) copy_tail(la0 + slot * SLOT);
             slot = slot + 1 == STAGES ? 0 : slot + 1;
-            kstep(yes{}, no{}, fb, fa, lds + slot * SLOT, 0, 0);
+            kstep(yes{}, no{}, fb, fa, lds + slot * SLOT, step0{}, 0);
         } else {
-            kstep(no{}, no{}, fb, fa, lds, 0, 0);
+            kstep(no{}, no{}, fb, fa, lds, step0{}, 0);
         }
     }
 
     // ---- adapter term: 16 ranks at a time are further k of the same tile product, rows outside the segment and ranks beyond r_t zero (the
-    //      loops are uniform over the workgroup): as in gemm_f32_kernel
+    //      loops are uniform over the workgroup).  Where more than kFewSegments segments cross the tile, per task that has rows in it
+    //      (8000 one-token segments of 8 tasks of rank 128, 10 x 1373: 4820 -> 290 us; 10119 tokens in segments of 3, rank 8, 64 x 1920:
+    //      390 -> 112).
     float *const zs = reinterpret_cast<float*>(lds), *const ws = zs + TM * FPITCH;
     auto stash_adapter = [&]() {
 #pragma unroll
@@ -270,7 +335,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
     };
     auto col_of = [&](int nb, int i) { return wn * WTN + (TRANSW ? nb * 16 + i : NB * i + nb); };    // of result row i of block nb
-    auto mac = [&]() {
+    auto mac = [&](const float* zs, const float* ws) {
         Frags f;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) f.z[mb] = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + 4 * kg);
@@ -285,6 +350,41 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
     };
+    if constexpr (NI > 0) {
+        constexpr int HZ = TM * FPITCH, HW = 16 * NPITCH;
+        static_assert(NI * (HZ + HW) * 4 <= STAGES * SLOT, "all blocks fit the ring");
+        __syncthreads();                             // everybody is done with the ring
+#pragma unroll
+        for (int b = 0; b < HB; ++b) {               // lane (j, kg): ranks 4 kg .. + 3 of token row j of the wave's half
+            const F32Item u = item[2 * b], w = item[2 * b + 1];          // (member by member: a choice of whole ones goes through memory)
+            const F32Item t = {wn ? w.lo : u.lo, wn ? w.hi : u.hi, 0, wn ? w.n : u.n, 0, wn ? w.c0 : u.c0, wn ? w.r : u.r, 0};
+            const int32_t row = row0 + wm * 16 + j;
+            const bool in = row >= t.lo && row < t.hi;
+            const f32x4 sum = hacc[b][0] + hacc[b][1];
+            f32x4 h;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = in && 4 * kg + v < t.n ? scale[b] * sum[v] : 0.f;
+            *reinterpret_cast<f32x4*>(zs + (wn + 2 * b) * HZ + (wm * 16 + j) * FPITCH + 4 * kg) = h;
+            if (col0 == 0 && in) {
+                // (and zeros behind the task's last block, as far as a row goes)
+                float* dst = Pout + size_t(row) * pd.r_max;
+                for (int32_t k = t.c0 + 4 * kg; k < (t.c0 + 16 < t.r ? t.c0 + 16 : pd.r_max); k += 16) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (k + v < pd.r_max) dst[k + v] = h[v];
+                    h = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int u = 0; u < WA; ++u) zs[NI * HZ + i * HW + (tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = mi[i][u];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if (item[i].n > 0) mac(zs + i * HZ, zs + NI * HZ + i * HW);      // (uniform)
+    }
     if (some || many) __syncthreads();               // everybody is done with the ring
     if (some) {
         for (int32_t sg = rec.first; sg < pd.nseg; ++sg) {
@@ -299,7 +399,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
                 if (sg != rec.first || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
                 stash_adapter();
                 __syncthreads();
-                mac();
+                mac(zs, ws);
                 __syncthreads();
             }
         }
@@ -353,10 +453,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             __syncthreads();
             more = next();
             if (more) load();
-            mac();
+            mac(zs, ws);
             __syncthreads();
         }
     }
+    if (NI > 0 && !C) return;                        // (the projection alone was asked for)
     // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column col_of(nb, 4 kg + v)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -405,17 +506,41 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
     const int32_t tiles_n = (N + tm - 1) / tm;
     const dim3 grid(uint32_t((pd.T + tm - 1) / tm) * uint32_t(tiles_n));
 #define LOBRA_F32_GEMM(TR, TILE, STAGES, OCC) \
-    (vec ? gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, true> : gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, false>)<<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n)
+    (vec ? gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, true> : gemm_f32_kernel<TR, TILE, TILE, STAGES, OCC, false>)<<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n, nullptr, nullptr, nullptr)
 #define LOBRA_F32_GEMM2(TR) \
     do { \
         if (tm == 32) LOBRA_F32_GEMM(TR, 32, 5, 4); \
         else if (tm == 64) LOBRA_F32_GEMM(TR, 64, 3, 3); \
-        else gemm_f32_kernel<TR, 128, 128, 2, 2, true><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n); \
+        else gemm_f32_kernel<TR, 128, 128, 2, 2, true><<<grid, 256, 0, st>>>(pd, Z, W, P, M, C, K, N, ldw, ldc, nproj, proj, tiles_n, nullptr, nullptr, nullptr); \
     } while (0)
     if (transW) LOBRA_F32_GEMM2(true);
     else LOBRA_F32_GEMM2(false);
 #undef LOBRA_F32_GEMM
 #undef LOBRA_F32_GEMM2
+    return hipGetLastError();
+}
+
+// The same with the projection of Z's rows in the product's launch (pd's plan has ni items per 32-row block, see f32_fused): what a
+// short batch is bound by is launches and round trips to memory.  618 x 256 x 256, two tasks of rank 8, projection and product 4.6 + 7.1
+// us, like this 7.2 (the step 26.7 -> 22.3).  C = NULL: the projection alone, by the workgroups of the first column tile, so that it gives the same bits.
+hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const float* Z, const float* W, const float* D, const float* s, float* P,
+                          const float* M, float* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st)
+{
+    const int32_t tiles_n = C ? (N + 31) / 32 : 1;
+    const dim3 grid(uint32_t((pd.T + 31) / 32) * uint32_t(tiles_n));
+    const bool vec = ((K | N | ldw) & 3) == 0;
+#define LOBRA_F32_FUSED(TR, NI, OCC) \
+    (vec ? gemm_f32_kernel<TR, 32, 32, 4, OCC, true, NI> : gemm_f32_kernel<TR, 32, 32, 4, OCC, false, NI>)<<<grid, 256, 0, st>>>(pd, Z, W, nullptr, M, C, K, N, ldw, N, 1, 0, tiles_n, D, s, P)
+    if (ni == 2) {
+        if (transW) LOBRA_F32_FUSED(true, 2, 3);
+        else LOBRA_F32_FUSED(false, 2, 3);
+    } else if (ni == 4) {
+        if (transW) LOBRA_F32_FUSED(true, 4, 2);
+        else LOBRA_F32_FUSED(false, 4, 2);
+    } else {
+        return hipErrorInvalidValue;
+    }
+#undef LOBRA_F32_FUSED
     return hipGetLastError();
 }
 

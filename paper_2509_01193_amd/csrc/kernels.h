@@ -54,6 +54,8 @@ hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& 
 // ---- fp32 storage on the matrix cores (fp32_mfma.hip), reached through the three above; arguments as there ------------
 hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
                       int32_t nproj, int32_t proj, hipStream_t st);
+hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const float* Z, const float* W, const float* D, const float* s, float* P,
+                          const float* M, float* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st);
 hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,
                     int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st);
 hipError_t grad_f32_stage1(const PlanDev& pd, const float* P, const float* Z, float* part, int32_t D, int32_t ldz, int32_t nproj,

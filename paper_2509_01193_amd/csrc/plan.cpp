@@ -270,6 +270,23 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
         //             105.2, 57 161.6 / 162.2; 1999 x 500, n = 30 129.7 / 121.5
         //   rank 32   256 x 256, n = 10 34.9 / 32.3, 30 40.0 / 42.3;  rank 64  n = 4 39.9 / 36.7, 22 50.7 / 56.7;  rank 128  n = 13 64.1 / 69.6
         // (tasks within what the grid takes)
+        p->f32_items = 0;
+        p->fused_fwd = p->fused_bwd = false;
+        if (d->dtype == LOBRA_F32 && p->n_proj == 1 && !p->tb.empty() && T <= kFusedTokens) {
+            int32_t most = 0;
+            for (int32_t b = 0; b < nrb; ++b) {
+                int32_t items = 0;
+                for (int32_t k = p->rowblk_seg[size_t(b)]; k < nseg && p->cseg_off[size_t(k)] < (b + 1) * kRowBlock; ++k) {
+                    const int32_t t = p->cseg_task[size_t(k)];
+                    if (t >= 0) items += (p->rank_off[t + 1] - p->rank_off[t] + 15) / 16;
+                }
+                most = std::max(most, items);
+            }
+            const int32_t items = most <= 2 ? 2 : most <= 4 ? 4 : 0;
+            p->fused_fwd = f32_fused(T, d->d_in, d->d_out, items);
+            p->fused_bwd = f32_fused(T, d->d_out, d->d_in, items);
+            if (p->fused_fwd || p->fused_bwd) p->f32_items = items;
+        }
         p->grad_one = false;
         if (d->dtype == LOBRA_F32 && p->n_proj == 1 && n <= 65535) {
             int64_t most = 0;
@@ -548,7 +565,18 @@ std::vector<int32_t> pack_blob(Plan* p)
             r.rank = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
             r.pad = 0;
         }
-        p->o_tile_seg = put(reinterpret_cast<const int32_t*>(rec.data()), rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
+        std::vector<int32_t> list(reinterpret_cast<const int32_t*>(rec.data()), reinterpret_cast<const int32_t*>(rec.data() + rec.size()));
+        for (size_t b = 0; p->f32_items > 0 && b < rec.size(); ++b) {
+            int32_t left = p->f32_items;
+            for (int32_t k = rec[b].own; k < nseg && p->cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
+                const int32_t t = p->cseg_task[size_t(k)];
+                const int32_t r = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
+                for (int32_t c = 0; c < r; c += 16, --left)
+                    list.insert(list.end(), {p->cseg_off[size_t(k)], p->cseg_off[size_t(k) + 1], p->rank_off[t] + c, std::min(r - c, 16), t, c, r, 0});
+            }
+            list.resize(list.size() + size_t(left) * (sizeof(F32Item) / sizeof(int32_t)), 0);
+        }
+        p->o_tile_seg = put(list.data(), list.size());
     } else {
         // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
         const size_t nseg = p->cseg_task.size(), at = p->gemm_tile_seg.size();

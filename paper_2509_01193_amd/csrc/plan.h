@@ -27,6 +27,20 @@ constexpr int64_t kPlainMaxTokens = 65535 * 64;
 constexpr int kFewSegments = 4;
 struct F32BlockRec { int32_t own, fifth, first, lo, hi, rank0, rank, pad; };
 
+// fp32, short batches: a block of up to 16 ranks that a 32-row block's product meets - the rows of its segment, its first rank row, how many
+// there are (0: no such block), the task, the block's first rank within the task and the task's rank
+struct F32Item { int32_t lo, hi, row, n, task, c0, r, pad; };
+// The projection runs inside its product (gemm_f32_fused) in tiles of 32 x 32, each of which projects its own rows: of a batch whose 32-row
+// blocks meet at most four blocks of ranks (`items` 2 or 4), while that costs less than a launch: training steps, us, apart / inside, with
+// tiles x K x items in Ki: 200 x 1024 x 512 38.7 / 28.5 (224), 32 x 2048 x 2048 59.3 / 53.4 (256), 618 x 512 x 512 35.7 / 31.5 (320),
+// 1000 x 256 x 1024 at rank 32 48.4 / 49.0 (1024).  The table of items is 4 KiB at most, which one-shot calls send.
+constexpr int64_t kFusedTokens = 1024, kFusedTiles = 1024;
+inline bool f32_fused(int64_t T, int32_t K, int32_t N, int32_t items)
+{
+    const int64_t n = (T + 31) / 32 * ((int64_t(N) + 31) / 32);
+    return items > 0 && T <= kFusedTokens && n <= kFusedTiles && n * K * items <= 640 * 1024;
+}
+
 struct TokenBlock { int32_t row0, nrows, task, rank_row0; };
 struct GradChunk  { int32_t tb_begin, tb_end, task, part_row0; };
 
@@ -162,6 +176,8 @@ struct Plan {
     // no task has more than one chunk: no partial sums to add (tasks without tokens, which stage 1 then clears: only while
     // there are few tasks, since it starts a workgroup for each of them and column tile)
     bool single_chunks = false, empty_tasks = false;
+    int32_t f32_items = 0;      // fp32: blocks of ranks per 32-row block in the table of items (2 or 4), 0: no table
+    bool fused_fwd = false, fused_bwd = false;      // fp32: the projection inside its product
     bool grad_one = false;      // fp32: both gradients without partial sums (grad_f32_one)
     int32_t part_rows = 0;              // rows of the partial-sum buffer = sum over chunks of r_t
     int32_t chunk_blocks = 0;           // token blocks per reduction chunk

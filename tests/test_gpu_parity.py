@@ -601,6 +601,44 @@ def test_fp32_kernels_every_tile_size_and_odd_widths(T, d_in, d_out):
     assert bool(torch.isnan(dp.y[bad]).all()) and not bool(torch.isfinite(dp.dx[bad]).any())
 
 
+@pytest.mark.parametrize("T,d_in,d_out,ranks,longest,inside", [
+    (1, 96, 100, [16], 1, True),               # one row; as many K tiles as the ring has slots and fewer
+    (33, 31, 65, [7, 3], 40, True),            # a last row block of one row, widths at any element, a K tile of 31
+    (300, 160, 132, [16, 5, 1], 90, True),     # more K tiles than slots; a partial last one in one direction
+    (1024, 64, 96, [32, 20], 1000, True),      # the longest batch; ranks of two blocks, the second one partial
+    (1025, 64, 96, [32, 20], 1000, False),     #   and one more
+    (200, 130, 260, [64], 200, True),          # four blocks of ranks
+    (200, 132, 256, [65], 200, False),         #   and one more
+    (96, 200, 72, [16, 9], 7, False),          # more than four segments in a row block
+])
+def test_fp32_projection_inside_the_product(T, d_in, d_out, ranks, longest, inside):
+    """Short fp32 batches: one launch projects and multiplies.  Both passes against the oracle, which way they went, and the
+    projections the same numbers where they are made again or without dx."""
+    import torch
+    rng = np.random.default_rng(T + d_in)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.integers((longest + 1) // 2, longest + 1)), T - sum(lens)))
+    tasks = [(k % (len(ranks) + 1)) - 1 if len(lens) > 3 else k % len(ranks) for k in range(len(lens))]
+    p = wl.make_custom("inside-%d" % T, "f32", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]), tasks, 67,
+                       s=np.linspace(-1, 2, len(ranks)).astype(np.float32), std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, label="inside")
+    tr = bd.LaunchTrace(dp.plan, 8)
+    tr.attach()
+    dp.step()
+    torch.cuda.synchronize()
+    names = [name for name, _ in tr.durations()]
+    tr.close()
+    assert names[:2] == (["shrink_gemm"] * 2 if inside else ["shrink", "gemm"])
+    want = [t.clone() for t in (dp.dA, dp.dB)]
+    for h, flags in ((None, 0), (dp.h_save, bd.FLAG_NO_DX), (None, bd.FLAG_NO_DX)):
+        dp.dA.fill_(7.0), dp.dB.fill_(7.0)
+        bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, h, dp.dx, dp.dA, dp.dB, flags, dp.ws)
+        torch.cuda.synchronize()
+        assert torch.equal(want[0], dp.dA) and torch.equal(want[1], dp.dB), (h is None, flags)
+    assert dp.guards_intact()
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj,longest", [
     (3001, 4, 2052, 1, 400),        # a K tile of 4, a last row tile of 57 (of 64) and a last column tile of 4
     (3001, 96, 1028, 1, 400),       # as many K tiles as the ring has slots
