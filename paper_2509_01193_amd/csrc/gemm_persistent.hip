@@ -10,9 +10,9 @@
 //   * the K tiles of ALL of a workgroup's output tiles form one stream through the two LDS stages: while the
 //     last K tiles of an output tile are multiplied, the first K tiles of the next one are already being
 //     copied, so no stage fill is exposed except the very first;
-//   * the epilogue keeps its hands off the two stages: the adapter slice of the fused up projection is staged
-//     in a third LDS region (for the tile's first segment it and the tile's rows of P are copied there while the
-//     last K tile is multiplied, see prefetch_adapter), and the result is rounded, passed through the same region
+//   * the epilogue keeps its hands off the two stages: the operands of the fused up projection's steps are copied
+//     to a third LDS region (the first step's while the tile's last K tile is multiplied, see prefetch_adapter;
+//     every other's under the step before), and the result is rounded, passed through the same region
 //     (a 64 x 64 block per wave at a time) and stored in whole 128-byte lines; the stores drain under the next
 //     tile's first MFMAs.
 // One workgroup per output tile instead costs about 15 us per tile (workgroup start, two exposed stage fills,
@@ -29,7 +29,7 @@
 // software-pipelined by hand and its order is pinned (the MFMAs are volatile asm statements, sched_barrier
 // between the slots); see kstep for the schedule of a K step.
 //
-// LDS: stage 0, stage 1 (64 KiB each: Z tile then W tile), adapter slice / result staging (32 KiB).
+// LDS: stage 0, stage 1 (64 KiB each: Z tile then W tile), up projection's step / result staging (32 KiB).
 //   Z tile, and the W tile when K is fastest (backward): [256 rows][64 k], 16-byte chunk c of a row
 //       stored at c ^ ((row >> 1) & 7): the 16 rows of one ds_read_b128 pass hit 16 bank groups.
 //   W tile when N is fastest (forward), adapter slice: [k][256 n], chunk c of k-row k stored at c ^ kn_swz2(k);
