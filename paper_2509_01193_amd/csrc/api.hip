@@ -702,7 +702,11 @@ lobra_status lobra_token_task_map(const lobra_mlora_desc* desc, int32_t* out_tas
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     void* dev = nullptr;
     // the call has no workspace argument: the tables go into the library's static device array
-    if (p->blob_bytes > size_t(LOBRA_STATIC_WS_BYTES)) st = LOBRA_ERR_WORKSPACE;
+    // (all but the last list, which is about products; what is refused is counted with eight numbers per tile row for it)
+    const size_t all = (p->o_tile_seg + std::max<size_t>(p->gemm_tile_tab.size(), 1) + 3) / 4 * 16;
+    p->host_blob.resize(p->o_tile_seg);
+    p->blob_bytes = p->host_blob.size() * sizeof(int32_t);
+    if (all > size_t(LOBRA_STATIC_WS_BYTES)) st = LOBRA_ERR_WORKSPACE;
     else if ((st = static_scratch_address(&dev)) == LOBRA_OK && (st = upload_oneshot(p, dev, stream)) == LOBRA_OK) {
         st = lobra_mlora_plan_token_task_map(p, out_task, out_count, hip_stream);
         const lobra_status rel = release_after(stream, p);

@@ -1110,6 +1110,24 @@ def test_fwd_bwd_under_hip_graph_capture(kernels):
             assert torch.equal(a, b), (rep, name)
 
 
+@pytest.mark.parametrize("T,fits", [(550000, True), (600000, False)])
+def test_token_task_map_of_as_many_segments_as_the_static_array_holds(T, fits):
+    """One-token segments: the one-shot map takes a batch up to the same number of them whatever tables the products need beside."""
+    import torch
+    tasks = (np.arange(T) % 2).astype(np.int32)
+    d, keep = bd.make_desc("bf16", T, 64, 64, [0, 8, 16], np.arange(T + 1, dtype=np.int32), tasks)
+    out_task = torch.full((T,), -7, dtype=torch.int32, device="cuda")
+    out_cnt = torch.full((2,), -7, dtype=torch.int64, device="cuda")
+    if not fits:
+        with pytest.raises(bd.LobraError):
+            bd.lobra_token_task_map(d, out_task, out_cnt)
+        return
+    assert bd.plan_device_bytes(d) > bd.STATIC_WS_BYTES
+    bd.lobra_token_task_map(d, out_task, out_cnt)
+    torch.cuda.synchronize()
+    assert np.array_equal(out_task.cpu().numpy(), tasks) and out_cnt.tolist() == [T // 2, T // 2]
+
+
 @pytest.mark.parametrize("which", ["cfg1-f32", "cfg2-bf16-narrow", "adversarial-bf16"])
 def test_one_shot_descriptor_forms_against_the_oracle(which):
     """lobra_mlora_workspace_bytes / lobra_mlora_fwd / lobra_mlora_bwd / lobra_token_task_map on the descriptor
