@@ -350,86 +350,93 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
     //      acc += M_t^T[:, cols] * P[rows, :]^T, rows outside the segment and ranks beyond r_t cleared in registers.  A step has
     //      two halves of 16 ranks: the two of one segment's window of 32, or, where a window has at most 16 ranks left, those
     //      and all of the next segment's, if it has at most 16.  (A window of more is never divided between steps, so a row's
-    //      sum does not depend on what else is in its tile.)
+    //      sum does not depend on what else is in its tile.)  Of two segments each is multiplied only with the blocks of 16 rows
+    //      that it crosses: zeros in place of a row of P would not keep out what is not finite in another task's adapter.
     //      Both operands are copied into the adapter region, M_t in the [k][256 n] layout (rows beyond a half's last repeat it),
     //      P 64 bytes a row (chunks beyond repeat the half's first): the first step's while the tile's last K tile is multiplied,
     //      and every other's behind the reads of the one before, under its MFMAs.  What a step costs beyond its 64 MFMAs per wave
     //      is what is left of one round trip to memory.  (With each segment's slice passing through registers behind its own
-    //      chain of table reads, five round trips at rank 64, a step of 49152 x 8192 x 8192, 32 tasks of rank 64, took 9955 us, with
-    //      this 9823; 8190 x 1376 x 4096, rank 16, 235.8 -> 232.2, its products 95 -> 89 each; the forward product of 47000 x 600 x
-    //      7232 at rank 128 804 -> 625, of 12000 x 584 x 1000 in segments of four tokens 151 -> 91.)
+    //      chain of table reads, five round trips at rank 64, a step of 49152 x 8192 x 8192, 32 tasks of rank 64, took 9837 us, with
+    //      this 9764; 8190 x 1376 x 4096, rank 16, 236.4 -> 232.4; 16384 x 2048 x 4096 in segments of 40 tokens 508 -> 487; the forward
+    //      product of 47000 x 600 x 7232 at rank 128 804 -> 625, of 12000 x 584 x 1000 in segments of four tokens 151 -> 85.)
     //      tile_seg's record of the tile row, read when the tile's main loop begins: scalar registers.
     auto rfl = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
     int32_t rec[kGemmTileSegRec];
-    int32_t u_e, u_sg, u_lo, u_hi, u_m, u_r, u_k;    // the walk: entry, next segment to look at, the segment, its window, next rank of it
-    int32_t u_pc = 0, u_mcol0 = 0, u_mpitch = 0, u_pj = 0;
     struct Half { int32_t lo, hi, m, n, pc; };       // rows, first row of M, ranks (0: none), first column of P
-    Half ha, hb;                                     // the step that is in the region, or on its way
-    auto window = [&](int32_t lo, int32_t hi, int32_t r0, int32_t stacked) __attribute__((always_inline)) {
-        u_lo = lo;
-        u_hi = hi;
-        u_r = nproj == 1 ? stacked : rfl(stacked / nproj);
-        u_pc = u_pj * u_r;
-        u_m = r0 + u_pc;
-        u_k = 0;
+    struct Walk {                                    // over a tile's segments:
+        int32_t e, sg, lo, hi, m, r, k, pc;          // entry, next segment to look at, the segment, its window, next rank of it
+        int32_t pj, mcol0, mpitch;                   // the tile's projection, its first column, the row pitch of M
+        Half a, b;                                   // the step that is in the region, or on its way
     };
-    auto next_segment = [&](int32_t row_end) __attribute__((always_inline)) {     // u_r = 0: there is none
-        ++u_e;
-        if (u_e < kGemmTileSegs) {
-            const bool one = u_e == 1;
-            window(one ? rec[4] : rec[8], one ? rec[5] : rec[9], one ? rec[6] : rec[10], one ? rec[7] : rec[11]);
+    auto window = [&](Walk& w, int32_t lo, int32_t hi, int32_t r0, int32_t stacked) __attribute__((always_inline)) {
+        w.lo = lo;
+        w.hi = hi;
+        w.r = nproj == 1 ? stacked : rfl(stacked / nproj);
+        w.pc = w.pj * w.r;
+        w.m = r0 + w.pc;
+        w.k = 0;
+    };
+    auto next_segment = [&](Walk& w, int32_t row_end) __attribute__((always_inline)) {     // w.r = 0: there is none
+        ++w.e;
+        if (w.e < kGemmTileSegs) {
+            const bool one = w.e == 1;
+            window(w, one ? rec[4] : rec[8], one ? rec[5] : rec[9], one ? rec[6] : rec[10], one ? rec[7] : rec[11]);
             return;
         }
-        u_r = 0;
-        for (; u_sg < pd.nseg; ++u_sg) {
-            const int32_t lo = rfl(cseg_off[u_sg]);
+        w.r = 0;
+        for (; w.sg < pd.nseg; ++w.sg) {
+            const int32_t lo = rfl(cseg_off[w.sg]);
             if (lo >= row_end) return;
-            const int32_t t = rfl(cseg_task[u_sg]);
+            const int32_t t = rfl(cseg_task[w.sg]);
             if (t < 0) continue;
             const int32_t r0 = rfl(rank_off[t]);
-            window(lo, rfl(cseg_off[u_sg + 1]), r0, rfl(rank_off[t + 1]) - r0);
-            ++u_sg;
+            window(w, lo, rfl(cseg_off[w.sg + 1]), r0, rfl(rank_off[t + 1]) - r0);
+            ++w.sg;
             return;
         }
     };
-    auto load_table = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+    auto load_table = [&](int32_t row0) __attribute__((always_inline)) {
         if (!P) return;
         // (the last tile row may start above a multiple of the tile height)
         const int32_t* src = tile_seg + size_t((row0 + BM - 1) / BM) * kGemmTileSegRec;
 #pragma unroll
         for (int i = 0; i < 4 * kGemmTileSegs + 1; ++i) rec[i] = src[i];
-        u_pj = proj >= 0 ? proj : rfl(col0 / pd.dg);                 // this tile's projection,
-        u_mcol0 = proj >= 0 ? 0 : u_pj * pd.dg;                      // its first column
-        u_mpitch = proj >= 0 ? N : pd.dg;                            // and the row pitch of M
     };
-    auto first_segment = [&]() __attribute__((always_inline)) {
-        u_e = 0;
-        u_sg = rec[4 * kGemmTileSegs];
-        window(rec[0], rec[1], rec[2], rec[3]);
-    };
-    // the next step into (ha, hb); false: there is none
-    auto next_step = [&](int32_t row_end) __attribute__((always_inline)) {
-        if (u_r == 0) return false;
-        const int32_t left = u_r - u_k;
-        ha = Half{u_lo, u_hi, u_m + u_k, min(left, 16), u_pc + u_k};
-        hb = Half{u_lo, u_hi, ha.m, 0, ha.pc};
+    // the next step into (w.a, w.b); false: there is none
+    auto next_step = [&](Walk& w, int32_t row_end) __attribute__((always_inline)) {
+        if (w.r == 0) return false;
+        const int32_t left = w.r - w.k;
+        w.a = Half{w.lo, w.hi, w.m + w.k, min(left, 16), w.pc + w.k};
+        w.b = Half{w.lo, w.hi, w.a.m, 0, w.a.pc};
         if (left > 16) {
-            hb.m += 16;
-            hb.n = min(left - 16, 16);
-            hb.pc += 16;
+            w.b.m += 16;
+            w.b.n = min(left - 16, 16);
+            w.b.pc += 16;
         }
-        u_k += 32;
-        if (u_k >= u_r) {
-            next_segment(row_end);
-            if (left <= 16 && u_r > 0 && u_r <= 16) {
-                hb = Half{u_lo, u_hi, u_m, u_r, u_pc};
-                next_segment(row_end);
+        w.k += 32;
+        if (w.k >= w.r) {
+            next_segment(w, row_end);
+            if (left <= 16 && w.r > 0 && w.r <= 16) {
+                w.b = Half{w.lo, w.hi, w.m, w.r, w.pc};
+                next_segment(w, row_end);
             }
         }
         return true;
     };
+    // the first step.  (Worked out where its operands are copied and once more in the epilogue: carried through the main loop, a walk's
+    // numbers take the scalar registers of the loop's own counts, whose way back from vector registers it then waits for: 1 % of
+    // 16384 x 4096 x 4096.)
+    auto first_step = [&](Walk& w, int32_t row0, int32_t col0) __attribute__((always_inline)) {
+        w.e = 0;
+        w.sg = rec[4 * kGemmTileSegs];
+        w.pj = proj >= 0 ? proj : rfl(col0 / pd.dg);
+        w.mcol0 = proj >= 0 ? 0 : w.pj * pd.dg;
+        w.mpitch = proj >= 0 ? N : pd.dg;
+        window(w, rec[0], rec[1], rec[2], rec[3]);
+        return next_step(w, min(row0 + BM, T));
+    };
     // copies a step's operands for the tile at (row0, col0): 2 RCOPIES copies per wave
-    auto copy_step = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
+    auto copy_step = [&](const Walk& w, int32_t row0, int32_t col0) __attribute__((always_inline)) {
         // (opaque to the optimiser: the per-lane offsets are worked out here instead of living in loop-invariant registers
         //  through the main loop)
         int ln = lane;
@@ -437,24 +444,22 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
 #pragma unroll
         for (int c = 0; c < RCOPIES; ++c) {
             const int krow = 2 * (wave_u + NW * c) + (ln >> 5);      // half c / 2
-            const int32_t m = c < RCOPIES / 2 ? ha.m : hb.m, n = c < RCOPIES / 2 ? ha.n : hb.n;
+            const int32_t m = c < RCOPIES / 2 ? w.a.m : w.b.m, n = c < RCOPIES / 2 ? w.a.n : w.b.n;
             dma16(lds0 + MSLICE_OFF + (wave_u + NW * c) * 1024,
-                  reinterpret_cast<const unsigned char*>(M + size_t(m) * u_mpitch + (col0 - u_mcol0)),
-                  (uint32_t(min(krow & 15, max(n - 1, 0))) * uint32_t(u_mpitch) + 8u * ((ln & 31) ^ kn_swz2(krow))) * 2u);
+                  reinterpret_cast<const unsigned char*>(M + size_t(m) * w.mpitch + (col0 - w.mcol0)),
+                  (uint32_t(min(krow & 15, max(n - 1, 0))) * uint32_t(w.mpitch) + 8u * ((ln & 31) ^ kn_swz2(krow))) * 2u);
         }
         const int ch = ln & 3, k = 8 * (ch & 1);
-        const int32_t pcol = ch < 2 ? ha.pc + (k < ha.n ? k : 0) : hb.pc + (k < hb.n ? k : 0);
+        const int32_t pcol = ch < 2 ? w.a.pc + (k < w.a.n ? k : 0) : w.b.pc + (k < w.b.n ? k : 0);
 #pragma unroll
         for (int c = 0; c < RCOPIES; ++c)
             dma16(lds0 + MSLICE_OFF + P_OFF + (wave_u + NW * c) * 1024, reinterpret_cast<const unsigned char*>(P + size_t(row0) * pd.r_pad),
                   (uint32_t(16 * (wave_u + NW * c) + (ln >> 2)) * uint32_t(pd.r_pad) + uint32_t(pcol)) * 2u);
     };
-    bool up = false;                                 // the tile has an up projection, and its first step is on its way
     auto prefetch_adapter = [&](int32_t row0, int32_t col0) __attribute__((always_inline)) {
         if (!P) return;                              // uniform
-        first_segment();
-        up = next_step(min(row0 + BM, T));
-        if (up) copy_step(row0, col0);
+        Walk w;
+        if (first_step(w, row0, col0)) copy_step(w, row0, col0);
     };
     // ---- epilogue of the tile at (row0, col0): fused up projection, then fp32 -> bf16 and the stores.
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
@@ -474,6 +479,8 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
         const int32_t row_end = min(row0 + BM, T);
         const int32_t wrow0 = row0 + wm * TM;        // the wave's rows are wrow0 .. wrow0 + TM - 1
         // ---- the up projection's steps (uniform over the workgroup, the barriers too)
+        Walk walk;
+        bool up = P && rec[3] > 0;
         for (bool first = true; up; first = false) {
             const unsigned char* ml = lds + MSLICE_OFF;
             if (!first) {                            // (the first step was waited for at the last K tile's barrier)
@@ -481,55 +488,62 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
-            // lane (j, kg) holds ranks 8 (kg % 2) .. + 7 of half kg / 2 in both operands
-            const Half h = Half{kg < 2 ? ha.lo : hb.lo, kg < 2 ? ha.hi : hb.hi, 0, kg < 2 ? ha.n : hb.n, 0};
-            const int32_t any_lo = hb.n > 0 ? min(ha.lo, hb.lo) : ha.lo, any_hi = hb.n > 0 ? max(ha.hi, hb.hi) : ha.hi;
-            const bool mine = any_hi > wrow0 && any_lo < wrow0 + TM;     // wave-uniform: the step has rows of this wave
             const unsigned char* pl = ml + P_OFF + (wm * TM + j) * (RSTEP * 2) + kg * 16;
             u32x4 pv[MB];
             bf16x8 mf[NB];
-            if (mine) {
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) pv[mb] = *reinterpret_cast<const u32x4*>(pl + mb * 16 * (RSTEP * 2));
+            for (int mb = 0; mb < MB; ++mb) pv[mb] = *reinterpret_cast<const u32x4*>(pl + mb * 16 * (RSTEP * 2));
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, 0, nb, j, kg);
-            }
+            for (int nb = 0; nb < NB; ++nb) mf[nb] = read_kn(ml, 0, nb, j, kg);
+            __builtin_amdgcn_sched_barrier(0);       // (the scalar work of the step, and of the next one, under the reads)
+            if (first) first_step(walk, row0, col0);
+            // lane (j, kg) holds ranks 8 (kg % 2) .. + 7 of half kg / 2 in both operands
+            const Half ha = walk.a, hb = walk.b;
+            const int32_t srow0 = row0 + wave_u / WN * TM;           // (wrow0, in a scalar register)
+            const bool two = hb.lo != ha.lo;         // the second half is another (later) segment's
+            int32_t lo = ha.lo, hi = ha.hi, n = kg < 2 ? ha.n : two ? 0 : hb.n;
+            const int32_t lo2 = hb.lo, hi2 = hb.hi, n2 = kg < 2 ? 0 : hb.n;
+            const bool mine = (hi > srow0 && lo < srow0 + TM) || (two && hi2 > srow0 && lo2 < srow0 + TM);
+            up = next_step(walk, row_end);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();            // everybody has read the step: the region is free
             asm volatile("" ::: "memory");
-            up = next_step(row_end);
-            if (up) copy_step(row0, col0);
+            if (up) copy_step(walk, row0, col0);
             if (!mine) continue;
-            const int nv = min(max(h.n - 8 * (kg & 1), 0), 8);
-            u32x4 km;
+            // once per segment, with the ranks of the other cleared in both operands
+            for (int again = rfl(two);;) {
+                const int nv = min(max(n - 8 * (kg & 1), 0), 8);
+                u32x4 km;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
+                for (int w = 0; w < 4; ++w) km[w] = (2 * w < nv ? 0xffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
+                bf16x8 m[NB];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int32_t row = wrow0 + mb * 16 + j;
-                pv[mb] = (row >= h.lo && row < h.hi) ? (pv[mb] & km) : zero4;
+                for (int nb = 0; nb < NB; ++nb) {
+                    union { bf16x8 b; u32x4 u; } cv;
+                    cv.b = mf[nb];
+                    cv.u &= km;
+                    m[nb] = cv.b;
+                }
+                // The MFMAs are asm statements, which the compiler's hazard pass does not look into: an MFMA must not read a
+                // register in the two wait states after a vector ALU instruction has written it, and the masking above is such a
+                // write (operands that come straight from a load need nothing).  The statements below order the masking before the
+                // wait states and the MFMAs behind them.
+                asm volatile("s_nop 1" : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "+v"(m[4]), "+v"(m[5]), "+v"(m[6]), "+v"(m[7]));
+                static_for<0, MB>([&](auto mb_c) {
+                    constexpr int mb = decltype(mb_c)::value;
+                    const int32_t rb = srow0 + mb * 16, row = rb + j;
+                    if (hi <= rb || lo >= rb + 16) return;           // wave-uniform
+                    bf16x8 pf = as_bf16x8((row >= lo && row < hi) ? (pv[mb] & km) : zero4);
+                    asm volatile("s_nop 1" : "+v"(pf));
+                    static_for<0, NB>([&](auto nb_c) { mfma_acc<acc_reg(mb, decltype(nb_c)::value)>(m[decltype(nb_c)::value], pf); });
+                });
+                if (!again) break;
+                again = 0;
+                lo = lo2;
+                hi = hi2;
+                n = n2;
+                asm volatile("" : "+s"(again), "+s"(lo), "+s"(hi), "+v"(n));      // (opaque to the optimiser, which would make two copies of the loop's body)
             }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                union { bf16x8 b; u32x4 u; } cv;
-                cv.b = mf[nb];
-                cv.u &= km;
-                mf[nb] = cv.b;
-            }
-            // The MFMAs are asm statements, which the compiler's hazard pass does not look into: an MFMA must not read a
-            // register in the two wait states after a vector ALU instruction has written it, and the masking above is such a
-            // write (operands that come straight from a load need nothing).  The statements below order the masking before the
-            // wait states and the MFMAs behind them.
-            asm volatile("s_nop 1" : "+v"(mf[0]), "+v"(mf[1]), "+v"(mf[2]), "+v"(mf[3]), "+v"(mf[4]), "+v"(mf[5]),
-                         "+v"(mf[6]), "+v"(mf[7]));
-            static_for<0, MB>([&](auto mb_c) {
-                constexpr int mb = decltype(mb_c)::value;
-                const int32_t rb = wrow0 + mb * 16;
-                if (any_hi <= rb || any_lo >= rb + 16) return;          // wave-uniform
-                bf16x8 pf = as_bf16x8(pv[mb]);
-                asm volatile("s_nop 1" : "+v"(pf));
-                static_for<0, NB>([&](auto nb_c) { mfma_acc<acc_reg(mb, decltype(nb_c)::value)>(mf[decltype(nb_c)::value], pf); });
-            });
         }
         if (P) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         // (block_col: a lane with odd kg holds its high four columns in block 2 p and its low four in block 2 p + 1)
@@ -614,7 +628,7 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
         dma16(copy_lds_addr(ldsw + STAGE_BYTES, c), c < NBZ ? zcur : wcur, c < NBZ ? zvo[c] : wvo[c - NBZ]);
     int32_t t_n = 0, t_kt = 0, t_row0, t_col0;       // the compute cursor
     tile_origin(0, t_row0, t_col0);
-    load_table(t_row0, t_col0);
+    load_table(t_row0);
     wait_vmcnt<0>();                                 // the first two K tiles have landed
     __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -685,7 +699,7 @@ void LOBRA_GP_KERNEL(PlanDev pd, const uint16_t* __restrict__ Z, const uint16_t*
             t_kt = 0;
             if (++t_n == my_tiles) break;
             tile_origin(t_n, t_row0, t_col0);
-            load_table(t_row0, t_col0);
+            load_table(t_row0);
             // the first fragments of the next output tile once more: holding 64 registers of them through
             // the epilogue costs more (spills) than these sixteen reads
 #pragma unroll

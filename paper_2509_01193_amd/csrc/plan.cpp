@@ -466,7 +466,7 @@ GemmChoice choose_gemm(int64_t T, int32_t K, int32_t N, int32_t group, int32_t n
         float fixed = t.fixed;
         if (i == kPersistentTile && ktail)
             fixed = kKTailFixed + (N % 32 ? kKTailOddRows : 0.f) + kKTailRank * std::max(0.f, float(rank - 32) / 32.f);
-        if (i == kPersistentTile) fixed += (rank <= 16 ? kSegmentCost.persistent16 : kSegmentCost.persistent) * segments;
+        if (i == kPersistentTile) fixed += kSegmentCost.persistent * segments;
         if (i == kStagedTile) fixed += kSegmentCost.staged * segments;
         const int64_t tiles = (T + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn), slots = cus * t.per_cu;
         for (int32_t s = 1; s <= kMaxSplits; ++s) {

@@ -70,11 +70,11 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D);
 // for its `fixed`) and pays more again for rows of C that start inside a 64-byte sector (kKTailOddRows where N is no multiple
 // of 32: 20000 x 840 x 5240 268 us, the staged kernel 251; x 4096 154, 174) and for ranks above 32, a step of the up projection each
 // (kKTailRank; 47000 x 600 x 7232 at rank 32, 64 and 128, this kernel / the staged one: 579, 560 and 625 / 621, 613 and 646 us).
-// The persistent and the staged kernel do the up projection segment by segment - the persistent one two segments of up to 16
-// ranks in one step -, the tiled kernels by task (kSegmentCost).  Measured, us per round of 256 tiles (N = 7552, 55000 tokens),
+// The persistent and the staged kernel do the up projection segment by segment - the persistent one with the operands of two segments of
+// up to 16 ranks at a time -, the tiled kernels by task (kSegmentCost).  Measured, us per round of 256 tiles (N = 7552, 55000 tokens),
 // and us in all for 12000 x 584 x 1000 and 12000 x 1024 x 1024 in segments of n tokens, rank 16:
 //     K                 64    200   328   520   712   968   1376  2248      n = 400   20    4     n = 400   20    4
-//     persistent                          23.6  26.9  33.7  41.6  65.5      35        42    91        32    45    92
+//     persistent                          23.6  26.9  33.7  41.6  65.5      35        42    85        30    43    88
 //     staged            9.3   15.0  18.6  25.1  31.0  38.6  48.6  75.8      30        46    103       42    58    113
 //     128 x 256 (x 2)   14.8  21    24    29    35    42    50    73        38        41    47        43    46    51
 struct GemmTile { int32_t tm, tn, per_cu; float k1, k2, fixed, once; };
@@ -88,9 +88,12 @@ constexpr GemmTile kGemmTiles[] = {
 };
 constexpr int32_t kPersistentTile = 0, kStagedTile = 5;
 constexpr float kKTailFixed = 10.f, kKTailOddRows = 4.f, kKTailRank = 0.75f;  // (kKTailRank: per 32 ranks beyond the first 32)
-// us per round and segment of a tile row beyond the first (persistent kernel: ranks up to 16, above)
-struct SegmentCost { float persistent16, persistent, staged; };
-constexpr SegmentCost kSegmentCost = {0.8f, 1.4f, 1.0f};
+// us per round and segment of a tile row beyond the first.  (Persistent kernel, training steps at rank 16, us, with 0.8 / 1.4: 16384 x 2048 x
+// 2048 in segments of 12 tokens 354 / 326, of 16 349 / 323, 9000 x 4096 x 4096 of 20 643 / 602, 12000 x 1376 x 4096 of 22 365 / 362, 30000 x
+// 1024 x 4096 of 18 630 / 612, 49152 x 768 x 768 of 36 252 / 241, 6000 x 2048 x 2048 of 20 152 / 159; 19 batches on which the two
+// differ, 0.98 on average.)
+struct SegmentCost { float persistent, staged; };
+constexpr SegmentCost kSegmentCost = {1.4f, 1.0f};
 constexpr int32_t kGemmKTile = 64;
 // The persistent kernel's loop for such a K needs an ordinary pair of K tiles in front of the two special ones (K > 256).  It runs
 // from here on, where it is the better one for wide products (30000 x 520 x 1000 / 2048 / 7552, staged / persistent: 62 / 76,

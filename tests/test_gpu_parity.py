@@ -184,6 +184,43 @@ def test_persistent_gemm_up_projection_of_many_segments(d_in, d_out, n_proj):
     check_problem(p, rows=sample_rows(p, 100)[::3], label="up")
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("d_in,d_out", [(2048, 2048), (2056, 2048), (2048, 2056)])
+def test_persistent_gemm_adapters_of_no_finite_value_stay_with_their_task(d_in, d_out, value):
+    """One task's adapter holds no finite value; tokens and adapters of the others, and tokens without one, are what they are with
+    a finite one, bit for bit - except rows that may share a block of 16 with that task's (zero times NaN).  Segments of ranks up
+    to 16, two to a step of the up projection, with and without others between them.  (Products of the persistent kernel, with
+    whole K tiles and, for 2056, without.)"""
+    import torch
+    T, bad, rng = 5632 + 13, 1, np.random.default_rng(d_in + d_out)
+    lens = []
+    while sum(lens) < T:
+        lens.append(min(int(rng.choice([20, 33, 60, 90, 140])), T - sum(lens)))
+    off, tasks = np.concatenate([[0], np.cumsum(lens)]), rng.integers(-1, 4, len(lens))
+    p = wl.make_custom("alone-%d-%d" % (d_in, d_out), "bf16", d_in, d_out, [16, 16, 8, 24], off, tasks, 43,
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    good = bd.DeviceProblem(p)
+    good.step()
+    bits, rows = np.uint16(0x7fc0 if np.isnan(value) else 0x7f80), slice(16, 32)
+    p.A[rows, ::7], p.B[rows] = bits, bits
+    dp = bd.DeviceProblem(p)
+    dp.step()
+    torch.cuda.synchronize()
+    assert dp.guards_intact()
+    own = torch.from_numpy(np.repeat(tasks == bad, lens)).cuda()
+    near = torch.nn.functional.max_pool1d(own[None, None].float(), 31, 1, 15)[0, 0] > 0
+    assert bool(near.any()) and int((~near).sum()) > T // 4
+    assert not bool(torch.isfinite(dp.y[own].float()).any()) and not bool(torch.isfinite(dp.dx[own, ::7].float()).any())
+    for name in ("y", "dx"):
+        a, b = getattr(dp, name)[~near].view(torch.int16), getattr(good, name)[~near].view(torch.int16)
+        wrong = (a != b).any(1)
+        assert not bool(wrong.any()), (name, int(wrong.sum()), "of", len(wrong))
+    for name in ("dA", "dB"):
+        a, b = getattr(dp, name), getattr(good, name)
+        others = [i for i in range(p.R_tot) if not 16 <= i < 32]
+        assert bool((a[others] == b[others]).all()), name
+
+
 @pytest.mark.parametrize("d_in,d_out", [
     (72, 4104),       # a whole K tile and 8 of the next; backward: 65 K tiles, the last of 8, on two narrow column tiles
     (8, 4000),        # K shorter than a K tile
