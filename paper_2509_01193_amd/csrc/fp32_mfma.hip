@@ -38,6 +38,9 @@ template <bool VEC> __device__ __forceinline__ f32x4 load4(const float* __restri
     }
 }
 
+// K tiles of 32 to a range of a projection's sums, at most eight of them
+__device__ __forceinline__ int32_t f32_range(int32_t ktiles) { return (ktiles + 7) / 8; }
+
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 }  // namespace
@@ -248,9 +251,27 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 hacc[HB > 0 ? HB : 1][2];                  // the projections, first and second K steps of a K tile apart
+    // The projections: a chain of sums over an eighth of the K tiles, first and second K steps of a K tile apart, and the sum of those before,
+    // so that as few products follow each other as in the 16 waves of shrink_f32_kernel.  (Two chains over all of K, 1000 x 2500 x 64:
+    // gradients 6.7e-7 from 64 bits, like this 2.6e-7, with a projection of its own 2.7e-7.)
+    struct Chain { f32x4 run, all; };
+    Chain h[HB > 0 ? HB : 1][2];
 #pragma unroll
-    for (int b = 0; b < HB; ++b) hacc[b][0] = hacc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < HB; ++b)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) h[b][k].run = h[b][k].all = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int32_t range = NI > 0 ? f32_range(KT) : 0;
+    int32_t range_end = range;
+    auto fold = [&]() {                              // in front of K tile range_end
+#pragma unroll
+        for (int b = 0; b < HB; ++b)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                h[b][k].all = h[b][k].all + h[b][k].run;
+                h[b][k].run = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        range_end += range;
+    };
     // the MFMAs on `f`, fragments of K step ks ^ 1, with the reads of the next step's fragments (ks) and (COPY) a K tile's copies dealt
     // evenly behind them
     auto kstep = [&](auto read_c, auto copy_c, const Frags& f, Frags& next, const unsigned char* slot, auto ks_c, uint32_t la) __attribute__((always_inline)) {
@@ -258,8 +279,12 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         constexpr int NM = 4 * PQ, R = decltype(read_c)::value ? NR : 0, CC = decltype(copy_c)::value ? CPW : 0;
         static_for<0, NM>([&](auto m_c) {
             constexpr int m = decltype(m_c)::value, q = m / PQ, mb = m % PQ / NB, nb = m % PQ % NB;
-            if constexpr (m % PQ < MB * NB) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
-            else hacc[m % PQ - MB * NB][ks ^ 1] = mfma4(f.a[m % PQ - MB * NB][q], f.z[0][q], hacc[m % PQ - MB * NB][ks ^ 1]);
+            if constexpr (m % PQ < MB * NB) {
+                acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+            } else {
+                f32x4& run = h[m % PQ - MB * NB][ks ^ 1].run;
+                run = mfma4(f.a[m % PQ - MB * NB][q], f.z[0][q], run);
+            }
             static_for<m * R / NM, (m + 1) * R / NM>([&](auto i_c) { read(i_c, next, slot, ks); });
             static_for<m * CC / NM, (m + 1) * CC / NM>([&](auto c_c) { copy(c_c, la); });
             __builtin_amdgcn_sched_barrier(0);
@@ -304,9 +329,18 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         kstep(yes{}, yes{}, fb, fa, lds + slot * SLOT, step0{}, la);
         next_copy_tile();
     };
-    for (; kt < KF - STAGES; ++kt) ktile();
+    if constexpr (NI > 0) {
+        while (kt < KF - STAGES) {
+            const int32_t end = min(range_end, KF - STAGES);
+            for (; kt < end; ++kt) ktile();
+            if (kt == range_end) fold();
+        }
+    } else {
+        for (; kt < KF - STAGES; ++kt) ktile();
+    }
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;            // uniform
+        if (NI > 0 && kt == range_end) fold();
         if (tail) clear_tail(fa, 0);
         kstep(yes{}, no{}, fa, fb, lds + slot * SLOT, step1{}, 0);
         if (tail) clear_tail(fb, 1);
@@ -360,19 +394,19 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             const F32Item t = {wn ? w.lo : u.lo, wn ? w.hi : u.hi, 0, wn ? w.n : u.n, 0, wn ? w.c0 : u.c0, wn ? w.r : u.r, 0};
             const int32_t row = row0 + wm * 16 + j;
             const bool in = row >= t.lo && row < t.hi;
-            const f32x4 sum = hacc[b][0] + hacc[b][1];
-            f32x4 h;
+            const f32x4 sum = (h[b][0].all + h[b][0].run) + (h[b][1].all + h[b][1].run);
+            f32x4 p;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) h[v] = in && 4 * kg + v < t.n ? scale[b] * sum[v] : 0.f;
-            *reinterpret_cast<f32x4*>(zs + (wn + 2 * b) * HZ + (wm * 16 + j) * FPITCH + 4 * kg) = h;
+            for (int v = 0; v < 4; ++v) p[v] = in && 4 * kg + v < t.n ? scale[b] * sum[v] : 0.f;
+            *reinterpret_cast<f32x4*>(zs + (wn + 2 * b) * HZ + (wm * 16 + j) * FPITCH + 4 * kg) = p;
             if (col0 == 0 && in) {
                 // (and zeros behind the task's last block, as far as a row goes)
                 float* dst = Pout + size_t(row) * pd.r_max;
                 for (int32_t k = t.c0 + 4 * kg; k < (t.c0 + 16 < t.r ? t.c0 + 16 : pd.r_max); k += 16) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (k + v < pd.r_max) dst[k + v] = h[v];
-                    h = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (k + v < pd.r_max) dst[k + v] = p[v];
+                    p = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             }
         }

@@ -676,6 +676,31 @@ def test_fp32_projection_inside_the_product(T, d_in, d_out, ranks, longest, insi
     assert dp.guards_intact()
 
 
+@pytest.mark.parametrize("ranks", [[16], [40, 16]])
+@pytest.mark.parametrize("K", [2048, 2047, 8200])
+def test_fp32_projection_inside_the_product_loses_no_more_in_its_sums(K, ranks):
+    """One product of 2^24 and others of 0.25, which vanish where they meet it one by one, or four at a time.  A projection of its own has
+    16 waves with K / 16 products each: at most one wave's are lost, and a rounding of 1 for every further sum.  The same is asked of
+    the projection inside the product, of both passes (one token: dA is the projected dy times x = 1)."""
+    import torch
+    bound = 0.25 * (K + 15) // 16 + 16
+    for d_in, d_out in ((K, 24), (24, K)):
+        p = wl.make_custom("chains-%d" % K, "f32", d_in, d_out, ranks, [0, 1], [0], 71, s=[1.0] * len(ranks))
+        p.x[:], p.dy[:], p.W[:], p.A[:], p.B[:] = 1, 1, 0, 1, 1
+        for a in ((p.x, p.A) if d_in == K else (p.dy, p.B)):
+            a[:, 1:], a[:, 0] = 0.5, 4096
+        dp = bd.DeviceProblem(p)
+        tr = bd.LaunchTrace(dp.plan, 8)
+        tr.attach()
+        dp.step()
+        torch.cuda.synchronize()
+        assert [name for name, _ in tr.durations()][:2] == ["shrink_gemm"] * 2
+        tr.close()
+        got = dp.h_save.view(torch.float32)[:ranks[0]] if d_in == K else dp.dA[:ranks[0], 0]
+        off = (got.double() - (2.0 ** 24 + 0.25 * (K - 1))).abs().max()
+        assert float(off) <= bound, (d_in, d_out, float(off), bound)
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj,longest", [
     (3001, 4, 2052, 1, 400),        # a K tile of 4, a last row tile of 57 (of 64) and a last column tile of 4
     (3001, 96, 1028, 1, 400),       # as many K tiles as the ring has slots
