@@ -451,9 +451,7 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
             if (!H) {
                 float* Hr = reinterpret_cast<float*>(wsb + p.bwd_off_h);
                 LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
-                             p.fused_fwd ? gemm_f32_fused(pd, p.f32_items, false, static_cast<const float*>(x), static_cast<const float*>(W),
-                                                          static_cast<const float*>(A), s, Hr, static_cast<const float*>(B), nullptr, pd.d_in, pd.d_out,
-                                                          pd.d_out, st)
+                             p.fused_fwd ? shrink_f32(pd, static_cast<const float*>(x), static_cast<const float*>(A), s, Hr, pd.d_in, pd.d_in, 1, 0, st, true)
                                          : plain_shrink(pd, dt, x, A, s, Hr, pd.d_in, st));
                 H = Hr;
             }
@@ -463,10 +461,13 @@ lobra_status lobra_mlora_plan_bwd(const lobra_mlora_plan* plan, const void* x, c
                              plain_shrink(pd, dt, static_cast<const char*>(dy) + size_t(j) * pd.dg * esz, B, s, G,
                                           pd.dg, st, pd.d_out, p.n_proj, j));
         }
-        if (adapters && p.fused_bwd)                 // (without dx: the projection alone)
-            LOBRA_LAUNCH(p, st, want_dx ? LOBRA_K_SHRINK_GEMM : LOBRA_K_SHRINK,
+        if (adapters && p.fused_bwd && !want_dx)
+            LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK,
+                         shrink_f32(pd, static_cast<const float*>(dy), static_cast<const float*>(B), s, G, pd.d_out, pd.d_out, 1, 0, st, true));
+        else if (adapters && p.fused_bwd)
+            LOBRA_LAUNCH(p, st, LOBRA_K_SHRINK_GEMM,
                          gemm_f32_fused(pd, p.f32_items, true, static_cast<const float*>(dy), static_cast<const float*>(W), static_cast<const float*>(B), s, G,
-                                        static_cast<const float*>(A), want_dx ? static_cast<float*>(dx) : nullptr, pd.d_out, pd.d_in, pd.d_out, st));
+                                        static_cast<const float*>(A), static_cast<float*>(dx), pd.d_out, pd.d_in, pd.d_out, st));
         else if (want_dx && p.desc.T > 0)
             LOBRA_LAUNCH(p, st, LOBRA_K_GEMM,
                          plain_gemm(pd, dt, true, dy, W, G, A, dx, pd.d_out, pd.d_in, pd.d_out, st));

@@ -491,7 +491,6 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             __syncthreads();
         }
     }
-    if (NI > 0 && !C) return;                        // (the projection alone was asked for)
     // acc[mb][nb][v]: token row mb 16 + j of the wave tile, column col_of(nb, 4 kg + v)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -556,11 +555,11 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
 
 // The same with the projection of Z's rows in the product's launch (pd's plan has ni items per 32-row block, see f32_fused): what a
 // short batch is bound by is launches and round trips to memory.  618 x 256 x 256, two tasks of rank 8, projection and product 4.6 + 7.1
-// us, like this 7.2 (the step 26.7 -> 22.3).  C = NULL: the projection alone, by the workgroups of the first column tile, so that it gives the same bits.
+// us, like this 7.2 (the step 26.7 -> 22.3).
 hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const float* Z, const float* W, const float* D, const float* s, float* P,
                           const float* M, float* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st)
 {
-    const int32_t tiles_n = C ? (N + 31) / 32 : 1;
+    const int32_t tiles_n = (N + 31) / 32;
     const dim3 grid(uint32_t((pd.T + 31) / 32) * uint32_t(tiles_n));
     const bool vec = ((K | N | ldw) & 3) == 0;
 #define LOBRA_F32_FUSED(TR, NI, OCC) \
@@ -583,8 +582,11 @@ hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const floa
 // groups of 16; both operands go straight from global memory into registers, "A" = 16 rank rows, "B" = 16 token rows, four
 // rank blocks at a time.
 // Latency and memory bound: a wave has the loads of four groups in flight (two at large ranks).
+// RANGES: the groups and the order of the sums are those of the projection inside its product, so that it gives the same bits: wave
+// 2 i + k has the K steps k of the K tiles of range i.  (Through the product's kernel without the product, one K tile after another:
+// backward passes without dx, 32 x 2048 x 2048, 27.0 us, like this 12.9, without the saved activations, 1000 x 2500 x 64, 64 and 34.)
 // -------------------------------------------------------------------------------------------
-template <int NRB, int NW, bool VEC>
+template <int NRB, int NW, bool VEC, bool RANGES>
 __global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const float* __restrict__ Z, const float* __restrict__ M,
                                                          const float* __restrict__ s, float* __restrict__ P, int32_t D,
                                                          int32_t ldz, int32_t nproj, int32_t proj)
@@ -594,6 +596,7 @@ __global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const f
     // [proj r, (proj + 1) r) is read and written
     constexpr int DEPTH = NRB == 4 ? 2 : 4;          // (128 registers per wave)
     static_assert(NW >= NRB, "a wave per rank block adds the sums");
+    static_assert(!RANGES || NW == 16, "two waves for each of eight ranges");
     __shared__ f32x4 red[NW][NRB][64];
     const TokenBlock b = pd.tb[blockIdx.x >> 1];
     const int half = blockIdx.x & 1;
@@ -615,11 +618,12 @@ __global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const f
         }
         const int32_t nrb = min(NRB, (r - p0 + 15) >> 4);           // rank blocks with ranks of the task (uniform)
         f32x4 z[DEPTH], m[DEPTH][NRB];
-        const int32_t ng = (D + 15) >> 4;
-        for (int32_t g = wave; nrb > 0 && g < ng; g += DEPTH * NW) {            // (groups beyond D read as zero)
+        const int32_t range = 2 * f32_range((D + 31) >> 5), STRIDE = RANGES ? 2 : NW;
+        const int32_t g0 = RANGES ? (wave >> 1) * range + (wave & 1) : wave, ng = RANGES ? (wave >> 1) * range + range : (D + 15) >> 4;
+        for (int32_t g = g0; nrb > 0 && g < ng; g += DEPTH * STRIDE) {          // (groups beyond D, or the range, read as zero)
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
-                const int32_t k = 16 * (g + u * NW) + 4 * kg;
+                const int32_t gu = g + u * STRIDE, k = RANGES && gu >= ng ? D : 16 * gu + 4 * kg;
                 z[u] = load4<VEC>(zrow, k, D);
 #pragma unroll
                 for (int rb = 0; rb < NRB; ++rb)
@@ -638,9 +642,17 @@ __global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const f
         __syncthreads();
         // rank block rb is summed by wave rb, in wave order: lane (j, kg) stores ranks 4 kg .. 4 kg + 3 of token j
         if (wave < NRB) {
-            f32x4 sum = red[0][wave][lane];
+            f32x4 sum;
+            if constexpr (RANGES) {
+                f32x4 all[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-            for (int w = 1; w < NW; ++w) sum = sum + red[w][wave][lane];
+                for (int w = 0; w < NW; ++w) all[w & 1] = all[w & 1] + red[w][wave][lane];
+                sum = all[0] + all[1];
+            } else {
+                sum = red[0][wave][lane];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum = sum + red[w][wave][lane];
+            }
             if (tok < b.nrows)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -653,7 +665,7 @@ __global__ __launch_bounds__(64 * NW) void shrink_f32_kernel(PlanDev pd, const f
 }
 
 hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
-                      int32_t nproj, int32_t proj, hipStream_t st)
+                      int32_t nproj, int32_t proj, hipStream_t st, bool as_fused)
 {
     const bool vec = ((D | ldz) & 3) == 0;
     const int nrb = (pd.r_max / nproj + 15) / 16;
@@ -664,12 +676,17 @@ hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const f
     // blocks: 512 threads each, and no more blocks than tokens (kPlainMaxTokens).
     static_assert(kPlainMaxTokens * 2 * 256 < (int64_t(1) << 32), "the grid of four waves per half block");
     const bool few = pd.ntb <= 128;
-#define LOBRA_F32_SHRINK2(NRB, NW)                                                                                         \
+#define LOBRA_F32_SHRINK2(NRB, NW, RANGES)                                                                                 \
     do {                                                                                                                   \
-        if (vec) shrink_f32_kernel<NRB, NW, true><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);     \
-        else shrink_f32_kernel<NRB, NW, false><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);        \
+        if (vec) shrink_f32_kernel<NRB, NW, true, RANGES><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);     \
+        else shrink_f32_kernel<NRB, NW, false, RANGES><<<2 * pd.ntb, 64 * NW, 0, st>>>(pd, Z, M, s, P, D, ldz, nproj, proj);        \
     } while (0)
-#define LOBRA_F32_SHRINK(NRB) do { if (few) LOBRA_F32_SHRINK2(NRB, 16); else LOBRA_F32_SHRINK2(NRB, 4); } while (0)
+#define LOBRA_F32_SHRINK(NRB)                                  \
+    do {                                                       \
+        if (as_fused) LOBRA_F32_SHRINK2(NRB, 16, true);        \
+        else if (few) LOBRA_F32_SHRINK2(NRB, 16, false);       \
+        else LOBRA_F32_SHRINK2(NRB, 4, false);                 \
+    } while (0)
     if (nrb <= 1) LOBRA_F32_SHRINK(1);
     else if (nrb <= 2) LOBRA_F32_SHRINK(2);
     else LOBRA_F32_SHRINK(4);

@@ -52,8 +52,9 @@ hipError_t plain_grad_stage1(const PlanDev& pd, int dtype, const void* P, const 
 hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& jb, bool accumulate, bool skip_single,
                            hipStream_t st);
 // ---- fp32 storage on the matrix cores (fp32_mfma.hip), reached through the three above; arguments as there ------------
+// (as_fused: what gemm_f32_fused would write, bit for bit, without the product; plans of whose passes one has the projection inside)
 hipError_t shrink_f32(const PlanDev& pd, const float* Z, const float* M, const float* s, float* P, int32_t D, int32_t ldz,
-                      int32_t nproj, int32_t proj, hipStream_t st);
+                      int32_t nproj, int32_t proj, hipStream_t st, bool as_fused = false);
 hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const float* Z, const float* W, const float* D, const float* s, float* P,
                           const float* M, float* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st);
 hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float* W, const float* P, const float* M, float* C,

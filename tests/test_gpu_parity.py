@@ -701,6 +701,31 @@ def test_fp32_projection_inside_the_product_loses_no_more_in_its_sums(K, ranks):
         assert float(off) <= bound, (d_in, d_out, float(off), bound)
 
 
+@pytest.mark.parametrize("T,d_in,d_out,ranks", [
+    (33, 2048, 40, [16, 7]), (40, 44, 1337, [40, 16]), (17, 8200, 200, [5]), (100, 288, 256, [33, 1]), (64, 300, 257, [32]),
+])
+def test_fp32_projection_alone_gives_what_the_one_inside_the_product_does(T, d_in, d_out, ranks):
+    """Backward passes without dx, or without the saved activations: a launch of the projection alone, the same bits - with ranges of one and
+    more K tiles, empty ones, and a K that ends inside a K step."""
+    import torch
+    cut = [0, T // 3, T // 3 + 1, T]
+    p = wl.make_custom("alone-f32", "f32", d_in, d_out, ranks, cut, [0, -1, len(ranks) - 1], 73, s=np.linspace(-1, 2, len(ranks)).astype(np.float32),
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    dp, _ = check_problem(p, label="alone")
+    want = [t.clone() for t in (dp.dA, dp.dB)]
+    tr = bd.LaunchTrace(dp.plan, 8)
+    for h, flags, launches in ((None, 0, ["shrink", "shrink_gemm"]), (dp.h_save, bd.FLAG_NO_DX, ["shrink", "grad_stage1"]),
+                               (None, bd.FLAG_NO_DX, ["shrink", "shrink"])):
+        dp.dA.fill_(7.0), dp.dB.fill_(7.0)
+        tr.attach()
+        bd.lobra_mlora_plan_bwd(dp.plan, dp.x, dp.W, dp.A, dp.B, dp.s, dp.dy, h, dp.dx, dp.dA, dp.dB, flags, dp.ws)
+        torch.cuda.synchronize()
+        assert [name for name, _ in tr.durations()][:2] == launches
+        assert torch.equal(want[0], dp.dA) and torch.equal(want[1], dp.dB), (h is None, flags)
+    tr.close()
+    assert dp.guards_intact()
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj,longest", [
     (3001, 4, 2052, 1, 400),        # a K tile of 4, a last row tile of 57 (of 64) and a last column tile of 4
     (3001, 96, 1028, 1, 400),       # as many K tiles as the ring has slots
