@@ -338,9 +338,12 @@ __global__ __launch_bounds__(256) void plain_gradreduce_kernel(PlanDev pd, const
 // stage 2: out[R, col] (+)= sum over the chunks of task(R), in chunk order.  One workgroup per
 // (rank row, 1024 columns), one float4 per thread, up to eight chunk loads in flight.  What bounds it where the sums are few: the chain of
 // reads in front of them - the row's task, its first chunk, that chunk's first row; a task's chunks follow each
-// other in the partial sums, r_t rows each.  (With a search one task at a time and a table read per chunk / like this, us: 8190 x 1376 x 4096
-// 7.7 / 6.3; fp32 3000 x 1024 x 1024 5.7 / 4.7, 1500 x 700 x 333 15.1 / 6.7; 49152 x 8192 x 8192 at rank 64, 32768 workgroups
-// most of which find one chunk and have nothing to add, 42 / 46.)  Registers for eight waves on a SIMD.
+// other in the partial sums, r_t rows each.  PER_TASK: the grid says which task, with a workgroup for every rank up to the highest.
+// (With a search one task at a time and a table read per chunk / with a search by eight / like this, us: 8190 x 1376 x 4096
+// 7.8 / 6.3 / 6.4; fp32 3000 x 1024 x 1024 5.3 / 4.8 / 4.8, 1500 x 700 x 333 15.1 / 6.7 / 6.5; 49152 x 8192 x 8192 at rank 64, 32768 workgroups
+// most of which find one chunk and have nothing to add, 42 / 47 / 33; 32768 x 4096 x 11008, ranks 8 .. 64, where it makes 2.1 times
+// as many workgroups, 10.4 / 9.8 / 10.7.)  Registers for eight waves on a SIMD.
+template <bool PER_TASK>
 __global__ __launch_bounds__(256, 8) void reduce_partials_kernel(PlanDev pd, GradJob ja, GradJob jb,
                                                               int32_t tiles_a, int accumulate, int skip_single)
 {
@@ -350,26 +353,34 @@ __global__ __launch_bounds__(256, 8) void reduce_partials_kernel(PlanDev pd, Gra
     float* __restrict__ out = first ? ja.out : jb.out;
     const int32_t D = first ? ja.D : jb.D;
     const int32_t coltile = first ? int32_t(blockIdx.y) : int32_t(blockIdx.y) - tiles_a;
-    const int32_t R = blockIdx.x;
-    int32_t t = 0, te = pd.n_tasks;                  // the row's task is one of t .. te - 1
-    while (te - t > 8) {
-        const int32_t m = (t + te) >> 1;
-        if (pd.rank_off[m] <= R) t = m;
-        else te = m;
+    int32_t R = blockIdx.x, t = 0;
+    if constexpr (PER_TASK) {                        // r_max workgroups per task
+        t = R / pd.r_max;
+    } else {
+        int32_t te = pd.n_tasks;                     // the row's task is one of t .. te - 1
+        while (te - t > 8) {
+            const int32_t m = (t + te) >> 1;
+            if (pd.rank_off[m] <= R) t = m;
+            else te = m;
+        }
+        int32_t off[8], behind = 0;                  // (scalar loads, all at once)
+#pragma unroll
+        for (int k = 1; k < 8; ++k) off[k] = pd.rank_off[min(t + k, te)];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) behind += int(t + k < te) & int(off[k] <= R);
+        t += behind;
     }
-    int32_t off[8], behind = 0;                      // (scalar loads, all at once)
-#pragma unroll
-    for (int k = 1; k < 8; ++k) off[k] = pd.rank_off[min(t + k, te)];
-#pragma unroll
-    for (int k = 1; k < 8; ++k) behind += int(t + k < te) & int(off[k] <= R);
-    t += behind;
     const int32_t r0 = pd.rank_off[t], r = pd.rank_off[t + 1] - r0;
+    const int32_t c0 = pd.task_chunk_off[t], nc = pd.task_chunk_off[t + 1] - c0;
+    if constexpr (PER_TASK) {
+        R = r0 + (R - t * pd.r_max);
+        if (R >= r0 + r) return;
+    }
     const int32_t col = coltile * 1024 + threadIdx.x * 4;
     if (col >= D) return;
     // the partial sums of a task: one per reduction chunk, or (fcnt) one per run of the fused pass that covers
     // this thread's 512-column slice
     const int32_t* fcnt = first ? ja.fcnt : jb.fcnt;
-    const int32_t c0 = pd.task_chunk_off[t], nc = pd.task_chunk_off[t + 1] - c0;
     const int32_t n = fcnt ? fcnt[t * (first ? ja.fnsl : jb.fnsl) + (col >> 9)] : nc;
     if (skip_single && !fcnt && n == 1) return;
     const int32_t row0 = (fcnt ? (first ? ja.frow0 : jb.frow0)[t] : nc > 0 ? pd.chunks[c0].part_row0 : 0) + (R - r0);
@@ -408,9 +419,11 @@ hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& 
 {
     if (pd.R_tot == 0) return hipSuccess;
     const int32_t tiles_a = (ja.D + 1023) / 1024, tiles_b = jb.out ? (jb.D + 1023) / 1024 : 0;
-    const dim3 grid(pd.R_tot, tiles_a + tiles_b);
+    // a workgroup per task and rank up to the highest, so that none has to find its task, unless that makes twice as many
+    const bool per_task = int64_t(pd.n_tasks) * pd.r_max <= 2 * int64_t(pd.R_tot);
+    const dim3 grid(per_task ? pd.n_tasks * pd.r_max : pd.R_tot, tiles_a + tiles_b);
     if (grid.y > 65535u) return hipErrorInvalidValue;
-    reduce_partials_kernel<<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, accumulate ? 1 : 0, skip_single ? 1 : 0);
+    (per_task ? reduce_partials_kernel<true> : reduce_partials_kernel<false>)<<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, accumulate ? 1 : 0, skip_single ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -753,6 +753,33 @@ def test_fp32_products_through_the_ring(T, d_in, d_out, n_proj, longest):
     check_problem(p, rows=rows, label="ring")
 
 
+@pytest.mark.parametrize("dtype,d_in,d_out", [("bf16", 1032, 264), ("f32", 1030, 260)])
+@pytest.mark.parametrize("ranks", [
+    [17, 17, 17, 17, 17],       # as many workgroups as rows
+    [1, 128], [43, 1],          # at most twice as many,
+    [127, 1, 1],                #   and more than that: every workgroup looks for its task
+    [3] * 6 + [60] * 3,
+])
+def test_second_stage_of_the_gradients_finds_every_rank_row(dtype, d_in, d_out, ranks):
+    """Tasks of many reduction chunks, of one and of no token in one batch, overwriting and adding, for both ways a workgroup of the
+    second stage finds its rank row."""
+    import torch
+    n = len(ranks)
+    lens = [2 * 2048 + 40 if t == 0 else 300 if t == 1 else 0 if t == 2 else 900 for t in range(n)]
+    kw = dict(std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    p = wl.make_custom("stage2", dtype, d_in, d_out, ranks, np.concatenate([[0], np.cumsum(lens)]), list(range(n)), 79,
+                       s=np.linspace(-1, 2, n).astype(np.float32), **kw)
+    plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
+    assert np.diff(plan.query(bd.Q_TASK_CHUNKS))[0] > 1
+    plan.close()
+    dp, _ = check_problem(p, rows=np.arange(0, p.T, 31), label="stage 2")
+    once = [g.clone() for g in (dp.dA, dp.dB)]
+    dp.bwd(True, bd.FLAG_ACCUMULATE_GRADS)
+    torch.cuda.synchronize()
+    for g, o in zip((dp.dA, dp.dB), once):
+        assert torch.equal(g, o + o)
+
+
 @pytest.mark.parametrize("T,d_in,d_out,n_proj", [
     (33, 40, 64, 1), (300, 100, 36, 1), (2100, 48, 1028, 1), (2100, 31, 1025, 1), (6200, 20, 1028, 1), (6200, 23, 1031, 1), (6200, 16, 1032, 2),
 ])
