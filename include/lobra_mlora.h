@@ -253,7 +253,7 @@ LOBRA_API lobra_status lobra_mlora_plan_token_task_map(const lobra_mlora_plan *p
 
 /* ---- one-shot forms: the same operations on the descriptor itself (section 1 / Figure 1: the fused batch is
  * given as its task-tagged token runs; section 2.1: the layer).  Each call validates the descriptor, builds the
- * tables on the host, sends them (on hip_stream) to the start of ws - as kernel arguments, above 80 KiB by an
+ * tables on the host, sends them (on hip_stream) to the start of ws - as kernel arguments, above some 90 KiB by an
  * asynchronous copy whose source a host callback on the stream releases - and runs the kernels behind that.  No
  * device memory is allocated or freed and nothing synchronises.  (Not for capture in a HIP graph: a replay would bring
  * the same tables again; use a plan there.)

@@ -31,7 +31,7 @@ PlanDev device_view(const Plan& p)
     d.task_tb_off = b + p.o_task_tb;
     d.sb_off = b + p.o_sb;
     d.tb_order = p.tb_order.empty() ? nullptr : b + p.o_tb_order;
-    d.sb_order = p.sb_order.empty() ? nullptr : b + p.o_sb_order;
+    d.sb_order = p.sb_order.empty() || p.shrink_group == 1 ? nullptr : b + p.o_sb_order;
     d.fb_wg_run_off = p.fused_db ? b + p.o_fb_wg : nullptr;
     d.fb_run_row = p.fused_db ? b + p.o_fb_run : nullptr;
     d.fb_cnt = p.fused_db ? b + p.o_fb_cnt : nullptr;
@@ -585,11 +585,7 @@ inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 // A piece of a one-shot call's tables, on its way to the device as a kernel argument: the runtime has taken its copy
 // when the launch returns, so nothing of the host's has to outlive the call, and nothing waits.
-struct UploadPiece { int32_t v[1008]; };      // with the other arguments just below the 4 KiB of a launch
-// A piece takes 2.3 us of stream time; a copy from pageable memory and the host callback that releases it take 55 to 62 us
-// (73 to 166 KB of tables, with the host ahead of the stream; some 180 us a call where it is not: padded chunks of 3072
-// tokens, four calls, 730 -> 173 us).  So 25 pieces are worth it; up to 21 are sent, 80 KiB (some 35000 tokens in segments of 20).
-constexpr size_t kUploadByArgument = 80 * 1024;
+struct UploadPiece { int32_t v[kUploadPiece]; };
 
 __global__ __launch_bounds__(256) void upload_kernel(int32_t* __restrict__ dst, int32_t n, UploadPiece piece)
 {
@@ -619,7 +615,7 @@ lobra_status upload_oneshot(lobra_mlora_plan* p, void* dev, hipStream_t st)
 {
     if (hipGetDevice(&p->device) != hipSuccess) return LOBRA_ERR_HIP;
     if (p->blob_bytes <= kUploadByArgument) {
-        constexpr size_t most = sizeof(UploadPiece::v) / sizeof(int32_t);
+        constexpr size_t most = kUploadPiece;
         UploadPiece piece;
         for (size_t at = 0; at < p->host_blob.size(); at += most) {
             const size_t n = std::min(most, p->host_blob.size() - at);
@@ -703,8 +699,11 @@ lobra_status lobra_token_task_map(const lobra_mlora_desc* desc, int32_t* out_tas
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     void* dev = nullptr;
     // the call has no workspace argument: the tables go into the library's static device array
-    // (all but the last list, which is about products; what is refused is counted with eight numbers per tile row for it)
-    const size_t all = (p->o_tile_seg + std::max<size_t>(p->gemm_tile_tab.size(), 1) + 3) / 4 * 16;
+    // (all but the last list, which is about products; what is refused is counted with eight numbers per tile row for it, and with the
+    // runs of token blocks and their order also where they are not sent)
+    auto room = [](size_t n) { return (std::max<size_t>(n, 1) + 3) / 4 * 4; };
+    const size_t unsent = p->shrink_group > 1 ? 0 : room(p->sb_off.size()) - 4 + room(p->sb_order.size()) - 4;
+    const size_t all = (p->o_tile_seg + unsent + room(p->gemm_tile_tab.size())) * 4;
     p->host_blob.resize(p->o_tile_seg);
     p->blob_bytes = p->host_blob.size() * sizeof(int32_t);
     if (all > size_t(LOBRA_STATIC_WS_BYTES)) st = LOBRA_ERR_WORKSPACE;

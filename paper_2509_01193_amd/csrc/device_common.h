@@ -17,7 +17,7 @@ struct PlanDev {
     const int32_t* task_chunk_off; // [n_tasks+1]
     const int32_t* rank_off;       // [n_tasks+1]
     const int32_t* task_tb_off;    // [n_tasks+1]
-    const int32_t* sb_off;         // [nsb+1]
+    const int32_t* sb_off;         // [nsb+1] (this and sb_order only with shrink_group > 1)
     const int32_t* tb_order;       // [ntb] launch order of the token blocks, or NULL = as stored
     const int32_t* sb_order;       // [nsb] launch order of the runs, or NULL = as stored
     // dB fused into the sliced projection of dy (NULL when the plan does not use it, see Plan::fused_db)
@@ -38,12 +38,17 @@ __device__ __forceinline__ const int32_t* cseg_rank(const PlanDev& pd)
 }
 
 // [ceil(T/32)], in plans of fp32 batches, where the MFMA kernels' records would be
-__device__ __forceinline__ const F32BlockRec* f32_block_rec(const PlanDev& pd) { return reinterpret_cast<const F32BlockRec*>(pd.gemm_tile_seg); }
+__device__ __forceinline__ F32BlockRec f32_block_rec(const PlanDev& pd, int32_t block)
+{
+    const int32_t* rec = pd.gemm_tile_seg + 3 * size_t(block);
+    const uint32_t v = uint32_t(rec[0]);             // (scalar loads, which know no bytes)
+    return F32BlockRec{uint8_t(v), uint8_t(v >> 8), uint8_t(v >> 16), uint8_t(v >> 24), rec[1], rec[2]};
+}
 
 // [ceil(T/32)][Plan::f32_items], behind them
 __device__ __forceinline__ const F32Item* f32_items(const PlanDev& pd)
 {
-    return reinterpret_cast<const F32Item*>(f32_block_rec(pd) + (pd.T + kRowBlock - 1) / kRowBlock);
+    return reinterpret_cast<const F32Item*>(reinterpret_cast<const F32BlockRec*>(pd.gemm_tile_seg) + (pd.T + kRowBlock - 1) / kRowBlock);
 }
 
 // [T][2], in plans with a projection beside its product and at most kRowTableTokens tokens: first rank row and rank of every row's task

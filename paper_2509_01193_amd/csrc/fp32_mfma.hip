@@ -91,8 +91,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     const int32_t row0 = id / tiles_n * TM, col0 = id % tiles_n * TN;
     const int32_t T = pd.T, row_end = min(row0 + TM, T);
 
-    const F32BlockRec rec = P ? f32_block_rec(pd)[row0 / kRowBlock] : F32BlockRec{};     // (in front of the copies: a scalar load)
-    const bool many = P && rec.fifth < row_end;      // more than kFewSegments segments in the tile
+    const F32BlockRec rec = P ? f32_block_rec(pd, row0 / kRowBlock) : F32BlockRec{};       // (in front of the copies: a scalar load)
+    const int32_t first_sg = rec.own + (rec.lo > 0);
+    const bool many = P && rec.fifth < row_end - row0;           // more than kFewSegments segments in the tile
     F32Item item[NI > 0 ? NI : 1];
     if constexpr (NI > 0) {
 #pragma unroll
@@ -194,10 +195,10 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     auto load_adapter = [&](int32_t lo, int32_t hi, int32_t r, int32_t pofs, int32_t r0, int32_t c0) {
         load_adapter_of([&](int, int32_t row) { return row >= lo && row < hi; }, r, pofs, r0, c0);
     };
-    const bool some = P && !many && rec.lo < row_end;
+    const bool some = P && !many && rec.lo < row_end - row0;
     if (some) {
         const int32_t r = rec.rank / nproj;
-        load_adapter(max(rec.lo, row0), min(rec.hi, row_end), r, proj * r, rec.rank0 + proj * r, 0);
+        load_adapter(row0 + rec.lo, min(row0 + rec.hi, row_end), r, proj * r, rec.rank0 + proj * r, 0);
     }
 
     float mi[NI > 0 ? NI : 1][WA], scale[NI > 0 ? NI / 2 : 1];       // the up factors' rows of the blocks; the scales of this wave's
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     }
     if (some || many) __syncthreads();               // everybody is done with the ring
     if (some) {
-        for (int32_t sg = rec.first; sg < pd.nseg; ++sg) {
+        for (int32_t sg = first_sg; sg < pd.nseg; ++sg) {
             const int32_t seg_lo = pd.cseg_off[sg];
             if (seg_lo >= row_end) break;
             const int32_t t = pd.cseg_task[sg];
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             const int32_t r = (pd.rank_off[t + 1] - pd.rank_off[t]) / nproj, pofs = proj * r;
             const int32_t r0 = pd.rank_off[t] + pofs;
             for (int32_t c0 = 0; c0 < r; c0 += 16) {
-                if (sg != rec.first || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
+                if (sg != first_sg || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
                 stash_adapter();
                 __syncthreads();
                 mac(zs, ws);

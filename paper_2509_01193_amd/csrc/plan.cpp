@@ -540,9 +540,10 @@ std::vector<int32_t> pack_blob(Plan* p)
     p->o_task_chunk = put(p->task_chunk_off.data(), p->task_chunk_off.size());
     p->o_rank_off = put(p->rank_off.data(), p->rank_off.size());
     p->o_task_tb = put(p->task_tb_off.data(), p->task_tb_off.size());
-    p->o_sb = put(p->sb_off.data(), p->sb_off.size());
+    const size_t runs = p->shrink_group > 1;         // (runs of one block are the blocks)
+    p->o_sb = put(p->sb_off.data(), runs * p->sb_off.size());
     p->o_tb_order = put(p->tb_order.data(), p->tb_order.size());
-    p->o_sb_order = put(p->sb_order.data(), p->sb_order.size());
+    p->o_sb_order = put(p->sb_order.data(), runs * p->sb_order.size());
     p->o_fb_wg = put(p->fb_wg_run_off.data(), p->fb_wg_run_off.size());
     p->o_fb_run = put(p->fb_run_row.data(), p->fb_run_row.size());
     p->o_fb_cnt = put(p->fb_cnt.data(), p->fb_cnt.size());
@@ -550,25 +551,24 @@ std::vector<int32_t> pack_blob(Plan* p)
     if (p->desc.dtype == LOBRA_F32) {
         const int32_t nseg = int32_t(p->cseg_task.size());
         std::vector<F32BlockRec> rec(p->rowblk_seg.size());
-        int32_t first = nseg;                        // of the blocks from the last to the first, so that each step looks at few segments
-        for (size_t b = rec.size(), seen = size_t(nseg); b-- > 0;) {
+        for (size_t b = 0; b < rec.size(); ++b) {
+            const int32_t row0 = int32_t(b) * kRowBlock, own = p->rowblk_seg[b], first = p->cseg_task[size_t(own)] >= 0 ? own : own + 1;
+            auto rows = [&](int32_t k) { return uint8_t(std::max(0, std::min(p->cseg_off[size_t(k)] - row0, 255))); };    // to where segment k starts
             F32BlockRec& r = rec[b];
-            r.own = p->rowblk_seg[b];
-            for (; seen > size_t(r.own); --seen)
-                if (p->cseg_task[seen - 1] >= 0) first = int32_t(seen - 1);
-            const int32_t t = first < nseg ? p->cseg_task[size_t(first)] : -1;
-            r.fifth = r.own + kFewSegments < nseg ? p->cseg_off[size_t(r.own + kFewSegments)] : INT32_MAX;
-            r.first = first;
-            r.lo = t >= 0 ? p->cseg_off[size_t(first)] : INT32_MAX;
-            r.hi = t >= 0 ? p->cseg_off[size_t(first) + 1] : INT32_MAX;
-            r.rank0 = t >= 0 ? p->rank_off[t] : 0;
-            r.rank = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
-            r.pad = 0;
+            r = F32BlockRec{255, 255, 255, 0, 0, own};
+            if (own + kFewSegments < nseg) r.fifth = rows(own + kFewSegments);
+            if (first == nseg) continue;
+            const int32_t t = p->cseg_task[size_t(first)];
+            r.lo = rows(first);
+            r.hi = rows(first + 1);
+            r.rank = uint8_t(p->rank_off[t + 1] - p->rank_off[t]);
+            r.rank0 = p->rank_off[t];
         }
-        std::vector<int32_t> list(reinterpret_cast<const int32_t*>(rec.data()), reinterpret_cast<const int32_t*>(rec.data() + rec.size()));
+        std::vector<int32_t> list(rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
+        if (!rec.empty()) std::memcpy(list.data(), rec.data(), rec.size() * sizeof(F32BlockRec));
         for (size_t b = 0; p->f32_items > 0 && b < rec.size(); ++b) {
             int32_t left = p->f32_items;
-            for (int32_t k = rec[b].own; k < nseg && p->cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
+            for (int32_t k = p->rowblk_seg[b]; k < nseg && p->cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
                 const int32_t t = p->cseg_task[size_t(k)];
                 const int32_t r = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
                 for (int32_t c = 0; c < r; c += 16, --left)
@@ -579,8 +579,9 @@ std::vector<int32_t> pack_blob(Plan* p)
         p->o_tile_seg = put(list.data(), list.size());
     } else {
         // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
-        const size_t nseg = p->cseg_task.size(), at = p->gemm_tile_seg.size();
-        std::vector<int32_t> list(p->gemm_tile_seg);
+        // (nothing of it without adapters)
+        const size_t nseg = p->tb.empty() ? 0 : p->cseg_task.size(), at = p->tb.empty() ? 0 : p->gemm_tile_seg.size();
+        std::vector<int32_t> list(p->gemm_tile_seg.begin(), p->gemm_tile_seg.begin() + at);
         list.resize(at + 2 * nseg, 0);
         for (size_t k = 0; k < nseg; ++k) {
             const int32_t t = p->cseg_task[k];

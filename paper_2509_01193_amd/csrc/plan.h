@@ -21,11 +21,13 @@ constexpr bool kMfmaKernels = true;   // bf16 storage runs on the MFMA kernels
 // projections start up to 512 threads per token, which a launch of less than 2^32 threads has room for.
 constexpr int64_t kPlainMaxTokens = 65535 * 64;
 
-// fp32: what a 32-row block says about the tiles that start with it - the segment of its first row, where the segment
-// kFewSegments further on starts, and the first segment from there on that has an adapter: its index, tokens, and its task's first rank
-// row and stacked rank (first tokens INT32_MAX: none)
+// fp32: what a 32-row block says about the tiles that start with it.  In rows from its first on, at most 255: where the segment
+// kFewSegments further on starts, and first row and last + 1 of the first segment from there on that has an adapter (255, 255: none) - the
+// block's own, or the next one, since no two without an adapter are neighbours.  That segment's task: its stacked rank and first rank
+// row.  And the segment of the block's first row (Plan::rowblk_seg once more: a second line of the tables would be a second round trip).
 constexpr int kFewSegments = 4;
-struct F32BlockRec { int32_t own, fifth, first, lo, hi, rank0, rank, pad; };
+struct F32BlockRec { uint8_t fifth, lo, hi, rank; int32_t rank0, own; };
+static_assert(LOBRA_MAX_RANK < 256 && sizeof(F32BlockRec) == 12, "a record is three numbers of 32 bits");
 
 // fp32, short batches: a block of up to 16 ranks that a 32-row block's product meets - the rows of its segment, its first rank row, how many
 // there are (0: no such block), the task, the block's first rank within the task and the task's rank
@@ -40,6 +42,14 @@ inline bool f32_fused(int64_t T, int32_t K, int32_t N, int32_t items)
     const int64_t n = (T + 31) / 32 * ((int64_t(N) + 31) / 32);
     return items > 0 && T <= kFusedTokens && n <= kFusedTiles && n * K * items <= 640 * 1024;
 }
+
+// A one-shot call's tables go to the device as arguments of launches, kUploadPiece numbers each, up to this many bytes; larger ones by a copy.
+// A piece takes 2.3 us of stream time and some 3.5 of the host's; a copy from pageable memory and the host callback that releases it take
+// 55 to 62 us of either (73 to 166 KB of tables), and some 180 us a call where the host is not ahead of the stream (padded chunks of 3072
+// tokens, four calls, 730 -> 173 us).  Calls that the host bounds take as long either way at 21 pieces (2070 one-token segments, 512 x 512,
+// 175 and 173 us); 24 keep what lists of the products add to tables of 64 KiB from turning such a call into a copy.
+constexpr size_t kUploadPiece = 1008;         // with the other arguments just below the 4 KiB of a launch
+constexpr size_t kUploadByArgument = 24 * kUploadPiece * sizeof(int32_t);
 
 struct TokenBlock { int32_t row0, nrows, task, rank_row0; };
 struct GradChunk  { int32_t tb_begin, tb_end, task, part_row0; };

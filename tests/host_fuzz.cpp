@@ -35,6 +35,26 @@ int main() {
     st = lobra_dynamic_buckets(lens.data(), ns, u.data(), U, R, ob.data(), &on, &pad);
     if (st != LOBRA_OK || on > R) { printf("bucket %d\n", st); return 1; }
   }
+  // long tables: the lists of the products (from o_tile_seg on) must not make a one-shot call's tables too large for launch arguments
+  // where all other lists, the runs and their order also where they are not sent, and eight numbers for each 256 rows are no more than 64 KiB
+  for (int it = 0; it < 1500; ++it) {
+    const int n = 1 + int(rng() % (it % 2 ? 16 : 2)), S = it % 5 == 4 ? 1 + int(rng() % 40) : 1500 + int(rng() % 2500), most = it % 3 == 0 ? 1 : 1 + int(rng() % 60);
+    std::vector<int32_t> off(1, 0), task, ro(1, 0);
+    for (int t = 0; t < n; ++t) ro.push_back(ro.back() + (it % 4 < 2 ? 16 : 1 + int(rng() % 128)));
+    for (int k = 0; k < S; ++k) {
+      off.push_back(off.back() + (it % 5 == 4 ? int(rng() % 10000) : 1 + int(rng() % most)));
+      task.push_back(it % 7 == 0 ? k % 2 - 1 : int(rng() % (n + 1)) - 1);
+    }
+    lobra_mlora_desc d{};
+    d.dtype = rng() % 2; d.d_in = 8 * (1 + rng() % 600); d.d_out = 8 * (1 + rng() % 600); d.T = off.back(); d.n_tasks = n; d.S = S;
+    d.rank_off = ro.data(); d.seg_off = off.data(); d.seg_task = task.data();
+    lobra::Plan p;
+    lobra_status st = lobra::build_host_plan(&d, 0, &p);
+    if (st != LOBRA_OK) { printf("long plan %d\n", st); return 1; }
+    const size_t bytes = lobra::pack_blob(&p).size() * 4, runs = p.shrink_group > 1 ? 0 : p.sb_off.size() + p.sb_order.size();
+    const size_t before = (p.o_tile_seg + runs + 8 * size_t((d.T + 255) / 256)) * 4;
+    if (before <= 65536 && bytes > lobra::kUploadByArgument) { printf("%zu bytes of tables, %zu without the products'\n", bytes, before); return 1; }
+  }
   printf("host fuzz ok\n");
   return 0;
 }
