@@ -521,9 +521,14 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
                     int32_t K, int32_t N, int32_t ldw, int32_t ldc, int32_t nproj, int32_t proj, hipStream_t st)
 {
     // The larger the tile the fewer loads per MFMA, as long as every compute unit has work: by an estimate of rounds of workgroups
-    // (us; four of 32, three of 64, two of 128 to a compute unit).  Tiles of 32 / 64 / 128, rows on 16-byte boundaries and not:
-    //     600 x 1024 x 1024  23 / 25 / 70      1000 x 1024 x 1024  30 / 27 / 74     4000 x 1024 x 1024  104 / 92 / 80
-    //     2000 x 512 x 512  17 / 16 / 43       4000 x 96 x 512  16 / 12 / 20        8000 x 128 x 1024  50 / 36 / 37
+    // (us; four of 32, three of 64, two of 128 to a compute unit; the rounds of a short K overlap).  Tiles of 32 / 64 / 128:
+    //     600 x 1024 x 1024  23 / 25 / 70      1000 x 1024 x 1024  30 / 27 / 74     4000 x 1024 x 1024  104 / 89 / 77
+    //     2000 x 512 x 512  17 / 16 / 43       4000 x 96 x 512  16 / 12 / 20        8000 x 128 x 1024  50 / 33 / 36
+    //     3000 x 256 x 256  11.0 / 11.5        1500 x 512 x 512  15.1 / 16.2        8000 x 512 x 96  15.1 / 17.3
+    //     3000 x 128 x 512  13.1 / 12.5        2000 x 256 x 384  10.6 / 11.2        8000 x 64 x 64  6.3 / 8.6
+    //     8000 x 256 x 256  21.5 / 17.3        8000 x 512 x 512  - / 49 / 45        8000 x 2048 x 2048  - / 587 / 549
+    //     3000 x 2048 x 2048  - / 205 / 245    4000 x 2048 x 2048  - / 268 / 255    5000 x 384 x 768  - / 34.3 / 37.2
+    // (W read along K, in backward passes: tiles of 64 take 620 for 8000 x 2048 x 2048, of 128 548), and at rows on no 16-byte boundaries
     //     600 x 1357 x 1676  40 / 51 / 149     2000 x 1357 x 1676  130 / 104 / 157  4000 x 1357 x 1676  262 / 187 / 262
     // (128 four bytes a lane: behind the others everywhere, the addresses of 32 copies a K tile do not fit the registers)
     const bool vec = ((K | N | ldw | ldc) & 3) == 0;
@@ -531,9 +536,11 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
     auto estimate = [&](int32_t t) {
         const float k = float(K) / 1024.f;
         const int64_t n = tiles(t), per = t == 64 ? 768 : 512, full = n / per, rest = n % per;
-        if (t == 32) return 6.f + k + float(n) * (0.0205f * k + 0.003f);
-        if (t == 64) return float(full) * (6.f + 47.f * k) + (rest == 0 ? 4.f : rest <= 256 ? 7.f + 18.5f * k : rest <= 512 ? 10.f + 32.f * k : 10.f + 47.f * k);
-        return float(full) * (20.f + 127.f * k) + (rest == 0 ? 0.f : rest <= 256 ? 15.f + 65.f * k : 20.f + 127.f * k);
+        if (t == 32) return 4.5f + 3.f * k + float(n) * (0.0205f * k + 0.003f);
+        if (t == 64)
+            return (transW ? 1.04f : 1.f) * (float(full) * (2.f + 48.f * k) +
+                                             (rest == 0 ? 4.f : rest <= 256 ? (full ? 5.f + 24.f * k : 7.f + 18.5f * k) : rest <= 512 ? 8.5f + 34.f * k : 10.f + 47.f * k));
+        return float(full) * (20.f + 120.f * k) + (rest == 0 ? 0.f : rest <= 256 ? 11.f + (full ? 48.f : 63.f) * k : 22.f + 118.f * k);
     };
     int32_t tm = estimate(64) < estimate(32) ? 64 : 32;
     if (vec && estimate(128) < estimate(tm)) tm = 128;
