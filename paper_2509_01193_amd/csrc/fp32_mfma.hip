@@ -113,11 +113,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     auto swz_k = [](int k) { return TN == 128 ? 0 : ((k >> 2) & 1) << (TN == 64 ? 3 : 2); };
     // (element e of a row lies at swizzled(e, s): its chunk of 16 bytes exchanged)
     auto swizzled = [](int e, int s) { return (((e >> 2) ^ s) << 2) | (e & 3); };
-    auto z_off = [&](int c, int32_t left) {          // of copy c, with `left` k in the K tile
+    auto z_off = [&](int c, int32_t left, int lane) {          // of copy c, with `left` k in the K tile
         const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
         return (uint32_t(min(row, T - 1 - row0)) * uint32_t(K) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
     };
-    auto w_off = [&](int c, int32_t left) {
+    auto w_off = [&](int c, int32_t left, int lane) {
         if (TRANSW) {
             const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
             return (uint32_t(min(row, N - 1 - col0)) * uint32_t(ldw) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
@@ -128,15 +128,15 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     };
     uint32_t zvo[ZC], wvo[WC];
 #pragma unroll
-    for (int c = 0; c < ZC; ++c) zvo[c] = z_off(c, FK);
+    for (int c = 0; c < ZC; ++c) zvo[c] = z_off(c, FK, lane);
 #pragma unroll
-    for (int c = 0; c < WC; ++c) wvo[c] = w_off(c, FK);
+    for (int c = 0; c < WC; ++c) wvo[c] = w_off(c, FK, lane);
     // (rank rows: a copy has rows of one block; those beyond its last repeat it)
     const unsigned char* abase[AC > 0 ? AC : 1];
     int32_t an[AC > 0 ? AC : 1];
     uint32_t avo[AC > 0 ? AC : 1];
     size_t aat = 0;
-    auto a_off = [&](int c, int32_t left) {
+    auto a_off = [&](int c, int32_t left, int lane) {
         const int row = 64 / ZL * (wave + 4 * c) + lane / ZL;
         return (uint32_t(min(row & 15, max(an[c] - 1, 0))) * uint32_t(K) + uint32_t(min(swizzled(E * (lane % ZL), swz_row(row)), left - E))) * 4u;
     };
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
             for (int i = 1; i < NI; ++i)
                 if ((64 / ZL * (wave + 4 * c)) >> 4 == i) row = item[i].row, an[c] = item[i].n;
             abase[c] = reinterpret_cast<const unsigned char*>(D + size_t(row) * K);
-            avo[c] = a_off(c, FK);
+            avo[c] = a_off(c, FK, lane);
         }
     }
     auto copy = [&](auto c_c, uint32_t la) __attribute__((always_inline)) {
@@ -161,12 +161,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     auto next_copy_tile = [&]() __attribute__((always_inline)) { zcur += FK * 4, wcur += wstep, aat += FK * 4; };
     const int32_t KT = (K + FK - 1) / FK, ktail = K % FK, KF = K / FK;
     auto copy_tail = [&](uint32_t la) {
+        int ln = lane;
+        if constexpr (TM == 128) asm volatile("" : "+v"(ln));        // (its addresses are worked out here: no registers are left for them in the main loop)
 #pragma unroll
-        for (int c = 0; c < ZC; ++c) dma(la + 4 * c * LB, zcur, z_off(c, ktail));
+        for (int c = 0; c < ZC; ++c) dma(la + 4 * c * LB, zcur, z_off(c, ktail, ln));
 #pragma unroll
-        for (int c = 0; c < WC; ++c) dma(la + ZT + 4 * c * LB, wcur, w_off(c, ktail));
+        for (int c = 0; c < WC; ++c) dma(la + ZT + 4 * c * LB, wcur, w_off(c, ktail, ln));
 #pragma unroll
-        for (int c = 0; c < AC; ++c) dma(la + AOFF + 4 * c * LB, abase[c] + aat, a_off(c, ktail));
+        for (int c = 0; c < AC; ++c) dma(la + AOFF + 4 * c * LB, abase[c] + aat, a_off(c, ktail, ln));
     };
     for (int s = 0; s < STAGES; ++s) {
         if (s < KF) static_for<0, CPW>([&](auto c_c) { copy(c_c, la0 + s * SLOT); });

@@ -268,3 +268,18 @@ def test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, source, l
 
 def test_lds_writes_of_the_ring_projection_are_waited_for(tmp_path):
     test_lds_writes_are_waited_for_in_front_of_every_barrier(tmp_path, "shrink_ring.hip", 6)
+
+
+@pytest.mark.parametrize("source,least", [("fp32_mfma.hip", 30), ("gemm_tile.hip", 8), ("shrink_ring.hip", 6), ("kernels_plain.hip", 8)])
+def test_no_kernel_takes_scratch_memory(tmp_path, source, least):
+    """Registers that do not fit go to scratch memory, whose loads the counted waits of the copies would wait for as well."""
+    out = str(tmp_path / "k.s")
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "hip", "--cuda-device-only",
+           "-S", os.path.join(CSRC, source), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-3000:]
+    parts = re.split(r"^\s*\.amdhsa_kernel (\w+)$", open(out).read(), flags=re.M)
+    sizes = {name: int(re.search(r"; ScratchSize: (\d+)", body).group(1)) for name, body in zip(parts[1::2], parts[2::2])}
+    assert len(sizes) >= least, (source, len(sizes))
+    assert not {k: v for k, v in sizes.items() if v}
