@@ -265,15 +265,12 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         for (int k = 0; k < 2; ++k) h[b][k].run = h[b][k].all = f32x4{0.f, 0.f, 0.f, 0.f};
     const int32_t range = NI > 0 ? f32_range(KT) : 0;
     int32_t range_end = range;
-    auto fold = [&]() {                              // in front of K tile range_end
+    auto fold = [&](int k) {                         // in front of the K step k that begins a range, half a K tile behind the chain's last MFMA
 #pragma unroll
-        for (int b = 0; b < HB; ++b)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                h[b][k].all = h[b][k].all + h[b][k].run;
-                h[b][k].run = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        range_end += range;
+        for (int b = 0; b < HB; ++b) {
+            h[b][k].all = h[b][k].all + h[b][k].run;
+            h[b][k].run = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     };
     // the MFMAs on `f`, fragments of K step ks ^ 1, with the reads of the next step's fragments (ks) and (COPY) a K tile's copies dealt
     // evenly behind them
@@ -320,9 +317,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     Frags fa, fb;
     static_for<0, NR>([&](auto i_c) { read(i_c, fa, lds, 0); });
     int32_t kt = 0, slot = 0;
-    auto ktile = [&]() __attribute__((always_inline)) {              // a whole K tile is still to be copied
+    auto ktile = [&](auto fold_c) __attribute__((always_inline)) {   // a whole K tile is still to be copied
         const unsigned char* cur = lds + slot * SLOT;
+        if constexpr (decltype(fold_c)::value) fold(0);
         kstep(yes{}, no{}, fa, fb, cur, step1{}, 0);
+        if constexpr (decltype(fold_c)::value) fold(1);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wait_vmcnt<(STAGES - 2) * CPW>();
         __builtin_amdgcn_s_barrier();
@@ -334,18 +333,27 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
     };
     if constexpr (NI > 0) {
         while (kt < KF - STAGES) {
+            if (kt == range_end) {
+                ktile(yes{});
+                ++kt;
+                range_end += range;
+            }
             const int32_t end = min(range_end, KF - STAGES);
-            for (; kt < end; ++kt) ktile();
-            if (kt == range_end) fold();
+            for (; kt < end; ++kt) ktile(no{});
         }
     } else {
-        for (; kt < KF - STAGES; ++kt) ktile();
+        for (; kt < KF - STAGES; ++kt) ktile(no{});
     }
     for (; kt < KT; ++kt) {                          // the last STAGES K tiles, and the partial one
         const bool tail = ktail != 0 && kt + 1 == KT;            // uniform
-        if (NI > 0 && kt == range_end) fold();
+        const bool begins = NI > 0 && kt == range_end;
+        if (begins) fold(0);
         if (tail) clear_tail(fa, 0);
         kstep(yes{}, no{}, fa, fb, lds + slot * SLOT, step1{}, 0);
+        if (begins) {
+            fold(1);
+            range_end += range;
+        }
         if (tail) clear_tail(fb, 1);
         if (kt + 1 < KT) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
