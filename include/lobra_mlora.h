@@ -191,13 +191,23 @@ LOBRA_API lobra_status lobra_mlora_plan_sizes(const lobra_mlora_plan *plan, size
  *   LOBRA_Q_GEMM_TILE_ROWS  n x 8, one record per 256-token tile row of the base product (tile row i starts at token
  *                        max(0, min(256 i, T - 256))): {segment, first token, last token + 1, task or -1, the task's
  *                        first rank row, its stacked rank, 0, 0} of the compacted segment that holds that token
+ *   LOBRA_Q_PRODUCT_TABLES  the list that the products' kernels read besides the segments, as it is sent to the device.  bf16 (empty
+ *                        without adapters): per 256-token tile row 16 numbers, the first three adapter segments that cross it as {first
+ *                        token, last token + 1, first rank row of the task, stacked rank} (0 where there is none), the segment
+ *                        of LOBRA_Q_SEGMENTS at which to look for further ones, 0, 0, 0; then per segment the task's first rank row, then per
+ *                        segment its rank (0, 0 without a task); then, for up to 256 tokens with a product of LOBRA_Q_BESIDE, both per token.
+ *                        fp32: per 32-row block 3 numbers, {bytes in rows from the block's first, at most 255: start of the fourth segment
+ *                        after its own, first row and last + 1 of the first adapter segment from there on (255, 255: none); that task's
+ *                        rank}, its first rank row, the block's own segment; then, where short batches are projected inside the product, 2
+ *                        or 4 per block of {first token, last token + 1, first rank row, ranks (0: unused), task, first rank within the
+ *                        task, rank of the task, 0}: its blocks of up to 16 ranks
  *   LOBRA_Q_BESIDE       {forward, backward}: given workspace for the sums, the projection runs in the launch of its product,
  *                        whose K is split this many ways (0: it is a launch of its own) */
 enum { LOBRA_Q_SEGMENTS = 0, LOBRA_Q_ROWBLOCK_SEG = 1, LOBRA_Q_TOKEN_BLOCKS = 2,
        LOBRA_Q_GRAD_CHUNKS = 3, LOBRA_Q_TASK_CHUNKS = 4, LOBRA_Q_BLOCK_RUNS = 5,
        LOBRA_Q_BLOCK_ORDER = 6, LOBRA_Q_RUN_ORDER = 7, LOBRA_Q_SLICED = 8, LOBRA_Q_FUSED_WG_RUNS = 9,
        LOBRA_Q_FUSED_RUN_ROW = 10, LOBRA_Q_FUSED_COUNT = 11, LOBRA_Q_FUSED_TASK_ROW = 12,
-       LOBRA_Q_GEMM_TILE_ROWS = 13, LOBRA_Q_BESIDE = 14 };
+       LOBRA_Q_GEMM_TILE_ROWS = 13, LOBRA_Q_BESIDE = 14, LOBRA_Q_PRODUCT_TABLES = 15 };
 LOBRA_API lobra_status lobra_mlora_plan_query(const lobra_mlora_plan *plan, int32_t what, int32_t *out,
                                     size_t capacity, size_t *count);
 

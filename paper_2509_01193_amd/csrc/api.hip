@@ -255,6 +255,7 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
     std::vector<int32_t> tmp;
     const int32_t* src = nullptr;
     size_t n = 0;
+    try {
     switch (what) {
     case LOBRA_Q_SEGMENTS:
         for (size_t k = 0; k < plan->cseg_task.size(); ++k) {
@@ -320,11 +321,26 @@ lobra_status lobra_mlora_plan_query(const lobra_mlora_plan* plan, int32_t what, 
         n = tmp.size();
         break;
     case LOBRA_Q_GEMM_TILE_ROWS:
-        src = plan->gemm_tile_tab.data();
-        n = plan->gemm_tile_tab.size();
+        for (int64_t i = 0; i * kGemmTileRows < plan->desc.T; ++i) {
+            const int64_t row0 = std::max<int64_t>(0, std::min<int64_t>(i * kGemmTileRows, plan->desc.T - kGemmTileRows));
+            int32_t k = plan->rowblk_seg[size_t(row0 / kRowBlock)];
+            while (plan->cseg_off[size_t(k) + 1] <= row0) ++k;
+            const int32_t t = plan->cseg_task[size_t(k)], r0 = t >= 0 ? plan->rank_off[size_t(t)] : 0, r = t >= 0 ? plan->rank_off[size_t(t) + 1] - r0 : 0;
+            tmp.insert(tmp.end(), {k, plan->cseg_off[size_t(k)], plan->cseg_off[size_t(k) + 1], t, r0, r, 0, 0});
+        }
+        src = tmp.data();
+        n = tmp.size();
+        break;
+    case LOBRA_Q_PRODUCT_TABLES:
+        tmp = product_tables(*plan);
+        src = tmp.data();
+        n = tmp.size();
         break;
     default:
         return LOBRA_ERR_SHAPE;
+    }
+    } catch (const std::bad_alloc&) {
+        return LOBRA_ERR_NOMEM;
     }
     *count = n;
     if (out && n) std::memcpy(out, src, sizeof(int32_t) * (n < capacity ? n : capacity));
@@ -703,7 +719,7 @@ lobra_status lobra_token_task_map(const lobra_mlora_desc* desc, int32_t* out_tas
     // runs of token blocks and their order also where they are not sent)
     auto room = [](size_t n) { return (std::max<size_t>(n, 1) + 3) / 4 * 4; };
     const size_t unsent = p->shrink_group > 1 ? 0 : room(p->sb_off.size()) - 4 + room(p->sb_order.size()) - 4;
-    const size_t all = (p->o_tile_seg + unsent + room(p->gemm_tile_tab.size())) * 4;
+    const size_t all = (p->o_tile_seg + unsent + room(8 * size_t((desc->T + kGemmTileRows - 1) / kGemmTileRows))) * 4;
     p->host_blob.resize(p->o_tile_seg);
     p->blob_bytes = p->host_blob.size() * sizeof(int32_t);
     if (all > size_t(LOBRA_STATIC_WS_BYTES)) st = LOBRA_ERR_WORKSPACE;

@@ -101,22 +101,13 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             p->rowblk_seg[b] = k;
         }
 
-        // 2b. what the first rows of every GEMM tile row belong to
+        // 2b. the segments that cross every GEMM tile row
         {
             const int32_t ntr = (T + kGemmTileRows - 1) / kGemmTileRows;
-            p->gemm_tile_tab.assign(size_t(ntr) * kGemmTileRec, 0);
             p->gemm_tile_seg.assign(size_t(ntr) * kGemmTileSegRec, 0);
             for (int32_t i = 0, k = 0; i < ntr; ++i) {
                 const int32_t row0 = std::max(0, std::min(i * kGemmTileRows, T - kGemmTileRows));
                 while (p->cseg_off[k + 1] <= row0) ++k;      // row0 does not decrease with i
-                const int32_t t = p->cseg_task[k];
-                int32_t* rec = &p->gemm_tile_tab[size_t(i) * kGemmTileRec];
-                rec[0] = k;
-                rec[1] = p->cseg_off[k];
-                rec[2] = p->cseg_off[k + 1];
-                rec[3] = t;
-                rec[4] = t >= 0 ? p->rank_off[t] : 0;
-                rec[5] = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
                 int32_t* seg = &p->gemm_tile_seg[size_t(i) * kGemmTileSegRec];
                 const int32_t row_end = std::min(row0 + kGemmTileRows, T);
                 int32_t g = k, found = 0;
@@ -522,6 +513,57 @@ SlicedShape sliced_shrink_shape(int64_t ntb, int32_t r_pad, int32_t D)
     return SlicedShape{int32_t(nsl)};
 }
 
+std::vector<int32_t> product_tables(const Plan& p)
+{
+    if (p.desc.dtype == LOBRA_F32) {
+        const int32_t nseg = int32_t(p.cseg_task.size());
+        std::vector<F32BlockRec> rec(p.rowblk_seg.size());
+        for (size_t b = 0; b < rec.size(); ++b) {
+            const int32_t row0 = int32_t(b) * kRowBlock, own = p.rowblk_seg[b], first = p.cseg_task[size_t(own)] >= 0 ? own : own + 1;
+            auto rows = [&](int32_t k) { return uint8_t(std::max(0, std::min(p.cseg_off[size_t(k)] - row0, 255))); };    // to where segment k starts
+            F32BlockRec& r = rec[b];
+            r = F32BlockRec{255, 255, 255, 0, 0, own};
+            if (own + kFewSegments < nseg) r.fifth = rows(own + kFewSegments);
+            if (first == nseg) continue;
+            const int32_t t = p.cseg_task[size_t(first)];
+            r.lo = rows(first);
+            r.hi = rows(first + 1);
+            r.rank = uint8_t(p.rank_off[t + 1] - p.rank_off[t]);
+            r.rank0 = p.rank_off[t];
+        }
+        std::vector<int32_t> list(rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
+        if (!rec.empty()) std::memcpy(list.data(), rec.data(), rec.size() * sizeof(F32BlockRec));
+        for (size_t b = 0; p.f32_items > 0 && b < rec.size(); ++b) {
+            int32_t left = p.f32_items;
+            for (int32_t k = p.rowblk_seg[b]; k < nseg && p.cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
+                const int32_t t = p.cseg_task[size_t(k)];
+                const int32_t r = t >= 0 ? p.rank_off[t + 1] - p.rank_off[t] : 0;
+                for (int32_t c = 0; c < r; c += 16, --left)
+                    list.insert(list.end(), {p.cseg_off[size_t(k)], p.cseg_off[size_t(k) + 1], p.rank_off[t] + c, std::min(r - c, 16), t, c, r, 0});
+            }
+            list.resize(list.size() + size_t(left) * (sizeof(F32Item) / sizeof(int32_t)), 0);
+        }
+        return list;
+    }
+
+    // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
+    // (nothing of it without adapters)
+    const size_t nseg = p.tb.empty() ? 0 : p.cseg_task.size(), at = p.tb.empty() ? 0 : p.gemm_tile_seg.size();
+    std::vector<int32_t> list(p.gemm_tile_seg.begin(), p.gemm_tile_seg.begin() + at);
+    list.resize(at + 2 * nseg, 0);
+    for (size_t k = 0; k < nseg; ++k) {
+        const int32_t t = p.cseg_task[k];
+        if (t < 0) continue;
+        list[at + k] = p.rank_off[t];
+        list[at + nseg + k] = p.rank_off[t + 1] - p.rank_off[t];
+    }
+    // and, where the sum of a split product adds the adapter term, the same for every row (see row_rank)
+    if ((p.beside_fwd.tile >= 0 || p.beside_bwd.tile >= 0) && p.desc.T <= kRowTableTokens)
+        for (size_t k = 0; k < nseg; ++k)
+            for (int32_t i = p.cseg_off[k]; i < p.cseg_off[k + 1]; ++i) list.insert(list.end(), {list[at + k], list[at + nseg + k]});
+    return list;
+}
+
 std::vector<int32_t> pack_blob(Plan* p)
 {
     std::vector<int32_t> blob;
@@ -548,53 +590,8 @@ std::vector<int32_t> pack_blob(Plan* p)
     p->o_fb_run = put(p->fb_run_row.data(), p->fb_run_row.size());
     p->o_fb_cnt = put(p->fb_cnt.data(), p->fb_cnt.size());
     p->o_fb_row0 = put(p->fb_task_row0.data(), p->fb_task_row0.size());
-    if (p->desc.dtype == LOBRA_F32) {
-        const int32_t nseg = int32_t(p->cseg_task.size());
-        std::vector<F32BlockRec> rec(p->rowblk_seg.size());
-        for (size_t b = 0; b < rec.size(); ++b) {
-            const int32_t row0 = int32_t(b) * kRowBlock, own = p->rowblk_seg[b], first = p->cseg_task[size_t(own)] >= 0 ? own : own + 1;
-            auto rows = [&](int32_t k) { return uint8_t(std::max(0, std::min(p->cseg_off[size_t(k)] - row0, 255))); };    // to where segment k starts
-            F32BlockRec& r = rec[b];
-            r = F32BlockRec{255, 255, 255, 0, 0, own};
-            if (own + kFewSegments < nseg) r.fifth = rows(own + kFewSegments);
-            if (first == nseg) continue;
-            const int32_t t = p->cseg_task[size_t(first)];
-            r.lo = rows(first);
-            r.hi = rows(first + 1);
-            r.rank = uint8_t(p->rank_off[t + 1] - p->rank_off[t]);
-            r.rank0 = p->rank_off[t];
-        }
-        std::vector<int32_t> list(rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
-        if (!rec.empty()) std::memcpy(list.data(), rec.data(), rec.size() * sizeof(F32BlockRec));
-        for (size_t b = 0; p->f32_items > 0 && b < rec.size(); ++b) {
-            int32_t left = p->f32_items;
-            for (int32_t k = p->rowblk_seg[b]; k < nseg && p->cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
-                const int32_t t = p->cseg_task[size_t(k)];
-                const int32_t r = t >= 0 ? p->rank_off[t + 1] - p->rank_off[t] : 0;
-                for (int32_t c = 0; c < r; c += 16, --left)
-                    list.insert(list.end(), {p->cseg_off[size_t(k)], p->cseg_off[size_t(k) + 1], p->rank_off[t] + c, std::min(r - c, 16), t, c, r, 0});
-            }
-            list.resize(list.size() + size_t(left) * (sizeof(F32Item) / sizeof(int32_t)), 0);
-        }
-        p->o_tile_seg = put(list.data(), list.size());
-    } else {
-        // behind the records, for every segment: its task's first rank row, then, for every segment again, its stacked rank (see cseg_rank)
-        // (nothing of it without adapters)
-        const size_t nseg = p->tb.empty() ? 0 : p->cseg_task.size(), at = p->tb.empty() ? 0 : p->gemm_tile_seg.size();
-        std::vector<int32_t> list(p->gemm_tile_seg.begin(), p->gemm_tile_seg.begin() + at);
-        list.resize(at + 2 * nseg, 0);
-        for (size_t k = 0; k < nseg; ++k) {
-            const int32_t t = p->cseg_task[k];
-            if (t < 0) continue;
-            list[at + k] = p->rank_off[t];
-            list[at + nseg + k] = p->rank_off[t + 1] - p->rank_off[t];
-        }
-        // and, where the sum of a split product adds the adapter term, the same for every row (see row_rank)
-        if ((p->beside_fwd.tile >= 0 || p->beside_bwd.tile >= 0) && p->desc.T <= kRowTableTokens)
-            for (size_t k = 0; k < nseg; ++k)
-                for (int32_t i = p->cseg_off[k]; i < p->cseg_off[k + 1]; ++i) list.insert(list.end(), {list[at + k], list[at + nseg + k]});
-        p->o_tile_seg = put(list.data(), list.size());
-    }
+    const std::vector<int32_t> list = product_tables(*p);
+    p->o_tile_seg = put(list.data(), list.size());
     while (blob.size() % 4) blob.push_back(0);
     return blob;
 }

@@ -12,7 +12,6 @@ namespace lobra {
 constexpr int kTokenBlock = 32;   // tokens per token block (one MFMA K step of the reductions)
 constexpr int kRowBlock = 32;     // granularity of the row -> segment lookup table
 constexpr int kGemmTileRows = 256;    // token rows of a base-GEMM output tile
-constexpr int kGemmTileRec = 8;       // ints per record of Plan::gemm_tile_tab
 constexpr int32_t kRowTableTokens = 256;  // batches that get a table of rows: 2 KiB of tables at most
 constexpr int kGemmTileSegs = 3, kGemmTileSegRec = 16;     // adapter segments and ints per record of Plan::gemm_tile_seg
 constexpr int kMaxClearedTasks = 4096;    // up to here stage 1 of the gradients clears the rows of tasks without tokens
@@ -168,12 +167,8 @@ struct Plan {
     std::vector<int32_t> seg_off_in, seg_task_in;   // the caller's table, as given
     std::vector<int32_t> cseg_off, cseg_task;       // compacted table
     std::vector<int32_t> rowblk_seg;    // [ceil(T/32)]
-    // One record of kGemmTileRec ints per tile row of the base GEMM (tile row i starts at token
-    // min(i kGemmTileRows, T - kGemmTileRows), never below 0): the compacted segment that holds that token, its
-    // first and last + 1 token, its task (-1: none), and that task's first rank row and stacked rank
-    // (0, 0 without a task); the rest is padding.  (For lobra_mlora_plan_query; the kernels read the next table.)
-    std::vector<int32_t> gemm_tile_tab; // [ceil(T/kGemmTileRows)][kGemmTileRec]
-    // One record of kGemmTileSegRec ints per tile row, which one 64-byte read brings to a GEMM workgroup: the first kGemmTileSegs
+    // One record of kGemmTileSegRec ints per tile row of the base GEMM (tile row i starts at token min(i kGemmTileRows, T - kGemmTileRows),
+    // never below 0), which one 64-byte read brings to a GEMM workgroup: the first kGemmTileSegs
     // segments with an adapter that cross it - first token, last + 1, the task's first rank row and stacked rank (0 where there
     // is no such segment) - and the compacted segment at which to look for further ones.
     std::vector<int32_t> gemm_tile_seg; // [ceil(T/kGemmTileRows)][kGemmTileSegRec]
@@ -244,6 +239,9 @@ struct Plan {
 lobra_status validate(const lobra_mlora_desc* d);
 // Fills every host field of `p` (not the device copy).  `d` has been validated.
 lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p);
+// The list that the products read besides the segments: for the MFMA kernels Plan::gemm_tile_seg and, behind it, rank rows and ranks per segment
+// and per row (cseg_rank, row_rank), for fp32 an F32BlockRec per 32-row block and, behind them, the F32Items.
+std::vector<int32_t> product_tables(const Plan& p);
 // Packs the lists into one int32 blob; sets the o_* offsets.
 std::vector<int32_t> pack_blob(Plan* p);
 

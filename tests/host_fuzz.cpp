@@ -25,8 +25,12 @@ int main() {
     lobra::Plan p;
     st = lobra::build_host_plan(&d, rng() % 4, &p);
     if (st != LOBRA_OK) { printf("plan %d\n", st); return 1; }
-    auto blob = lobra::pack_blob(&p);
-    (void)blob;
+    // the last list holds what the kernels look for behind each other: tile rows, segments, rows; fp32 blocks and items
+    const size_t behind = lobra::pack_blob(&p).size() - p.o_tile_seg, T = size_t(d.T), nseg = p.cseg_task.size();
+    const bool rows = T <= 256 && (p.beside_fwd.tile >= 0 || p.beside_bwd.tile >= 0);
+    const size_t want = d.dtype == LOBRA_F32 ? (T + 31) / 32 * (3 + 8 * size_t(p.f32_items))
+                        : p.tb.empty() ? 0 : (T + 255) / 256 * 16 + 2 * nseg + (rows ? 2 * T : 0);
+    if (behind != (want > 0 ? (want + 3) / 4 * 4 : 4)) { printf("%zu numbers behind the lists, %zu wanted, it %d\n", behind, want, it); return 1; }
     // bucketing
     int U = 1 + rng() % 64, R = 1 + rng() % 20;
     std::vector<int32_t> u; int32_t b = 0; for (int i = 0; i < U; ++i) { b += 1 + rng() % 300; u.push_back(b); }

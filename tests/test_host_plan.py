@@ -312,9 +312,84 @@ def brute_force_lists(p):
     return tok, segs
 
 
+def check_product_tables(p, plan, segs):
+    """The list that the products' kernels read, number by number and in full length: the kernels find its parts behind each other."""
+    got = plan.query(bd.Q_PRODUCT_TABLES).tolist()
+    ro, nseg = np.asarray(p.rank_off), len(segs)
+    rank = lambda t: int(ro[t + 1] - ro[t]) if t >= 0 else 0
+    row = lambda t: int(ro[t]) if t >= 0 else 0
+    if p.dtype == "f32":
+        want, blocks, items = [], (p.T + 31) // 32, []
+        own = [next(k for k, s in enumerate(segs) if s[1] > 32 * b) for b in range(blocks)] if nseg < 300 else plan.query(bd.Q_ROWBLOCK_SEG).tolist()
+        for b, k in enumerate(own):
+            at = lambda token: min(max(token - 32 * b, 0), 255)
+            first = next((i for i in range(k, nseg) if segs[i][2] >= 0), None)
+            fifth = at(segs[k + 4][0]) if k + 4 < nseg else 255
+            lo, hi, t = (at(segs[first][0]), at(segs[first][1]), segs[first][2]) if first is not None else (255, 255, -1)
+            want += [np.array([fifth, lo, hi, rank(t)], np.uint8).view(np.int32).item(), row(t), k]
+            cross = [s for s in segs[k:k + 32] if s[0] < 32 * b + 32 and s[2] >= 0]
+            items.append([[s[0], s[1], row(s[2]) + c, min(rank(s[2]) - c, 16), s[2], c, rank(s[2]), 0] for s in cross for c in range(0, rank(s[2]), 16)])
+        assert got[:len(want)] == want
+        rest = np.asarray(got[len(want):], np.int32)
+        if len(rest):
+            per = len(rest) // 8 // blocks
+            assert per in (2, 4) and p.T <= 1024 and len(rest) == 8 * per * blocks
+            for b, block in enumerate(rest.reshape(blocks, per, 8).tolist()):
+                assert block == items[b] + [[0] * 8] * (per - len(items[b]))
+        return len(rest) > 0
+    if not any(t >= 0 for _, _, t in segs):
+        assert got == []
+        return False
+    want = []
+    for i in range((p.T + 255) // 256):
+        row0 = max(0, min(256 * i, p.T - 256))
+        k = next(k for k, s in enumerate(segs) if s[1] > row0)
+        rec = []
+        while k < nseg and segs[k][0] < min(row0 + 256, p.T) and len(rec) < 12:
+            lo, hi, t = segs[k]
+            rec += [lo, hi, row(t), rank(t)] if t >= 0 else []
+            k += 1
+        want += rec + [0] * (12 - len(rec)) + [k, 0, 0, 0]
+    want += [row(t) for _, _, t in segs] + [rank(t) for _, _, t in segs]
+    rows = p.T <= 256 and bool(plan.query(bd.Q_BESIDE).any())
+    if rows:
+        want += [v for lo, hi, t in segs for _ in range(lo, hi) for v in (row(t), rank(t))]
+    assert got == want
+    return rows
+
+
+@pytest.mark.parametrize("dtype,T,d_in,d_out,ranks,lens,behind", [
+    ("bf16", 1, 4096, 4096, [16], [1], True),                # rows behind the segments: one,
+    ("bf16", 256, 8192, 512, [16, 8], [30, 34], True),        #   the most,
+    ("bf16", 257, 8192, 512, [16, 8], [30, 34], False),       #   and one more
+    ("bf16", 200, 512, 512, [16, 8], [1, 3], False),         # no product with the projection beside it
+    ("bf16", 1000, 512, 512, [3, 128, 20], [1, 100, 40, 2, 300], False),
+    ("f32", 33, 100, 60, [16], [33], True),                  # items of two, then four blocks of ranks
+    ("f32", 1024, 64, 96, [32, 20], [70, 200], True),
+    ("f32", 1025, 64, 96, [32, 20], [70, 200], False),
+    ("f32", 300, 64, 96, [128], [9], False),                 # more than four
+    ("f32", 5000, 64, 96, [40, 1, 128], [1, 2, 300, 5, 31], False),
+])
+def test_tables_of_the_products(dtype, T, d_in, d_out, ranks, lens, behind):
+    rng = np.random.default_rng(T)
+    for bare in (False, True):
+        cut = []
+        while sum(cut) < T:
+            cut.append(min(lens[len(cut) % len(lens)], T - sum(cut)))
+        tasks = [k % len(ranks) for k in range(len(cut))] if not bare else rng.integers(-1, len(ranks), len(cut))
+        if bare and (np.asarray(tasks) < 0).all():
+            continue
+        p = wl.make_custom("tables", dtype, d_in, d_out, ranks, np.concatenate([[0], np.cumsum(cut)]), tasks, 0, fill=False)
+        plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
+        _, segs = brute_force_lists(p)
+        assert check_product_tables(p, plan, segs) == behind
+        plan.close()
+
+
 def check_plan(p):
     plan = bd.Plan.for_problem(p, bd.PLAN_HOST_ONLY)
     tok, segs = brute_force_lists(p)
+    check_product_tables(p, plan, segs)
     got = plan.query(bd.Q_SEGMENTS).reshape(-1, 3)
     assert [tuple(r) for r in got.tolist()] == segs
     rb = plan.query(bd.Q_ROWBLOCK_SEG)
