@@ -101,8 +101,9 @@ lobra_status build_host_plan(const lobra_mlora_desc* d, uint32_t flags, Plan* p)
             p->rowblk_seg[b] = k;
         }
 
-        // 2b. the segments that cross every GEMM tile row
-        {
+        // 2b. the segments that cross every tile row of the MFMA kernels' products
+        p->gemm_tile_seg.clear();
+        if (d->dtype == LOBRA_BF16) {
             const int32_t ntr = (T + kGemmTileRows - 1) / kGemmTileRows;
             p->gemm_tile_seg.assign(size_t(ntr) * kGemmTileSegRec, 0);
             for (int32_t i = 0, k = 0; i < ntr; ++i) {
@@ -517,23 +518,26 @@ std::vector<int32_t> product_tables(const Plan& p)
 {
     if (p.desc.dtype == LOBRA_F32) {
         const int32_t nseg = int32_t(p.cseg_task.size());
-        std::vector<F32BlockRec> rec(p.rowblk_seg.size());
-        for (size_t b = 0; b < rec.size(); ++b) {
+        const size_t blocks = p.rowblk_seg.size();
+        constexpr size_t kRec = sizeof(F32BlockRec) / sizeof(int32_t), kItem = sizeof(F32Item) / sizeof(int32_t);
+        std::vector<int32_t> list;
+        list.reserve(blocks * (kRec + size_t(p.f32_items) * kItem));
+        list.resize(blocks * kRec);
+        for (size_t b = 0; b < blocks; ++b) {
             const int32_t row0 = int32_t(b) * kRowBlock, own = p.rowblk_seg[b], first = p.cseg_task[size_t(own)] >= 0 ? own : own + 1;
             auto rows = [&](int32_t k) { return uint8_t(std::max(0, std::min(p.cseg_off[size_t(k)] - row0, 255))); };    // to where segment k starts
-            F32BlockRec& r = rec[b];
-            r = F32BlockRec{255, 255, 255, 0, 0, own};
+            F32BlockRec r{255, 255, 255, 0, 0, own};
             if (own + kFewSegments < nseg) r.fifth = rows(own + kFewSegments);
-            if (first == nseg) continue;
-            const int32_t t = p.cseg_task[size_t(first)];
-            r.lo = rows(first);
-            r.hi = rows(first + 1);
-            r.rank = uint8_t(p.rank_off[t + 1] - p.rank_off[t]);
-            r.rank0 = p.rank_off[t];
+            if (first < nseg) {
+                const int32_t t = p.cseg_task[size_t(first)];
+                r.lo = rows(first);
+                r.hi = rows(first + 1);
+                r.rank = uint8_t(p.rank_off[t + 1] - p.rank_off[t]);
+                r.rank0 = p.rank_off[t];
+            }
+            std::memcpy(&list[b * kRec], &r, sizeof(r));
         }
-        std::vector<int32_t> list(rec.size() * (sizeof(F32BlockRec) / sizeof(int32_t)));
-        if (!rec.empty()) std::memcpy(list.data(), rec.data(), rec.size() * sizeof(F32BlockRec));
-        for (size_t b = 0; p.f32_items > 0 && b < rec.size(); ++b) {
+        for (size_t b = 0; p.f32_items > 0 && b < blocks; ++b) {
             int32_t left = p.f32_items;
             for (int32_t k = p.rowblk_seg[b]; k < nseg && p.cseg_off[size_t(k)] < int32_t(b + 1) * kRowBlock; ++k) {
                 const int32_t t = p.cseg_task[size_t(k)];
@@ -541,7 +545,7 @@ std::vector<int32_t> product_tables(const Plan& p)
                 for (int32_t c = 0; c < r; c += 16, --left)
                     list.insert(list.end(), {p.cseg_off[size_t(k)], p.cseg_off[size_t(k) + 1], p.rank_off[t] + c, std::min(r - c, 16), t, c, r, 0});
             }
-            list.resize(list.size() + size_t(left) * (sizeof(F32Item) / sizeof(int32_t)), 0);
+            list.resize(list.size() + size_t(left) * kItem, 0);
         }
         return list;
     }
