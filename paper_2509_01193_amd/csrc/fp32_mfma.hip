@@ -573,7 +573,7 @@ hipError_t gemm_f32(const PlanDev& pd, bool transW, const float* Z, const float*
 
 // The same with the projection of Z's rows in the product's launch (pd's plan has ni items per 32-row block, see f32_fused): what a
 // short batch is bound by is launches and round trips to memory.  618 x 256 x 256, two tasks of rank 8, projection and product 4.6 + 7.1
-// us, like this 7.2 (the step 26.7 -> 22.3).
+// us, like this 7.7 (the step 26.7 -> 22.3).
 hipError_t gemm_f32_fused(const PlanDev& pd, int32_t ni, bool transW, const float* Z, const float* W, const float* D, const float* s, float* P,
                           const float* M, float* C, int32_t K, int32_t N, int32_t ldw, hipStream_t st)
 {
