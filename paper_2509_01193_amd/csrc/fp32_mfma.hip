@@ -380,20 +380,26 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         for (int u = 0; u < WA; ++u) ws[(tid + 256 * u) / TN * NPITCH + (tid + 256 * u) % TN] = ma[u];
     };
     auto col_of = [&](int nb, int i) { return wn * WTN + (TRANSW ? nb * 16 + i : NB * i + nb); };    // of result row i of block nb
-    auto mac = [&](const float* zs, const float* ws) {
-        Frags f;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) f.z[mb] = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + 4 * kg);
+    // (crosses(mb): whether the segment, or the task, has rows in block mb of the wave, uniform.  The others are left alone: zeros in place of a
+    //  row of P would not keep out what is not finite in another task's adapter)
+    auto mac = [&](const float* zs, const float* ws, auto crosses) {
+        float w[NB][4];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) f.w[nb][q] = ws[(4 * kg + q) * NPITCH + col_of(nb, j)];
+            for (int q = 0; q < 4; ++q) w[nb][q] = ws[(4 * kg + q) * NPITCH + col_of(nb, j)];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int mb = 0; mb < MB; ++mb) {
+            if (!crosses(mb)) continue;
+            const f32x4 z = *reinterpret_cast<const f32x4*>(zs + (wm * WTM + mb * 16 + j) * FPITCH + 4 * kg);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(f.w[nb][q], f.z[mb][q], acc[mb][nb]);
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma4(w[nb][q], z[q], acc[mb][nb]);
+        }
+    };
+    auto crosses_rows = [&](int32_t lo, int32_t hi) {
+        return [=](int mb) { return hi > row0 + wm * WTM + mb * 16 && lo < row0 + wm * WTM + mb * 16 + 16; };
     };
     if constexpr (NI > 0) {
         constexpr int HZ = TM * FPITCH, HW = 16 * NPITCH;
@@ -428,7 +434,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            if (item[i].n > 0) mac(zs + i * HZ, zs + NI * HZ + i * HW);      // (uniform)
+            if (item[i].n > 0) mac(zs + i * HZ, zs + NI * HZ + i * HW, crosses_rows(item[i].lo, item[i].hi));        // (uniform)
     }
     if (some || many) __syncthreads();               // everybody is done with the ring
     if (some) {
@@ -444,7 +450,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
                 if (sg != first_sg || c0 > 0) load_adapter(lo, hi, r, pofs, r0, c0);
                 stash_adapter();
                 __syncthreads();
-                mac(zs, ws);
+                mac(zs, ws, crosses_rows(lo, hi));
                 __syncthreads();
             }
         }
@@ -496,9 +502,10 @@ __global__ __launch_bounds__(256, OCC) void gemm_f32_kernel(PlanDev pd, const fl
         while (more) {
             stash_adapter();
             __syncthreads();
+            const int32_t now = t;
             more = next();
             if (more) load();
-            mac(zs, ws);
+            mac(zs, ws, [&](int mb) { return __ballot(row_task[wm * WTM + mb * 16 + j] == now) != 0; });
             __syncthreads();
         }
     }

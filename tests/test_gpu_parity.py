@@ -184,6 +184,32 @@ def test_persistent_gemm_up_projection_of_many_segments(d_in, d_out, n_proj):
     check_problem(p, rows=sample_rows(p, 100)[::3], label="up")
 
 
+def check_adapter_stays_with_its_task(p, lens, tasks, bad, value, least):
+    """Task `bad` gets an adapter that holds no finite value: tokens of other tasks and of none that are 16 and more away from its own (the
+    kernels share blocks of 16 rows), and the other tasks' gradients, are what they are with a finite one, bit for bit."""
+    import torch
+    good = bd.DeviceProblem(p)
+    good.step()
+    ro = p.rank_off
+    rows = slice(int(ro[bad]), int(ro[bad + 1]))
+    bits = value if p.dtype == "f32" else np.uint16(0x7fc0 if np.isnan(value) else 0x7f80)
+    p.A[rows, ::7], p.B[rows] = bits, bits
+    dp = bd.DeviceProblem(p)
+    dp.step()
+    torch.cuda.synchronize()
+    assert dp.guards_intact()
+    own = torch.from_numpy(np.repeat(np.asarray(tasks) == bad, lens)).cuda()
+    near = torch.nn.functional.max_pool1d(own[None, None].float(), 31, 1, 15)[0, 0] > 0
+    assert bool(own.any()) and int((~near).sum()) > least
+    assert not bool(torch.isfinite(dp.y[own].float()).any()) and not bool(torch.isfinite(dp.dx[own, ::7].float()).any())
+    for name in ("y", "dx"):
+        wrong = (getattr(dp, name)[~near] != getattr(good, name)[~near]).any(1)
+        assert not bool(wrong.any()), (name, int(wrong.sum()), "of", len(wrong))
+    others = [i for i in range(p.R_tot) if not rows.start <= i < rows.stop]
+    for name in ("dA", "dB"):
+        assert bool((getattr(dp, name)[others] == getattr(good, name)[others]).all()), name
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("d_in,d_out", [(2048, 2048), (2056, 2048), (2048, 2056)])
 def test_persistent_gemm_adapters_of_no_finite_value_stay_with_their_task(d_in, d_out, value):
@@ -191,7 +217,6 @@ def test_persistent_gemm_adapters_of_no_finite_value_stay_with_their_task(d_in, 
     a finite one, bit for bit - except rows that may share a block of 16 with that task's (zero times NaN).  Segments of ranks up
     to 16, two to a step of the up projection, with and without others between them.  (Products of the persistent kernel, with
     whole K tiles and, for 2056, without.)"""
-    import torch
     T, bad, rng = 5632 + 13, 1, np.random.default_rng(d_in + d_out)
     lens = []
     while sum(lens) < T:
@@ -199,26 +224,25 @@ def test_persistent_gemm_adapters_of_no_finite_value_stay_with_their_task(d_in, 
     off, tasks = np.concatenate([[0], np.cumsum(lens)]), rng.integers(-1, 4, len(lens))
     p = wl.make_custom("alone-%d-%d" % (d_in, d_out), "bf16", d_in, d_out, [16, 16, 8, 24], off, tasks, 43,
                        std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
-    good = bd.DeviceProblem(p)
-    good.step()
-    bits, rows = np.uint16(0x7fc0 if np.isnan(value) else 0x7f80), slice(16, 32)
-    p.A[rows, ::7], p.B[rows] = bits, bits
-    dp = bd.DeviceProblem(p)
-    dp.step()
-    torch.cuda.synchronize()
-    assert dp.guards_intact()
-    own = torch.from_numpy(np.repeat(tasks == bad, lens)).cuda()
-    near = torch.nn.functional.max_pool1d(own[None, None].float(), 31, 1, 15)[0, 0] > 0
-    assert bool(near.any()) and int((~near).sum()) > T // 4
-    assert not bool(torch.isfinite(dp.y[own].float()).any()) and not bool(torch.isfinite(dp.dx[own, ::7].float()).any())
-    for name in ("y", "dx"):
-        a, b = getattr(dp, name)[~near].view(torch.int16), getattr(good, name)[~near].view(torch.int16)
-        wrong = (a != b).any(1)
-        assert not bool(wrong.any()), (name, int(wrong.sum()), "of", len(wrong))
-    for name in ("dA", "dB"):
-        a, b = getattr(dp, name), getattr(good, name)
-        others = [i for i in range(p.R_tot) if not 16 <= i < 32]
-        assert bool((a[others] == b[others]).all()), name
+    check_adapter_stays_with_its_task(p, lens, tasks, bad, value, T // 4)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("T,d_in,d_out,lens", [
+    (60, 4096, 1032, [1]),                  # the projection beside the split product, the adapter term with its sum
+    (700, 712, 520, [20, 33, 5]),           # tiled products
+    (2100, 712, 4096, [20, 90]),
+    (12000, 328, 1000, [60, 90, 400]),      # the register-staged one
+])
+def test_bf16_adapters_of_no_finite_value_stay_with_their_task(T, d_in, d_out, lens, value):
+    bad, rng = 1, np.random.default_rng(T)
+    cut = []
+    while sum(cut) < T:
+        cut.append(min(int(rng.choice(lens)), T - sum(cut)))
+    tasks = rng.choice([-1, 0, 0, 0, 2, 2, 2, 2, bad], len(cut)) if T > 60 else np.where(np.arange(T) == 5, bad, np.arange(T) % 2 * 2)
+    p = wl.make_custom("alone-bf16-%d" % T, "bf16", d_in, d_out, [16, 16, 8], np.concatenate([[0], np.cumsum(cut)]), tasks, 53,
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    check_adapter_stays_with_its_task(p, cut, tasks, bad, value, T // 8)
 
 
 @pytest.mark.parametrize("d_in,d_out", [
@@ -674,6 +698,29 @@ def test_fp32_projection_inside_the_product(T, d_in, d_out, ranks, longest, insi
         torch.cuda.synchronize()
         assert torch.equal(want[0], dp.dA) and torch.equal(want[1], dp.dB), (h is None, flags)
     assert dp.guards_intact()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("T,d_in,d_out,lens,ranks", [
+    (600, 64, 96, [20, 33, 60], [16, 16, 8]),            # the projection inside the product
+    (600, 130, 97, [20, 33, 60], [16, 128, 8]),          # tiles of 32,
+    (600, 130, 97, [3, 5, 2], [16, 40, 8]),              #   crossed by many segments
+    (3000, 256, 1028, [20, 33, 300], [16, 40, 8]),       # of 64,
+    (3000, 256, 1028, [9, 5, 12], [16, 40, 8]),
+    (8200, 1028, 1036, [40, 33, 300], [16, 40, 8]),      # of 128
+    (8200, 1028, 1036, [9, 5, 12], [16, 40, 8]),
+])
+def test_fp32_adapters_of_no_finite_value_stay_with_their_task(T, d_in, d_out, lens, ranks, value):
+    """As for the persistent bf16 kernel: one task's adapter holds no finite value, and what has no row in a block of 16 with it is what it
+    is with a finite one, bit for bit."""
+    bad, rng = 1, np.random.default_rng(T + d_in + lens[0])
+    cut = []
+    while sum(cut) < T:
+        cut.append(min(int(rng.choice(lens)), T - sum(cut)))
+    tasks = rng.choice([-1, 0, 0, 0, 2, 2, 2, 2, bad], len(cut))
+    p = wl.make_custom("alone-f32-%d" % T, "f32", d_in, d_out, ranks, np.concatenate([[0], np.cumsum(cut)]), tasks, 47,
+                       std_x=1.0, std_w=0.05, std_a=0.05, std_b=0.05)
+    check_adapter_stays_with_its_task(p, cut, tasks, bad, value, T // 8)
 
 
 @pytest.mark.parametrize("ranks", [[16], [40, 16]])
