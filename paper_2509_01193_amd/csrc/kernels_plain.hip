@@ -419,9 +419,11 @@ hipError_t reduce_partials(const PlanDev& pd, const GradJob& ja, const GradJob& 
 {
     if (pd.R_tot == 0) return hipSuccess;
     const int32_t tiles_a = (ja.D + 1023) / 1024, tiles_b = jb.out ? (jb.D + 1023) / 1024 : 0;
-    // a workgroup per task and rank up to the highest, so that none has to find its task, unless that makes twice as many
-    const bool per_task = int64_t(pd.n_tasks) * pd.r_max <= 2 * int64_t(pd.R_tot);
-    const dim3 grid(per_task ? pd.n_tasks * pd.r_max : pd.R_tot, tiles_a + tiles_b);
+    // a workgroup per task and rank up to the highest, so that none has to find its task, unless that makes twice as many, or as many as a
+    // dimension of a launch has no room for (2^32 threads)
+    const int64_t every = int64_t(pd.n_tasks) * pd.r_max;
+    const bool per_task = every <= 2 * int64_t(pd.R_tot) && every < (1 << 24);
+    const dim3 grid(per_task ? uint32_t(every) : uint32_t(pd.R_tot), tiles_a + tiles_b);
     if (grid.y > 65535u) return hipErrorInvalidValue;
     (per_task ? reduce_partials_kernel<true> : reduce_partials_kernel<false>)<<<grid, 256, 0, st>>>(pd, ja, jb, tiles_a, accumulate ? 1 : 0, skip_single ? 1 : 0);
     return hipGetLastError();
